@@ -199,11 +199,11 @@ def work(case):
 
 
 def tolerance(case):
-    """About four times what a pass differs from the same operation in 64 bits: the largest seen were, in bf16,
+    """Three to four times what a pass differs from the same operation in 64 bits: the largest seen were, in bf16,
     2.9e-3 (2-norm) and 0.28 (one element of dK, where thousands of rounded p and ds cancel) for the
     attention, 1.9e-3 and 3.9e-3 (one rounding) for the others; in fp32 6.0e-7 and 1.2e-5 for the
     attention, 1.1e-7 and 7.0e-7 for the loss."""
     attention = case["kind"] in ATTENTION
     if case["dtype"] == "bf16":
-        return {"rel": 1.1e-2, "max": 1.1} if attention else {"rel": 7.5e-3, "max": 1.6e-2}
+        return {"rel": 1.1e-2, "max": 0.9} if attention else {"rel": 7.5e-3, "max": 1.6e-2}
     return {"rel": 2.4e-6, "max": 5e-5} if attention else {"rel": 4.4e-7, "max": 2.8e-6}
