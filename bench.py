@@ -258,14 +258,14 @@ def main():
     kernel_ms = {name: ms / args.steps for name, ms in binding.ttt_attn_profile_totals().items()}
     binding.ttt_attn_profile_enable(False)
 
-    # dominant kernel: the key-stationary dK/dV kernel does S, dP, dV, dK on the block-0 (causal) pairs
+    # dominant kernel: one launch does S, dP, dV, dK on the block-0 (causal) pairs (key-stationary part)
+    # and dQ on all pairs (query-stationary part; its recomputation of S and dP is not counted)
     causal_pairs = wl.hq * sum(wl.k * L * (L + 1) // 2 for L in wl.doc_lens)
+    bwd_main = 8 * wl.d * causal_pairs + 2 * wl.d * wl.pairs()
     alg = {
         "ttt_fwd_kernel": 4 * wl.d * wl.pairs(),
-        "ttt_bwd_dkv_kernel": 8 * wl.d * causal_pairs,
-        "ttt_bwd_dkv_p8_kernel": 8 * wl.d * causal_pairs,
-        "ttt_bwd_dq_kernel": 2 * wl.d * wl.pairs(),
-        "ttt_bwd_dq_pipe_kernel": 2 * wl.d * wl.pairs(),
+        "ttt_bwd_main_kernel": bwd_main,
+        "ttt_bwd_main_f32_kernel": bwd_main,
     }
     dom = max((n for n in kernel_ms if n in alg), key=lambda n: kernel_ms[n], default=None)
     roofline = None

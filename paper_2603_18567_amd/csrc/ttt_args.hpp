@@ -59,11 +59,13 @@ struct BwdArgs {
     float* dvl_acc;
     int accumulate;         // 0/1
     int carry_reset;        // accumulate mode: this call starts the sweep (carry is overwritten, not read)
-    int n_tiles;            // tiles of the kernel being launched
+    int n_tiles_q;          // query tiles of the dQ part
+    int n_tiles_kv;         // key tiles of the dK/dV part
+    int grid_kv;            // workgroups of the dK/dV part; the dQ part follows them
     int n_split;            // dK/dV kernel: ways the (step, head) list of one kv tile is split
     int n_units;            // dK/dV kernel (16-bit): (key tile, query chunk) units per kv head and split
     int chunk_blocks;       // dK/dV kernel (16-bit): 32-row query blocks per chunk (a multiple of 4)
-    HeadMap map;
+    HeadMap map_q, map_kv;
     // host side only (the launchers' work-split model reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base
     int cu_base;

@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
 // dQ: query-stationary
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int QB, int NW>
-__global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_kernel(const BwdArgs a) {
+TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;
@@ -291,18 +291,17 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_kernel(const BwdArgs a) {
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
 
-    extern __shared__ __align__(16) char smem[];
     auto sK = [&](int s) -> char* { return smem + s * TILE_BYTES; };
     auto sV = [&](int s) -> char* { return smem + (2 + s) * TILE_BYTES; };
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map, blockIdx.x, g, rest)) return;
+    if (!decode_block(a.map_q, wg, g, rest)) return;
     const int hg = rest % geo.G;
     rest /= geo.G;
     const int js = rest % geo.n_steps;
     const int j = geo.step_begin + js;
-    const int tile = a.n_tiles - 1 - rest / geo.n_steps;
+    const int tile = a.n_tiles_q - 1 - rest / geo.n_steps;
     const int h = g * geo.G + hg;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -479,7 +478,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_kernel(const BwdArgs a) {
 // LDS: two stages of [K tile | V tile]; the stage bit is bit 16 of the per-lane addresses.
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int NW>
-__global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_pipe_kernel(const BwdArgs a) {
+TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
     static_assert(sizeof(T) == 2, "this dQ kernel is for 16-bit elements");
     static_assert(NW == 8, "two waves per SIMD supply the overlap; no other wave count is built");
     using E = Elem<T>;
@@ -499,17 +498,16 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_pipe_kernel(const BwdArgs 
     constexpr int PDT = 2;       // K^T fragments requested ahead
     typedef __attribute__((address_space(3))) char lds_char;
 
-    extern __shared__ __align__(16) char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map, blockIdx.x, g, rest)) return;
+    if (!decode_block(a.map_q, wg, g, rest)) return;
     const int hg = rest % geo.G;
     rest /= geo.G;
     const int js = rest % geo.n_steps;
     const int j = geo.step_begin + js;
-    const int tile = a.n_tiles - 1 - rest / geo.n_steps;
+    const int tile = a.n_tiles_q - 1 - rest / geo.n_steps;
     const int h = g * geo.G + hg;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -788,7 +786,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dq_pipe_kernel(const BwdArgs 
 // dK_0, dV_0: key-stationary
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int NW>
-__global__ __launch_bounds__(NW * 64) void ttt_bwd_dkv_kernel(const BwdArgs a) {
+TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KVT = NW * 32;   // kv rows per workgroup, 32 per wave
@@ -800,7 +798,6 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dkv_kernel(const BwdArgs a) {
     constexpr int ROWV_BYTES = QTL * 4;
     constexpr int STAGE_BYTES = 2 * TILE_BYTES + 3 * ROWV_BYTES;
 
-    extern __shared__ __align__(16) char smem[];
     auto sQ = [&](int s) -> char* { return smem + s * STAGE_BYTES; };
     auto sG = [&](int s) -> char* { return smem + s * STAGE_BYTES + TILE_BYTES; };
     auto sLse = [&](int s) -> float* { return reinterpret_cast<float*>(smem + s * STAGE_BYTES + 2 * TILE_BYTES); };
@@ -809,7 +806,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_bwd_dkv_kernel(const BwdArgs a) {
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map, blockIdx.x, g, rest)) return;
+    if (!decode_block(a.map_kv, wg, g, rest)) return;
     const int sp = rest % a.n_split;
     const int tile = rest / a.n_split;   // low tiles of a document have the longest query range: first
 
@@ -1338,19 +1335,39 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
 // number of blocks -- except the few tiles on the chunk's diagonal -- so they stay together and the
 // rows are read from HBM once per XCD, not once per workgroup.
 template <typename T, int D>
-__global__ __launch_bounds__(512) void ttt_bwd_dkv_p8_kernel(const BwdArgs a) {
-    extern __shared__ __align__(16) char smem[];
+TTT_DEV void dkv_p8_unit(const BwdArgs& a, char* smem, const int wg) {
     int g, rest;
-    if (!decode_block(a.map, blockIdx.x, g, rest)) return;
+    if (!decode_block(a.map_kv, wg, g, rest)) return;
     const int sp = rest / a.n_units;
     int r = rest % a.n_units;
     int chunk = 0;
     for (;; ++chunk) {
-        const int tiles = min(a.n_tiles, (chunk + 1) * a.chunk_blocks / 4);   // 128-key tiles = 4 blocks
+        const int tiles = min(a.n_tiles_kv, (chunk + 1) * a.chunk_blocks / 4);   // 128-key tiles = 4 blocks
         if (r < tiles) break;
         r -= tiles;
     }
     dkv_p8_tile<T, D>(a, smem, g, sp, r, chunk);
+}
+
+// ------------------------------------------------------------------------------------------------
+// One launch for both streaming passes: the dK/dV units first (they are the longer ones), then the dQ
+// tiles in order of falling length.  Neither needs anything from the other, so what one pass leaves of
+// the device while its last units finish is filled by the other.
+// ------------------------------------------------------------------------------------------------
+template <typename T, int D>
+__global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    const int wg = blockIdx.x;
+    if (wg < a.grid_kv) dkv_p8_unit<T, D>(a, smem, wg);
+    else dq_pipe_tile<T, D, 8>(a, smem, wg - a.grid_kv);
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs a) {
+    extern __shared__ __align__(16) char smem[];
+    const int wg = blockIdx.x;
+    if (wg < a.grid_kv) dkv_tile<T, D, 4>(a, smem, wg);
+    else dq_tile<T, D, 1, 4>(a, smem, wg - a.grid_kv);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1512,7 +1529,7 @@ static DkvPlan plan_dkv_split(const BwdArgs& a, int n_jh, int n_cu) {
     return best;
 }
 
-template <typename T, int D, int QB_DQ, int NW_DQ, int NW_KV>
+template <typename T, int D>
 static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
     const Geometry& geo = a.geo;
     hipError_t e;
@@ -1559,77 +1576,55 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
-    // 3. dQ
+    // 3. dQ and block 0's dK, dV in one launch
     {
-        constexpr bool kPipe = sizeof(T) == 2;
-        constexpr int NWQ = kPipe ? 8 : NW_DQ;
-        constexpr int QT = NWQ * (kPipe ? 1 : QB_DQ) * 32;
-        constexpr int LDS = kPipe ? 2 * (1 << 16) : 4 * 64 * D * (int)sizeof(T);
-        const void* kern;
-        if constexpr (kPipe) kern = (const void*)ttt_bwd_dq_pipe_kernel<T, D, NWQ>;
-        else kern = (const void*)ttt_bwd_dq_kernel<T, D, QB_DQ, NW_DQ>;
+        constexpr bool k16 = sizeof(T) == 2;      // eight waves; fp32: four
+        constexpr int NW = k16 ? 8 : 4;
+        constexpr int QT = NW * 32, KVT = 128;
+        constexpr int LDS_Q = k16 ? 2 * (1 << 16) : 4 * 64 * D * (int)sizeof(T);
+        constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
+        constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
+        void (*kern)(BwdArgs);
+        if constexpr (k16) kern = ttt_bwd_main_kernel<T, D>;
+        else kern = ttt_bwd_main_f32_kernel<T, D>;
         static LdsOptIn lds_opt_in;
-        if ((e = lds_opt_in.ensure(kern, LDS)) != hipSuccess) return e;
-        // the pipelined kernel addresses the pieces of up to 64 rows of K or V with 32-bit byte offsets
-        if (kPipe && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
-        a.n_tiles = (geo.T + QT - 1) / QT;
-        int64_t grid;
-        set_head_map(a.map, geo.hkv, a.n_tiles * geo.n_steps * geo.G, grid);
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        {
-            ProfileScope prof(kPipe ? "ttt_bwd_dq_pipe_kernel" : "ttt_bwd_dq_kernel", stream);
-            if constexpr (kPipe)
-                hipLaunchKernelGGL((ttt_bwd_dq_pipe_kernel<T, D, NWQ>), dim3((unsigned)grid), dim3(NWQ * 64), LDS, stream, a);
-            else
-                hipLaunchKernelGGL((ttt_bwd_dq_kernel<T, D, QB_DQ, NW_DQ>), dim3((unsigned)grid), dim3(NW_DQ * 64), LDS, stream, a);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-
-    // 4. dK_0, dV_0
-    {
-        constexpr bool kWs = sizeof(T) == 2;      // the eight-equal-waves kernel is for 16-bit types
-        constexpr int KVT = kWs ? 128 : NW_KV * 32;
-        constexpr int P8_LDS = DkvP8<T, D>::kLds;
-        constexpr int LDS = kWs ? P8_LDS : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
-        const void* kern;
-        if constexpr (kWs) kern = (const void*)ttt_bwd_dkv_p8_kernel<T, D>;
-        else kern = (const void*)ttt_bwd_dkv_kernel<T, D, NW_KV>;
-        static LdsOptIn lds_opt_in;
-        if ((e = lds_opt_in.ensure(kern, LDS)) != hipSuccess) return e;
-        // that kernel addresses the rows of a 32-row block with 32-bit byte offsets
-        if (kWs && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
-        a.n_tiles = (geo.T + KVT - 1) / KVT;
-        // split the (step, head) list of a unit so that the grid fills the device evenly
+        if ((e = lds_opt_in.ensure((const void*)kern, LDS)) != hipSuccess) return e;
+        // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
+        // 32-bit byte offsets
+        if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
+        if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
+        a.n_tiles_q = (geo.T + QT - 1) / QT;
+        a.n_tiles_kv = (geo.T + KVT - 1) / KVT;
+        // split the (step, head) list of a dK/dV unit so that the grid fills the device evenly
         const int n_jh = geo.n_steps * geo.G;
         int n_split = 1;
-        int n_units = a.n_tiles;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
-        if constexpr (kWs) {
+        int n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
+        if constexpr (k16) {
             int n_cu = 0;
             if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
             const DkvPlan plan = plan_dkv_split(a, n_jh, n_cu);
             a.chunk_blocks = plan.chunk_blocks;
             n_split = plan.n_split;
-            n_units = dkv_units_of(geo.T, a.n_tiles, a.chunk_blocks);
+            n_units = dkv_units_of(geo.T, a.n_tiles_kv, a.chunk_blocks);
             a.n_units = n_units;
         } else {
             while (n_split < n_jh && (int64_t)n_units * geo.hkv * n_split < 2048) ++n_split;
         }
         a.n_split = n_split;
-        int64_t grid;
-        set_head_map(a.map, geo.hkv, n_units * n_split, grid);
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+        int64_t grid_kv, grid_q;
+        set_head_map(a.map_kv, geo.hkv, n_units * n_split, grid_kv);
+        set_head_map(a.map_q, geo.hkv, a.n_tiles_q * geo.n_steps * geo.G, grid_q);
+        grid_kv = (grid_kv + 7) / 8 * 8;   // workgroups go to the XCDs in turn: keep the dQ part's map in step with them
+        if (grid_kv + grid_q > 0x7fffffffLL) return hipErrorInvalidValue;
+        a.grid_kv = (int)grid_kv;
         {
-            ProfileScope prof(kWs ? "ttt_bwd_dkv_p8_kernel" : "ttt_bwd_dkv_kernel", stream);
-            if constexpr (kWs)
-                hipLaunchKernelGGL((ttt_bwd_dkv_p8_kernel<T, D>), dim3((unsigned)grid), dim3(512), LDS, stream, a);
-            else
-                hipLaunchKernelGGL((ttt_bwd_dkv_kernel<T, D, NW_KV>), dim3((unsigned)grid), dim3(NW_KV * 64), LDS, stream, a);
+            ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : "ttt_bwd_main_f32_kernel", stream);
+            hipLaunchKernelGGL(kern, dim3((unsigned)(grid_kv + grid_q)), dim3(NW * 64), LDS, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
-    // 5. block-0 sums -> output dtype, once the sweep has covered step 0
+    // 4. block-0 sums -> output dtype, once the sweep has covered step 0
     if (!a.accumulate || geo.step_begin == 0) {
         const int blocks = (int)((acc_n4 + 255) / 256 < 4096 ? (acc_n4 + 255) / 256 : 4096);
         {
@@ -1642,10 +1637,10 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t launch_bwd(int dtype, int head_dim, BwdArgs& a, hipStream_t stream) {
-    if (dtype == 1 && head_dim == 128) return launch_bwd_t<__bf16, 128, 1, 8, 4>(a, stream);
-    if (dtype == 1 && head_dim == 64) return launch_bwd_t<__bf16, 64, 1, 4, 4>(a, stream);
-    if (dtype == 0 && head_dim == 128) return launch_bwd_t<float, 128, 1, 4, 4>(a, stream);
-    if (dtype == 0 && head_dim == 64) return launch_bwd_t<float, 64, 1, 4, 4>(a, stream);
+    if (dtype == 1 && head_dim == 128) return launch_bwd_t<__bf16, 128>(a, stream);
+    if (dtype == 1 && head_dim == 64) return launch_bwd_t<__bf16, 64>(a, stream);
+    if (dtype == 0 && head_dim == 128) return launch_bwd_t<float, 128>(a, stream);
+    if (dtype == 0 && head_dim == 64) return launch_bwd_t<float, 64>(a, stream);
     return hipErrorInvalidValue;
 }
 
