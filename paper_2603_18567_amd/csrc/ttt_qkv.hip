@@ -8,21 +8,22 @@
 // With no rotated heads at all the same kernel is the plain projection y = x w^T (the output
 // projection that reads O_j).
 //
-// One workgroup = 256 tokens x 2 heads (256 features), eight waves: wave (wm, wn) owns 64 tokens x
-// the 128 features of head wn, i.e. 2 x 4 accumulator blocks of 32 x 32 (a 128-token variant, one
-// block of tokens per wave, is taken when it fills the device in fewer, shorter rounds).  The accumulators hold
-// y^T (row = feature, lane = token), so the two elements of a rotary pair (features i and i + 64)
-// sit in the same lane at the same index of accumulator blocks nb and nb + 2: the rotation needs no
-// exchange between lanes.  Both operands are contraction-contiguous in memory, so both are read
-// from their LDS tiles as row fragments; 64-column slices of the x and w tiles stream through two
-// LDS stages, filled by LDS-DMA copies.  Tiles are numbered so that the workgroups resident on one
-// XCD form a block of token tiles x feature tiles: each x and w slice that enters that XCD's L2 is
-// used by several of them.
+// Two kernels.  ttt_qkv_rope_kernel, for many tokens: one workgroup = 256 tokens x 2 heads (256 features), four waves
+// of 128 tokens x the 128 features of one head, one to a SIMD: 4 x 4 accumulator blocks of 32 x 32 fill one half
+// of its 512 registers.  What bounds it is LDS traffic and, with all compute units at work, the clock under the
+// board's power cap: a wave reads half an operand fragment per matrix instruction (eight waves of 64 x 128
+// read three quarters) and 64-column slices of both tiles stream through two LDS stages by LDS-DMA copies.
+// Measured against that eight-wave form: 4096 x 4096 x 4096 126 -> 109 us (1.26 PFLOP/s), 8192 tokens x 8192 x
+// 9216 1.26 PFLOP/s, 1500 tokens x 4096 x 9216 221 -> 100 us (there mostly by dealing out the tiles evenly).
+// ttt_qkv_rope_splitk_kernel, for few tokens or the features that the large tiles leave over: smaller tiles, see
+// there; kQkvTiles has their times and the choice.
+//
+// Both compute y^T (row = feature, lane = token).  Both operands are contraction-contiguous in memory, so
+// both are read from their LDS tiles as row fragments.  The token tiles of one feature tile go to one XCD
+// in groups: each x and w slice that enters that XCD's L2 is used by several workgroups.
 #include "ttt_args.hpp"
 
 namespace ttt {
-
-constexpr double kSmallTileCost = 0.67;   // time of a 128-token tile relative to a 256-token tile (measured)
 
 struct QkvArgs {
     const void* x;
@@ -36,20 +37,20 @@ struct QkvArgs {
     int T, Hin, n_pos;
     int n_q, n_k, n_v;    // heads written to q (rotated), k (rotated), v (as they are); weight rows in this order
     int64_t x_st, w_st;   // row strides in elements
-    int m_tiles, n_tiles, per_xcd;
-    int n_first;          // first 256-feature tile of this launch (a call may be carried out as two launches)
+    int m_tiles, n_tiles;
+    int f_first, f_count; // features of this launch (a call may be carried out as two launches)
 };
 
-template <typename T, int MB>
-__global__ __launch_bounds__(512) void ttt_qkv_rope_kernel(const QkvArgs a) {
+template <typename T>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void ttt_qkv_rope_kernel(const QkvArgs a) {
     static_assert(sizeof(T) == 2, "16-bit operands");
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int D = 128;         // head_dim
-    constexpr int MT = MB * 128;   // tokens per workgroup: MB blocks of 32 per wave
+    constexpr int MB = 4;          // blocks of 32 tokens per wave
+    constexpr int MT = MB * 64;    // tokens per workgroup
     constexpr int NT = 256;        // features per workgroup (two heads)
     constexpr int KT = 64;         // contraction slice per stage
-    constexpr int NTHR = 512;
     using TL = Tile<T, KT>;
     constexpr int X_BYTES = MT * KT * E::kBytes;
     constexpr int STAGE_BYTES = X_BYTES + NT * KT * E::kBytes;
@@ -58,52 +59,55 @@ __global__ __launch_bounds__(512) void ttt_qkv_rope_kernel(const QkvArgs a) {
     extern __shared__ __align__(16) char smem[];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
 
-    // Workgroup ids go round-robin over the 8 XCDs; the 32 workgroups that an XCD holds at a time
-    // (consecutive slots) are the 4 x 8 tiles of one block of the tile grid.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int blocks_n = (a.n_tiles + 7) / 8;
-    const int blk = (slot >> 5) * 8 + xcd;              // block number: blocks are dealt out to the XCDs in turn
-    const int in_blk = slot & 31;
-    const int tm = (blk / blocks_n) * 4 + (in_blk >> 3), tn = (blk % blocks_n) * 8 + (in_blk & 7);
+    // groups of up to 4 token tiles of one feature tile on one XCD, as in the kernel below
+    const int slot = blockIdx.x >> 3;
+    const int m_groups = (a.m_tiles + 3) / 4, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int grp = slot / m_per * 8 + (blockIdx.x & 7);
+    const int tm = grp % m_groups * m_per + slot % m_per, tn = grp / m_groups;
     if (tm >= a.m_tiles || tn >= a.n_tiles) return;
     const int m0 = tm * MT;
-    const int n0 = (a.n_first + tn) * NT;
-    const int n_feat = (a.n_q + a.n_k + a.n_v) * D;
+    const int n0 = a.f_first + tn * NT;
+    const int n_feat = a.f_first + a.f_count;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave & 3, wn = wave >> 2;
+    const int wm = wave & 1, wn = wave >> 1;
     const int n = lane & 31, hh = lane >> 5;
 
-    const T* X = static_cast<const T*>(a.x);
-    const T* W = static_cast<const T*>(a.w);
-
-    // ---- copies of one slice (KT columns) of the two tiles
-    TileCopy<T, KT, MT, NTHR> copy_x;
-    TileCopy<T, KT, NT, NTHR> copy_w;
-    copy_x.init(a.x_st, tid);
-    copy_w.init(a.w_st, tid);
-    const bool x_inside = m0 + MT <= a.T, w_inside = n0 + NT <= n_feat;
-    auto issue = [&](int ks, int s) {
-        const uint32_t st = lds0 + s * STAGE_BYTES;
-        const int c0 = ks * KT;
-        if (x_inside) copy_x.copy(st, X + (int64_t)m0 * a.x_st + c0);
-        else tile_load_async<T, KT, MT, NTHR>(smem + s * STAGE_BYTES, X + c0, a.x_st, m0, a.T - 1, tid);
-        if (w_inside) copy_w.copy(st + X_BYTES, W + (int64_t)n0 * a.w_st + c0);
-        else tile_load_async<T, KT, NT, NTHR>(smem + s * STAGE_BYTES + X_BYTES, W + c0, a.w_st, n0, n_feat - 1, tid);
+    // ---- copies of one slice (KT columns) of the two tiles: 8 rows per wave and instruction, 16 instructions
+    const T* xs = static_cast<const T*>(a.x) + (int64_t)m0 * a.x_st;
+    const T* ws = static_cast<const T*>(a.w) + (int64_t)n0 * a.w_st;
+    uint32_t off_x[8], off_w[8];
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+        const int r = it * 32 + wave * 8 + (lane >> 3);
+        const uint32_t piece = 16 * ((lane & 7) ^ TL::swz(r));
+        // rows past the end repeat the last one and are not stored
+        off_x[it] = (uint32_t)min(r, a.T - 1 - m0) * (uint32_t)(a.x_st * 2) + piece;
+        off_w[it] = (uint32_t)min(r, n_feat - 1 - n0) * (uint32_t)(a.w_st * 2) + piece;
+    }
+    auto copy = [&](int ks, int s, int i) {
+        const uint32_t dst = lds0 + s * STAGE_BYTES + wave * 1024;
+        if (i < 8) async_copy16(xs + ks * KT, off_x[i], dst + i * 4096);
+        else async_copy16(ws + ks * KT, off_w[i - 8], dst + X_BYTES + (i - 8) * 4096);
     };
 
-    // ---- per-lane LDS addresses of the row fragments (stage 0): chunk t of row n of a 32-row block
-    uint32_t ra[KT / 16];
+    // ---- per-lane LDS addresses of the row fragments: chunk t of row n of this wave's first block, in the
+    // stage that is read next (the two stages differ in one address bit)
+    constexpr int BLK = 32 * TL::kRowBytes;   // one 32-row block of a tile
+    static_assert(STAGE_BYTES == 65536, "stages are told apart by bit 16 of an LDS address");
+    uint32_t rx[KT / 16], rw[KT / 16];
     {
         LaneFrags<T, KT> lf;
         lf.init(lane);
 #pragma unroll
-        for (int t = 0; t < KT / 16; ++t) ra[t] = lds0 + lf.row[t];
+        for (int t = 0; t < KT / 16; ++t) {
+            rx[t] = lds0 + lf.row[t] + wm * MB * BLK;
+            rw[t] = lds0 + lf.row[t] + X_BYTES + wn * 4 * BLK;
+        }
     }
     auto ld = [&](uint32_t addr) -> frag {
         return *reinterpret_cast<const __attribute__((address_space(3))) frag*>((uintptr_t)addr);
     };
-    constexpr int BLK = 32 * TL::kRowBytes;   // one 32-row block of a tile
 
     f32x16 acc[MB][4];
 #pragma unroll
@@ -114,42 +118,76 @@ __global__ __launch_bounds__(512) void ttt_qkv_rope_kernel(const QkvArgs a) {
             for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.f;
 
     const int n_k = a.Hin / KT;
-    auto step = [&](int ks, auto stage_c) {
-        constexpr int ST = decltype(stage_c)::value;
-        wait_async_copies();
-        __syncthreads();   // slice ks is in LDS for everyone; everyone is done with the other stage
-        if (ks + 1 < n_k) issue(ks + 1, ST ^ 1);
-        const uint32_t xo = ST * STAGE_BYTES + (wm * MB) * BLK;
-        const uint32_t wo = ST * STAGE_BYTES + X_BYTES + (wn * 4) * BLK;
-        // the fragments of chunk t + 1 are requested before the matrix instructions of chunk t are issued
-        frag xf[KT / 16][MB], wf[KT / 16][4];
-        auto request = [&](int t) {
-#pragma unroll
-            for (int mb = 0; mb < MB; ++mb) xf[t][mb] = ld(ra[t] + xo + mb * BLK);
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb) wf[t][nb] = ld(ra[t] + wo + nb * BLK);
-        };
-        request(0);
+    frag xf[2][MB], wf[2][4];   // of the chunk at work and of the next one
+    auto request = [&](int buf, int t, int i) {   // fragment i of chunk t
+        if (i < 4) wf[buf][i] = ld(rw[t] + i * BLK);
+        else xf[buf][i - 4] = ld(rx[t] + (i - 4) * BLK);
+    };
+    // One slice.  Between its third and last chunk the next slice is in LDS for everyone and everyone has the
+    // last fragments of this one, so its stage is requested again (the slice after the next) and the first
+    // fragments of the next slice are, too: no wave waits for LDS with its matrix core idle.
+    auto step = [&](int ks, auto fill_c, auto next_c) {
+        constexpr bool FILL = decltype(fill_c)::value, NEXT = decltype(next_c)::value;
 #pragma unroll
         for (int t = 0; t < KT / 16; ++t) {
-            if (t + 1 < KT / 16) request(t + 1);
-            issue_fence();
+            const bool last = t == KT / 16 - 1;
+            if (last && NEXT) {
+                wait_async_copies();
+                lds_barrier();
 #pragma unroll
-            for (int mb = 0; mb < MB; ++mb)
+                for (int u = 0; u < KT / 16; ++u) {
+                    rx[u] ^= STAGE_BYTES;
+                    rw[u] ^= STAGE_BYTES;
+                }
+            }
 #pragma unroll
-                for (int nb = 0; nb < 4; ++nb) acc[mb][nb] = mma(wf[t][nb], xf[t][mb], acc[mb][nb]);
+            for (int i = 0; i < 8; ++i) {
+                if (!last || NEXT) request((t + 1) & 1, last ? 0 : t + 1, i);
+                if (last && FILL) {
+                    copy(ks + 2, ks & 1, 2 * i);
+                    copy(ks + 2, ks & 1, 2 * i + 1);
+                }
+                issue_fence();
+                acc[i / 2][2 * (i & 1)] = mma(wf[t & 1][2 * (i & 1)], xf[t & 1][i / 2], acc[i / 2][2 * (i & 1)]);
+                acc[i / 2][2 * (i & 1) + 1] = mma(wf[t & 1][2 * (i & 1) + 1], xf[t & 1][i / 2], acc[i / 2][2 * (i & 1) + 1]);
+                issue_fence();
+            }
         }
     };
-    issue(0, 0);
-    for (int ks = 0; ks < n_k; ks += 2) {
-        step(ks, IntC<0>{});
-        if (ks + 1 < n_k) step(ks + 1, IntC<1>{});
+    auto pin = [&]() {   // the accumulators' home is the accumulation half of the register file
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) asm volatile("" : "+a"(acc[mb][nb]));
+    };
+#pragma unroll
+    for (int i = 0; i < 16; ++i) copy(0, 0, i);
+    if (n_k > 1) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) copy(1, 1, i);
+        wait_copies_but(IntC<16>{});
+    } else {
+        wait_async_copies();
     }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) request(0, 0, i);
+    pin();
+    for (int ks = 0; ks < n_k - 2; ++ks) {
+        step(ks, IntC<1>{}, IntC<1>{});
+        pin();
+    }
+    if (n_k > 1) step(n_k - 2, IntC<0>{}, IntC<1>{});
+    step(n_k - 1, IntC<0>{}, IntC<0>{});
+    pin();
+    lds_barrier();   // the stages are free
 
-    // ---- epilogue: rotate, convert, store.  Lane (n, hh) holds, of accumulator block (mb, nb), the
-    // features 32 nb + 8 k4 + 4 hh + 0..3 (k4 = 0..3) of token m0 + 64 wm + 32 mb + n.
+    // ---- epilogue, 32 tokens of a wave at a time through LDS: a lane puts the features 32 nb + 8 k4 + 4 hh + 0..3 of
+    // token n there and takes 8 pairs of a token, so that eight lanes read one row of the angle table and write
+    // 128 consecutive bytes (storing from the accumulators, 8 bytes in each of 32 rows per instruction, cost a
+    // tile 10 us).  The table rows of the next 32 tokens are requested ahead.
     const int head = n0 / D + wn;
-    if (head >= a.n_q + a.n_k + a.n_v) return;
+    if (head * D >= n_feat) return;
     const bool rotate = head < a.n_q + a.n_k;
     T* out;
     int64_t out_st;
@@ -163,63 +201,351 @@ __global__ __launch_bounds__(512) void ttt_qkv_rope_kernel(const QkvArgs a) {
         out = static_cast<T*>(a.v) + (int64_t)(head - a.n_q - a.n_k) * D;
         out_st = (int64_t)a.n_v * D;
     }
+    constexpr int PITCH = D + 4;   // floats: rows 16 bytes apart modulo the banks
+    float* part = reinterpret_cast<float*>(smem) + wave * (32 * PITCH);
+    const int t8 = lane >> 3, i0 = 8 * (lane & 7);
+    const int m_wave = m0 + wm * (32 * MB);
+    int p[MB][4];
+    f32x8 c8[2][4], s8[2][4];
+    auto angles = [&](int mb) {
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            c8[mb & 1][it] = gload_frag<float>(a.cos_tab + (int64_t)p[mb][it] * (D / 2) + i0);
+            s8[mb & 1][it] = gload_frag<float>(a.sin_tab + (int64_t)p[mb][it] * (D / 2) + i0);
+        }
+    };
+    if (rotate) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int v = a.pos[min(m_wave + mb * 32 + it * 8 + t8, a.T - 1)];
+                p[mb][it] = v < 0 ? 0 : (v >= a.n_pos ? a.n_pos - 1 : v);
+            }
+        angles(0);
+    }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-        const int m = m0 + wm * (32 * MB) + mb * 32 + n;
-        if (m >= a.T) continue;
-        T* row = out + (int64_t)m * out_st;
-        if (rotate) {
-            int p = a.pos[m];
-            p = p < 0 ? 0 : (p >= a.n_pos ? a.n_pos - 1 : p);
-            const float* cr = a.cos_tab + (int64_t)p * (D / 2);
-            const float* sr = a.sin_tab + (int64_t)p * (D / 2);
+        issue_fence();   // one block of rows at a time leaves the accumulators
+        if (rotate && mb + 1 < MB) angles(mb + 1);
 #pragma unroll
-            for (int nb = 0; nb < 2; ++nb)
+        for (int nb = 0; nb < 4; ++nb)
 #pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const int i0 = 32 * nb + 8 * k4 + 4 * hh;
-                    const f32x4 c4 = *reinterpret_cast<const f32x4*>(cr + i0);
-                    const f32x4 s4 = *reinterpret_cast<const f32x4*>(sr + i0);
-                    float lo[4], hi[4];
+            for (int k4 = 0; k4 < 4; ++k4)
+                *reinterpret_cast<f32x4*>(part + n * PITCH + nb * 32 + 8 * k4 + 4 * hh) =
+                    f32x4{acc[mb][nb][4 * k4], acc[mb][nb][4 * k4 + 1], acc[mb][nb][4 * k4 + 2], acc[mb][nb][4 * k4 + 3]};
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float y0 = acc[mb][nb][4 * k4 + e], y1 = acc[mb][nb + 2][4 * k4 + e];
-                        lo[e] = y0 * c4[e] - y1 * s4[e];
-                        hi[e] = y1 * c4[e] + y0 * s4[e];
-                    }
-                    gstore_vec4<T>(row + i0, lo[0], lo[1], lo[2], lo[3]);
-                    gstore_vec4<T>(row + D / 2 + i0, hi[0], hi[1], hi[2], hi[3]);
-                }
-        } else {
+        for (int it = 0; it < 4; ++it) {
+            const int m = m_wave + mb * 32 + it * 8 + t8;
+            const f32x8 y0 = gload_frag<float>(part + (it * 8 + t8) * PITCH + i0);
+            const f32x8 y1 = gload_frag<float>(part + (it * 8 + t8) * PITCH + D / 2 + i0);
+            bf16x8 lo, hi;
 #pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const int i0 = 32 * nb + 8 * k4 + 4 * hh;
-                    gstore_vec4<T>(row + i0, acc[mb][nb][4 * k4], acc[mb][nb][4 * k4 + 1], acc[mb][nb][4 * k4 + 2],
-                                   acc[mb][nb][4 * k4 + 3]);
-                }
+            for (int e = 0; e < 8; ++e) {
+                lo[e] = (__bf16)(rotate ? y0[e] * c8[mb & 1][it][e] - y1[e] * s8[mb & 1][it][e] : y0[e]);
+                hi[e] = (__bf16)(rotate ? y1[e] * c8[mb & 1][it][e] + y0[e] * s8[mb & 1][it][e] : y1[e]);
+            }
+            if (m < a.T) {
+                T* row = out + (int64_t)m * out_st + i0;
+                *reinterpret_cast<bf16x8*>(row) = lo;
+                *reinterpret_cast<bf16x8*>(row + D / 2) = hi;
+            }
         }
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
-template <int MB>
-static hipError_t launch_qkv_rope_t(QkvArgs& a, hipStream_t stream) {
-    using T = __bf16;
-    constexpr int MT = MB * 128;
-    constexpr int LDS = 2 * (MT + 256) * 64 * 2;
-    auto kern = ttt_qkv_rope_kernel<T, MB>;
+// ------------------------------------------------------------------------------------------------
+// Few tokens: the weights outweigh the activations
+// ------------------------------------------------------------------------------------------------
+// Tiles of MT tokens x NT features, so small that even a short batch makes about one workgroup per compute unit;
+// what keeps the matrix work of such a tile apart is the contraction: the eight waves are KG groups of
+// MW x NW waves, wave group kg taking every KG-th 16-column chunk of the slices that stream through LDS
+// (each wave has 64 x 64 accumulators or fewer, and reads one operand fragment from LDS per matrix
+// instruction where a split of the tile would read two).  The groups' partial sums meet once, in LDS, at
+// the end.  NST stages of SUB 64-column slices, requested NST - 1 ahead: the copies are the bound here.
+// A tile of NT < 128 features holds both elements of its rotary pairs: NT / 2 features of the lower half
+// of one head and the NT / 2 that they are paired with.
+template <typename T, int MT, int NT, int KG, int MW, int NW, int SUB, int NST>
+struct QkvSplitK {
+    static constexpr int KT = 64;
+    static constexpr int ROW_BYTES = KT * 2;
+    static constexpr int SLICE_ROWS = MT + NT;
+    static constexpr int STAGE_BYTES = SUB * SLICE_ROWS * ROW_BYTES;
+    static constexpr int MB = MT / (32 * MW), NB = NT / (32 * NW);   // 32 x 32 blocks of a wave
+    static constexpr int PITCH = NB * 32 + 4;                        // floats; rows 16 bytes apart modulo the banks
+    static constexpr int PART_BYTES = MB * 32 * PITCH * 4;
+    // Where the partial sums of all eight waves would need more LDS than the stages, the upper half of the
+    // contraction groups hands its sums to the lower half first.
+    static constexpr bool FOLD = 8 * PART_BYTES > NST * STAGE_BYTES;
+    static constexpr int KGE = FOLD ? KG / 2 : KG;                   // partial sums that the outputs are added up from
+    static constexpr int EPI_BYTES = KGE * MW * NW * PART_BYTES;
+    static constexpr int LDS = NST * STAGE_BYTES > EPI_BYTES ? NST * STAGE_BYTES : EPI_BYTES;
+    static_assert(KG * MW * NW == 8 && SUB * 4 % KG == 0 && SUB * SLICE_ROWS % 64 == 0 && LDS <= 160 * 1024, "work split");
+};
+
+template <typename T, int MT, int NT, int KG, int MW, int NW, int SUB, int NST>
+__global__ __launch_bounds__(512) void ttt_qkv_rope_splitk_kernel(const QkvArgs a) {
+    static_assert(sizeof(T) == 2, "16-bit operands");
+    using C = QkvSplitK<T, MT, NT, KG, MW, NW, SUB, NST>;
+    using frag = typename Elem<T>::frag;
+    using TL = Tile<T, C::KT>;
+    constexpr int D = 128;
+    constexpr int MB = C::MB, NB = C::NB;
+    constexpr int CH = SUB * 4 / KG;                      // chunks of a stage that a wave works on
+    constexpr int PASSES = SUB * C::SLICE_ROWS / 64;      // copy instructions of a wave per stage, 8 rows each
+    typedef __attribute__((address_space(3))) char lds_char;
+
+    extern __shared__ __align__(16) char smem[];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_char*)smem;
+
+    // Groups of up to 8 token tiles of one feature tile are consecutive workgroups of one XCD (workgroup ids go
+    // round-robin over the 8): with few tokens its weight rows enter that L2 once; with many the groups are
+    // dealt out token group by token group, so that an XCD keeps to the same x rows.
+    const int slot = blockIdx.x >> 3;
+    const int m_groups = (a.m_tiles + 7) / 8, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int grp = slot / m_per * 8 + (blockIdx.x & 7);
+    const int tm = grp % m_groups * m_per + slot % m_per, tn = grp / m_groups;
+    if (tm >= a.m_tiles || tn >= a.n_tiles) return;
+    const int m0 = tm * MT;
+    constexpr int TILES_PER_HEAD = D / NT;
+    const int head = a.f_first / D + tn / TILES_PER_HEAD, pair0 = tn % TILES_PER_HEAD * (NT / 2);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wn = wave % NW, wm = wave / NW % MW, kg = wave / (NW * MW);
+    const int n = lane & 31, hh = lane >> 5;
+
+    // ---- copies: 8 stage rows per wave and pass; a lane's source row stays the same from stage to stage
+    const T* src[PASSES];
+    int sub_of[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int rr = p * 64 + wave * 8 + (lane >> 3);
+        const int r = rr % C::SLICE_ROWS, piece = (lane & 7) ^ TL::swz(r);   // MT is a multiple of 16: swz(r) == swz(r - MT)
+        sub_of[p] = __builtin_amdgcn_readfirstlane(rr / C::SLICE_ROWS);
+        if (r < MT) {
+            const int m = m0 + r < a.T ? m0 + r : a.T - 1;   // rows past the end repeat the last one and are not stored
+            src[p] = static_cast<const T*>(a.x) + (int64_t)m * a.x_st;
+        } else {
+            const int f = r - MT;
+            const int row = head * D + pair0 + (f < NT / 2 ? f : D / 2 + f - NT / 2);
+            src[p] = static_cast<const T*>(a.w) + (int64_t)row * a.w_st;
+        }
+        src[p] += sub_of[p] * C::KT + piece * 8;
+    }
+    const int n_slices = a.Hin / C::KT;
+    const int n_stages = (n_slices + SUB - 1) / SUB;
+    auto issue = [&](int st, int slot_bytes) {
+#pragma unroll
+        for (int p = 0; p < PASSES; ++p) {
+            if (SUB == 1 || st * SUB + sub_of[p] < n_slices)
+                async_copy16(src[p], lds0 + slot_bytes + (p * 64 + wave * 8) * C::ROW_BYTES);
+            src[p] += SUB * C::KT;
+        }
+    };
+
+    uint32_t ra[CH];   // this wave's chunks: row n of the tile's first block, in stage 0
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int chunk = kg + KG * c;
+        ra[c] = lds0 + chunk / 4 * (C::SLICE_ROWS * C::ROW_BYTES) + TL::offset(n, chunk % 4 * 16 + hh * 8);
+    }
+    auto ld = [&](uint32_t addr) -> frag {
+        return *reinterpret_cast<const __attribute__((address_space(3))) frag*>((uintptr_t)addr);
+    };
+    constexpr int BLK = 32 * C::ROW_BYTES;
+    const uint32_t xo = wm * MB * BLK, wo = MT * C::ROW_BYTES + wn * NB * BLK;
+
+    f32x16 acc[MB][NB];
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[mb][nb][i] = 0.f;
+
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s)
+        if (s < n_stages) issue(s, s * C::STAGE_BYTES);
+    int cur = 0;                                   // byte offset of the stage to read
+    int nxt = (NST - 1) * C::STAGE_BYTES;          // and of the one to fill: the stage read in the step before
+    for (int s = 0; s < n_stages; ++s) {
+        // stage s has landed; the NST - 2 stages behind it stay in flight while all of them are whole ones
+        const bool more = s + NST - 1 < n_stages;
+        if (more) wait_copies_but(IntC<(NST - 2) * PASSES>{});
+        else wait_async_copies();
+        lds_barrier();
+        if (more) issue(s + NST - 1, nxt);
+        frag xf[CH][MB], wf[CH][NB];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const uint32_t base = ra[c] + cur;
+#pragma unroll
+            for (int mb = 0; mb < MB; ++mb) xf[c][mb] = ld(base + xo + mb * BLK);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) wf[c][nb] = ld(base + wo + nb * BLK);
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (SUB == 1 || s * SUB + (kg + KG * c) / 4 < n_slices) {
+#pragma unroll
+                for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mma(wf[c][nb], xf[c][mb], acc[mb][nb]);
+            }
+        nxt = cur;
+        cur = cur + C::STAGE_BYTES == NST * C::STAGE_BYTES ? 0 : cur + C::STAGE_BYTES;
+    }
+
+    // ---- partial sums to LDS (as [token][feature] per wave), then 16 outputs per thread: 8 features of the
+    // lower half of the tile and the 8 that they are paired with
+    lds_barrier();
+    float* part = reinterpret_cast<float*>(smem + wave % (C::KGE * MW * NW) * C::PART_BYTES) + n * C::PITCH + 4 * hh;
+    auto each_piece = [&](auto&& f) {   // 4 consecutive features of one token
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4)
+                    f(*reinterpret_cast<f32x4*>(part + mb * 32 * C::PITCH + nb * 32 + 8 * k4), acc[mb][nb], 4 * k4);
+    };
+    auto put = [](f32x4& at, const f32x16& v, int i) { at = f32x4{v[i], v[i + 1], v[i + 2], v[i + 3]}; };
+    if constexpr (C::FOLD) {
+        if (kg >= C::KGE) each_piece(put);
+        __syncthreads();
+        if (kg < C::KGE) {
+            each_piece([](const f32x4& at, f32x16& v, int i) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i + e] += at[e];
+            });
+            each_piece(put);   // the same lane wrote and read this place: nobody else's sums are touched
+        }
+    } else {
+        each_piece(put);
+    }
+    __syncthreads();
+    const bool rotate = head < a.n_q + a.n_k;
+    T* out;
+    int64_t out_st;
+    if (head < a.n_q) {
+        out = static_cast<T*>(a.q) + (int64_t)head * D;
+        out_st = (int64_t)a.n_q * D;
+    } else if (rotate) {
+        out = static_cast<T*>(a.k) + (int64_t)(head - a.n_q) * D;
+        out_st = (int64_t)a.n_k * D;
+    } else {
+        out = static_cast<T*>(a.v) + (int64_t)(head - a.n_q - a.n_k) * D;
+        out_st = (int64_t)a.n_v * D;
+    }
+    constexpr int PER_ROW = NT / 16;
+    for (int it = tid; it < MT * PER_ROW; it += 512) {
+        const int t = it / PER_ROW, u = it % PER_ROW, m = m0 + t;
+        if (m >= a.T) break;
+        float y[2][8];
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int f = half * (NT / 2) + 8 * u;
+            const char* at = smem + (t / (MB * 32) * NW + f / (NB * 32)) * C::PART_BYTES;
+            const int within = t % (MB * 32) * C::PITCH + f % (NB * 32);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[half][e] = 0.f;
+#pragma unroll
+            for (int k = 0; k < C::KGE; ++k) {
+                const float* row = reinterpret_cast<const float*>(at + k * (MW * NW) * C::PART_BYTES) + within;
+                const f32x4 v0 = *reinterpret_cast<const f32x4*>(row), v1 = *reinterpret_cast<const f32x4*>(row + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    y[half][e] += v0[e];
+                    y[half][4 + e] += v1[e];
+                }
+            }
+        }
+        const int i0 = pair0 + 8 * u;
+        bf16x8 lo, hi;
+        if (rotate) {
+            int p = a.pos[m];
+            p = p < 0 ? 0 : (p >= a.n_pos ? a.n_pos - 1 : p);
+            const f32x8 c8 = gload_frag<float>(a.cos_tab + (int64_t)p * (D / 2) + i0);
+            const f32x8 s8 = gload_frag<float>(a.sin_tab + (int64_t)p * (D / 2) + i0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                lo[e] = (__bf16)(y[0][e] * c8[e] - y[1][e] * s8[e]);
+                hi[e] = (__bf16)(y[1][e] * c8[e] + y[0][e] * s8[e]);
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                lo[e] = (__bf16)y[0][e];
+                hi[e] = (__bf16)y[1][e];
+            }
+        }
+        T* row = out + (int64_t)m * out_st + i0;
+        *reinterpret_cast<bf16x8*>(row) = lo;
+        *reinterpret_cast<bf16x8*>(row + D / 2) = hi;
+    }
+}
+
+template <int MT, int NT, int KG, int MW, int NW, int SUB, int NST>
+static hipError_t launch_qkv_rope_splitk(QkvArgs& a, hipStream_t stream) {
+    using C = QkvSplitK<__bf16, MT, NT, KG, MW, NW, SUB, NST>;
+    auto kern = ttt_qkv_rope_splitk_kernel<__bf16, MT, NT, KG, MW, NW, SUB, NST>;
     static LdsOptIn lds_opt_in;
-    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS); e != hipSuccess) return e;
+    if (hipError_t e = lds_opt_in.ensure((const void*)kern, C::LDS); e != hipSuccess) return e;
     a.m_tiles = (a.T + MT - 1) / MT;
-    // blocks of 4 x 8 tiles, dealt out to the 8 XCDs in turn: 32 slots per block and XCD
-    const int64_t blocks = (int64_t)((a.m_tiles + 3) / 4) * ((a.n_tiles + 7) / 8);
-    a.per_xcd = (int)((blocks + 7) / 8) * 32;
-    const int64_t grid = 8 * (int64_t)a.per_xcd;
+    a.n_tiles = a.f_count / NT;
+    const int64_t m_groups = (a.m_tiles + 7) / 8, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int64_t grid = 8 * m_per * ((m_groups * a.n_tiles + 7) / 8);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     ProfileScope prof("ttt_qkv_rope_kernel", stream);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), LDS, stream, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), C::LDS, stream, a);
     return hipGetLastError();
+}
+
+static hipError_t launch_qkv_rope_256(QkvArgs& a, hipStream_t stream) {
+    constexpr int LDS = 2 * (256 + 256) * 64 * 2;
+    auto kern = ttt_qkv_rope_kernel<__bf16>;
+    static LdsOptIn lds_opt_in;
+    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS); e != hipSuccess) return e;
+    a.m_tiles = (a.T + 255) / 256;
+    a.n_tiles = (a.f_count + 255) / 256;
+    const int64_t m_groups = (a.m_tiles + 3) / 4, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int64_t grid = 8 * m_per * ((m_groups * a.n_tiles + 7) / 8);
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    ProfileScope prof("ttt_qkv_rope_kernel", stream);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), LDS, stream, a);
+    return hipGetLastError();
+}
+
+// The tiles a call can be cut into, and what they were measured to take (us; sweeps over 16 to 8192 tokens, hidden_in
+// 64 to 8192, 2048 to 9216 features): `round` once per round of the device (first copies, epilogue), and per
+// 64-column slice `t1` with one workgroup on every compute unit, `lo` in the limit of few workgroups (copies and
+// clock are shared), and `t2` with two side by side on one unit.  Model and measurement agree within 8 %.
+struct QkvTile {
+    int mt, nt, per_cu;
+    double round, lo, t1, t2;
+    hipError_t (*launch)(QkvArgs&, hipStream_t);
+};
+static const QkvTile kQkvTiles[] = {
+    {256, 256, 1, 8., 0.95, 1.55, 0., launch_qkv_rope_256},
+    {128, 128, 2, 5., 0.57, 0.57, 1.03, launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 2>},
+    {128, 128, 1, 4., 0.44, 0.55, 0., launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 4>},
+    {128, 64, 1, 3., 0.30, 0.37, 0., launch_qkv_rope_splitk<128, 64, 4, 2, 1, 1, 6>},
+    {64, 64, 2, 3., 0.18, 0.18, 0.36, launch_qkv_rope_splitk<64, 64, 4, 1, 2, 1, 4>},
+    {64, 32, 2, 2., 0.17, 0.17, 0.28, launch_qkv_rope_splitk<64, 32, 4, 2, 1, 2, 3>},
+    {32, 32, 2, 2., 0.14, 0.14, 0.22, launch_qkv_rope_splitk<32, 32, 8, 1, 1, 2, 4>},
+};
+constexpr double kQkvLaunchUs = 3.;
+
+// estimated time of `tiles` tiles: full rounds of the device and a last one, as full as it is
+static double qkv_cost(const QkvTile& v, int64_t tiles, int n_cu, int slices) {
+    const int64_t slots = (int64_t)n_cu * v.per_cu, rest = tiles % slots;
+    const double full = v.round + slices * (v.per_cu == 2 ? v.t2 : v.t1);
+    double us = kQkvLaunchUs + (double)(tiles / slots) * full;
+    if (rest > n_cu) us += full;
+    else if (rest > 0) us += v.round + slices * (v.lo + (v.t1 - v.lo) * (double)rest / (double)n_cu);
+    return us;
 }
 
 // n_q + n_k heads are rotated and go to q and k, n_v heads go to v as they are.  With n_q = n_k = 0 the
@@ -246,38 +572,50 @@ hipError_t launch_qkv_rope(const void* x, const void* w, const float* cos_tab, c
     a.n_pos = n_pos;
     a.x_st = x_st;
     a.w_st = w_st;
-    const int n_tiles = ((n_q + n_k + n_v) * 128 + 255) / 256;
-    // One workgroup per compute unit at a time, so a launch takes rounds x tile time.  Token tiles of
-    // 256 rows are the efficient ones; a tile of 128 rows costs a little more than half of one.  The
-    // feature tiles are cut into a first part done with 256-row tiles and a rest done with 128-row
-    // tiles (either may be empty) so that both launches fill their last round: 4096 tokens x 6144
-    // features are 16 x 24 large tiles = one and a half rounds of 256; as 16 x 16 large tiles plus
-    // 32 x 8 small ones they are two full rounds costing 1 + 0.67.
     int n_cu = 0;
     if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-    const int64_t m_big = (tokens + 255) / 256, m_small = (tokens + 127) / 128;
-    int best_nb = n_tiles;
-    double best_cost = -1.;
-    for (int nb = n_tiles; nb >= 0; --nb) {
-        const double cost = (double)((m_big * nb + n_cu - 1) / n_cu) * 1.0 +
-                            (double)((m_small * (n_tiles - nb) + n_cu - 1) / n_cu) * kSmallTileCost +
-                            (nb > 0 && nb < n_tiles ? 0.02 : 0.);   // a second launch is not free
-        if (best_cost < 0. || cost < best_cost - 1e-9) {
-            best_cost = cost;
-            best_nb = nb;
+    // One kind of tile for all features, or the full rounds of a large kind and the rest of the features with
+    // another, whichever is estimated shortest: 4096 tokens x 6144 features are 16 x 24 of the largest tiles =
+    // one and a half rounds of 256 compute units (371 us at hidden_in 8192), or 16 x 16 of them and 32 x 16 of
+    // 128 x 128, two to a unit (356 us).  The largest kind addresses its 256 rows with 32-bit offsets.
+    const int features = (n_q + n_k + n_v) * 128, slices = hidden_in / 64;
+    const bool largest_fits = x_st * 256 * 2 < (int64_t)1 << 32 && w_st * 256 * 2 < (int64_t)1 << 32;
+    auto row_tiles = [&](const QkvTile& t) { return (tokens + t.mt - 1) / t.mt; };
+    auto cost = [&](const QkvTile& t, int f) { return qkv_cost(t, row_tiles(t) * ((f + t.nt - 1) / t.nt), n_cu, slices); };
+    const QkvTile* const kinds = kQkvTiles + (largest_fits ? 0 : 1);
+    const QkvTile* const end = kQkvTiles + sizeof(kQkvTiles) / sizeof(kQkvTiles[0]);
+    const QkvTile *first = nullptr, *second = nullptr;
+    int f_first = features;
+    double best = 0.;
+    for (const QkvTile* t = kinds; t < end; ++t) {
+        const double c = cost(*t, features);
+        if (!first || c < best) {
+            best = c;
+            first = t;
         }
     }
-    if (best_nb > 0) {
-        a.n_first = 0;
-        a.n_tiles = best_nb;
-        if (hipError_t e = launch_qkv_rope_t<2>(a, stream); e != hipSuccess) return e;
+    for (const QkvTile* t = kinds; t < kQkvTiles + 2; ++t) {
+        const int64_t slots = (int64_t)n_cu * t->per_cu, m = row_tiles(*t);
+        const int64_t rounds = m * ((features + t->nt - 1) / t->nt) / slots;
+        const int64_t f = rounds * slots / m * t->nt;
+        if (f <= 0 || f >= features) continue;
+        const double head = cost(*t, (int)f);
+        for (const QkvTile* u = kinds; u < end; ++u) {
+            const double c = head + cost(*u, features - (int)f);
+            if (c < best) {
+                best = c;
+                first = t;
+                second = u;
+                f_first = (int)f;
+            }
+        }
     }
-    if (best_nb < n_tiles) {
-        a.n_first = best_nb;
-        a.n_tiles = n_tiles - best_nb;
-        if (hipError_t e = launch_qkv_rope_t<1>(a, stream); e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    a.f_first = 0;
+    a.f_count = f_first;
+    if (hipError_t e = first->launch(a, stream); e != hipSuccess || !second) return e;
+    a.f_first = f_first;
+    a.f_count = features - f_first;
+    return second->launch(a, stream);
 }
 
 }  // namespace ttt

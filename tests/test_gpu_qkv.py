@@ -61,7 +61,7 @@ CASES = [
     ("single_token", 1, 64, 1, 1, 0, 0),
     ("gqa_draft_heads_short", 512, 256, 32, 8, 0, 0),     # 48 heads = 24 feature tiles
     ("large_token_tiles_ragged", 4000, 64, 24, 4, 0, 0),  # 16 x 16 tiles of 256 tokens fill the device in one
-                                                          # round: the 256-token variant, last tile ragged
+                                                          # round: the largest tiles, last one ragged
 ]
 
 
@@ -76,6 +76,40 @@ def test_producer_matches_oracle(name, T, hin, hq, hkv, x_pad, w_pad):
     check(q, rq, "Q")
     check(k, rk, "K")
     check(v, rv, "V")
+
+
+# One case per kind of tile that the launcher cuts a call into (tokens x features, workgroups per compute unit),
+# with a ragged last token tile and an odd number of 64-column slices (some kinds stream two per stage), fewer
+# slices than the copies run ahead, and the same call with more of them.
+TILE_CASES = [
+    ("32x32_one_slice", 5, 64, 32, 8),
+    ("32x32", 31, 192, 32, 8),
+    ("64x32", 33, 192, 32, 8),
+    ("64x32_many_slices", 64, 1088, 32, 8),
+    ("128x64", 65, 192, 64, 8),
+    ("128x64_many_slices", 200, 1088, 32, 8),
+    ("64x64", 300, 192, 32, 8),
+    ("64x64_many_slices", 200, 1088, 20, 6),
+    ("128x128", 257, 192, 64, 4),
+    ("128x128_two_per_unit", 1000, 448, 32, 8),
+    ("256x256", 2047, 832, 32, 8),
+    ("256x256_odd_head_count", 2047, 832, 35, 7),
+    ("256x256_two_slices", 4000, 128, 32, 8),
+]
+
+
+@pytest.mark.parametrize("name,T,hin,hq,hkv", TILE_CASES, ids=[c[0] for c in TILE_CASES])
+def test_every_tile_kind_matches_oracle(name, T, hin, hq, hkv):
+    d = 128
+    print(f"case {name} T={T} hidden_in={hin} hq={hq} hkv={hkv}", flush=True)
+    x, w, pos, cos_t, sin_t = make(T, hin, hq, hkv, d, seed=900 + T)
+    q, k, v = run_gpu(x, w, pos, cos_t, sin_t, hq, hkv, d, hin)
+    assert np.isfinite(q).all() and np.isfinite(k).all() and np.isfinite(v).all()
+    rows = np.arange(T) if T <= 300 else np.unique(np.r_[np.arange(0, T, 37), 127, 128, 255, 256, T - 1])
+    rq, rk, rv = qkv_rope(x[rows].float().numpy(), w.float().numpy(), cos_t.numpy(), sin_t.numpy(), pos[rows].numpy(), hq, hkv, d)
+    check(q[rows], rq, "Q")
+    check(k[rows], rk, "K")
+    check(v[rows], rv, "V")
 
 
 def test_positions_out_of_range_are_clamped_and_no_tokens_is_a_noop():
