@@ -40,6 +40,13 @@ CASES = [   # name, rows, vocabulary, dtype, stride padding; the position in thi
     ("f32_streamed_long_row", 3, 70001, torch.float32, 0),      # beyond the register cache
     ("bf16_streamed_long_row", 2, 151936, torch.bfloat16, 0),
     ("f32_vocab_1", 3, 1, torch.float32, 0),
+    ("bf16_256_threads_last_size", 5, 16384, torch.bfloat16, 0),
+    ("bf16_unaligned_rows", 5, 16385, torch.bfloat16, 0),       # contiguous odd vocabulary: rows start at any element
+    ("bf16_long_fewest_slabs", 5, 65537, torch.bfloat16, 0),    # 16 slabs of 4096 (18 in registers) and one column
+    ("bf16_long_registers_and_lds", 5, 110592, torch.bfloat16, 0),   # 27 whole slabs, no columns left over
+    ("bf16_long_one_slab_twice", 5, 147456 + 4093, torch.bfloat16, 0),
+    ("f32_long_odd_stride", 4, 55299, torch.float32, 3),
+    ("f32_long_many_slabs_twice", 3, 151937, torch.float32, 0),
 ]
 
 
@@ -68,6 +75,36 @@ def test_loss_backward_matches_oracle(seed, name, n, v, dtype, pad):
     assert torch.equal(pd, p_before), "the target must not be written"
     if pad:
         assert torch.equal(zd[:, v:].cpu(), z[:, v:]), "columns past the vocabulary must not be touched"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("v,dtype", [(2000, torch.float32), (30001, torch.float32), (70001, torch.float32), (151937, torch.bfloat16)])
+def test_loss_backward_extreme_rows(v, dtype):
+    """Logits that grow along the row (every vector raises the running maximum), fall along it, are masked
+    with -inf except for a few, start with -inf, or lie at the type's ends of the usual range."""
+    from paper_2603_18567_amd import binding as B
+    _, p, g = make(5, v, dtype, seed=77)
+    z = torch.zeros(5, v)
+    z[0] = torch.linspace(-60, 60, v)
+    z[1] = torch.linspace(60, -60, v)
+    z[2] = float("-inf")
+    z[2, [0, v // 3, v - 1]] = torch.tensor([1.0, 2.0, 3.0])
+    z[3, : v // 2] = float("-inf")
+    z[4] = torch.where(torch.arange(v) % 7 == 0, 3.0e4, -3.0e4)
+    z = z.to(dtype)
+    ref = logsoftmax_loss_bwd(z.float().numpy(), p.float().numpy(), g.numpy())
+    dev = torch.device("cuda:0")
+    zd = z.to(dev)
+    B.ttt_loss_bwd_inplace(zd, p.to(dev), g.to(dev))
+    torch.cuda.synchronize()
+    got = zd.float().cpu().numpy().astype(np.float64)
+    assert np.isfinite(got).all()
+    # as above, row by row; the exponent z log2(e) is rounded at |z| = 60 and 3e4 before the maximum is
+    # subtracted: 2^-24 * |z| * log2(e) * ln 2 relative in exp(z - max), 3.6e-6 at 60 (at 3e4 all terms that count are equal)
+    terms = np.abs(p.double().numpy() * g.double().numpy()[:, None]).max(axis=1)
+    bound = TOL[dtype] * np.maximum(np.abs(ref).max(axis=1), terms)
+    err = np.abs(got - ref).max(axis=1)
+    assert np.all(err <= bound), (err, bound)
 
 
 @pytest.mark.gpu
