@@ -256,10 +256,15 @@ static int fwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
     ps.step_begin = sl.step_begin;
     ps.step_end = sl.step_end;
     const Layout L = make_layout(&ps, TTT_PASS_FWD);
-    int* tok_start = reinterpret_cast<int*>(ws + L.tok_start);
-    int* tok_end = reinterpret_cast<int*>(ws + L.tok_end);
-    hipError_t e = ttt::launch_tok_bounds(cu_dev + sl.doc0, cu_host[sl.doc0], sl.n_docs, sl.tokens, tok_start, tok_end, stream);
-    if (e != hipSuccess) return fail(TTT_ERR_HIP, "token-bounds kernel launch: %s", hipGetErrorString(e));
+    // a few documents: the kernel finds the bounds in cu_seqlens itself, which saves the launch before it
+    int* tok_start = nullptr;
+    hipError_t e = hipSuccess;
+    if (sl.n_docs > ttt::kMaxInlineDocs) {
+        tok_start = reinterpret_cast<int*>(ws + L.tok_start);
+        e = ttt::launch_tok_bounds(cu_dev + sl.doc0, cu_host[sl.doc0], sl.n_docs, sl.tokens, tok_start,
+                                   reinterpret_cast<int*>(ws + L.tok_end), stream);
+        if (e != hipSuccess) return fail(TTT_ERR_HIP, "token-bounds kernel launch: %s", hipGetErrorString(e));
+    }
 
     const size_t esz = p->dtype == TTT_F32 ? 4 : 2;
     const size_t qoff = (size_t)sl.tok0 * (size_t)p->q_stride_token * esz;
@@ -277,6 +282,9 @@ static int fwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
         a.lse[s] = lse[s] ? lse[s] + sl.tok0 : nullptr;
     }
     a.tok_start = tok_start;
+    a.cu = cu_dev + sl.doc0;
+    a.cu_base = cu_host[sl.doc0];
+    a.n_docs = sl.n_docs;
     e = ttt::launch_fwd(p->dtype, p->head_dim, a, stream);
     if (e != hipSuccess) return fail(TTT_ERR_HIP, "forward kernel launch: %s", hipGetErrorString(e));
     return TTT_OK;
@@ -386,11 +394,6 @@ static int bwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
     ps.step_end = sl.step_end;
     const int pass = accumulate_dkv ? TTT_PASS_BWD_ACCUM : TTT_PASS_BWD;
     const Layout L = make_layout(&ps, pass);
-    int* tok_start = reinterpret_cast<int*>(ws + L.tok_start);
-    int* tok_end = reinterpret_cast<int*>(ws + L.tok_end);
-    hipError_t e = ttt::launch_tok_bounds(cu_dev + sl.doc0, cu_host[sl.doc0], sl.n_docs, sl.tokens, tok_start, tok_end, stream);
-    if (e != hipSuccess) return fail(TTT_ERR_HIP, "token-bounds kernel launch: %s", hipGetErrorString(e));
-
     const size_t esz = p->dtype == TTT_F32 ? 4 : 2;
     const size_t qoff = (size_t)sl.tok0 * (size_t)p->q_stride_token * esz;
     const size_t kvoff = (size_t)sl.tok0 * (size_t)p->kv_stride_token * esz;
@@ -410,8 +413,9 @@ static int bwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
         a.dk[s] = const_cast<char*>(at(dk[s], kvoff));
         a.dv[s] = const_cast<char*>(at(dv[s], kvoff));
     }
-    a.tok_start = tok_start;
-    a.tok_end = tok_end;
+    a.tok_start = reinterpret_cast<int*>(ws + L.tok_start);
+    a.tok_end = reinterpret_cast<int*>(ws + L.tok_end);
+    a.cu = cu_dev + sl.doc0;
     a.cu_host = cu_host + sl.doc0;
     a.cu_base = cu_host[sl.doc0];
     a.n_docs = sl.n_docs;
@@ -425,7 +429,7 @@ static int bwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
         a.dkl_acc = reinterpret_cast<float*>(ws + L.dkl);
         a.dvl_acc = reinterpret_cast<float*>(ws + L.dvl);
     }
-    e = ttt::launch_bwd(p->dtype, p->head_dim, a, stream);
+    const hipError_t e = ttt::launch_bwd(p->dtype, p->head_dim, a, stream);
     if (e != hipSuccess) return fail(TTT_ERR_HIP, "backward kernel launch: %s", hipGetErrorString(e));
     return TTT_OK;
 }

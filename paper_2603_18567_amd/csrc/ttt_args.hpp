@@ -31,7 +31,9 @@ struct FwdArgs {
     const void* v[kMaxSteps];
     void* o[kMaxSteps];
     float* lse[kMaxSteps];
-    const int* tok_start;   // [T] first token of each token's document
+    const int* tok_start;   // [T] first token of each token's document, or null: at most 64 documents, found in `cu`
+    const int* cu;          // device cu_seqlens of the documents of this call, first entry = cu_base
+    int cu_base, n_docs;
     int n_tiles;            // query tiles over the packed token axis
     int pack_log2;          // log2 of the query heads (of one kv group) that share a workgroup
     int diag_lds;           // 1: the rows of the diagonal keys are staged in LDS (64-row workgroups)
@@ -49,8 +51,9 @@ struct BwdArgs {
     void* dq[kMaxSteps];
     void* dk[kMaxSteps];
     void* dv[kMaxSteps];
-    const int* tok_start;   // [T]
-    const int* tok_end;     // [T] one past the last token of each token's document
+    int* tok_start;         // [T] first token of each token's document
+    int* tok_end;           // [T] one past its last token
+    const int* cu;          // device cu_seqlens of the documents of this call, first entry = cu_base
     float* delta;           // [n_steps][hq][T]  D = <dO, O>
     float* lse2;            // [n_steps][hq][T]  LSE * log2(e), the exponent offset the kernels use
     float* dk0_acc;         // [T][hkv][d] fp32, block-0 partial sums (atomics)
@@ -66,14 +69,17 @@ struct BwdArgs {
     int n_units;            // dK/dV kernel (16-bit): (key tile, query chunk) units per kv head and split
     int chunk_blocks;       // dK/dV kernel (16-bit): 32-row query blocks per chunk (a multiple of 4)
     HeadMap map_q, map_kv;
+    int cu_base, n_docs;
+    int64_t clear_n4;       // 16-byte pieces of each block-0 sum to clear
+    int pre_blocks;         // workgroups of the preprocess launch that do its main work; after them:
+    int bounds_blocks;      // those that write tok_start, tok_end; and the rest clear the block-0 sums
     // host side only (the launchers' work-split model reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base
-    int cu_base;
-    int n_docs;
 };
 
 // launchers (defined in the kernel files); all enqueue on `stream` and return the launch status
 hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int* tok_start, int* tok_end, hipStream_t stream);
+constexpr int kMaxInlineDocs = 64;   // documents whose bounds the forward kernel finds by itself (one per lane)
 hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream);
 hipError_t launch_bwd(int dtype, int head_dim, BwdArgs& a, hipStream_t stream);
 hipError_t launch_loss_bwd(int dtype, void* logits, const void* target, const float* grad, int64_t n_rows, int vocab,

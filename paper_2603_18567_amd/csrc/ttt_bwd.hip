@@ -33,8 +33,29 @@ template <int LPR> TTT_DEV float group_sum(float v) {
     return v;
 }
 
+// What the streaming passes need besides, done by further workgroups of the same launch (as launches of their own
+// these took longer to start than to run: three of the five or six launches of a short call): document bounds per
+// token, and cleared block-0 sums.
+TTT_DEV void bwd_pre_side_work(const BwdArgs& a, int blk) {
+    const Geometry& geo = a.geo;
+    if (blk < a.bounds_blocks) {
+        const int i = blk * 256 + threadIdx.x;
+        if (i < geo.T) write_doc_bounds(a.cu, a.cu_base, a.n_docs, i, a.tok_start, a.tok_end);
+        return;
+    }
+    const int clear_blocks = (int)gridDim.x - a.pre_blocks - a.bounds_blocks;
+    for (int64_t i = (int64_t)(blk - a.bounds_blocks) * 256 + threadIdx.x; i < a.clear_n4; i += (int64_t)clear_blocks * 256) {
+        reinterpret_cast<f32x4*>(a.dk0_acc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        reinterpret_cast<f32x4*>(a.dv0_acc)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
 template <typename T, int D>
 __global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs a) {
+    if ((int)blockIdx.x >= a.pre_blocks) {
+        bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
+        return;
+    }
     using frag = typename Elem<T>::frag;
     constexpr int LPR = D / 8;       // lanes that share one (token, kv head): 8 elements each
     constexpr int UPB = 256 / LPR;   // (token, kv head) units per workgroup
@@ -154,6 +175,10 @@ template <int LPR> TTT_DEV float group_sum_dpp(float v) {
 template <typename T, int D, int KMAX, int PF>
 __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) {
     static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
+    if ((int)blockIdx.x >= a.pre_blocks) {
+        bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
+        return;
+    }
     using frag = typename Elem<T>::frag;
     constexpr int LPR = D / 8;
     constexpr int UPB = 256 / LPR;
@@ -1370,13 +1395,8 @@ __global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs a) 
 }
 
 // ------------------------------------------------------------------------------------------------
-// small helpers: clear the block-0 accumulators; convert them to the output dtype
+// small helper: the block-0 sums in the output dtype
 // ------------------------------------------------------------------------------------------------
-__global__ void ttt_fill_zero_kernel(f32x4* __restrict__ p, int64_t n4) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += stride) p[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-}
-
 template <typename T, int D>
 __global__ void ttt_bwd_finish_kernel(const BwdArgs a) {
     const Geometry& geo = a.geo;
@@ -1578,27 +1598,18 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
     hipError_t e;
     const int64_t acc_n4 = (int64_t)geo.T * geo.hkv * (D / 4);
 
-    // 1. clear the block-0 accumulators unless a carry from later steps is being continued
-    if (!a.accumulate || a.carry_reset) {
-        ProfileScope prof("ttt_fill_zero_kernel", stream);
-        // the two accumulators follow each other in the workspace (the second one 256-byte aligned):
-        // one launch clears both when nothing lies between them
-        const bool adjacent = a.dv0_acc == a.dk0_acc + 4 * acc_n4;
-        const int64_t n4 = adjacent ? 2 * acc_n4 : acc_n4;
-        const int blocks = (int)((n4 + 255) / 256 < 8192 ? (n4 + 255) / 256 : 8192);
-        hipLaunchKernelGGL(ttt_fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, reinterpret_cast<f32x4*>(a.dk0_acc), n4);
-        if (!adjacent)
-            hipLaunchKernelGGL(ttt_fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, reinterpret_cast<f32x4*>(a.dv0_acc), n4);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-
-    // 2. D and the diagonal blocks
+    // 1. D and the diagonal blocks, the tokens' document bounds, and cleared block-0 sums unless a carry from later
+    // steps is being continued
     {
         constexpr int UPB = 256 / (D / 8);
         const int64_t units = (int64_t)geo.T * geo.hkv;
-        const int64_t grid = (units + UPB - 1) / UPB;
+        const int64_t pre_blocks = (units + UPB - 1) / UPB;
+        a.bounds_blocks = (geo.T + 255) / 256;
+        a.clear_n4 = !a.accumulate || a.carry_reset ? acc_n4 : 0;
+        const int64_t grid = pre_blocks + a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
         const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);
         if (grid > 0x7fffffffLL || lds > 160 * 1024) return hipErrorInvalidValue;
+        a.pre_blocks = (int)pre_blocks;
         constexpr int KREG = 8;   // steps whose diagonal rows and gradients fit the register file
         bool in_regs = false;
         if constexpr (sizeof(T) == 2) in_regs = geo.step_begin + geo.n_steps <= KREG;
@@ -1619,7 +1630,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
-    // 3. dQ and block 0's dK, dV in one launch
+    // 2. dQ and block 0's dK, dV in one launch
     {
         constexpr bool k16 = sizeof(T) == 2;      // eight waves; fp32: four
         constexpr int NW = k16 ? 8 : 4;
@@ -1667,7 +1678,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
-    // 4. block-0 sums -> output dtype, once the sweep has covered step 0
+    // 3. block-0 sums -> output dtype, once the sweep has covered step 0
     if (!a.accumulate || geo.step_begin == 0) {
         const int blocks = (int)((acc_n4 + 255) / 256 < 4096 ? (acc_n4 + 255) / 256 : 4096);
         {

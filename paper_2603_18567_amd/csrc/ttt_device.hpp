@@ -422,6 +422,19 @@ template <> TTT_DEV void gstore_vec4<__bf16>(__bf16* p, float a, float b, float 
     *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
 }
 
+// bounds of token i's document, by binary search in cu_seqlens (`cu` may be a slice of a longer array: `base` = its
+// first entry, subtracted so that the bounds count from the slice's first token)
+TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int base, int n_docs, int i, int* __restrict__ tok_start,
+                              int* __restrict__ tok_end) {
+    int lo = 0, hi = n_docs;   // find the largest r with cu[r] <= i (then cu[r+1] > i)
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (cu[mid] - base <= i) lo = mid; else hi = mid;
+    }
+    tok_start[i] = cu[lo] - base;
+    tok_end[i] = cu[lo + 1] - base;
+}
+
 // Workgroup index -> (kv head, remaining index) so that workgroups that share one kv head's K_0/V_0
 // land on the same XCD (consecutive workgroup ids go round-robin over the 8 XCDs, each with its own
 // L2).  `rest_count` items per kv head; returns false for padding workgroups.

@@ -64,19 +64,38 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
     const T* K0 = static_cast<const T*>(a.k[0]) + (int64_t)g * geo.kv_sh;
     const T* V0 = static_cast<const T*>(a.v[0]) + (int64_t)g * geo.kv_sh;
 
-    // rows of this lane, their clamped copies and document starts
+    // rows of this lane, their clamped copies and document starts; the starts of the wave's first and last row
     int qi[QB], qc[QB], st[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         qi[qb] = wq0 + 32 * qb + n;
         qc[qb] = qi[qb] < Tn ? qi[qb] : Tn - 1;
-        st[qb] = a.tok_start[qc[qb]];
     }
     const int hi_w = min(wq0 + QB * 32 - 1, Tn - 1);
-    const int lo_w = active ? __builtin_amdgcn_readfirstlane(a.tok_start[min(wq0, Tn - 1)]) : 0;
-    const int st_hi = active ? __builtin_amdgcn_readfirstlane(a.tok_start[hi_w]) : 0;
-    const int lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
     const int hi = min(q_tile0 + qt_rows - 1, Tn - 1);
+    int lo, lo_w, st_hi;
+    if (a.tok_start) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) st[qb] = a.tok_start[qc[qb]];
+        lo_w = active ? __builtin_amdgcn_readfirstlane(a.tok_start[min(wq0, Tn - 1)]) : 0;
+        st_hi = active ? __builtin_amdgcn_readfirstlane(a.tok_start[hi_w]) : 0;
+        lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
+    } else {
+        // one document start per lane: the last one at or before the workgroup's first row, then those inside its rows
+        const int starts = a.cu[min(lane, a.n_docs - 1)] - a.cu_base;
+        int r = __popcll(__ballot(lane < a.n_docs && starts <= q_tile0)) - 1;
+        lo = lo_w = st_hi = __builtin_amdgcn_readlane(starts, r);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) st[qb] = lo;
+        for (++r; r < a.n_docs; ++r) {
+            const int s = __builtin_amdgcn_readlane(starts, r);
+            if (s > hi) break;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) st[qb] = s <= qc[qb] ? s : st[qb];
+            lo_w = s <= min(wq0, Tn - 1) ? s : lo_w;
+            st_hi = s <= hi_w ? s : st_hi;
+        }
+    }
     const int u_lo = lo / KT, u_hi = hi / KT;
 
     // Q as the stationary B operand: lane (n,hh) holds Q[row n][16t + 8hh .. +8]
@@ -354,20 +373,11 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
     }
 }
 
-// first / one-past-last token of each token's document, by binary search in cu_seqlens
-// (`cu` may be a slice of a longer cu_seqlens array: `base` = its first entry, subtracted so that
-// the bounds count from the slice's first token)
+// first / one-past-last token of each token's document
 __global__ void ttt_tok_bounds_kernel(const int* __restrict__ cu, int base, int n_docs, int T, int* __restrict__ tok_start,
                                       int* __restrict__ tok_end) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= T) return;
-    int lo = 0, hi = n_docs;   // find the largest r with cu[r] <= i (then cu[r+1] > i)
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (cu[mid] - base <= i) lo = mid; else hi = mid;
-    }
-    tok_start[i] = cu[lo] - base;
-    tok_end[i] = cu[lo + 1] - base;
+    if (i < T) write_doc_bounds(cu, base, n_docs, i, tok_start, tok_end);
 }
 
 hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int* tok_start, int* tok_end, hipStream_t stream) {
