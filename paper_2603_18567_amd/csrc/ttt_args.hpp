@@ -36,8 +36,10 @@ struct FwdArgs {
     int cu_base, n_docs;
     int n_tiles;            // query tiles over the packed token axis
     int pack_log2;          // log2 of the query heads (of one kv group) that share a workgroup
-    int diag_lds;           // 1: the rows of the diagonal keys are staged in LDS (64-row workgroups)
+    int diag_lds;           // 1: the rows of the diagonal keys are staged in LDS (64-row workgroups, 32 with two key groups)
     HeadMap map;
+    // host side only (the launcher's choice of the work split reads the document structure from it)
+    const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base
 };
 
 struct BwdArgs {
@@ -72,6 +74,7 @@ struct BwdArgs {
     int cu_base, n_docs;
     int64_t clear_n4;       // 16-byte pieces of each block-0 sum to clear
     int pre_blocks;         // workgroups of the preprocess launch that do its main work; after them:
+    int pre_passes;         // (16-bit) in so many passes over the later blocks
     int bounds_blocks;      // those that write tok_start, tok_end; and the rest clear the block-0 sums
     // host side only (the launchers' work-split model reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base

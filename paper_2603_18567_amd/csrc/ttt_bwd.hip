@@ -168,11 +168,13 @@ template <int LPR> TTT_DEV float group_sum_dpp(float v) {
     return v;
 }
 
-// The same work for 16-bit types and at most KMAX steps, reading every Q_j, dO_j, O_j row exactly
-// once: the K_l, V_l rows of this (token, kv head) and their fp32 gradients stay in registers while
-// one sweep over (step, head of the group) feeds all of them (the suffix part of Alg. 2 read from the
-// key's side: key (l, i) is seen only by the queries (j >= l, i) of Sec. 2.4's unrolled steps).
-template <typename T, int D, int KMAX, int PF>
+// The same work for 16-bit types, reading every Q_j, dO_j, O_j row once: the K_l, V_l rows of this (token, kv
+// head) and their fp32 gradients stay in registers while one sweep over (step, head of the group) feeds all of
+// them (the suffix part of Alg. 2 read from the key's side: key (l, i) is seen only by the queries (j >= l, i)
+// of Sec. 2.4's unrolled steps).  NL blocks fit; with more steps the blocks are taken NL at a time by further
+// workgroups, whose sweeps start at the first step that sees one of theirs (16384 tokens in documents of up to
+// 12 steps, mean of the launches with more than 8: 195 us; 379 when every block read its steps' rows again).
+template <typename T, int D, int NL, int PF>
 __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) {
     static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
     if ((int)blockIdx.x >= a.pre_blocks) {
@@ -182,12 +184,15 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
     using frag = typename Elem<T>::frag;
     constexpr int LPR = D / 8;
     constexpr int UPB = 256 / LPR;
-    constexpr int NL = KMAX - 1;
 
     const Geometry& geo = a.geo;
     const int Tn = geo.T, G = geo.G, ns = geo.n_steps, b = geo.step_begin, e = b + ns;
+    const int per_pass = a.pre_blocks / a.pre_passes;
+    const int pass = (int)blockIdx.x / per_pass;
+    const int l0 = 1 + pass * NL;                   // first block of this pass
+    const int j0 = pass > 0 ? max(b, l0) : b;       // first step of its sweep; the first pass also makes D
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-    const int64_t unit = (int64_t)blockIdx.x * UPB + grp;
+    const int64_t unit = (int64_t)((int)blockIdx.x % per_pass) * UPB + grp;
     if (unit >= (int64_t)Tn * geo.hkv) return;   // whole aligned lane groups leave together
     const int i = (int)(unit / geo.hkv);
     const int g = (int)(unit % geo.hkv);
@@ -197,9 +202,10 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
     float dk[NL][8], dv[NL][8];
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-        const int lb = l + 1 < e ? l + 1 : 0;     // unused slots read block 0's row (in bounds), never used
-        kf[l] = gload_frag<T>(static_cast<const T*>(a.k[lb]) + kvoff);
-        vf[l] = gload_frag<T>(static_cast<const T*>(a.v[lb]) + kvoff);
+        if (l0 + l < e) {
+            kf[l] = gload_frag<T>(static_cast<const T*>(a.k[l0 + l]) + kvoff);
+            vf[l] = gload_frag<T>(static_cast<const T*>(a.v[l0 + l]) + kvoff);
+        }
 #pragma unroll
         for (int x = 0; x < 8; ++x) dk[l][x] = dv[l][x] = 0.f;
     }
@@ -208,12 +214,12 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
     // before a pair is worked on, so that a lane group always has PF requests in flight beside the pair
     // it works on (the kernel is bound by HBM; measured at 4096 tokens, 0.98 GB per launch: no request
     // ahead 4.45 TB/s, one 4.75, two 5.07, four -- with one block fewer in registers -- 5.07).
-    const int n_pairs = ns * G;
+    const int n_pairs = (e - j0) * G;
     frag qf[PF], go[PF], oo[PF];
     float lse_raw[PF];
     auto request = [&](int n, auto slot_c) {
         constexpr int S = decltype(slot_c)::value;
-        const int j = b + n / G, h = g * G + n % G;
+        const int j = j0 + n / G, h = g * G + n % G;
         const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh + sub * 8;
         qf[S] = gload_frag<T>(static_cast<const T*>(a.q[j]) + off);
         go[S] = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
@@ -226,7 +232,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
     if constexpr (PF > 3) if (n_pairs > 3) request(3, IntC<3>{});
     static_assert(PF >= 1 && PF <= 4, "prefetch depth");
     for (int n = 0; n < n_pairs; ++n) {
-        const int js = n / G, j = b + js, h = g * G + n % G;
+        const int j = j0 + n / G, h = g * G + n % G;
         const frag cq = qf[0], cg = go[0], co = oo[0];
         const float lse2 = lse_raw[0] * kLog2e;
 #pragma unroll
@@ -238,8 +244,8 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
         }
         if (n + PF < n_pairs) request(n + PF, IntC<PF - 1>{});
         const float dsum = group_sum_dpp<LPR>(dot8(cg, co, 0.f));
-        if (sub == 0) {
-            const int64_t at = ((int64_t)js * geo.hq + h) * Tn + i;
+        if (sub == 0 && pass == 0) {
+            const int64_t at = ((int64_t)(j - b) * geo.hq + h) * Tn + i;
             a.delta[at] = dsum;
             a.lse2[at] = lse2;
         }
@@ -251,7 +257,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
         }
 #pragma unroll
         for (int l = 0; l < NL; ++l) {
-            if (l + 1 > j) break;              // block l+1 is visible from step j >= l+1 only
+            if (l0 + l > j) break;             // a block is visible from the step of its own number on
             const float s = group_sum_dpp<LPR>(dot8(cq, kf[l], 0.f));
             const float dp = group_sum_dpp<LPR>(dot8(cg, vf[l], 0.f));
             const float p = fast_exp2(s * (geo.scale * kLog2e) - lse2);
@@ -266,11 +272,11 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
 
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
-        const int lb = l + 1;
+        const int lb = l0 + l;
         if (lb >= e) break;
         if (a.accumulate) {
             // fp32 carry across the calls of a descending-step sweep; this group owns its slice
-            const int64_t coff = (((int64_t)l * Tn + i) * geo.hkv + g) * D + sub * 8;
+            const int64_t coff = (((int64_t)(lb - 1) * Tn + i) * geo.hkv + g) * D + sub * 8;
             f32x4* ck = reinterpret_cast<f32x4*>(a.dkl_acc + coff);
             f32x4* cv = reinterpret_cast<f32x4*>(a.dvl_acc + coff);
             if (!a.carry_reset) {
@@ -284,12 +290,14 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
                     }
                 }
             }
+            if (lb < b) {   // not complete yet: earlier steps' calls have not run
 #pragma unroll
-            for (int v4 = 0; v4 < 2; ++v4) {
-                ck[v4] = f32x4{dk[l][4 * v4], dk[l][4 * v4 + 1], dk[l][4 * v4 + 2], dk[l][4 * v4 + 3]};
-                cv[v4] = f32x4{dv[l][4 * v4], dv[l][4 * v4 + 1], dv[l][4 * v4 + 2], dv[l][4 * v4 + 3]};
+                for (int v4 = 0; v4 < 2; ++v4) {
+                    ck[v4] = f32x4{dk[l][4 * v4], dk[l][4 * v4 + 1], dk[l][4 * v4 + 2], dk[l][4 * v4 + 3]};
+                    cv[v4] = f32x4{dv[l][4 * v4], dv[l][4 * v4 + 1], dv[l][4 * v4 + 2], dv[l][4 * v4 + 3]};
+                }
+                continue;
             }
-            if (lb < b) continue;   // not complete yet: earlier steps' calls have not run
         }
         T* gk = static_cast<T*>(a.dk[lb]) + kvoff;
         T* gv = static_cast<T*>(a.dv[lb]) + kvoff;
@@ -1592,6 +1600,8 @@ static DkvPlan plan_dkv_split(const BwdArgs& a, int head_dim, int n_cu) {
     return best;
 }
 
+constexpr int kPreRegBlocks = 7;   // later blocks whose rows and gradients fit the registers of the preprocess kernel
+
 template <typename T, int D>
 static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
     const Geometry& geo = a.geo;
@@ -1603,21 +1613,18 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
     {
         constexpr int UPB = 256 / (D / 8);
         const int64_t units = (int64_t)geo.T * geo.hkv;
-        const int64_t pre_blocks = (units + UPB - 1) / UPB;
+        a.pre_passes = 1;
+        if constexpr (sizeof(T) == 2) a.pre_passes = std::max(1, (geo.step_begin + geo.n_steps - 2 + kPreRegBlocks) / kPreRegBlocks);
+        const int64_t pre_blocks = (units + UPB - 1) / UPB * a.pre_passes;
         a.bounds_blocks = (geo.T + 255) / 256;
         a.clear_n4 = !a.accumulate || a.carry_reset ? acc_n4 : 0;
         const int64_t grid = pre_blocks + a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
         const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);
         if (grid > 0x7fffffffLL || lds > 160 * 1024) return hipErrorInvalidValue;
         a.pre_blocks = (int)pre_blocks;
-        constexpr int KREG = 8;   // steps whose diagonal rows and gradients fit the register file
-        bool in_regs = false;
-        if constexpr (sizeof(T) == 2) in_regs = geo.step_begin + geo.n_steps <= KREG;
-        if (in_regs) {
-            if constexpr (sizeof(T) == 2) {
-                ProfileScope prof("ttt_bwd_pre_regs_kernel", stream);
-                hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D, KREG, 2>), dim3((unsigned)grid), dim3(256), 0, stream, a);
-            }
+        if constexpr (sizeof(T) == 2) {
+            ProfileScope prof("ttt_bwd_pre_regs_kernel", stream);
+            hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D, kPreRegBlocks, 2>), dim3((unsigned)grid), dim3(256), 0, stream, a);
         } else {
             auto kern = ttt_bwd_pre_kernel<T, D>;
             if (lds > 48 * 1024) {
