@@ -285,6 +285,7 @@ static int fwd_slice(const ttt_attn_params* p, const Slice& sl, const void* cons
     a.cu = cu_dev + sl.doc0;
     a.cu_base = cu_host[sl.doc0];
     a.n_docs = sl.n_docs;
+    a.cu_host = cu_host + sl.doc0;
     e = ttt::launch_fwd(p->dtype, p->head_dim, a, stream);
     if (e != hipSuccess) return fail(TTT_ERR_HIP, "forward kernel launch: %s", hipGetErrorString(e));
     return TTT_OK;

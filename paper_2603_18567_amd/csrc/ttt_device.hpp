@@ -172,6 +172,14 @@ template <typename T, int D> struct LaneFrags {
     TTT_DEV frag transposed(const char* tile, int c16, int db) const {
         return frag_transposed<T, D>(tile, c16 * 16, db * 32, lane);
     }
+    // the same with tiles given as byte offsets from the start of the workgroup's LDS
+    const char* lds;
+    TTT_DEV void init_at(const char* lds_, int lane_) {
+        lds = lds_;
+        init(lane_);
+    }
+    TTT_DEV frag rowwise_at(uint32_t tile, int rb, int t) const { return rowwise(lds + tile, rb, t); }
+    TTT_DEV frag transposed_at(uint32_t tile, int c16, int db) const { return transposed(lds + tile, c16, db); }
 };
 template <int D> struct LaneFrags<__bf16, D> {
     using TL = Tile<__bf16, D>;
@@ -197,6 +205,31 @@ template <int D> struct LaneFrags<__bf16, D> {
         union { s16x4 s[2]; bf16x8 v; } u;
         u.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(base + tr[db][0]));
         u.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(base + tr[db][1]));
+        return u.v;
+    }
+    // The same with tiles given as byte offsets from `lds` (a wave's place in the workgroup's LDS), in 32-bit
+    // address arithmetic: what is constant in a tile's offset is then an immediate of the read, where a sum of
+    // pointers becomes one address register per read (64 of the forward kernel's 256).
+    TTT_DEV void init_at(const char* lds, int lane) {
+        init(lane);
+        const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const char*)lds;
+#pragma unroll
+        for (int t = 0; t < D / 16; ++t) row[t] += at;
+#pragma unroll
+        for (int db = 0; db < D / 32; ++db) {
+            tr[db][0] += at;
+            tr[db][1] += at;
+        }
+    }
+    TTT_DEV bf16x8 rowwise_at(uint32_t tile, int rb, int t) const {
+        return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>((uintptr_t)(row[t] + (tile + rb * 32 * TL::kRowBytes)));
+    }
+    TTT_DEV bf16x8 transposed_at(uint32_t tile, int c16, int db) const {
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        const uint32_t off = tile + c16 * 16 * TL::kRowBytes;
+        union { s16x4 s[2]; bf16x8 v; } u;
+        u.s[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(tr[db][0] + off));
+        u.s[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(tr[db][1] + off));
         return u.v;
     }
 };

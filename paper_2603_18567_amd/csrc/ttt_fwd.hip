@@ -3,6 +3,8 @@
 // cache blocks (suffix part of Alg. 2) row by row on the vector ALU.
 //
 // Work split: one workgroup = one tile of QT consecutive packed tokens x one query head x one step.
+// With two key groups (KS = 2, for launches that would end with a few long workgroups) the halves of a
+// workgroup take every second key tile of the same rows and meet at the end, in LDS.
 // Each wave owns QB blocks of 32 query rows and keeps, per lane, everything that belongs to ONE
 // query row: scores are computed transposed (S^T = K Q^T) so that the accumulator's column index --
 // the lane -- is the query row; running max / sum / rescale are then per-lane scalars and the only
@@ -12,29 +14,33 @@
 // Tiles are cut over the packed token axis, not per document: a row's visible prefix is
 // [tok_start[i], i], so a wave visits the kv tiles that intersect [tok_start[first row], last row]
 // and nothing else; tiles strictly inside that range for every row skip the mask code.
+#include <algorithm>
 #include <type_traits>
 
 #include "ttt_args.hpp"
 
 namespace ttt {
 
-template <typename T, int D, int QB, int NW, int MINB>
-__global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a) {
+template <typename T, int D, int QB, int NW, int KS>
+__global__ __launch_bounds__(NW * 64) void ttt_fwd_kernel(const FwdArgs a) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;                // kv rows per LDS tile
     constexpr int KB = KT / 32;
-    constexpr int QT = NW * QB * 32;
+    constexpr int NWG = NW / KS;          // waves of a key group
+    constexpr int QT = NWG * QB * 32;
     constexpr int DC = D / 16;            // contraction chunks over head_dim
     constexpr int DB = D / 32;            // 32-wide blocks of head_dim
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
     constexpr float kLazy = 8.f;          // log2 of the largest p tolerated before the reference max moves
-    constexpr bool kDiagLds = sizeof(T) == 2 && KT == 64;   // diagonal rows may be staged in LDS (64-row tiles)
-    constexpr int kDiagSlots = 3;         // blocks whose rows are staged at once
+    constexpr bool kDiagLds = sizeof(T) == 2 && KT == 64;   // diagonal rows may be staged in LDS
+    constexpr int kDiagRows = 64 / KS;    // of workgroups of so many rows
+    constexpr int kDiagSlots = KS == 1 ? 3 : 2;   // blocks whose rows are staged at once
 
     extern __shared__ __align__(16) char smem[];
-    // LDS: K stage 0, K stage 1, V stage 0, V stage 1
+    // LDS of a key group: K stage 0, K stage 1, V stage 0, V stage 1
+    constexpr int GROUP_BYTES = 4 * TILE_BYTES;
     auto sK = [&](int s) -> char* { return smem + s * TILE_BYTES; };
     auto sV = [&](int s) -> char* { return smem + (2 + s) * TILE_BYTES; };
 
@@ -52,12 +58,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
     const int tile = a.n_tiles - 1 - rest / geo.n_steps;   // long-prefix tiles first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int h = g * geo.G + (hgrp << pk) + (wave & ((1 << pk) - 1));
+    const int kg = KS == 1 ? 0 : wave / NWG, gwave = wave % NWG;   // key group, wave within it
+    const int h = g * geo.G + (hgrp << pk) + (gwave & ((1 << pk) - 1));
     const int n = lane & 31, hh = lane >> 5;
     const int Tn = geo.T;   // packed tokens
     const int qt_rows = QT >> pk;   // rows of a workgroup
     const int q_tile0 = tile * qt_rows;
-    const int wq0 = q_tile0 + (wave >> pk) * (QB * 32);
+    const int wq0 = q_tile0 + (gwave >> pk) * (QB * 32);
     const bool active = wq0 < Tn;
 
     const T* Qj = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
@@ -120,7 +127,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
     const float c = geo.scale_log2;
 
     LaneFrags<T, D> lf;
-    lf.init(lane);
+    lf.init_at(smem + kg * GROUP_BYTES, lane);
 
     // K_0 / V_0 rows of tile u -> stage s.  Tiles that lie inside the tensor (all but the last one)
     // take the copy with precomputed lane offsets.
@@ -128,29 +135,37 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
     struct NoCopy { TTT_DEV void init(int64_t, int) {} };
     typename std::conditional<kFastCopy, TileCopy<T, D, KT, NT>, NoCopy>::type tile_copy;
     tile_copy.init(geo.kv_st, tid);
-    auto load_tile = [&](int s, int u) {
-        if constexpr (kFastCopy) {
-            if ((u + 1) * KT <= Tn) {
-                const int64_t first = (int64_t)u * KT * geo.kv_st;
-                tile_copy.copy(lds_addr(sK(s)), K0 + first);
-                tile_copy.copy(lds_addr(sV(s)), V0 + first);
-                return;
+    auto load_tile = [&](int s, int u0) {
+#pragma unroll
+        for (int x = 0; x < KS; ++x) {
+            const int u = u0 + x;
+            if (KS > 1 && u > u_hi) break;
+            char* const tk = sK(s) + x * GROUP_BYTES;
+            char* const tv = sV(s) + x * GROUP_BYTES;
+            if constexpr (kFastCopy) {
+                if ((u + 1) * KT <= Tn) {
+                    const int64_t first = (int64_t)u * KT * geo.kv_st;
+                    tile_copy.copy(lds_addr(tk), K0 + first);
+                    tile_copy.copy(lds_addr(tv), V0 + first);
+                    continue;
+                }
             }
+            int tid_here = tid;
+            if constexpr (KS > 1) asm volatile("" : "+v"(tid_here));   // computed here, not carried through the main loop
+            tile_load_async<T, D, KT, NT>(tk, K0, geo.kv_st, u * KT, Tn - 1, tid_here);
+            tile_load_async<T, D, KT, NT>(tv, V0, geo.kv_st, u * KT, Tn - 1, tid_here);
         }
-        tile_load_async<T, D, KT, NT>(sK(s), K0, geo.kv_st, u * KT, Tn - 1, tid);
-        tile_load_async<T, D, KT, NT>(sV(s), V0, geo.kv_st, u * KT, Tn - 1, tid);
     };
 
-    // one kv tile: wait for its copy, start the next one into the other stage, compute from this one
+    // one kv tile (of each key group): wait for its copy, start the next one into the other stage, compute from this one
     auto step = [&](auto stage_c, int u) {
         constexpr int ST = decltype(stage_c)::value;
         wait_async_copies();
         __syncthreads();   // tile u is in LDS for everyone; everyone is done with the other stage
-        if (u < u_hi) load_tile(ST ^ 1, u + 1);
-        const int kv0 = u * KT;
+        if (u + KS <= u_hi) load_tile(ST ^ 1, u + KS);
+        const int kv0 = (u + kg) * KT;
         if (!(active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w)) return;
-        const char* tk = smem + ST * TILE_BYTES;
-        const char* tv = smem + (2 + ST) * TILE_BYTES;
+        constexpr uint32_t tk = ST * TILE_BYTES, tv = (2 + ST) * TILE_BYTES;
         // S^T[kv, q] = K Q^T
         f32x16 sacc[KB][QB];
 #pragma unroll
@@ -163,7 +178,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
         for (int t = 0; t < DC; ++t) {
             frag kf[KB];
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) kf[kb] = lf.rowwise(tk, kb, t);
+            for (int kb = 0; kb < KB; ++kb) kf[kb] = lf.rowwise_at(tk, kb, t);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
@@ -224,7 +239,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
             for (int qb = 0; qb < QB; ++qb) pf[qb] = acc_chunk<T>(sacc[c4 / 2][qb], c4 % 2);
 #pragma unroll
             for (int db = 0; db < DB; ++db) {
-                const frag vf = lf.transposed(tv, c4, db);
+                const frag vf = lf.transposed_at(tv, c4, db);
 #pragma unroll
                 for (int qb = 0; qb < QB; ++qb) oacc[qb][db] = mma(vf, pf[qb], oacc[qb][db]);
             }
@@ -273,36 +288,39 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
         // the rows of up to kDiagSlots blocks are copied into LDS at once, behind the tile stages, so
         // their latency is paid once per group of blocks, not once per block, and once per kv group,
         // not once per head.  j is the same for the whole workgroup: the barriers are uniform.
+        // (With two key groups: workgroups of 32 rows, and every second block goes to each group.)
         if constexpr (kDiagLds) {
-            char* dbase = smem + 4 * TILE_BYTES;
+            constexpr int DIAG_BYTES = kDiagRows * D * E::kBytes;
+            char* dbase = smem + KS * GROUP_BYTES;
             for (int base = 1; base <= j; base += kDiagSlots) {
                 const int nb = min(kDiagSlots, j - base + 1);
                 if (base > 1) __syncthreads();   // the slots are free again
                 for (int i = 0; i < nb; ++i) {
                     const T* Kl = static_cast<const T*>(a.k[base + i]) + (int64_t)g * geo.kv_sh;
                     const T* Vl = static_cast<const T*>(a.v[base + i]) + (int64_t)g * geo.kv_sh;
-                    tile_load_async<T, D, 64, NT>(dbase + (2 * i) * TILE_BYTES, Kl, geo.kv_st, q_tile0, Tn - 1, tid);
-                    tile_load_async<T, D, 64, NT>(dbase + (2 * i + 1) * TILE_BYTES, Vl, geo.kv_st, q_tile0, Tn - 1, tid);
+                    tile_load_async<T, D, kDiagRows, NT>(dbase + (2 * i) * DIAG_BYTES, Kl, geo.kv_st, q_tile0, Tn - 1, tid);
+                    tile_load_async<T, D, kDiagRows, NT>(dbase + (2 * i + 1) * DIAG_BYTES, Vl, geo.kv_st, q_tile0, Tn - 1, tid);
                 }
                 wait_async_copies();
                 __syncthreads();
                 if (active) {
                     const int rb = (wq0 - q_tile0) / 32;   // this wave's first row block inside the workgroup's rows
-                    for (int i = 0; i < nb; ++i) {
+                    for (int i = kg; i < nb; i += KS) {
+                        const uint32_t drow = KS * GROUP_BYTES + (2 * i) * DIAG_BYTES - kg * GROUP_BYTES;
                         frag dk[QB][DC], dv[QB][DC];
 #pragma unroll
                         for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
                             for (int t = 0; t < DC; ++t) {
-                                dk[qb][t] = lf.rowwise(dbase + (2 * i) * TILE_BYTES, rb + qb, t);
-                                dv[qb][t] = lf.rowwise(dbase + (2 * i + 1) * TILE_BYTES, rb + qb, t);
+                                dk[qb][t] = lf.rowwise_at(drow, rb + qb, t);
+                                dv[qb][t] = lf.rowwise_at(drow + DIAG_BYTES, rb + qb, t);
                             }
                         diag_key(dk, dv);
                     }
                 }
             }
         }
-    } else if (active && j >= 1) {
+    } else if (active && j >= 1 + kg) {
         // the fragments of block lb + 1 are requested from global memory before block lb is consumed
         frag dk[QB][DC], dv[QB][DC], nk[QB][DC], nv[QB][DC];
         auto request = [&](int lb, frag (&rk)[QB][DC], frag (&rv)[QB][DC]) {
@@ -319,9 +337,9 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
                 }
             }
         };
-        request(1, dk, dv);
-        for (int lb = 1; lb <= j; ++lb) {
-            if (lb < j) request(lb + 1, nk, nv);
+        request(1 + kg, dk, dv);
+        for (int lb = 1 + kg; lb <= j; lb += KS) {
+            if (lb + KS <= j) request(lb + KS, nk, nv);
             diag_key(dk, dv);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
@@ -333,17 +351,55 @@ __global__ __launch_bounds__(NW * 64, MINB) void ttt_fwd_kernel(const FwdArgs a)
         }
     }
 
-    for (int u = u_lo; u <= u_hi; u += 2) {
+    for (int u = u_lo; u <= u_hi; u += 2 * KS) {
         step(IntC<0>{}, u);
-        if (u + 1 <= u_hi) step(IntC<1>{}, u + 1);
+        if (u + KS <= u_hi) step(IntC<1>{}, u + KS);
     }
 
     // normalise; rows go through a wave-private LDS patch (carved out of the tile stages, which
     // everybody has finished reading after this barrier) so that every global store is a full
     // 16-byte piece of a row and a wave instruction covers whole rows
     __syncthreads();
+    if constexpr (KS == 2) {
+        // The second key group's rows join the first one's: reference maximum, sum and O of the same lane of wave
+        // gwave, as 16-byte pieces side by side.  A group that saw no key of a row brings m = -inf, l = 0, O = 0.
+        static_assert(NWG * QB * (DB * 4 + 1) * 1024 <= KS * GROUP_BYTES, "one group's rows fit in the tile stages");
+        f32x4* piece = reinterpret_cast<f32x4*>(smem) + gwave * (QB * (DB * 4 + 1) * 64) + lane;
+        if (kg == 1) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        piece[(qb * (DB * 4 + 1) + db * 4 + i4) * 64] =
+                            f32x4{oacc[qb][db][4 * i4], oacc[qb][db][4 * i4 + 1], oacc[qb][db][4 * i4 + 2], oacc[qb][db][4 * i4 + 3]};
+                piece[(qb * (DB * 4 + 1) + DB * 4) * 64] = f32x4{m[qb], l[qb], 0.f, 0.f};
+            }
+        }
+        __syncthreads();
+        if (kg == 1) return;
+        if (active) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                const f32x4 ml = piece[(qb * (DB * 4 + 1) + DB * 4) * 64];
+                const float m_new = fmaxf(m[qb], ml[0]);   // one of them is finite: a row sees its own key
+                const float a0 = fast_exp2((m[qb] - m_new) * c), a1 = fast_exp2((ml[0] - m_new) * c);
+                m[qb] = m_new;
+                l[qb] = l[qb] * a0 + ml[1] * a1;
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4) {
+                        const f32x4 o4 = piece[(qb * (DB * 4 + 1) + db * 4 + i4) * 64];
+#pragma unroll
+                        for (int x = 0; x < 4; ++x) oacc[qb][db][4 * i4 + x] = oacc[qb][db][4 * i4 + x] * a0 + o4[x] * a1;
+                    }
+            }
+        }
+    }
     if (!active) return;
-    char* patch = smem + wave * (32 * D * E::kBytes);
+    char* patch = smem + (KS == 1 ? 0 : NWG * QB * (DB * 4 + 1) * 1024) + gwave * (32 * D * E::kBytes);
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         const float lt = half_sum(l[qb]);
@@ -388,26 +444,18 @@ hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int
     return hipGetLastError();
 }
 
-template <typename T, int D, int QB, int NW, int MINB> struct FwdCfg {
-    static constexpr int kQT = NW * QB * 32;
-    static constexpr int kLds = 4 * 64 * D * (int)sizeof(T);   // two stages of K and V tiles
-    static constexpr int kDiagLds = 3 * 2 * 64 * D * (int)sizeof(T);   // three blocks of 64 diagonal K and V rows
-};
-
-template <typename T, int D, int QB, int NW, int MINB> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
-    using C = FwdCfg<T, D, QB, NW, MINB>;
-    auto kern = ttt_fwd_kernel<T, D, QB, NW, MINB>;
+template <typename T, int D, int QB, int NW, int KS> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
+    constexpr int LDS_TILES = 4 * KS * 64 * D * (int)sizeof(T);   // two stages of K and V tiles
+    constexpr int DIAG_ROWS = 64 / KS;
+    constexpr int LDS_DIAG = (KS == 1 ? 3 : 2) * 2 * DIAG_ROWS * D * (int)sizeof(T);   // the rows of so many blocks' diagonal keys
+    auto kern = ttt_fwd_kernel<T, D, QB, NW, KS>;
     static LdsOptIn lds_opt_in;
-    if (hipError_t e = lds_opt_in.ensure((const void*)kern, C::kLds + (sizeof(T) == 2 ? C::kDiagLds : 0)); e != hipSuccess) return e;
+    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS_TILES + (sizeof(T) == 2 ? LDS_DIAG : 0)); e != hipSuccess) return e;
     const Geometry& geo = a.geo;
-    // as many heads of a kv group per workgroup as divide both the group and the waves (at most 4:
-    // a workgroup keeps at least 64 rows)
-    a.pack_log2 = 0;
-    while ((2 << a.pack_log2) <= 4 && geo.G % (2 << a.pack_log2) == 0 && NW % (2 << a.pack_log2) == 0) ++a.pack_log2;
-    const int qt_rows = C::kQT >> a.pack_log2;
+    const int qt_rows = (NW / KS * QB * 32) >> a.pack_log2;
     a.n_tiles = (geo.T + qt_rows - 1) / qt_rows;
-    a.diag_lds = sizeof(T) == 2 && qt_rows == 64;   // the diagonal rows of a 64-row workgroup go through LDS
-    const int lds_bytes = C::kLds + (a.diag_lds ? C::kDiagLds : 0);
+    a.diag_lds = sizeof(T) == 2 && qt_rows == DIAG_ROWS;
+    const int lds_bytes = LDS_TILES + (a.diag_lds ? LDS_DIAG : 0);
     a.map.hkv = geo.hkv;
     a.map.rest_count = a.n_tiles * geo.n_steps * (geo.G >> a.pack_log2);
     int64_t grid;
@@ -431,8 +479,51 @@ template <typename T, int D, int QB, int NW, int MINB> static hipError_t launch_
     return hipGetLastError();
 }
 
+// Which work split ends first: one key group (all eight waves share a 64-key tile) or two (each tile pair's tiles go
+// to the two halves of the workgroup, which covers half as many rows).  Two groups halve the longest
+// workgroup -- a causal launch of one step at 2048 tokens is one workgroup per compute unit, and ends with the
+// one that has all the keys -- but copy every tile for half as many waves and pay set-up, merge and epilogue
+// twice as often.  Estimate per split: the longest workgroup, or the work of all over the compute units,
+// whichever is more.  Measured (16-bit, head_dim 128, us): a workgroup 3, a tile 1.55 while the device is not
+// full and 1.85 when it is, a tile pair 2.0 and 2.2, a diagonal key 2.0 and 1.3 through LDS and twice that
+// otherwise.  One step, 32/8 heads: 1024 tokens 40 -> 29 us, 2048 70 -> 59, 3000 98 (114 with two groups); all
+// seven steps at 2048 293 (373).
+static bool two_key_groups_end_first(const FwdArgs& a, int n_cu) {
+    const Geometry& geo = a.geo;
+    const int rows = (8 * 32) >> a.pack_log2;      // of a workgroup with one key group
+    const int64_t per_tile = (int64_t)geo.hkv * (geo.G >> a.pack_log2) * geo.n_steps;
+    if ((int64_t)(geo.T + rows - 1) / rows * per_tile > 6 * n_cu) return false;   // many rounds: the work decides
+    const double j_mean = geo.step_begin + 0.5 * (geo.n_steps - 1), j_max = geo.step_begin + geo.n_steps - 1;
+    double est[2];
+    for (int ks = 1; ks <= 2; ++ks) {
+        const int r = rows / ks;
+        const double diag = (ks == 1 ? 2.0 : 1.3) * (r * ks == 64 ? 1. : 2.);
+        int doc = 0;
+        int64_t steps = 0, n = 0, most = 0;
+        for (int row = 0; row < geo.T; row += r, ++n) {
+            while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
+            const int64_t tiles = std::min(row + r - 1, geo.T - 1) / 64 - (a.cu_host[doc] - a.cu_base) / 64 + 1;
+            const int64_t s = (tiles + ks - 1) / ks;
+            steps += s;
+            most = std::max(most, s);
+        }
+        const double longest = 3. + most * (ks == 1 ? 1.55 : 2.0) + j_max * diag;
+        const double work = (n * (3. + j_mean * diag) + steps * (ks == 1 ? 1.85 : 2.2)) * (double)per_tile / n_cu;
+        est[ks - 1] = std::max(longest, work);
+    }
+    return est[1] < 0.97 * est[0];
+}
+
 hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
-    if (dtype == 1 && head_dim == 128) return launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
+    // as many heads of a kv group per workgroup as divide the group, at most 4
+    a.pack_log2 = 0;
+    while ((2 << a.pack_log2) <= 4 && a.geo.G % (2 << a.pack_log2) == 0) ++a.pack_log2;
+    if (dtype == 1 && head_dim == 128) {
+        int n_cu = 0;
+        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
+        if (two_key_groups_end_first(a, n_cu)) return launch_fwd_t<__bf16, 128, 1, 8, 2>(a, stream);
+        return launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
+    }
     if (dtype == 1 && head_dim == 64) return launch_fwd_t<__bf16, 64, 2, 4, 1>(a, stream);
     if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, stream);
     if (dtype == 0 && head_dim == 64) return launch_fwd_t<float, 64, 1, 4, 1>(a, stream);

@@ -1,0 +1,32 @@
+"""GPU parity of the forward where a workgroup's waves are split into two key groups (launches of few, long
+workgroups): rows whose keys all lie in one group's tiles, an odd number of tiles, ragged last rows, document
+starts inside a tile pair, 4, 2 and 1 query heads per workgroup, and no, one, two and more diagonal keys."""
+import pytest
+import torch
+
+from paper_2603_18567_amd.workloads import custom_workload
+from ttt_testlib import Case, compare_full
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    ("one_tile", [50], 8, 2, 2),
+    ("two_tiles_ragged", [127], 8, 2, 3),
+    ("odd_tiles", [321], 4, 1, 4),
+    ("documents_inside_tile_pairs", [70, 1, 130, 64, 33], 8, 2, 4),
+    ("two_heads_per_workgroup", [200, 95], 12, 2, 5),
+    ("one_head_per_workgroup", [260, 3], 3, 3, 4),
+]
+
+
+@pytest.mark.parametrize("name,docs,hq,hkv,k", CASES, ids=[c[0] for c in CASES])
+def test_two_key_groups_match_oracle(name, docs, hq, hkv, k):
+    print(f"case {name} documents={docs} heads={hq}/{hkv} k={k}", flush=True)
+    wl = custom_workload(f"groups_{name}", "bf16", docs, hq, hkv, 128, k, seed=len(docs) + 5)
+    case = Case(wl, "cuda:0")
+    for j in range(k):
+        case.run.forward(j, j + 1)
+    case.run.backward(case.d_o)
+    torch.cuda.synchronize()
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
