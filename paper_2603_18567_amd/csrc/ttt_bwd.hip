@@ -507,7 +507,7 @@ TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
 // blocks of 32, each taken through S^T, dP^T, dS^T and the dQ^T update in turn, with the LDS
 // fragments of the next matrix instructions requested ahead.  Eight waves (two per SIMD) overlap
 // one wave's vector work with the other's matrix work.
-// LDS: two stages of [K tile | V tile]; the stage bit is bit 16 of the per-lane addresses.
+// LDS: two stages of [K tile | V tile], which differ in one bit of the per-lane addresses.
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int NW>
 TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
@@ -523,8 +523,8 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
     constexpr int DB = D / 32;
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
-    constexpr int STAGE_BYTES = 1 << 16;
-    static_assert(2 * TILE_BYTES <= STAGE_BYTES, "stage layout");
+    constexpr int STAGE_BYTES = 2 * TILE_BYTES;
+    static_assert((STAGE_BYTES & (STAGE_BYTES - 1)) == 0, "the stages differ in one address bit");
     constexpr int NE = 2 * DB;   // matrix instructions of one dQ block update
     constexpr int PDR = 2;       // row-wise K / V fragments requested ahead of their matrix instruction
     constexpr int PDT = 2;       // K^T fragments requested ahead
@@ -1650,7 +1650,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         constexpr bool k16 = sizeof(T) == 2;      // eight waves; fp32: four
         constexpr int NW = k16 ? 8 : 4;
         constexpr int QT = NW * 32, KVT = 128;
-        constexpr int LDS_Q = k16 ? 2 * (1 << 16) : 4 * 64 * D * (int)sizeof(T);
+        constexpr int LDS_Q = k16 ? 2 * 2 * 128 * D * (int)sizeof(T) : 4 * 64 * D * (int)sizeof(T);
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
         void (*kern)(BwdArgs);

@@ -21,8 +21,8 @@
 
 namespace ttt {
 
-template <typename T, int D, int QB, int NW, int KS>
-__global__ __launch_bounds__(NW * 64) void ttt_fwd_kernel(const FwdArgs a) {
+template <typename T, int D, int QB, int NW, int KS, int WPE>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void ttt_fwd_kernel(const FwdArgs a) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;                // kv rows per LDS tile
@@ -35,7 +35,7 @@ __global__ __launch_bounds__(NW * 64) void ttt_fwd_kernel(const FwdArgs a) {
     constexpr int TILE_BYTES = KT * D * E::kBytes;
     constexpr float kLazy = 8.f;          // log2 of the largest p tolerated before the reference max moves
     constexpr bool kDiagLds = sizeof(T) == 2 && KT == 64;   // diagonal rows may be staged in LDS
-    constexpr int kDiagRows = 64 / KS;    // of workgroups of so many rows
+    constexpr int kDiagRows = KS == 2 && D == 64 ? 64 : 64 / KS;   // rows copied (the threads' pieces make whole rows)
     constexpr int kDiagSlots = KS == 1 ? 3 : 2;   // blocks whose rows are staged at once
 
     extern __shared__ __align__(16) char smem[];
@@ -444,17 +444,17 @@ hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int
     return hipGetLastError();
 }
 
-template <typename T, int D, int QB, int NW, int KS> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
+template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
     constexpr int LDS_TILES = 4 * KS * 64 * D * (int)sizeof(T);   // two stages of K and V tiles
-    constexpr int DIAG_ROWS = 64 / KS;
+    constexpr int DIAG_ROWS = KS == 2 && D == 64 ? 64 : 64 / KS;   // as in the kernel
     constexpr int LDS_DIAG = (KS == 1 ? 3 : 2) * 2 * DIAG_ROWS * D * (int)sizeof(T);   // the rows of so many blocks' diagonal keys
-    auto kern = ttt_fwd_kernel<T, D, QB, NW, KS>;
+    auto kern = ttt_fwd_kernel<T, D, QB, NW, KS, WPE>;
     static LdsOptIn lds_opt_in;
     if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS_TILES + (sizeof(T) == 2 ? LDS_DIAG : 0)); e != hipSuccess) return e;
     const Geometry& geo = a.geo;
     const int qt_rows = (NW / KS * QB * 32) >> a.pack_log2;
     a.n_tiles = (geo.T + qt_rows - 1) / qt_rows;
-    a.diag_lds = sizeof(T) == 2 && qt_rows == DIAG_ROWS;
+    a.diag_lds = sizeof(T) == 2 && qt_rows == 64 / KS;
     const int lds_bytes = LDS_TILES + (a.diag_lds ? LDS_DIAG : 0);
     a.map.hkv = geo.hkv;
     a.map.rest_count = a.n_tiles * geo.n_steps * (geo.G >> a.pack_log2);
@@ -514,6 +514,26 @@ static bool two_key_groups_end_first(const FwdArgs& a, int n_cu) {
     return est[1] < 0.97 * est[0];
 }
 
+// The same choice for head_dim 64, whose workgroups leave room for others on their compute unit: eight waves in 128
+// registers (two workgroups per unit; 0), four waves and half the rows (three per unit; 1), or two key groups
+// (one per unit; 2).  Swept over 128 to 8192 tokens, five head geometries, one to seven steps, one and nine
+// documents (us, kinds 0 / 1 / 2; last, what four waves of 64 rows took before):
+//   32/8 heads, one step: 1024 tokens 24 / 17 / 16 (30), 2048 44 / 31 / 31 (53), 4096 96 / 85 / 103 (111)
+//   32/8, seven steps: 4096 tokens 545 / 580 / 783 (790);  64/4, 8192 tokens 4095 / 4240 / 5414 (5774)
+//   4096 tokens in nine documents, 32/8, one step: 23 / 26 / 34 (43)
+// Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest passes over
+// the keys.
+static int work_split_64(const FwdArgs& a, int n_cu) {
+    const Geometry& geo = a.geo;
+    const int rows = (8 * 32) >> a.pack_log2;
+    const int64_t n = (int64_t)((geo.T + rows - 1) / rows) * geo.hkv * (geo.G >> a.pack_log2) * geo.n_steps;
+    int longest = 0;
+    for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+    const bool is_long = longest >= 16 * 64;
+    if (is_long && n <= n_cu) return 2;
+    return n <= n_cu || (is_long && n <= 3 * (int64_t)n_cu) ? 1 : 0;
+}
+
 hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
     // as many heads of a kv group per workgroup as divide the group, at most 4
     a.pack_log2 = 0;
@@ -524,7 +544,15 @@ hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
         if (two_key_groups_end_first(a, n_cu)) return launch_fwd_t<__bf16, 128, 1, 8, 2>(a, stream);
         return launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
     }
-    if (dtype == 1 && head_dim == 64) return launch_fwd_t<__bf16, 64, 2, 4, 1>(a, stream);
+    if (dtype == 1 && head_dim == 64) {
+        int n_cu = 0;
+        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
+        switch (work_split_64(a, n_cu)) {
+            case 2: return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, stream);
+            case 1: return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, stream);
+            default: return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, stream);
+        }
+    }
     if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, stream);
     if (dtype == 0 && head_dim == 64) return launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
     return hipErrorInvalidValue;

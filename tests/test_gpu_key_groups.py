@@ -19,14 +19,33 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("name,docs,hq,hkv,k", CASES, ids=[c[0] for c in CASES])
-def test_two_key_groups_match_oracle(name, docs, hq, hkv, k):
-    print(f"case {name} documents={docs} heads={hq}/{hkv} k={k}", flush=True)
-    wl = custom_workload(f"groups_{name}", "bf16", docs, hq, hkv, 128, k, seed=len(docs) + 5)
+# head_dim 64: two key groups while there are few, long workgroups; four waves while there are few; eight otherwise
+CASES_64 = [
+    ("two_key_groups", [1100], 4, 1, 2, 1),
+    ("two_key_groups_documents", [3, 1030, 40], 2, 2, 3, 1),
+    ("four_waves", [70, 1, 130, 64, 33], 8, 2, 4, 1),
+    ("four_waves_one_head", [200, 95], 3, 3, 3, 1),
+    ("eight_waves", [63, 200, 1, 336], 32, 8, 4, 4),
+]
+
+
+def run(name, docs, hq, hkv, d, k, steps_per_call):
+    print(f"case {name} documents={docs} heads={hq}/{hkv} head_dim={d} k={k}", flush=True)
+    wl = custom_workload(f"groups_{name}", "bf16", docs, hq, hkv, d, k, seed=len(docs) + 5)
     case = Case(wl, "cuda:0")
-    for j in range(k):
-        case.run.forward(j, j + 1)
+    for j in range(0, k, steps_per_call):
+        case.run.forward(j, j + steps_per_call)
     case.run.backward(case.d_o)
     torch.cuda.synchronize()
     for key, (err, bound) in compare_full(case).items():
         assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
+
+
+@pytest.mark.parametrize("name,docs,hq,hkv,k", CASES, ids=[c[0] for c in CASES])
+def test_two_key_groups_match_oracle(name, docs, hq, hkv, k):
+    run(name, docs, hq, hkv, 128, k, 1)
+
+
+@pytest.mark.parametrize("name,docs,hq,hkv,k,steps", CASES_64, ids=[c[0] for c in CASES_64])
+def test_head_dim_64_splits_match_oracle(name, docs, hq, hkv, k, steps):
+    run(name, docs, hq, hkv, 64, k, steps)
