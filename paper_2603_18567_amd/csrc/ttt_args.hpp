@@ -68,6 +68,7 @@ struct BwdArgs {
     int n_tiles_kv;         // key tiles of the dK/dV part
     int grid_kv;            // workgroups of the dK/dV part; the dQ part follows them
     int n_split;            // dK/dV kernel: ways the (step, head) list of one kv tile is split
+    int q_split;            // dK/dV kernel (fp32): ways the query rows of one kv tile are split
     int n_units;            // dK/dV kernel (16-bit): (key tile, query chunk) units per kv head and split
     int chunk_blocks;       // dK/dV kernel (16-bit): 32-row query blocks per chunk (a multiple of 4)
     HeadMap map_q, map_kv;

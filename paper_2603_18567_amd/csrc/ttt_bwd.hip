@@ -840,7 +840,9 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
     int g, rest;
     if (!decode_block(a.map_kv, wg, g, rest)) return;
     const int sp = rest % a.n_split;
-    const int tile = rest / a.n_split;   // low tiles of a document have the longest query range: first
+    rest /= a.n_split;
+    const int part = rest % a.q_split;
+    const int tile = rest / a.q_split;   // low tiles of a document have the longest query range: first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
@@ -852,9 +854,10 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
     // query rows that can see this workgroup's / this wave's keys
     const int q_end = __builtin_amdgcn_readfirstlane(a.tok_end[min(kv_tile0 + KVT - 1, Tn - 1)]);
     const int wq_end = active ? __builtin_amdgcn_readfirstlane(a.tok_end[wk_hi]) : 0;
-    const int qt_lo = kv_tile0 / QTL;
-    const int qt_hi = (q_end - 1) / QTL;
-    const int nqt = qt_hi - qt_lo + 1;
+    const int qt_first = kv_tile0 / QTL, qt_all = (q_end - 1) / QTL - qt_first + 1;
+    const int qt_lo = qt_first + qt_all * part / a.q_split;   // this workgroup's part of them
+    const int nqt = qt_first + qt_all * (part + 1) / a.q_split - qt_lo;
+    if (nqt <= 0) return;
     const int n_jh = geo.n_steps * geo.G;
     const int n_c = (n_jh - sp + a.n_split - 1) / a.n_split;   // (step, head) pairs of this split
     const int n_it = n_c * nqt;
@@ -1667,6 +1670,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         // split the (step, head) list of a dK/dV unit so that the grid fills the device evenly
         const int n_jh = geo.n_steps * geo.G;
         int n_split = 1;
+        a.q_split = 1;
         int n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
         if constexpr (k16) {
             int n_cu = 0;
@@ -1678,6 +1682,13 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
             a.n_units = n_units;
         } else {
             while (n_split < n_jh && (int64_t)n_units * geo.hkv * n_split < 2048) ++n_split;
+            // a short launch lasts as long as one workgroup's query rows: they are split as well while compute units
+            // are idle (whole backward, one step: 300 tokens, 8/2 heads of 64: 64 -> 47 us, 700 tokens, 8/1 of 128: 236 -> 160)
+            int n_cu = 0;
+            if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
+            while (n_split == n_jh && a.q_split < (geo.T + 63) / 64 && (int64_t)n_units * geo.hkv * n_split * (a.q_split + 1) <= n_cu)
+                ++a.q_split;
+            n_units *= a.q_split;
         }
         a.n_split = n_split;
         int64_t grid_kv, grid_q;

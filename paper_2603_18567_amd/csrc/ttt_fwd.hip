@@ -554,7 +554,19 @@ hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
         }
     }
     if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, stream);
-    if (dtype == 0 && head_dim == 64) return launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
+    if (dtype == 0 && head_dim == 64) {
+        // fp32 matrix instructions are slow and a short launch lasts as long as one wave's key tiles: two key groups
+        // (LDS for one workgroup per compute unit) while every workgroup still gets a unit of its own (128 tokens, 4/4
+        // heads, three steps 20 -> 13 us; 700 tokens, 8/1 heads, one step 56 -> 37)
+        int n_cu = 0;
+        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
+        FwdArgs b = a;
+        b.pack_log2 = std::min(a.pack_log2, 1);   // two waves per key group
+        const int rows = (2 * 32) >> b.pack_log2;
+        if ((int64_t)((a.geo.T + rows - 1) / rows) * a.geo.hkv * (a.geo.G >> b.pack_log2) * a.geo.n_steps <= n_cu)
+            return launch_fwd_t<float, 64, 1, 4, 2>(b, stream);
+        return launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
+    }
     return hipErrorInvalidValue;
 }
 

@@ -49,3 +49,19 @@ def test_two_key_groups_match_oracle(name, docs, hq, hkv, k):
 @pytest.mark.parametrize("name,docs,hq,hkv,k,steps", CASES_64, ids=[c[0] for c in CASES_64])
 def test_head_dim_64_splits_match_oracle(name, docs, hq, hkv, k, steps):
     run(name, docs, hq, hkv, 64, k, steps)
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,steps", [([128], 4, 4, 64, 3, 3), ([300], 8, 2, 64, 1, 1), ([65, 1, 70], 8, 2, 64, 2, 1),
+                                                   ([200, 3], 8, 1, 128, 2, 1), ([250], 3, 1, 64, 1, 1)])
+def test_fp32_short_launches_match_oracle(docs, hq, hkv, d, k, steps):
+    """fp32: two key groups in the forward (head_dim 64), query rows of a key tile split over workgroups in the
+    backward, also into more parts than a tile has query tiles."""
+    print(f"fp32 documents={docs} heads={hq}/{hkv} head_dim={d} k={k}", flush=True)
+    case = Case(custom_workload(f"f32_{len(docs)}_{d}_{k}", "f32", docs, hq, hkv, d, k, seed=d + len(docs)), "cuda:0")
+    for j in range(0, k, steps):
+        case.run.forward(j, j + steps)
+    for j in reversed(range(0, k, steps)):
+        case.run.backward(case.d_o, j, j + steps, accumulate=steps < k)
+    torch.cuda.synchronize()
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
