@@ -2,17 +2,16 @@
 // (Sec. 4.2.1), so every kernel here recomputes p = exp(s - LSE) from Q and K tile by tile and
 // applies the softmax-attention VJP:  D = <dO,O>, dp = <dO,V>, ds = p (dp - D).
 //
-//   ttt_bwd_pre_kernel   D for every (step, head, token); and the complete dK_l, dV_l of the later
-//                        cache blocks l >= 1, which are only ever read on the diagonal (suffix part
-//                        of Alg. 2), so one small group of lanes owns each (token, kv head) -- no atomics.
-//   ttt_bwd_dq_kernel    query-stationary, same streaming structure as the forward: dQ_j
-//                        (ttt_bwd_dq_pipe_kernel: block-pipelined variant for 16-bit types).
-//   ttt_bwd_dkv_kernel   key-stationary over block 0: each wave keeps 32 rows of K_0, V_0 as
-//                        operands and their dK, dV accumulators in registers while every
-//                        (step, head of the group, query tile at or below the diagonal) streams past
-//                        through LDS; partial sums of the (step, head) splits meet in fp32 atomics
-//                        (ttt_bwd_dkv_p8_kernel: eight equal waves, for 16-bit types).
-//   ttt_bwd_finish_kernel  fp32 block-0 sums -> dK_0, dV_0 in the tensor dtype.
+//   ttt_bwd_pre_kernel     D for every (step, head, token); and the complete dK_l, dV_l of the later
+//                          cache blocks l >= 1, which are only ever read on the diagonal (suffix part
+//                          of Alg. 2), so one small group of lanes owns each (token, kv head) -- no atomics
+//                          (ttt_bwd_pre_regs_kernel for 16-bit types)
+//   ttt_bwd_main_kernel    both streaming passes in one launch (ttt_bwd_main_f32_kernel for fp32):
+//     dkv_p8_tile, dkv_tile   key-stationary over block 0: dK, dV accumulators of 32 keys per wave in registers
+//                          while every (step, head of the group, query block at or below the diagonal) streams
+//                          past through LDS; partial sums of the splits meet in fp32 atomics
+//     dq_pipe_tile, dq_tile   query-stationary, same streaming structure as the forward: dQ_j
+//   ttt_bwd_finish_kernel  fp32 block-0 sums -> dK_0, dV_0 in the tensor dtype
 #include <algorithm>
 #include <functional>
 #include <mutex>
@@ -920,7 +919,7 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
                 const int qb0 = q0 + qb * 32;
                 if (qb0 + 31 < wk0 || qb0 >= wq_end) continue;
                 // fragments are read where they are used (this kernel serves the fp32 instantiation;
-                // 16-bit types take ttt_bwd_dkv_p8_kernel)
+                // 16-bit types take dkv_p8_tile)
                 frag qa[DC], ga[DC], gt[2][DB], qt[2][DB];
                 // S[q, kv] = Q K^T and dP[q, kv] = dO V^T : lane = kv column, values = query rows
                 f32x16 sacc, pacc;
