@@ -7,6 +7,7 @@
 #include <atomic>
 
 #include "ttt_device.hpp"
+#include "ttt_plan.hpp"
 
 namespace ttt {
 
@@ -80,6 +81,10 @@ struct BwdArgs {
     // host side only (the launchers' work-split model reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base
 };
+
+inline CallShape call_shape(const Geometry& geo, int n_docs, const int32_t* cu_host, int cu_base) {
+    return CallShape{geo.T, geo.step_begin, geo.n_steps, geo.G, geo.hkv, n_docs, cu_host, cu_base};
+}
 
 // launchers (defined in the kernel files); all enqueue on `stream` and return the launch status
 hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int* tok_start, int* tok_end, hipStream_t stream);

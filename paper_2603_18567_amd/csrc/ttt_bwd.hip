@@ -12,10 +12,8 @@
 //                          past through LDS; partial sums of the splits meet in fp32 atomics
 //     dq_pipe_tile, dq_tile   query-stationary, same streaming structure as the forward: dQ_j
 //   ttt_bwd_finish_kernel  fp32 block-0 sums -> dK_0, dV_0 in the tensor dtype
+
 #include <algorithm>
-#include <functional>
-#include <mutex>
-#include <vector>
 
 #include "ttt_args.hpp"
 
@@ -1453,163 +1451,6 @@ static void set_head_map(HeadMap& m, int hkv, int rest_count, int64_t& grid) {
     }
 }
 
-// ------------------------------------------------------------------------------------------------
-// Work split of the 16-bit backward launch: 32-row query blocks per dK/dV chunk and ways to split the
-// (step, head) list, chosen by a model of the launch.
-//
-// One workgroup fills a compute unit.  Measured on MI355X (chunk size x split swept at 512 ... 16384
-// tokens, all steps and one step per call, five head geometries): a dK/dV unit = (128-key tile, chunk,
-// split) costs about 1.9 us per step (one 32-row query block per wave group and (step, head) pair) plus
-// about 13 us of its own (workgroup launch, the K_0/V_0 tile and first query block arriving, the flush
-// of its sums through LDS and fp32 atomics), an empty unit (a tile that no row of the chunk sees) about
-// 1 us; a dQ tile costs about 5 us per 128-key tile, 1.7 per diagonal key and 8 of its own; with
-// head_dim 64 the streaming parts take 0.6 of that.  The model deals the units of one XCD in launch order
-// to its compute units (each to the one that frees up first); over the sweeps its choice is 1.1 % slower
-// than the best one on average and 5 % at most (the dK/dV units dealt alone, with 512 ... 2048-row
-// chunks: 6 % and 17 %).  Long lists stop at 1024-row chunks: the model does not see HBM traffic, and
-// with longer ones the units of one XCD no longer stream the same Q / dO rows together (2048 rows, 4096
-// tokens, all steps: 2.6 GB fetched against 0.9 GB with 512).
-// ------------------------------------------------------------------------------------------------
-struct DkvPlan {
-    int chunk_blocks, n_split;
-};
-
-static int dkv_units_of(int T, int n_tiles, int chunk_blocks) {
-    const int n_chunks = (T + chunk_blocks * 32 - 1) / (chunk_blocks * 32);
-    int n = 0;
-    for (int ch = 0; ch < n_chunks; ++ch) n += std::min(n_tiles, (ch + 1) * chunk_blocks / 4);
-    return n;
-}
-
-// the share of one XCD of a launch part: unit number u of every kv head, in launch order (decode_block)
-template <typename F> static void for_units_of_an_xcd(int hkv, int n_units, F&& f) {
-    if (hkv % 8 == 0) {
-        for (int u = 0; u < n_units; ++u)
-            for (int hp = 0; hp < hkv / 8; ++hp) f(u);
-    } else if (8 % hkv == 0) {
-        for (int u = 0; u < n_units; u += 8 / hkv) f(u);
-    } else {
-        for (int64_t id = 0; id < (int64_t)n_units * hkv; id += 8) f((int)(id / hkv));
-    }
-}
-
-static DkvPlan plan_dkv_split(const BwdArgs& a, int head_dim, int n_cu) {
-    const Geometry& geo = a.geo;
-    const int T = geo.T, n_jh = geo.n_steps * geo.G;
-    const int n_tiles = (T + 127) / 128, n_tiles_q = (T + 255) / 256;
-    const float stream = head_dim == 64 ? 0.6f : 1.f;
-    const float kStepUs = 1.9f * stream, kUnitUs = 13.f, kEmptyUs = 1.f;
-    const float kTileUs = 5.f * stream, kDiagUs = 1.7f * stream, kQUs = 8.f;
-    // one entry per distinct request: the plan depends on the document structure, the steps, the heads and the device
-    struct Key {
-        int T, n_docs, step_begin, n_steps, G, hkv, head_dim, n_cu;
-        uint64_t cu_hash;
-        bool operator==(const Key& o) const {
-            return T == o.T && n_docs == o.n_docs && step_begin == o.step_begin && n_steps == o.n_steps && G == o.G &&
-                   hkv == o.hkv && head_dim == o.head_dim && n_cu == o.n_cu && cu_hash == o.cu_hash;
-        }
-    };
-    uint64_t h = 1469598103934665603ull;
-    for (int r = 0; r <= a.n_docs; ++r) h = (h ^ (uint64_t)(uint32_t)(a.cu_host[r] - a.cu_base)) * 1099511628211ull;
-    const Key key{T, a.n_docs, geo.step_begin, geo.n_steps, geo.G, geo.hkv, head_dim, n_cu, h};
-    static std::mutex mu;
-    static std::vector<std::pair<Key, DkvPlan>> cache;
-    {
-        std::lock_guard<std::mutex> lock(mu);
-        for (const auto& e : cache)
-            if (e.first == key) return e.second;
-    }
-    const int cus = std::max(1, n_cu / 8);
-    // document of token i, asked for rising i
-    int doc = 0;
-    auto doc_of = [&](int i) {
-        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= i) ++doc;
-        return doc;
-    };
-    // last query row (+1) that sees the last key of each tile: the end of that key's document
-    std::vector<int> q_end(n_tiles), q_keys(n_tiles_q);
-    for (int t = 0; t < n_tiles; ++t) q_end[t] = a.cu_host[doc_of(std::min(t * 128 + 127, T - 1)) + 1] - a.cu_base;
-    doc = 0;
-    for (int t = 0; t < n_tiles_q; ++t)
-        q_keys[t] = std::min(t * 256 + 255, T - 1) / 128 - (a.cu_host[doc_of(t * 256)] - a.cu_base) / 128 + 1;
-    // the dQ tiles of one XCD in launch order
-    std::vector<float> dq;
-    double dq_work = 0.;
-    for_units_of_an_xcd(geo.hkv, n_tiles_q * n_jh, [&](int u) {
-        const int js = u / geo.G % geo.n_steps, t = n_tiles_q - 1 - u / n_jh;
-        dq.push_back(kQUs + q_keys[t] * kTileUs + (geo.step_begin + js) * kDiagUs);
-        dq_work += dq.back();
-    });
-    struct Option {
-        int cb, ns;
-        double bound;   // no schedule ends before this
-    };
-    std::vector<Option> options;
-    std::vector<std::vector<int>> steps_of;   // per chunk size: steps per (step, head) pair of each unit
-    std::vector<int> sizes;
-    for (int cb : {8, 16, 32, 64, 128}) {
-        if (cb > 32 && n_jh > 8) break;
-        if (cb > 8 && cb * 16 >= T) break;    // one chunk covers everything already
-        std::vector<int> nqb2;
-        double blocks = 0.;
-        int used = 0, most = 0;
-        const int n_chunks = (T + cb * 32 - 1) / (cb * 32);
-        for (int ch = 0; ch < n_chunks; ++ch) {
-            const int tiles = std::min(n_tiles, (ch + 1) * cb / 4);
-            for (int t = 0; t < tiles; ++t) {
-                const int qb_lo = std::max(t * 4, ch * cb);
-                const int nqb = std::min((q_end[t] - 1) / 32, (ch + 1) * cb - 1) - qb_lo + 1;
-                const int n2 = nqb > 0 ? (nqb + 1) / 2 : 0;
-                nqb2.push_back(n2);
-                blocks += n2;
-                used += n2 > 0;
-                most = std::max(most, n2);
-            }
-        }
-        const double share = (double)geo.hkv / 8.;   // heads per XCD
-        for (int ns : {1, 2, 3, 4, 6, 8}) {
-            if (ns > n_jh) break;
-            const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((int)nqb2.size() - used) * kEmptyUs));
-            const double longest = (double)((n_jh + ns - 1) / ns) * most * kStepUs + kUnitUs;
-            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work) / cus)});
-        }
-        sizes.push_back(cb);
-        steps_of.push_back(std::move(nqb2));
-    }
-    std::sort(options.begin(), options.end(), [](const Option& x, const Option& y) { return x.bound < y.bound; });
-    DkvPlan best{16, 1};
-    double best_us = -1.;
-    std::vector<float> heap;
-    int dealt = 0;
-    for (const Option& o : options) {
-        if (best_us >= 0. && o.bound >= best_us) break;
-        const std::vector<int>& nqb2 = steps_of[std::find(sizes.begin(), sizes.end(), o.cb) - sizes.begin()];
-        heap.assign(cus, 0.f);
-        float finish = 0.f;
-        auto deal = [&](float us) {   // to the compute unit that frees up first
-            std::pop_heap(heap.begin(), heap.end(), std::greater<float>());
-            heap.back() += us;
-            finish = std::max(finish, heap.back());
-            std::push_heap(heap.begin(), heap.end(), std::greater<float>());
-            ++dealt;
-        };
-        for_units_of_an_xcd(geo.hkv, (int)nqb2.size() * o.ns, [&](int u) {
-            const int sp = u / (int)nqb2.size(), n2 = nqb2[u % nqb2.size()];
-            deal(n2 > 0 ? (float)((n_jh - sp + o.ns - 1) / o.ns * n2) * kStepUs + kUnitUs : kEmptyUs);
-        });
-        for (float us : dq) deal(us);
-        if (best_us < 0. || finish < best_us) {
-            best_us = finish;
-            best = DkvPlan{o.cb, o.ns};
-        }
-        if (dealt > 40000) break;   // very large launches: the bound, by which the options are sorted, is close
-    }
-    std::lock_guard<std::mutex> lock(mu);
-    if (cache.size() >= 64) cache.erase(cache.begin());
-    cache.emplace_back(key, best);
-    return best;
-}
-
 constexpr int kPreRegBlocks = 7;   // later blocks whose rows and gradients fit the registers of the preprocess kernel
 
 template <typename T, int D>
@@ -1674,19 +1515,17 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         if constexpr (k16) {
             int n_cu = 0;
             if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
-            const DkvPlan plan = plan_dkv_split(a, D, n_cu);
+            const DkvPlan plan = plan_dkv_split(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), D, n_cu);
             a.chunk_blocks = plan.chunk_blocks;
             n_split = plan.n_split;
             n_units = dkv_units_of(geo.T, a.n_tiles_kv, a.chunk_blocks);
             a.n_units = n_units;
         } else {
-            while (n_split < n_jh && (int64_t)n_units * geo.hkv * n_split < 2048) ++n_split;
-            // a short launch lasts as long as one workgroup's query rows: they are split as well while compute units
-            // are idle (whole backward, one step: 300 tokens, 8/2 heads of 64: 64 -> 47 us, 700 tokens, 8/1 of 128: 236 -> 160)
             int n_cu = 0;
             if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
-            while (n_split == n_jh && a.q_split < (geo.T + 63) / 64 && (int64_t)n_units * geo.hkv * n_split * (a.q_split + 1) <= n_cu)
-                ++a.q_split;
+            const DkvPlanF32 plan = plan_dkv_split_f32(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), n_cu);
+            n_split = plan.n_split;
+            a.q_split = plan.q_split;
             n_units *= a.q_split;
         }
         a.n_split = n_split;

@@ -14,7 +14,6 @@
 // Tiles are cut over the packed token axis, not per document: a row's visible prefix is
 // [tok_start[i], i], so a wave visits the kv tiles that intersect [tok_start[first row], last row]
 // and nothing else; tiles strictly inside that range for every row skip the mask code.
-#include <algorithm>
 #include <type_traits>
 
 #include "ttt_args.hpp"
@@ -492,94 +491,22 @@ template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hi
     return hipGetLastError();
 }
 
-// Which work split ends first: one key group (all eight waves share a 64-key tile) or two (each tile pair's tiles go
-// to the two halves of the workgroup, which covers half as many rows).  Two groups halve the longest
-// workgroup -- a causal launch of one step at 2048 tokens is one workgroup per compute unit, and ends with the
-// one that has all the keys -- but copy every tile for half as many waves and pay set-up, merge and epilogue
-// twice as often.  Estimate per split: the longest workgroup, or the work of all over the compute units,
-// whichever is more.  Measured (16-bit, head_dim 128, us): a workgroup 3, a tile 1.55 while the device is not
-// full and 1.85 when it is, a tile pair 2.0 and 2.2, a diagonal key 2.0 and 1.3 through LDS and twice that
-// otherwise.  One step, 32/8 heads: 1024 tokens 40 -> 29 us, 2048 70 -> 59, 3000 98 (114 with two groups); all
-// seven steps at 2048 293 (373).
-static bool two_key_groups_end_first(const FwdArgs& a, int n_cu) {
-    const Geometry& geo = a.geo;
-    const int rows = (8 * 32) >> a.pack_log2;      // of a workgroup with one key group
-    const int64_t per_tile = (int64_t)geo.hkv * (geo.G >> a.pack_log2) * geo.n_steps;
-    if ((int64_t)(geo.T + rows - 1) / rows * per_tile > 6 * n_cu) return false;   // many rounds: the work decides
-    const double j_mean = geo.step_begin + 0.5 * (geo.n_steps - 1), j_max = geo.step_begin + geo.n_steps - 1;
-    double est[2];
-    for (int ks = 1; ks <= 2; ++ks) {
-        const int r = rows / ks;
-        const double diag = (ks == 1 ? 2.0 : 1.3) * (r * ks == 64 ? 1. : 2.);
-        int doc = 0;
-        int64_t steps = 0, n = 0, most = 0;
-        for (int row = 0; row < geo.T; row += r, ++n) {
-            while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
-            const int64_t tiles = std::min(row + r - 1, geo.T - 1) / 64 - (a.cu_host[doc] - a.cu_base) / 64 + 1;
-            const int64_t s = (tiles + ks - 1) / ks;
-            steps += s;
-            most = std::max(most, s);
-        }
-        const double longest = 3. + most * (ks == 1 ? 1.55 : 2.0) + j_max * diag;
-        const double work = (n * (3. + j_mean * diag) + steps * (ks == 1 ? 1.85 : 2.2)) * (double)per_tile / n_cu;
-        est[ks - 1] = std::max(longest, work);
-    }
-    return est[1] < 0.97 * est[0];
-}
-
-// The same choice for head_dim 64, whose workgroups leave room for others on their compute unit: eight waves in 128
-// registers (two workgroups per unit; 0), four waves and half the rows (three per unit; 1), or two key groups
-// (one per unit; 2).  Swept over 128 to 8192 tokens, five head geometries, one to seven steps, one and nine
-// documents (us, kinds 0 / 1 / 2; last, what four waves of 64 rows took before):
-//   32/8 heads, one step: 1024 tokens 24 / 17 / 16 (30), 2048 44 / 31 / 31 (53), 4096 96 / 85 / 103 (111)
-//   32/8, seven steps: 4096 tokens 545 / 580 / 783 (790);  64/4, 8192 tokens 4095 / 4240 / 5414 (5774)
-//   4096 tokens in nine documents, 32/8, one step: 23 / 26 / 34 (43)
-// Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest passes over
-// the keys.
-static int work_split_64(const FwdArgs& a, int n_cu) {
-    const Geometry& geo = a.geo;
-    const int rows = (8 * 32) >> a.pack_log2;
-    const int64_t n = (int64_t)((geo.T + rows - 1) / rows) * geo.hkv * (geo.G >> a.pack_log2) * geo.n_steps;
-    int longest = 0;
-    for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
-    const bool is_long = longest >= 16 * 64;
-    if (is_long && n <= n_cu) return 2;
-    return n <= n_cu || (is_long && n <= 3 * (int64_t)n_cu) ? 1 : 0;
-}
-
 hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
-    // as many heads of a kv group per workgroup as divide the group, at most 4
-    a.pack_log2 = 0;
-    while ((2 << a.pack_log2) <= 4 && a.geo.G % (2 << a.pack_log2) == 0) ++a.pack_log2;
-    if (dtype == 1 && head_dim == 128) {
-        int n_cu = 0;
-        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-        if (two_key_groups_end_first(a, n_cu)) return launch_fwd_t<__bf16, 128, 1, 8, 2>(a, stream);
-        return launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
-    }
+    int n_cu = 0;
+    if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
+    const FwdPlan plan = plan_fwd(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), dtype == 1, head_dim, n_cu);
+    a.pack_log2 = plan.pack_log2;
+    const bool two_groups = plan.split == kFwdTwoKeyGroups;
+    if (dtype == 1 && head_dim == 128)
+        return two_groups ? launch_fwd_t<__bf16, 128, 1, 8, 2>(a, stream) : launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
     if (dtype == 1 && head_dim == 64) {
-        int n_cu = 0;
-        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-        switch (work_split_64(a, n_cu)) {
-            case 2: return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, stream);
-            case 1: return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, stream);
-            default: return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, stream);
-        }
+        if (two_groups) return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, stream);
+        if (plan.split == kFwdFourWaves) return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, stream);
+        return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, stream);
     }
     if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, stream);
-    if (dtype == 0 && head_dim == 64) {
-        // fp32 matrix instructions are slow and a short launch lasts as long as one wave's key tiles: two key groups
-        // (LDS for one workgroup per compute unit) while every workgroup still gets a unit of its own (128 tokens, 4/4
-        // heads, three steps 20 -> 13 us; 700 tokens, 8/1 heads, one step 56 -> 37)
-        int n_cu = 0;
-        if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-        FwdArgs b = a;
-        b.pack_log2 = std::min(a.pack_log2, 1);   // two waves per key group
-        const int rows = (2 * 32) >> b.pack_log2;
-        if ((int64_t)((a.geo.T + rows - 1) / rows) * a.geo.hkv * (a.geo.G >> b.pack_log2) * a.geo.n_steps <= n_cu)
-            return launch_fwd_t<float, 64, 1, 4, 2>(b, stream);
-        return launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
-    }
+    if (dtype == 0 && head_dim == 64)
+        return two_groups ? launch_fwd_t<float, 64, 1, 4, 2>(a, stream) : launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
     return hipErrorInvalidValue;
 }
 

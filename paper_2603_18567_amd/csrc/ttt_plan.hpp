@@ -1,0 +1,351 @@
+// Which kernel variant and work split a call takes: rules over sizes and measured times, host code only (no
+// HIP header, so that they can be compiled and looked at without a device).
+#pragma once
+#include <stdint.h>
+
+#include <algorithm>
+#include <functional>
+#include <mutex>
+#include <utility>
+#include <vector>
+
+namespace ttt {
+
+// what the rules read of an attention call (a slice of the batch)
+struct CallShape {
+    int T, step_begin, n_steps, G, hkv;
+    int n_docs;
+    const int32_t* cu_host;   // n_docs + 1 entries, first entry = cu_base
+    int cu_base;
+};
+
+// ------------------------------------------------------------------------------------------------
+// Forward
+// ------------------------------------------------------------------------------------------------
+// How the waves of a workgroup share its work: eight waves (or four) with 32 rows each, or two key groups that
+// take every second key tile of the same rows.
+enum FwdSplit { kFwdEightWaves, kFwdFourWaves, kFwdTwoKeyGroups };
+
+// Which work split ends first: one key group (all eight waves share a 64-key tile) or two (each tile pair's tiles go
+// to the two halves of the workgroup, which covers half as many rows).  Two groups halve the longest
+// workgroup -- a causal launch of one step at 2048 tokens is one workgroup per compute unit, and ends with the
+// one that has all the keys -- but copy every tile for half as many waves and pay set-up, merge and epilogue
+// twice as often.  Estimate per split: the longest workgroup, or the work of all over the compute units,
+// whichever is more.  Measured (16-bit, head_dim 128, us): a workgroup 3, a tile 1.55 while the device is not
+// full and 1.85 when it is, a tile pair 2.0 and 2.2, a diagonal key 2.0 and 1.3 through LDS and twice that
+// otherwise.  One step, 32/8 heads: 1024 tokens 40 -> 29 us, 2048 70 -> 59, 3000 98 (114 with two groups); all
+// seven steps at 2048 293 (373).
+inline bool two_key_groups_end_first(const CallShape& a, int pack_log2, int n_cu) {
+    const int rows = (8 * 32) >> pack_log2;      // of a workgroup with one key group
+    const int64_t per_tile = (int64_t)a.hkv * (a.G >> pack_log2) * a.n_steps;
+    if ((int64_t)(a.T + rows - 1) / rows * per_tile > 6 * n_cu) return false;   // many rounds: the work decides
+    const double j_mean = a.step_begin + 0.5 * (a.n_steps - 1), j_max = a.step_begin + a.n_steps - 1;
+    double est[2];
+    for (int ks = 1; ks <= 2; ++ks) {
+        const int r = rows / ks;
+        const double diag = (ks == 1 ? 2.0 : 1.3) * (r * ks == 64 ? 1. : 2.);
+        int doc = 0;
+        int64_t steps = 0, n = 0, most = 0;
+        for (int row = 0; row < a.T; row += r, ++n) {
+            while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
+            const int64_t tiles = std::min(row + r - 1, a.T - 1) / 64 - (a.cu_host[doc] - a.cu_base) / 64 + 1;
+            const int64_t s = (tiles + ks - 1) / ks;
+            steps += s;
+            most = std::max(most, s);
+        }
+        const double longest = 3. + most * (ks == 1 ? 1.55 : 2.0) + j_max * diag;
+        const double work = (n * (3. + j_mean * diag) + steps * (ks == 1 ? 1.85 : 2.2)) * (double)per_tile / n_cu;
+        est[ks - 1] = std::max(longest, work);
+    }
+    return est[1] < 0.97 * est[0];
+}
+
+// The same choice for head_dim 64, whose workgroups leave room for others on their compute unit: eight waves in 128
+// registers (two workgroups per unit), four waves and half the rows (three per unit), or two key groups
+// (one per unit).  Swept over 128 to 8192 tokens, five head geometries, one to seven steps, one and nine
+// documents (us, in that order; last, what four waves of 64 rows took before):
+//   32/8 heads, one step: 1024 tokens 24 / 17 / 16 (30), 2048 44 / 31 / 31 (53), 4096 96 / 85 / 103 (111)
+//   32/8, seven steps: 4096 tokens 545 / 580 / 783 (790);  64/4, 8192 tokens 4095 / 4240 / 5414 (5774)
+//   4096 tokens in nine documents, 32/8, one step: 23 / 26 / 34 (43)
+// Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest passes over
+// the keys.
+inline FwdSplit work_split_64(const CallShape& a, int pack_log2, int n_cu) {
+    const int rows = (8 * 32) >> pack_log2;
+    const int64_t n = (int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack_log2) * a.n_steps;
+    int longest = 0;
+    for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+    const bool is_long = longest >= 16 * 64;
+    if (is_long && n <= n_cu) return kFwdTwoKeyGroups;
+    return n <= n_cu || (is_long && n <= 3 * (int64_t)n_cu) ? kFwdFourWaves : kFwdEightWaves;
+}
+
+// The forward's split, and how many heads of a kv group share a workgroup (its log2).
+struct FwdPlan {
+    FwdSplit split;
+    int pack_log2;
+};
+
+inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu) {
+    // as many heads of a kv group per workgroup as divide the group, at most 4
+    int pack_log2 = 0;
+    while ((2 << pack_log2) <= 4 && a.G % (2 << pack_log2) == 0) ++pack_log2;
+    if (is_bf16 && head_dim == 128)
+        return FwdPlan{two_key_groups_end_first(a, pack_log2, n_cu) ? kFwdTwoKeyGroups : kFwdEightWaves, pack_log2};
+    if (is_bf16) return FwdPlan{work_split_64(a, pack_log2, n_cu), pack_log2};
+    if (head_dim == 64) {
+        // fp32 matrix instructions are slow and a short launch lasts as long as one wave's key tiles: two key groups
+        // (LDS for one workgroup per compute unit) while every workgroup still gets a unit of its own (128 tokens, 4/4
+        // heads, three steps 20 -> 13 us; 700 tokens, 8/1 heads, one step 56 -> 37)
+        const int pack = std::min(pack_log2, 1);   // two waves per key group
+        const int rows = (2 * 32) >> pack;
+        if ((int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack) * a.n_steps <= n_cu) return FwdPlan{kFwdTwoKeyGroups, pack};
+    }
+    return FwdPlan{kFwdFourWaves, pack_log2};
+}
+
+// ------------------------------------------------------------------------------------------------
+// Work split of the 16-bit backward launch: 32-row query blocks per dK/dV chunk and ways to split the
+// (step, head) list, chosen by a model of the launch.
+//
+// One workgroup fills a compute unit.  Measured on MI355X (chunk size x split swept at 512 ... 16384
+// tokens, all steps and one step per call, five head geometries): a dK/dV unit = (128-key tile, chunk,
+// split) costs about 1.9 us per step (one 32-row query block per wave group and (step, head) pair) plus
+// about 13 us of its own (workgroup launch, the K_0/V_0 tile and first query block arriving, the flush
+// of its sums through LDS and fp32 atomics), an empty unit (a tile that no row of the chunk sees) about
+// 1 us; a dQ tile costs about 5 us per 128-key tile, 1.7 per diagonal key and 8 of its own; with
+// head_dim 64 the streaming parts take 0.6 of that.  The model deals the units of one XCD in launch order
+// to its compute units (each to the one that frees up first); over the sweeps its choice is 1.1 % slower
+// than the best one on average and 5 % at most (the dK/dV units dealt alone, with 512 ... 2048-row
+// chunks: 6 % and 17 %).  Long lists stop at 1024-row chunks: the model does not see HBM traffic, and
+// with longer ones the units of one XCD no longer stream the same Q / dO rows together (2048 rows, 4096
+// tokens, all steps: 2.6 GB fetched against 0.9 GB with 512).
+// ------------------------------------------------------------------------------------------------
+struct DkvPlan {
+    int chunk_blocks, n_split;
+};
+
+inline int dkv_units_of(int T, int n_tiles, int chunk_blocks) {
+    const int n_chunks = (T + chunk_blocks * 32 - 1) / (chunk_blocks * 32);
+    int n = 0;
+    for (int ch = 0; ch < n_chunks; ++ch) n += std::min(n_tiles, (ch + 1) * chunk_blocks / 4);
+    return n;
+}
+
+// the share of one XCD of a launch part: unit number u of every kv head, in launch order (decode_block)
+template <typename F> void for_units_of_an_xcd(int hkv, int n_units, F&& f) {
+    if (hkv % 8 == 0) {
+        for (int u = 0; u < n_units; ++u)
+            for (int hp = 0; hp < hkv / 8; ++hp) f(u);
+    } else if (8 % hkv == 0) {
+        for (int u = 0; u < n_units; u += 8 / hkv) f(u);
+    } else {
+        for (int64_t id = 0; id < (int64_t)n_units * hkv; id += 8) f((int)(id / hkv));
+    }
+}
+
+inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
+    const int T = a.T, n_jh = a.n_steps * a.G;
+    const int n_tiles = (T + 127) / 128, n_tiles_q = (T + 255) / 256;
+    const float stream = head_dim == 64 ? 0.6f : 1.f;
+    const float kStepUs = 1.9f * stream, kUnitUs = 13.f, kEmptyUs = 1.f;
+    const float kTileUs = 5.f * stream, kDiagUs = 1.7f * stream, kQUs = 8.f;
+    // one entry per distinct request: the plan depends on the document structure, the steps, the heads and the device
+    struct Key {
+        int T, n_docs, step_begin, n_steps, G, hkv, head_dim, n_cu;
+        uint64_t cu_hash;
+        bool operator==(const Key& o) const {
+            return T == o.T && n_docs == o.n_docs && step_begin == o.step_begin && n_steps == o.n_steps && G == o.G &&
+                   hkv == o.hkv && head_dim == o.head_dim && n_cu == o.n_cu && cu_hash == o.cu_hash;
+        }
+    };
+    uint64_t h = 1469598103934665603ull;
+    for (int r = 0; r <= a.n_docs; ++r) h = (h ^ (uint64_t)(uint32_t)(a.cu_host[r] - a.cu_base)) * 1099511628211ull;
+    const Key key{T, a.n_docs, a.step_begin, a.n_steps, a.G, a.hkv, head_dim, n_cu, h};
+    static std::mutex mu;
+    static std::vector<std::pair<Key, DkvPlan>> cache;
+    {
+        std::lock_guard<std::mutex> lock(mu);
+        for (const auto& e : cache)
+            if (e.first == key) return e.second;
+    }
+    const int cus = std::max(1, n_cu / 8);
+    // document of token i, asked for rising i
+    int doc = 0;
+    auto doc_of = [&](int i) {
+        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= i) ++doc;
+        return doc;
+    };
+    // last query row (+1) that sees the last key of each tile: the end of that key's document
+    std::vector<int> q_end(n_tiles), q_keys(n_tiles_q);
+    for (int t = 0; t < n_tiles; ++t) q_end[t] = a.cu_host[doc_of(std::min(t * 128 + 127, T - 1)) + 1] - a.cu_base;
+    doc = 0;
+    for (int t = 0; t < n_tiles_q; ++t)
+        q_keys[t] = std::min(t * 256 + 255, T - 1) / 128 - (a.cu_host[doc_of(t * 256)] - a.cu_base) / 128 + 1;
+    // the dQ tiles of one XCD in launch order
+    std::vector<float> dq;
+    double dq_work = 0.;
+    for_units_of_an_xcd(a.hkv, n_tiles_q * n_jh, [&](int u) {
+        const int js = u / a.G % a.n_steps, t = n_tiles_q - 1 - u / n_jh;
+        dq.push_back(kQUs + q_keys[t] * kTileUs + (a.step_begin + js) * kDiagUs);
+        dq_work += dq.back();
+    });
+    struct Option {
+        int cb, ns;
+        double bound;   // no schedule ends before this
+    };
+    std::vector<Option> options;
+    std::vector<std::vector<int>> steps_of;   // per chunk size: steps per (step, head) pair of each unit
+    std::vector<int> sizes;
+    for (int cb : {8, 16, 32, 64, 128}) {
+        if (cb > 32 && n_jh > 8) break;
+        if (cb > 8 && cb * 16 >= T) break;    // one chunk covers everything already
+        std::vector<int> nqb2;
+        double blocks = 0.;
+        int used = 0, most = 0;
+        const int n_chunks = (T + cb * 32 - 1) / (cb * 32);
+        for (int ch = 0; ch < n_chunks; ++ch) {
+            const int tiles = std::min(n_tiles, (ch + 1) * cb / 4);
+            for (int t = 0; t < tiles; ++t) {
+                const int qb_lo = std::max(t * 4, ch * cb);
+                const int nqb = std::min((q_end[t] - 1) / 32, (ch + 1) * cb - 1) - qb_lo + 1;
+                const int n2 = nqb > 0 ? (nqb + 1) / 2 : 0;
+                nqb2.push_back(n2);
+                blocks += n2;
+                used += n2 > 0;
+                most = std::max(most, n2);
+            }
+        }
+        const double share = (double)a.hkv / 8.;   // heads per XCD
+        for (int ns : {1, 2, 3, 4, 6, 8}) {
+            if (ns > n_jh) break;
+            const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((int)nqb2.size() - used) * kEmptyUs));
+            const double longest = (double)((n_jh + ns - 1) / ns) * most * kStepUs + kUnitUs;
+            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work) / cus)});
+        }
+        sizes.push_back(cb);
+        steps_of.push_back(std::move(nqb2));
+    }
+    std::sort(options.begin(), options.end(), [](const Option& x, const Option& y) { return x.bound < y.bound; });
+    DkvPlan best{16, 1};
+    double best_us = -1.;
+    std::vector<float> heap;
+    int dealt = 0;
+    for (const Option& o : options) {
+        if (best_us >= 0. && o.bound >= best_us) break;
+        const std::vector<int>& nqb2 = steps_of[std::find(sizes.begin(), sizes.end(), o.cb) - sizes.begin()];
+        heap.assign(cus, 0.f);
+        float finish = 0.f;
+        auto deal = [&](float us) {   // to the compute unit that frees up first
+            std::pop_heap(heap.begin(), heap.end(), std::greater<float>());
+            heap.back() += us;
+            finish = std::max(finish, heap.back());
+            std::push_heap(heap.begin(), heap.end(), std::greater<float>());
+            ++dealt;
+        };
+        for_units_of_an_xcd(a.hkv, (int)nqb2.size() * o.ns, [&](int u) {
+            const int sp = u / (int)nqb2.size(), n2 = nqb2[u % nqb2.size()];
+            deal(n2 > 0 ? (float)((n_jh - sp + o.ns - 1) / o.ns * n2) * kStepUs + kUnitUs : kEmptyUs);
+        });
+        for (float us : dq) deal(us);
+        if (best_us < 0. || finish < best_us) {
+            best_us = finish;
+            best = DkvPlan{o.cb, o.ns};
+        }
+        if (dealt > 40000) break;   // very large launches: the bound, by which the options are sorted, is close
+    }
+    std::lock_guard<std::mutex> lock(mu);
+    if (cache.size() >= 64) cache.erase(cache.begin());
+    cache.emplace_back(key, best);
+    return best;
+}
+
+// The fp32 backward: ways to split the (step, head) list of a 128-key tile, and its query rows.
+struct DkvPlanF32 {
+    int n_split, q_split;
+};
+
+inline DkvPlanF32 plan_dkv_split_f32(const CallShape& a, int n_cu) {
+    const int n_jh = a.n_steps * a.G, n_tiles = (a.T + 127) / 128;
+    DkvPlanF32 p{1, 1};
+    while (p.n_split < n_jh && (int64_t)n_tiles * a.hkv * p.n_split < 2048) ++p.n_split;
+    // a short launch lasts as long as one workgroup's query rows: they are split as well while compute units
+    // are idle (whole backward, one step: 300 tokens, 8/2 heads of 64: 64 -> 47 us, 700 tokens, 8/1 of 128: 236 -> 160)
+    while (p.n_split == n_jh && p.q_split < (a.T + 63) / 64 && (int64_t)n_tiles * a.hkv * p.n_split * (p.q_split + 1) <= n_cu)
+        ++p.q_split;
+    return p;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Projections
+// ------------------------------------------------------------------------------------------------
+// The tiles a call can be cut into, and what they were measured to take (us; sweeps over 16 to 8192 tokens, hidden_in
+// 64 to 8192, 2048 to 9216 features): `round` once per round of the device (first copies, epilogue), and per
+// 64-column slice `t1` with one workgroup on every compute unit, `lo` in the limit of few workgroups (copies and
+// clock are shared), and `t2` with two side by side on one unit.  Model and measurement agree within 8 %.
+struct QkvTile {
+    int mt, nt, per_cu;
+    double round, lo, t1, t2;
+};
+constexpr QkvTile kQkvTiles[] = {
+    {256, 256, 1, 8., 0.95, 1.55, 0.},
+    {128, 128, 2, 5., 0.57, 0.57, 1.03},
+    {128, 128, 1, 4., 0.44, 0.55, 0.},
+    {128, 64, 1, 3., 0.30, 0.37, 0.},
+    {64, 64, 2, 3., 0.18, 0.18, 0.36},
+    {64, 32, 2, 2., 0.17, 0.17, 0.28},
+    {32, 32, 2, 2., 0.14, 0.14, 0.22},
+};
+constexpr int kQkvTileKinds = sizeof(kQkvTiles) / sizeof(kQkvTiles[0]);
+constexpr double kQkvLaunchUs = 3.;
+
+// estimated time of `tiles` tiles: full rounds of the device and a last one, as full as it is
+inline double qkv_cost(const QkvTile& v, int64_t tiles, int n_cu, int slices) {
+    const int64_t slots = (int64_t)n_cu * v.per_cu, rest = tiles % slots;
+    const double full = v.round + slices * (v.per_cu == 2 ? v.t2 : v.t1);
+    double us = kQkvLaunchUs + (double)(tiles / slots) * full;
+    if (rest > n_cu) us += full;
+    else if (rest > 0) us += v.round + slices * (v.lo + (v.t1 - v.lo) * (double)rest / (double)n_cu);
+    return us;
+}
+
+// One kind of tile for all features, or the full rounds of a large kind and the rest of the features with
+// another, whichever is estimated shortest: 4096 tokens x 6144 features are 16 x 24 of the largest tiles =
+// one and a half rounds of 256 compute units (371 us at hidden_in 8192), or 16 x 16 of them and 32 x 16 of
+// 128 x 128, two to a unit (356 us).  largest_fits: the largest kind may be used.
+struct QkvPlan {
+    int first, second;   // kinds (places in kQkvTiles); second = -1: one launch
+    int f_first;         // features of the first launch
+};
+
+inline QkvPlan plan_qkv(int64_t tokens, int hidden_in, int features, bool largest_fits, int n_cu) {
+    const int slices = hidden_in / 64, kinds = largest_fits ? 0 : 1;
+    auto row_tiles = [&](const QkvTile& t) { return (tokens + t.mt - 1) / t.mt; };
+    auto cost = [&](const QkvTile& t, int f) { return qkv_cost(t, row_tiles(t) * ((f + t.nt - 1) / t.nt), n_cu, slices); };
+    QkvPlan plan{-1, -1, features};
+    double best = 0.;
+    for (int t = kinds; t < kQkvTileKinds; ++t) {
+        const double c = cost(kQkvTiles[t], features);
+        if (plan.first < 0 || c < best) {
+            best = c;
+            plan.first = t;
+        }
+    }
+    for (int t = kinds; t < 2; ++t) {
+        const QkvTile& large = kQkvTiles[t];
+        const int64_t slots = (int64_t)n_cu * large.per_cu, m = row_tiles(large);
+        const int64_t rounds = m * ((features + large.nt - 1) / large.nt) / slots;
+        const int64_t f = rounds * slots / m * large.nt;
+        if (f <= 0 || f >= features) continue;
+        const double head = cost(large, (int)f);
+        for (int u = kinds; u < kQkvTileKinds; ++u) {
+            const double c = head + cost(kQkvTiles[u], features - (int)f);
+            if (c < best) {
+                best = c;
+                plan = QkvPlan{t, u, (int)f};
+            }
+        }
+    }
+    return plan;
+}
+
+}  // namespace ttt

@@ -518,35 +518,17 @@ static hipError_t launch_qkv_rope_256(QkvArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// The tiles a call can be cut into, and what they were measured to take (us; sweeps over 16 to 8192 tokens, hidden_in
-// 64 to 8192, 2048 to 9216 features): `round` once per round of the device (first copies, epilogue), and per
-// 64-column slice `t1` with one workgroup on every compute unit, `lo` in the limit of few workgroups (copies and
-// clock are shared), and `t2` with two side by side on one unit.  Model and measurement agree within 8 %.
-struct QkvTile {
-    int mt, nt, per_cu;
-    double round, lo, t1, t2;
-    hipError_t (*launch)(QkvArgs&, hipStream_t);
+// in the order of kQkvTiles
+static hipError_t (*const kQkvLaunchers[])(QkvArgs&, hipStream_t) = {
+    launch_qkv_rope_256,
+    launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 2>,
+    launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 4>,
+    launch_qkv_rope_splitk<128, 64, 4, 2, 1, 1, 6>,
+    launch_qkv_rope_splitk<64, 64, 4, 1, 2, 1, 4>,
+    launch_qkv_rope_splitk<64, 32, 4, 2, 1, 2, 3>,
+    launch_qkv_rope_splitk<32, 32, 8, 1, 1, 2, 4>,
 };
-static const QkvTile kQkvTiles[] = {
-    {256, 256, 1, 8., 0.95, 1.55, 0., launch_qkv_rope_256},
-    {128, 128, 2, 5., 0.57, 0.57, 1.03, launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 2>},
-    {128, 128, 1, 4., 0.44, 0.55, 0., launch_qkv_rope_splitk<128, 128, 2, 2, 2, 1, 4>},
-    {128, 64, 1, 3., 0.30, 0.37, 0., launch_qkv_rope_splitk<128, 64, 4, 2, 1, 1, 6>},
-    {64, 64, 2, 3., 0.18, 0.18, 0.36, launch_qkv_rope_splitk<64, 64, 4, 1, 2, 1, 4>},
-    {64, 32, 2, 2., 0.17, 0.17, 0.28, launch_qkv_rope_splitk<64, 32, 4, 2, 1, 2, 3>},
-    {32, 32, 2, 2., 0.14, 0.14, 0.22, launch_qkv_rope_splitk<32, 32, 8, 1, 1, 2, 4>},
-};
-constexpr double kQkvLaunchUs = 3.;
-
-// estimated time of `tiles` tiles: full rounds of the device and a last one, as full as it is
-static double qkv_cost(const QkvTile& v, int64_t tiles, int n_cu, int slices) {
-    const int64_t slots = (int64_t)n_cu * v.per_cu, rest = tiles % slots;
-    const double full = v.round + slices * (v.per_cu == 2 ? v.t2 : v.t1);
-    double us = kQkvLaunchUs + (double)(tiles / slots) * full;
-    if (rest > n_cu) us += full;
-    else if (rest > 0) us += v.round + slices * (v.lo + (v.t1 - v.lo) * (double)rest / (double)n_cu);
-    return us;
-}
+static_assert(sizeof(kQkvLaunchers) / sizeof(kQkvLaunchers[0]) == kQkvTileKinds, "one launcher per kind of tile");
 
 // n_q + n_k heads are rotated and go to q and k, n_v heads go to v as they are.  With n_q = n_k = 0 the
 // call is a plain projection y = x w^T into v ([tokens, n_v * 128]).
@@ -574,48 +556,16 @@ hipError_t launch_qkv_rope(const void* x, const void* w, const float* cos_tab, c
     a.w_st = w_st;
     int n_cu = 0;
     if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-    // One kind of tile for all features, or the full rounds of a large kind and the rest of the features with
-    // another, whichever is estimated shortest: 4096 tokens x 6144 features are 16 x 24 of the largest tiles =
-    // one and a half rounds of 256 compute units (371 us at hidden_in 8192), or 16 x 16 of them and 32 x 16 of
-    // 128 x 128, two to a unit (356 us).  The largest kind addresses its 256 rows with 32-bit offsets.
-    const int features = (n_q + n_k + n_v) * 128, slices = hidden_in / 64;
+    // the largest kind addresses its 256 rows with 32-bit offsets
     const bool largest_fits = x_st * 256 * 2 < (int64_t)1 << 32 && w_st * 256 * 2 < (int64_t)1 << 32;
-    auto row_tiles = [&](const QkvTile& t) { return (tokens + t.mt - 1) / t.mt; };
-    auto cost = [&](const QkvTile& t, int f) { return qkv_cost(t, row_tiles(t) * ((f + t.nt - 1) / t.nt), n_cu, slices); };
-    const QkvTile* const kinds = kQkvTiles + (largest_fits ? 0 : 1);
-    const QkvTile* const end = kQkvTiles + sizeof(kQkvTiles) / sizeof(kQkvTiles[0]);
-    const QkvTile *first = nullptr, *second = nullptr;
-    int f_first = features;
-    double best = 0.;
-    for (const QkvTile* t = kinds; t < end; ++t) {
-        const double c = cost(*t, features);
-        if (!first || c < best) {
-            best = c;
-            first = t;
-        }
-    }
-    for (const QkvTile* t = kinds; t < kQkvTiles + 2; ++t) {
-        const int64_t slots = (int64_t)n_cu * t->per_cu, m = row_tiles(*t);
-        const int64_t rounds = m * ((features + t->nt - 1) / t->nt) / slots;
-        const int64_t f = rounds * slots / m * t->nt;
-        if (f <= 0 || f >= features) continue;
-        const double head = cost(*t, (int)f);
-        for (const QkvTile* u = kinds; u < end; ++u) {
-            const double c = head + cost(*u, features - (int)f);
-            if (c < best) {
-                best = c;
-                first = t;
-                second = u;
-                f_first = (int)f;
-            }
-        }
-    }
+    const int features = (n_q + n_k + n_v) * 128;
+    const QkvPlan plan = plan_qkv(tokens, hidden_in, features, largest_fits, n_cu);
     a.f_first = 0;
-    a.f_count = f_first;
-    if (hipError_t e = first->launch(a, stream); e != hipSuccess || !second) return e;
-    a.f_first = f_first;
-    a.f_count = features - f_first;
-    return second->launch(a, stream);
+    a.f_count = plan.f_first;
+    if (hipError_t e = kQkvLaunchers[plan.first](a, stream); e != hipSuccess || plan.second < 0) return e;
+    a.f_first = plan.f_first;
+    a.f_count = features - plan.f_first;
+    return kQkvLaunchers[plan.second](a, stream);
 }
 
 }  // namespace ttt
