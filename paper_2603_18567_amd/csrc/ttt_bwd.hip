@@ -1511,7 +1511,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         const int n_jh = geo.n_steps * geo.G;
         int n_split = 1;
         a.q_split = 1;
-        int n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
+        int64_t n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
         if constexpr (k16) {
             int n_cu = 0;
             if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
@@ -1519,7 +1519,8 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
             a.chunk_blocks = plan.chunk_blocks;
             n_split = plan.n_split;
             n_units = dkv_units_of(geo.T, a.n_tiles_kv, a.chunk_blocks);
-            a.n_units = n_units;
+            if (n_units * n_split > 0x7fffffffLL) return hipErrorInvalidValue;
+            a.n_units = (int)n_units;
         } else {
             int n_cu = 0;
             if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
@@ -1530,7 +1531,7 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         }
         a.n_split = n_split;
         int64_t grid_kv, grid_q;
-        set_head_map(a.map_kv, geo.hkv, n_units * n_split, grid_kv);
+        set_head_map(a.map_kv, geo.hkv, (int)(n_units * n_split), grid_kv);
         set_head_map(a.map_q, geo.hkv, a.n_tiles_q * geo.n_steps * geo.G, grid_q);
         grid_kv = (grid_kv + 7) / 8 * 8;   // workgroups go to the XCDs in turn: keep the dQ part's map in step with them
         if (grid_kv + grid_q > 0x7fffffffLL) return hipErrorInvalidValue;

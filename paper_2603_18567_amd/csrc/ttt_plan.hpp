@@ -4,7 +4,6 @@
 #include <stdint.h>
 
 #include <algorithm>
-#include <functional>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -124,31 +123,46 @@ struct DkvPlan {
     int chunk_blocks, n_split;
 };
 
-inline int dkv_units_of(int T, int n_tiles, int chunk_blocks) {
+inline int64_t dkv_units_of(int T, int n_tiles, int chunk_blocks) {
     const int n_chunks = (T + chunk_blocks * 32 - 1) / (chunk_blocks * 32);
-    int n = 0;
+    int64_t n = 0;
     for (int ch = 0; ch < n_chunks; ++ch) n += std::min(n_tiles, (ch + 1) * chunk_blocks / 4);
     return n;
 }
 
+// Steps per (step, head) pair of one unit: its 32-row query blocks (from the tile's first row, or the chunk's, to the
+// last row that sees the tile's last key), two at a time.  0: no row of the chunk sees the tile.
+inline int dkv_unit_steps(int tile, int q_end, int chunk, int chunk_blocks) {
+    const int first = std::max(tile * 4, chunk * chunk_blocks);
+    const int n = std::min((q_end - 1) / 32, (chunk + 1) * chunk_blocks - 1) - first + 1;
+    return n > 0 ? (n + 1) / 2 : 0;
+}
+
 // the share of one XCD of a launch part: unit number u of every kv head, in launch order (decode_block)
-template <typename F> void for_units_of_an_xcd(int hkv, int n_units, F&& f) {
+template <typename F> void for_units_of_an_xcd(int hkv, int64_t n_units, F&& f) {
     if (hkv % 8 == 0) {
-        for (int u = 0; u < n_units; ++u)
+        for (int64_t u = 0; u < n_units; ++u)
             for (int hp = 0; hp < hkv / 8; ++hp) f(u);
     } else if (8 % hkv == 0) {
-        for (int u = 0; u < n_units; u += 8 / hkv) f(u);
+        for (int64_t u = 0; u < n_units; u += 8 / hkv) f(u);
     } else {
-        for (int64_t id = 0; id < (int64_t)n_units * hkv; id += 8) f((int)(id / hkv));
+        for (int64_t id = 0; id < n_units * hkv; id += 8) f(id / hkv);
     }
 }
 
+// Planning is on the caller's thread, and a packed batch has a new layout every iteration: what is counted per chunk
+// size has a closed form per key tile, and units are listed only for options that are dealt, at most kMaxDealt in
+// all; a launch with more is judged by its bound, to which it is then close (the choices at 128 ... 16384 tokens are
+// those of dealing every option, up to 131072 tokens within 0.04 % by the model).  Seven calls of one step each,
+// fresh layout of documents of 256 ... 4096 tokens, 32/8 heads: 16384 tokens 0.17 ms, 65536 1.1, 524288 1.3 (lists of
+// all units per call: 0.36, 5.2 and 590).
 inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
     const int T = a.T, n_jh = a.n_steps * a.G;
     const int n_tiles = (T + 127) / 128, n_tiles_q = (T + 255) / 256;
     const float stream = head_dim == 64 ? 0.6f : 1.f;
     const float kStepUs = 1.9f * stream, kUnitUs = 13.f, kEmptyUs = 1.f;
     const float kTileUs = 5.f * stream, kDiagUs = 1.7f * stream, kQUs = 8.f;
+    constexpr int kMaxDealt = 12288;
     // one entry per distinct request: the plan depends on the document structure, the steps, the heads and the device
     struct Key {
         int T, n_docs, step_begin, n_steps, G, hkv, head_dim, n_cu;
@@ -169,6 +183,7 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
             if (e.first == key) return e.second;
     }
     const int cus = std::max(1, n_cu / 8);
+    const double share = (double)a.hkv / 8.;   // heads per XCD
     // document of token i, asked for rising i
     int doc = 0;
     auto doc_of = [&](int i) {
@@ -179,71 +194,80 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
     std::vector<int> q_end(n_tiles), q_keys(n_tiles_q);
     for (int t = 0; t < n_tiles; ++t) q_end[t] = a.cu_host[doc_of(std::min(t * 128 + 127, T - 1)) + 1] - a.cu_base;
     doc = 0;
-    for (int t = 0; t < n_tiles_q; ++t)
+    double keys = 0.;
+    for (int t = 0; t < n_tiles_q; ++t) {
         q_keys[t] = std::min(t * 256 + 255, T - 1) / 128 - (a.cu_host[doc_of(t * 256)] - a.cu_base) / 128 + 1;
+        keys += q_keys[t];
+    }
     // the dQ tiles of one XCD in launch order
+    const double n_dq = share * n_tiles_q * n_jh;
+    const double dq_work = n_dq * (kQUs + (a.step_begin + 0.5 * (a.n_steps - 1)) * kDiagUs) + share * n_jh * keys * kTileUs;
     std::vector<float> dq;
-    double dq_work = 0.;
-    for_units_of_an_xcd(a.hkv, n_tiles_q * n_jh, [&](int u) {
-        const int js = u / a.G % a.n_steps, t = n_tiles_q - 1 - u / n_jh;
-        dq.push_back(kQUs + q_keys[t] * kTileUs + (a.step_begin + js) * kDiagUs);
-        dq_work += dq.back();
-    });
+    if (n_dq <= kMaxDealt)
+        for_units_of_an_xcd(a.hkv, (int64_t)n_tiles_q * n_jh, [&](int64_t unit) {
+            const int u = (int)unit, js = u / a.G % a.n_steps, t = n_tiles_q - 1 - u / n_jh;
+            dq.push_back(kQUs + q_keys[t] * kTileUs + (a.step_begin + js) * kDiagUs);
+        });
     struct Option {
         int cb, ns;
-        double bound;   // no schedule ends before this
+        double bound;   // about when the best schedule ends: the longest unit, or the work over the compute units
+        double dealt;   // units and dQ tiles of one XCD
     };
     std::vector<Option> options;
-    std::vector<std::vector<int>> steps_of;   // per chunk size: steps per (step, head) pair of each unit
-    std::vector<int> sizes;
-    for (int cb : {8, 16, 32, 64, 128}) {
+    for (int log2_cb = 3; log2_cb <= 7; ++log2_cb) {
+        const int cb = 1 << log2_cb;
         if (cb > 32 && n_jh > 8) break;
         if (cb > 8 && cb * 16 >= T) break;    // one chunk covers everything already
-        std::vector<int> nqb2;
-        double blocks = 0.;
-        int used = 0, most = 0;
-        const int n_chunks = (T + cb * 32 - 1) / (cb * 32);
-        for (int ch = 0; ch < n_chunks; ++ch) {
-            const int tiles = std::min(n_tiles, (ch + 1) * cb / 4);
-            for (int t = 0; t < tiles; ++t) {
-                const int qb_lo = std::max(t * 4, ch * cb);
-                const int nqb = std::min((q_end[t] - 1) / 32, (ch + 1) * cb - 1) - qb_lo + 1;
-                const int n2 = nqb > 0 ? (nqb + 1) / 2 : 0;
-                nqb2.push_back(n2);
-                blocks += n2;
-                used += n2 > 0;
-                most = std::max(most, n2);
-            }
+        // A tile is seen from the chunk of its own first row to that of its last row's block: the first of these
+        // chunks and the last are partial, those between are whole.
+        double blocks = 0., used = 0.;
+        int most = 0;
+        for (int t = 0; t < n_tiles; ++t) {
+            const int c0 = t * 4 >> log2_cb, c1 = (q_end[t] - 1) >> (5 + log2_cb);
+            const int s0 = dkv_unit_steps(t, q_end[t], c0, cb), s1 = c1 > c0 ? dkv_unit_steps(t, q_end[t], c1, cb) : 0;
+            const int whole = std::max(0, c1 - c0 - 1);
+            blocks += s0 + s1 + (double)whole * (cb / 2);
+            used += c1 - c0 + 1;
+            most = std::max({most, s0, s1, whole > 0 ? cb / 2 : 0});
         }
-        const double share = (double)a.hkv / 8.;   // heads per XCD
+        const int64_t units = dkv_units_of(T, n_tiles, cb);
         for (int ns : {1, 2, 3, 4, 6, 8}) {
-            if (ns > n_jh) break;
-            const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((int)nqb2.size() - used) * kEmptyUs));
+            if (ns > n_jh || units * ns * a.hkv > 0x7fffffff) break;   // (more workgroups than a grid has)
+            const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((double)units - used) * kEmptyUs));
             const double longest = (double)((n_jh + ns - 1) / ns) * most * kStepUs + kUnitUs;
-            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work) / cus)});
+            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work) / cus), share * (double)units * ns + n_dq});
         }
-        sizes.push_back(cb);
-        steps_of.push_back(std::move(nqb2));
     }
     std::sort(options.begin(), options.end(), [](const Option& x, const Option& y) { return x.bound < y.bound; });
     DkvPlan best{16, 1};
-    double best_us = -1.;
-    std::vector<float> heap;
-    int dealt = 0;
+    if (!options.empty()) best = DkvPlan{options[0].cb, options[0].ns};
+    double best_us = -1., dealt = 0.;
+    std::vector<float> free_at;
+    std::vector<int> steps;
     for (const Option& o : options) {
         if (best_us >= 0. && o.bound >= best_us) break;
-        const std::vector<int>& nqb2 = steps_of[std::find(sizes.begin(), sizes.end(), o.cb) - sizes.begin()];
-        heap.assign(cus, 0.f);
+        if ((dealt += o.dealt) > kMaxDealt) break;
+        steps.clear();
+        const int n_chunks = (T + o.cb * 32 - 1) / (o.cb * 32);
+        for (int ch = 0; ch < n_chunks; ++ch)
+            for (int t = 0; t < std::min(n_tiles, (ch + 1) * o.cb / 4); ++t) steps.push_back(dkv_unit_steps(t, q_end[t], ch, o.cb));
+        free_at.assign(cus, 0.f);
         float finish = 0.f;
-        auto deal = [&](float us) {   // to the compute unit that frees up first
-            std::pop_heap(heap.begin(), heap.end(), std::greater<float>());
-            heap.back() += us;
-            finish = std::max(finish, heap.back());
-            std::push_heap(heap.begin(), heap.end(), std::greater<float>());
-            ++dealt;
+        auto deal = [&](float us) {   // to the compute unit that frees up first: the root of a heap, which then sinks
+            const float t = free_at[0] + us;
+            finish = std::max(finish, t);
+            int i = 0;
+            for (int c = 1; c < cus; c = 2 * i + 1) {
+                if (c + 1 < cus && free_at[c + 1] < free_at[c]) ++c;
+                if (!(free_at[c] < t)) break;
+                free_at[i] = free_at[c];
+                i = c;
+            }
+            free_at[i] = t;
         };
-        for_units_of_an_xcd(a.hkv, (int)nqb2.size() * o.ns, [&](int u) {
-            const int sp = u / (int)nqb2.size(), n2 = nqb2[u % nqb2.size()];
+        const int n = (int)steps.size();
+        for_units_of_an_xcd(a.hkv, (int64_t)n * o.ns, [&](int64_t u) {
+            const int sp = (int)u / n, n2 = steps[(int)u % n];
             deal(n2 > 0 ? (float)((n_jh - sp + o.ns - 1) / o.ns * n2) * kStepUs + kUnitUs : kEmptyUs);
         });
         for (float us : dq) deal(us);
@@ -251,7 +275,6 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
             best_us = finish;
             best = DkvPlan{o.cb, o.ns};
         }
-        if (dealt > 40000) break;   // very large launches: the bound, by which the options are sorted, is close
     }
     std::lock_guard<std::mutex> lock(mu);
     if (cache.size() >= 64) cache.erase(cache.begin());

@@ -1,0 +1,42 @@
+// The launch rules of the library (csrc/ttt_plan.hpp) behind C functions, built by a plain C++ compiler: which kernel
+// variant and work split a call takes on a device of n_cu compute units.
+#include "../paper_2603_18567_amd/csrc/ttt_plan.hpp"
+
+extern "C" {
+
+void plan_forward(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int is_bf16, int head_dim,
+                  int n_cu, int* split, int* pack_log2) {
+    const ttt::FwdPlan p = ttt::plan_fwd(ttt::CallShape{T, step_begin, n_steps, G, hkv, n_docs, cu, cu[0]}, is_bf16 != 0, head_dim, n_cu);
+    *split = p.split;
+    *pack_log2 = p.pack_log2;
+}
+
+void plan_backward(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int head_dim, int n_cu,
+                   int* chunk_blocks, int* n_split) {
+    const ttt::DkvPlan p = ttt::plan_dkv_split(ttt::CallShape{T, step_begin, n_steps, G, hkv, n_docs, cu, cu[0]}, head_dim, n_cu);
+    *chunk_blocks = p.chunk_blocks;
+    *n_split = p.n_split;
+}
+
+void plan_backward_f32(int T, int n_steps, int G, int hkv, int n_cu, int* n_split, int* q_split) {
+    const ttt::DkvPlanF32 p = ttt::plan_dkv_split_f32(ttt::CallShape{T, 0, n_steps, G, hkv, 0, nullptr, 0}, n_cu);
+    *n_split = p.n_split;
+    *q_split = p.q_split;
+}
+
+// tile sizes and workgroups per compute unit of the launches of a projection; returns how many there are
+int plan_projection(int64_t tokens, int hidden_in, int features, int largest_fits, int n_cu, int* mt_nt_per_cu, int* f_first) {
+    const ttt::QkvPlan p = ttt::plan_qkv(tokens, hidden_in, features, largest_fits != 0, n_cu);
+    int n = 0;
+    for (int kind : {p.first, p.second}) {
+        if (kind < 0) continue;
+        const ttt::QkvTile& t = ttt::kQkvTiles[kind];
+        mt_nt_per_cu[3 * n] = t.mt;
+        mt_nt_per_cu[3 * n + 1] = t.nt;
+        mt_nt_per_cu[3 * n + 2] = t.per_cu;
+        ++n;
+    }
+    *f_first = p.f_first;
+    return n;
+}
+}

@@ -1,0 +1,56 @@
+"""The library's launch rules on the CPU (plan_harness.cpp, built once per process with the C++ compiler)."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
+import numpy as np
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+SPLITS = ("eight_waves", "four_waves", "two_key_groups")
+
+
+@functools.lru_cache(maxsize=None)
+def _lib():
+    with tempfile.TemporaryDirectory() as d:
+        so = os.path.join(d, "plan.so")
+        subprocess.run(["g++", "-std=c++17", "-O2", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC", "-o", so,
+                        os.path.join(HERE, "plan_harness.cpp")], check=True)
+        return ctypes.CDLL(so)   # stays mapped
+
+
+def _cu(docs):
+    return np.concatenate([[0], np.cumsum(docs)]).astype(np.int32)
+
+
+def _call(fn, *args, n_out=2):
+    out = [ctypes.c_int() for _ in range(n_out)]
+    fn(*args, *(ctypes.byref(o) for o in out))
+    return tuple(o.value for o in out)
+
+
+def forward_split(docs, hq, hkv, d, dtype, step_begin, n_steps, n_cu=256):
+    """(split, query heads that share a workgroup)"""
+    cu = _cu(docs)
+    split, pack = _call(_lib().plan_forward, int(cu[-1]), step_begin, n_steps, hq // hkv, hkv, len(docs),
+                        cu.ctypes.data_as(ctypes.c_void_p), int(dtype == "bf16"), d, n_cu)
+    return SPLITS[split], 1 << pack
+
+
+def backward_split(cu, hq, hkv, d, step_begin, n_steps, n_cu=256):
+    """(32-row query blocks per chunk, parts of the (step, head) list); cu: int32 array"""
+    return _call(_lib().plan_backward, int(cu[-1] - cu[0]), step_begin, n_steps, hq // hkv, hkv, len(cu) - 1,
+                 cu.ctypes.data_as(ctypes.c_void_p), d, n_cu)
+
+
+def backward_split_f32(tokens, hq, hkv, n_steps, n_cu=256):
+    """(parts of the (step, head) list, parts of the query rows)"""
+    return _call(_lib().plan_backward_f32, tokens, n_steps, hq // hkv, hkv, n_cu)
+
+
+def projection_tiles(tokens, hidden_in, features, n_cu=256, largest_fits=True):
+    """[(tokens, features, workgroups per compute unit) of a tile] of the launches"""
+    tiles, f_first = (ctypes.c_int * 6)(), ctypes.c_int()
+    n = _lib().plan_projection(ctypes.c_int64(tokens), hidden_in, features, int(largest_fits), n_cu, tiles, ctypes.byref(f_first))
+    return [tuple(tiles[3 * i:3 * i + 3]) for i in range(n)]
