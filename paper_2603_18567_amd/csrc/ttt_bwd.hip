@@ -1470,14 +1470,15 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         a.bounds_blocks = (geo.T + 255) / 256;
         a.clear_n4 = !a.accumulate || a.carry_reset ? acc_n4 : 0;
         const int64_t grid = pre_blocks + a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
-        const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);
-        if (grid > 0x7fffffffLL || lds > 160 * 1024) return hipErrorInvalidValue;
+        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
         a.pre_blocks = (int)pre_blocks;
         if constexpr (sizeof(T) == 2) {
             ProfileScope prof("ttt_bwd_pre_regs_kernel", stream);
             hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D, kPreRegBlocks, 2>), dim3((unsigned)grid), dim3(256), 0, stream, a);
         } else {
             auto kern = ttt_bwd_pre_kernel<T, D>;
+            const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);   // D of a unit's (step, head) pairs
+            if (lds > 160 * 1024) return hipErrorInvalidValue;
             if (lds > 48 * 1024) {
                 e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
                 if (e != hipSuccess) return e;

@@ -25,3 +25,16 @@ def test_many_steps_match_oracle(k, d, calls):
     torch.cuda.synchronize()
     for key, (err, bound) in compare_full(case).items():
         assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
+
+
+def test_many_steps_times_heads_match_oracle():
+    """32 steps of 41 query heads per kv head: the bf16 kernels set no limit on (step, head) pairs (1312 here; a
+    preprocess that kept D in LDS would have room for 1280)."""
+    wl = custom_workload("steps_32_heads_41", "bf16", [21, 5], 41, 1, 64, 32, seed=93)
+    print("k=32 d=64 heads=41/1", flush=True)
+    case = Case(wl, "cuda:0")
+    case.run.forward()
+    case.run.backward(case.d_o)
+    torch.cuda.synchronize()
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
