@@ -535,8 +535,6 @@ static_assert(sizeof(kQkvLaunchers) / sizeof(kQkvLaunchers[0]) == kQkvTileKinds,
 hipError_t launch_qkv_rope(const void* x, const void* w, const float* cos_tab, const float* sin_tab, const int* pos, void* q,
                            void* k, void* v, int64_t tokens, int hidden_in, int n_q, int n_k, int n_v, int64_t x_st,
                            int64_t w_st, int n_pos, hipStream_t stream) {
-    // 64 rows of x or w are addressed with 32-bit byte offsets
-    if (x_st * 64 * 2 >= (int64_t)1 << 32 || w_st * 64 * 2 >= (int64_t)1 << 32) return hipErrorInvalidValue;
     QkvArgs a;
     a.x = x;
     a.w = w;
@@ -556,8 +554,8 @@ hipError_t launch_qkv_rope(const void* x, const void* w, const float* cos_tab, c
     a.w_st = w_st;
     int n_cu = 0;
     if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-    // the largest kind addresses its 256 rows with 32-bit offsets
-    const bool largest_fits = x_st * 256 * 2 < (int64_t)1 << 32 && w_st * 256 * 2 < (int64_t)1 << 32;
+    // the largest kind addresses its 256 rows with 32-bit byte offsets (the others with a 64-bit address per row)
+    const bool largest_fits = x_st < (int64_t)1 << 23 && w_st < (int64_t)1 << 23;
     const int features = (n_q + n_k + n_v) * 128;
     const QkvPlan plan = plan_qkv(tokens, hidden_in, features, largest_fits, n_cu);
     a.f_first = 0;

@@ -191,6 +191,30 @@ def test_output_projection_matches_oracle(name, T, hq, nout, o_pad, w_pad):
     assert np.isfinite(got).all()
 
 
+@pytest.mark.parametrize("x_stride,w_stride", [(2 ** 25 + 8, 128), (128, 2 ** 25 + 8), (2 ** 23, 128)])
+def test_rows_far_apart(x_stride, w_stride):
+    """Row strides from 2^23 elements on are beyond the 32-bit offsets of the largest tiles (256 rows of 2 bytes each),
+    from 2^25 beyond those of 64 rows: such calls take tiles that hold an address per row."""
+    from oracle.qkv_oracle import o_proj
+    from paper_2603_18567_amd import binding
+    T, fin, nout = 3, 128, 128
+    print(f"strides {x_stride} {w_stride}", flush=True)
+    gen = torch.Generator().manual_seed(x_stride % 1000)
+    o = torch.randn(T, fin, generator=gen).to(torch.bfloat16)
+    w = (torch.randn(nout, fin, generator=gen) / math.sqrt(fin)).to(torch.bfloat16)
+    dev = torch.device("cuda:0")
+
+    def spread(m, stride):
+        view = torch.empty((len(m) - 1) * stride + fin, dtype=torch.bfloat16, device=dev).as_strided(m.shape, (stride, 1))
+        view.copy_(m.to(dev))
+        return view
+
+    out = torch.full((T, nout), float("nan"), dtype=torch.bfloat16, device=dev)
+    binding.ttt_o_proj_fwd(spread(o, x_stride), spread(w, w_stride), out)
+    torch.cuda.synchronize()
+    check(out.float().cpu().numpy(), o_proj(o.float().numpy(), w.float().numpy()), "out")
+
+
 def test_output_projection_argument_errors():
     from paper_2603_18567_amd import binding
     dev = torch.device("cuda:0")
