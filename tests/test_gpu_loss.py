@@ -1,6 +1,7 @@
 """GPU parity of the in-place log-softmax-loss backward (Alg. 3) against the fp64 oracle, element by
-element, through the C ABI: vectorised and element-wise paths, register-cached and streamed rows,
-ragged vocabulary sizes, strided rows, masked rows (g = 0)."""
+element, through the C ABI: rows held in registers by 256, 512 and 1024 threads, rows held in registers and LDS, rows that
+are partly read twice, rows that start at any element, strided rows, masked rows (g = 0), and tensors above and
+below the size from which the caches are passed by."""
 import os
 import sys
 
@@ -36,9 +37,9 @@ CASES = [   # name, rows, vocabulary, dtype, stride padding; the position in thi
     ("f32_ragged_unaligned", 4, 4099, torch.float32, 0),        # vocab not a multiple of the vector width
     ("bf16_ragged", 4, 50257, torch.bfloat16, 0),
     ("f32_strided_rows", 6, 2048, torch.float32, 64),
-    ("f32_odd_stride_elementwise", 3, 777, torch.float32, 3),   # stride not 16-byte aligned: element path
-    ("f32_streamed_long_row", 3, 70001, torch.float32, 0),      # beyond the register cache
-    ("bf16_streamed_long_row", 2, 151936, torch.bfloat16, 0),
+    ("f32_odd_stride_elementwise", 3, 777, torch.float32, 3),   # rows start at any element: columns before the first vector
+    ("f32_streamed_long_row", 3, 70001, torch.float32, 0),      # registers and LDS
+    ("bf16_streamed_long_row", 2, 151936, torch.bfloat16, 0),   # the last slabs are read twice
     ("f32_vocab_1", 3, 1, torch.float32, 0),
     ("bf16_256_threads_last_size", 5, 16384, torch.bfloat16, 0),
     ("bf16_unaligned_rows", 5, 16385, torch.bfloat16, 0),       # contiguous odd vocabulary: rows start at any element
@@ -47,6 +48,23 @@ CASES = [   # name, rows, vocabulary, dtype, stride padding; the position in thi
     ("bf16_long_one_slab_twice", 5, 147456 + 4093, torch.bfloat16, 0),
     ("f32_long_odd_stride", 4, 55299, torch.float32, 3),
     ("f32_long_many_slabs_twice", 3, 151937, torch.float32, 0),
+    ("f32_512_threads", 5, 12001, torch.float32, 0),
+]
+
+# Logits and target together just above 256 MB, where the kernels pass the caches by: each kernel of each type.
+LARGE_CASES = [   # name, rows, vocabulary, dtype
+    ("f32_256_threads", 8200, 4099, torch.float32),
+    ("f32_512_threads", 2800, 12001, torch.float32),
+    ("f32_1024_threads", 1100, 32000, torch.float32),
+    ("f32_1024_threads_unaligned_rows", 1100, 32001, torch.float32),
+    ("f32_long_18_slabs", 680, 50001, torch.float32),
+    ("f32_long_one_part_twice", 450, 75001, torch.float32),
+    ("bf16_256_threads", 4200, 16001, torch.bfloat16),
+    ("bf16_512_threads", 2100, 32003, torch.bfloat16),
+    ("bf16_1024_threads", 1110, 61003, torch.bfloat16),
+    ("bf16_long_18_slabs", 600, 113001, torch.bfloat16),
+    ("bf16_long_one_part_twice", 450, 151936, torch.bfloat16),
+    ("bf16_long_one_part_twice_unaligned_rows", 450, 151937, torch.bfloat16),
 ]
 
 
@@ -75,6 +93,38 @@ def test_loss_backward_matches_oracle(seed, name, n, v, dtype, pad):
     assert torch.equal(pd, p_before), "the target must not be written"
     if pad:
         assert torch.equal(zd[:, v:].cpu(), z[:, v:]), "columns past the vocabulary must not be touched"
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,n,v,dtype", LARGE_CASES, ids=[c[0] for c in LARGE_CASES])
+def test_loss_backward_of_large_tensors(name, n, v, dtype):
+    """Every element of every row against the gradient in fp64 torch operations, three rows against the oracle too;
+    the bound is that of the cases above, row by row."""
+    from paper_2603_18567_amd import binding as B
+    print(f"case {name}: rows={n} vocab={v} dtype={dtype}", flush=True)
+    assert 2 * n * v * dtype.itemsize > 256 << 20
+    gen = torch.Generator(device="cuda:0").manual_seed(v)
+    z = (torch.randn(n, v, generator=gen, device="cuda:0") * 3).to(dtype)
+    p = torch.rand(n, v, generator=gen, device="cuda:0").pow_(6)
+    p = p.div_(p.sum(1, keepdim=True)).to(dtype)
+    g = torch.randn(n, generator=gen, device="cuda:0")
+    got = z.clone()
+    p_before = p.clone()
+    B.ttt_loss_bwd_inplace(got, p, g)
+    torch.cuda.synchronize()
+    assert torch.equal(p, p_before), "the target must not be written"
+    for rows in torch.arange(n).split(200):
+        rows = slice(int(rows[0]), int(rows[-1]) + 1)
+        p64, g64 = p[rows].double(), g[rows].double()[:, None]
+        pg = p64 * g64
+        ref = torch.softmax(z[rows].double(), 1) * (g64 * p64.sum(1, keepdim=True)) - pg
+        bound = TOL[dtype] * torch.maximum(ref.abs().amax(1), pg.abs().amax(1))
+        err = (got[rows].double() - ref).abs().amax(1)
+        assert bool((err <= bound).all()), (rows, float((err / bound).max()))   # (a NaN fails as well)
+    for r in (0, n // 2, n - 1):
+        ref = logsoftmax_loss_bwd(z[r:r + 1].float().cpu().numpy(), p[r:r + 1].float().cpu().numpy(), g[r:r + 1].cpu().numpy())
+        err = np.abs(got[r:r + 1].float().cpu().numpy() - ref).max()
+        assert err <= TOL[dtype] * max(np.abs(ref).max(), float((p[r].float() * g[r]).abs().max()))
 
 
 @pytest.mark.gpu
