@@ -1,16 +1,20 @@
-"""GPU parity of the forward where a workgroup's waves are split into two key groups (launches of few, long
-workgroups): rows whose keys all lie in one group's tiles, an odd number of tiles, ragged last rows, document
-starts inside a tile pair, 4, 2 and 1 query heads per workgroup, and no, one, two and more diagonal keys."""
+"""GPU parity of the forward's work splits.  Two key groups per workgroup (launches of few, long workgroups): rows
+whose keys all lie in one group's tiles, an odd number of tiles, ragged last rows, document starts inside a tile
+pair, 4, 2 and 1 query heads per workgroup, and no, one, two and more diagonal keys.  One key group (launches of
+many workgroups): the same heads per workgroup, rows of several documents in a wave, and more documents than the
+kernel looks up by itself.  Every test asserts the split that the launch rules choose for its calls."""
 import pytest
 import torch
 
+import oracle as O
 from paper_2603_18567_amd.workloads import custom_workload
-from ttt_testlib import Case, compare_full
+from plan_lib import backward_split_f32, forward_split
+from ttt_testlib import Case, check, compare_full, to_np32
 
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    ("one_tile", [50], 8, 2, 2),
+    ("one_tile", [50], 8, 2, 2),   # (without a diagonal key, at step 0, one key group is enough)
     ("two_tiles_ragged", [127], 8, 2, 3),
     ("odd_tiles", [321], 4, 1, 4),
     ("documents_inside_tile_pairs", [70, 1, 130, 64, 33], 8, 2, 4),
@@ -26,11 +30,24 @@ CASES_64 = [
     ("four_waves", [70, 1, 130, 64, 33], 8, 2, 4, 1),
     ("four_waves_one_head", [200, 95], 3, 3, 3, 1),
     ("eight_waves", [63, 200, 1, 336], 32, 8, 4, 4),
+    ("four_waves_two_heads", [33, 1, 130, 64], 4, 2, 4, 1),       # 64 rows: diagonal rows through LDS
+    ("eight_waves_one_head", [63, 200, 1, 300, 41], 32, 32, 3, 3),
+    ("eight_waves_two_heads", [63, 200, 1, 300, 41], 16, 8, 7, 7),
+    ("eight_waves_70_documents", [9, 1, 0, 17, 5] * 14, 48, 16, 6, 6),
 ]
 
 
-def run(name, docs, hq, hkv, d, k, steps_per_call):
+def compute_units():
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+def splits_of_calls(docs, hq, hkv, d, dtype, k, steps_per_call):
+    return [forward_split(docs, hq, hkv, d, dtype, j, steps_per_call, compute_units()) for j in range(0, k, steps_per_call)]
+
+
+def run(name, docs, hq, hkv, d, k, steps_per_call, split):
     print(f"case {name} documents={docs} heads={hq}/{hkv} head_dim={d} k={k}", flush=True)
+    assert all(s == split for s, _ in splits_of_calls(docs, hq, hkv, d, "bf16", k, steps_per_call)[int(name == "one_tile"):])
     wl = custom_workload(f"groups_{name}", "bf16", docs, hq, hkv, d, k, seed=len(docs) + 5)
     case = Case(wl, "cuda:0")
     for j in range(0, k, steps_per_call):
@@ -43,19 +60,46 @@ def run(name, docs, hq, hkv, d, k, steps_per_call):
 
 @pytest.mark.parametrize("name,docs,hq,hkv,k", CASES, ids=[c[0] for c in CASES])
 def test_two_key_groups_match_oracle(name, docs, hq, hkv, k):
-    run(name, docs, hq, hkv, 128, k, 1)
+    run(name, docs, hq, hkv, 128, k, 1, "two_key_groups")
 
 
 @pytest.mark.parametrize("name,docs,hq,hkv,k,steps", CASES_64, ids=[c[0] for c in CASES_64])
 def test_head_dim_64_splits_match_oracle(name, docs, hq, hkv, k, steps):
-    run(name, docs, hq, hkv, 64, k, steps)
+    run(name, docs, hq, hkv, 64, k, steps, next(s for s in ("two_key_groups", "four_waves", "eight_waves") if name.startswith(s)))
 
 
-@pytest.mark.parametrize("docs,hq,hkv,d,k,steps", [([128], 4, 4, 64, 3, 3), ([300], 8, 2, 64, 1, 1), ([65, 1, 70], 8, 2, 64, 2, 1),
-                                                   ([200, 3], 8, 1, 128, 2, 1), ([250], 3, 1, 64, 1, 1)])
-def test_fp32_short_launches_match_oracle(docs, hq, hkv, d, k, steps):
-    """fp32: two key groups in the forward (head_dim 64), query rows of a key tile split over workgroups in the
-    backward, also into more parts than a tile has query tiles."""
+# head_dim 128, one key group: launches of more than six rounds of the device
+ONE_GROUP = [
+    # name, documents, hq, hkv, k, query heads per workgroup
+    ("one_head", [300, 70, 1, 0, 29, 150, 47], 64, 64, 9, 1),
+    ("one_head_of_three", [301, 70, 1, 29, 150, 149], 48, 16, 11, 1),
+    ("two_heads", [300, 70, 1, 29, 150, 101], 32, 16, 17, 2),
+    ("two_heads_of_six", [75, 300, 70, 1, 29, 176], 48, 8, 11, 2),
+    ("one_head_100_documents", [5, 0, 11, 1, 13] * 20, 64, 64, 9, 1),
+    ("two_heads_70_documents", [20, 7, 0, 1, 19, 13, 4] * 10, 32, 16, 17, 2),
+    ("four_heads_80_documents", [30, 7, 17, 1] * 20, 32, 8, 11, 4),
+]
+
+
+@pytest.mark.parametrize("name,docs,hq,hkv,k,heads", ONE_GROUP, ids=[c[0] for c in ONE_GROUP])
+def test_one_key_group_matches_oracle(name, docs, hq, hkv, k, heads):
+    """Forward only: many heads and steps make the workgroups, and the backward does not depend on the split."""
+    print(f"case {name} documents={docs} heads={hq}/{hkv} k={k}", flush=True)
+    assert splits_of_calls(docs, hq, hkv, 128, "bf16", k, k) == [("eight_waves", heads)]
+    wl = custom_workload(f"one_group_{name}", "bf16", docs, hq, hkv, 128, k, seed=len(docs) + 31)
+    case = Case(wl, "cuda:0")
+    for t in case.run.o + case.run.lse:
+        t.fill_(float("nan"))
+    case.run.forward()
+    torch.cuda.synchronize()
+    Q, K, V, _ = case.oracle_inputs()
+    o, lse = O.oracle_full(Q, K, V, wl.cu_seqlens, wl.scale, None, 0, k)[:2]
+    for j in range(k):
+        check(f"O[{j}]", to_np32(case.run.o[j]), o[j], wl.dtype, rows=True)
+        check(f"LSE[{j}]", to_np32(case.run.lse[j]), lse[j], wl.dtype, lse=True)
+
+
+def run_fp32(docs, hq, hkv, d, k, steps):
     print(f"fp32 documents={docs} heads={hq}/{hkv} head_dim={d} k={k}", flush=True)
     case = Case(custom_workload(f"f32_{len(docs)}_{d}_{k}", "f32", docs, hq, hkv, d, k, seed=d + len(docs)), "cuda:0")
     for j in range(0, k, steps):
@@ -65,3 +109,21 @@ def test_fp32_short_launches_match_oracle(docs, hq, hkv, d, k, steps):
     torch.cuda.synchronize()
     for key, (err, bound) in compare_full(case).items():
         assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,steps", [([128], 4, 4, 64, 3, 3), ([300], 8, 2, 64, 1, 1), ([65, 1, 70], 8, 2, 64, 2, 1),
+                                                   ([200, 3], 8, 1, 128, 2, 1), ([250], 3, 1, 64, 1, 1)])
+def test_fp32_short_launches_match_oracle(docs, hq, hkv, d, k, steps):
+    """fp32: two key groups in the forward (head_dim 64), query rows of a key tile split over workgroups in the
+    backward, also into more parts than a tile has query tiles."""
+    assert all(s == ("two_key_groups" if d == 64 else "four_waves") for s, _ in splits_of_calls(docs, hq, hkv, d, "f32", k, steps))
+    assert backward_split_f32(sum(docs), hq, hkv, steps, compute_units())[1] > 1
+    run_fp32(docs, hq, hkv, d, k, steps)
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k", [([150, 1, 82], 16, 16, 64, 5), ([200, 60, 70], 64, 16, 64, 3), ([150, 1, 82], 16, 16, 128, 5)])
+def test_fp32_full_launches_match_oracle(docs, hq, hkv, d, k):
+    """fp32 with work for every compute unit: one key group, query rows in one part."""
+    assert [s for s, _ in splits_of_calls(docs, hq, hkv, d, "f32", k, k)] == ["four_waves"]
+    assert backward_split_f32(sum(docs), hq, hkv, k, compute_units())[1] == 1
+    run_fp32(docs, hq, hkv, d, k, k)

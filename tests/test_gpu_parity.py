@@ -44,7 +44,7 @@ SMALL = [
     custom_workload("bf16_hkv16", "bf16", [200, 120], 32, 16, 128, 2, 22),         # two kv heads per XCD in the block map
     custom_workload("bf16_d64_multi", "bf16", [500, 333, 100], 8, 2, 64, 4, 23),   # head_dim 64 over several tiles
     custom_workload("f32_multi_tile", "f32", [450, 310], 4, 2, 128, 3, 24),        # fp32 kernels over several tiles
-    custom_workload("bf16_gqa3", "bf16", [300, 45, 600], 6, 2, 128, 3, 25),        # 3 query heads per kv head: no head packing
+    custom_workload("bf16_gqa3", "bf16", [300, 45, 600], 6, 2, 128, 3, 25),        # 3 query heads per kv head: one head per workgroup
     custom_workload("bf16_hkv3", "bf16", [420, 130], 6, 3, 128, 3, 26),            # hkv neither divides nor is divided by 8
     custom_workload("bf16_hkv5", "bf16", [777], 10, 5, 128, 4, 27),                # the same with an odd head count, 7 key tiles
     custom_workload("bf16_g16", "bf16", [390, 260], 64, 4, 128, 3, 28),            # 16 query heads per kv head (the 235B shape's grouping)
@@ -86,7 +86,7 @@ def test_outputs_are_fully_overwritten_and_others_untouched():
 @pytest.mark.parametrize("wl", [
     custom_workload("steps_bf16", "bf16", [210, 90], 8, 2, 128, 4, 31),
     custom_workload("steps_f32", "f32", [150], 4, 4, 64, 3, 32),
-    # k > 8: the sweep's calls for steps >= 8 and < 8 take different preprocess kernels over one carry
+    # k > 8: the calls for steps >= 8 take the later blocks in two passes of the preprocess kernel, the others in one
     custom_workload("steps_bf16_k12", "bf16", [300, 77], 4, 2, 128, 12, 35),
 ], ids=lambda w: w.name)
 def test_step_at_a_time_equals_all_steps(wl):

@@ -12,6 +12,7 @@ import torch
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 from oracle.qkv_oracle import qkv_rope, rope_tables   # noqa: E402
+from plan_lib import projection_tiles   # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +103,10 @@ TILE_CASES = [
 def test_every_tile_kind_matches_oracle(name, T, hin, hq, hkv):
     d = 128
     print(f"case {name} T={T} hidden_in={hin} hq={hq} hkv={hkv}", flush=True)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    rows, features = (int(x) for x in name.split("_")[0].split("x"))
+    per_unit = 2 if rows < 128 or "two_per_unit" in name else 1
+    assert (rows, features, per_unit) in projection_tiles(T, hin, (hq + 2 * hkv) * d, n_cu)
     x, w, pos, cos_t, sin_t = make(T, hin, hq, hkv, d, seed=900 + T)
     q, k, v = run_gpu(x, w, pos, cos_t, sin_t, hq, hkv, d, hin)
     assert np.isfinite(q).all() and np.isfinite(k).all() and np.isfinite(v).all()
