@@ -17,6 +17,8 @@ CASES = [
     (custom_workload("ds_bf16_all_equal", "bf16", [130, 200], 4, 2, 128, 3, 32), [3, 3]),
     (custom_workload("ds_f32_mixed", "f32", [70, 33, 120], 4, 4, 64, 4, 33), [1, 4, 2]),
     (custom_workload("ds_bf16_empty_docs", "bf16", [0, 64, 0, 100], 2, 1, 128, 4, 34), [4, 1, 0, 4]),
+    # a run of more documents than the forward looks up by itself, after and before other runs
+    (custom_workload("ds_bf16_80_docs_in_a_run", "bf16", [45] + [3, 1, 0, 9] * 20 + [30, 50], 4, 2, 128, 4, 36), [3] + [2] * 80 + [4, 4]),
 ]
 
 

@@ -1,5 +1,5 @@
 """The library's calls inside a captured HIP graph: they allocate nothing, never synchronise and clear
-their accumulators with a fill kernel (no memset node), so the training-order pattern of Sec. 2.4
+their accumulators inside a kernel (no memset node), so the training-order pattern of Sec. 2.4
 (k forward calls, then k backward calls in descending order with the fp32 carry) can be recorded
 once and replayed.  Every replay is checked against the oracle and against the eager result, with
 eager work and synchronisations between the replays."""
@@ -21,8 +21,9 @@ def _stepwise(case, stream=None):
         run.backward(case.d_o, j, j + 1, accumulate=True, stream=stream)
 
 
-def test_training_order_replayed_from_a_graph():
-    wl = custom_workload("graph_bf16", "bf16", [300, 45, 131], 8, 2, 128, 4, 41)
+@pytest.mark.parametrize("docs", [[300, 45, 131], [20, 1, 0, 9, 3] * 15], ids=["3_documents", "75_documents"])
+def test_training_order_replayed_from_a_graph(docs):
+    wl = custom_workload("graph_bf16", "bf16", docs, 8, 2, 128, 4, 41)
     case = Case(wl)
     run = case.run
     _stepwise(case)                      # eager: allocates outputs and workspaces, sets kernel attributes

@@ -1,6 +1,6 @@
 """The workspace-free forward entry point (for callers that cannot allocate device memory) against
-the ordinary forward, through the C ABI: two calls in a row on the shared built-in scratch, the
-second with a smaller input."""
+the ordinary forward, through the C ABI: two calls in a row, the second with a smaller input, with
+up to 64 documents (the kernels read cu_seqlens) and with more (they read the shared built-in scratch)."""
 import pytest
 import torch
 
@@ -34,6 +34,13 @@ def test_static_scratch_forward_twice_second_call_smaller():
     _both_ways(custom_workload("static_large", "bf16", [700, 1, 799], 8, 2, 128, 4, 41))
     print("case static_small: 2 documents, 190 tokens", flush=True)
     _both_ways(custom_workload("static_small", "bf16", [130, 60], 4, 2, 128, 3, 42))
+
+
+def test_static_scratch_forward_of_many_documents_twice_second_call_smaller():
+    print("case static_100_documents: 1300 tokens", flush=True)
+    _both_ways(custom_workload("static_100_documents", "bf16", [40, 1, 0, 7, 17] * 20, 8, 2, 128, 4, 44))
+    print("case static_70_documents: 308 tokens", flush=True)
+    _both_ways(custom_workload("static_70_documents", "bf16", [3, 1, 0, 11, 7] * 14, 4, 2, 128, 3, 45))
 
 
 def test_static_scratch_forward_rejects_more_tokens_than_the_scratch_holds():
