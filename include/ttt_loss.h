@@ -12,10 +12,11 @@
  *
  * Memory: `logits`, `target` and `grad` are caller-owned DEVICE memory; logits and target are
  * [n_rows, vocab] with the given row strides (in elements, vocab contiguous), both of `dtype`
- * (TTT_F32 or TTT_BF16 of ttt_attn.h); arithmetic is fp32.  16-byte aligned pointers with strides
- * that are multiples of 16 bytes take the vectorised path; anything else is handled element by
- * element.  The library allocates nothing, enqueues one kernel on `hip_stream` and never
- * synchronises.  `logits` is read and then overwritten; `target` and `grad` are only read.
+ * (TTT_F32 or TTT_BF16 of ttt_attn.h); arithmetic is fp32.  Pointers need the alignment of their
+ * elements, and any row stride of at least `vocab` is taken: rows are read and written in 16-byte
+ * vectors from the first 16-byte boundary of the row's logits on, wherever the row starts.  The
+ * library allocates nothing, enqueues one kernel on `hip_stream` and never synchronises.  `logits`
+ * is read and then overwritten; `target` and `grad` are only read.
  *
  * Errors: returns TTT_OK or a negative TTT_ERR_* code (ttt_attn.h); ttt_attn_last_error() has the
  * message.  n_rows = 0 is a no-op.

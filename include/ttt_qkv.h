@@ -26,7 +26,8 @@
  *   accumulated in fp32 on the matrix cores, the rotation is done in fp32, results are rounded to
  *   bf16 once.
  *
- * The library allocates nothing, enqueues one kernel on `hip_stream` and never synchronises.
+ * The library allocates nothing, enqueues one kernel or two (for two ranges of features) on
+ * `hip_stream` and never synchronises.
  * Errors: returns TTT_OK or a negative TTT_ERR_* code (ttt_attn.h); ttt_attn_last_error() has the
  * message.  tokens = 0 is a no-op.
  */
@@ -48,7 +49,7 @@ int ttt_qkv_rope_fwd(const void* x, const void* w, const float* cos_tab, const f
  * The consumer on the other side of the attention: the output projection that reads O_j as the
  * attention kernels wrote it ([tokens, hq * head_dim] is [tokens, hq, head_dim] seen as a matrix):
  *     out[t, f] = sum_c o[t, c] * w[f, c]
- * Same kernel as above without the rotation (the paper names no fusion on this side; the call exists
+ * Same kernels as above without the rotation (the paper names no fusion on this side; the call exists
  * so that the attention block of the draft layer can be driven through this library alone).
  *   o   [tokens, in_features]        bf16, row stride o_row_stride elements (multiple of 8)
  *   w   [out_features, in_features]  bf16, row stride w_row_stride (multiple of 8)

@@ -116,8 +116,12 @@ inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu
 // to its compute units (each to the one that frees up first); over the sweeps its choice is 1.1 % slower
 // than the best one on average and 5 % at most (the dK/dV units dealt alone, with 512 ... 2048-row
 // chunks: 6 % and 17 %).  Long lists stop at 1024-row chunks: the model does not see HBM traffic, and
-// with longer ones the units of one XCD no longer stream the same Q / dO rows together (2048 rows, 4096
-// tokens, all steps: 2.6 GB fetched against 0.9 GB with 512).
+// with longer chunks the units of one XCD no longer stream the same Q / dO rows together (4096 tokens, all
+// steps, dK/dV units alone: 2.6 GB fetched with 2048 rows, 0.9 with 512).  1024 rows already cost some of it:
+// one launch fetches 2.9 GB there against 1.9 with 512, and at 2 x 8192 tokens, 64/4 heads 58 against 39 GB,
+// where a forward and backward with 512 would be 0.7 and 1.1 % faster (4382 against 4414 us, 64.2 against 64.9
+// ms).  Over 90 shapes of 768 ... 16384 tokens for which the two limits choose differently the backward takes 0.89 to
+// 1.22 times as long with 512 at most, 1.004 in the geometric mean, so the line stays here.
 // ------------------------------------------------------------------------------------------------
 struct DkvPlan {
     int chunk_blocks, n_split;
