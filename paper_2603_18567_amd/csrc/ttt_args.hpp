@@ -76,8 +76,10 @@ struct BwdArgs {
     int cu_base, n_docs;
     int64_t clear_n4;       // 16-byte pieces of each block-0 sum to clear
     int pre_blocks;         // workgroups of the preprocess launch that do its main work; after them:
-    int pre_passes;         // (16-bit) in so many passes over the later blocks
     int bounds_blocks;      // those that write tok_start, tok_end; and the rest clear the block-0 sums
+    int diag_units;         // (16-bit) workgroups that make the later blocks' dK, dV: of the preprocess launch, or of
+    int diag_first;         // the streaming launch from this one on,
+    int diag_passes;        // in so many passes over these blocks
     // host side only (the launchers' work-split model reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base
 };

@@ -5,12 +5,14 @@
 //   ttt_bwd_pre_kernel     D for every (step, head, token); and the complete dK_l, dV_l of the later
 //                          cache blocks l >= 1, which are only ever read on the diagonal (suffix part
 //                          of Alg. 2), so one small group of lanes owns each (token, kv head) -- no atomics
-//                          (ttt_bwd_pre_regs_kernel for 16-bit types)
+//                          (16-bit types: ttt_bwd_pre_regs_kernel; or ttt_bwd_delta_kernel for D, and the later
+//                          blocks as diag_unit workgroups of the next launch)
 //   ttt_bwd_main_kernel    both streaming passes in one launch (ttt_bwd_main_f32_kernel for fp32):
 //     dkv_p8_tile, dkv_tile   key-stationary over block 0: dK, dV accumulators of 32 keys per wave in registers
 //                          while every (step, head of the group, query block at or below the diagonal) streams
 //                          past through LDS; partial sums of the splits meet in fp32 atomics
 //     dq_pipe_tile, dq_tile   query-stationary, same streaming structure as the forward: dQ_j
+//     diag_unit            (16-bit) dK_l, dV_l of the later blocks
 //   ttt_bwd_finish_kernel  fp32 block-0 sums -> dK_0, dV_0 in the tensor dtype
 
 #include <algorithm>
@@ -165,86 +167,166 @@ template <int LPR> TTT_DEV float group_sum_dpp(float v) {
     return v;
 }
 
-// The same work for 16-bit types, reading every Q_j, dO_j, O_j row once: the K_l, V_l rows of this (token, kv
-// head) and their fp32 gradients stay in registers while one sweep over (step, head of the group) feeds all of
-// them (the suffix part of Alg. 2 read from the key's side: key (l, i) is seen only by the queries (j >= l, i)
-// of Sec. 2.4's unrolled steps).  NL blocks fit; with more steps the blocks are taken NL at a time by further
-// workgroups, whose sweeps start at the first step that sees one of theirs (16384 tokens in documents of up to
-// 12 steps, mean of the launches with more than 8: 195 us; 379 when every block read its steps' rows again).
-template <typename T, int D, int NL, int PF>
-__global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) {
-    static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
+// 16-bit types: D and LSE * log2(e) alone, which is all that the streaming passes wait for.  Bound by memory (16384
+// tokens, 32 heads, one step: 52 us, 5.2 TB/s); one workgroup takes 32 tokens x kDeltaHeads heads of one step: its loads
+// are all requested at once (whole rows of neighbouring heads), its results leave as runs of 32 tokens.
+constexpr int kDeltaTokens = 32, kDeltaHeads = 4;
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs a) {
+    static_assert(sizeof(T) == 2, "16-bit elements");
     if ((int)blockIdx.x >= a.pre_blocks) {
         bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
         return;
     }
     using frag = typename Elem<T>::frag;
     constexpr int LPR = D / 8;
-    constexpr int UPB = 256 / LPR;
+    constexpr int RPP = 256 / LPR;                                   // rows per pass
+    constexpr int NP = kDeltaTokens * kDeltaHeads / RPP;
+    __shared__ float sum[kDeltaHeads * kDeltaTokens];
 
     const Geometry& geo = a.geo;
-    const int Tn = geo.T, G = geo.G, ns = geo.n_steps, b = geo.step_begin, e = b + ns;
-    const int per_pass = a.pre_blocks / a.pre_passes;
-    const int pass = (int)blockIdx.x / per_pass;
-    const int l0 = 1 + pass * NL;                   // first block of this pass
-    const int j0 = pass > 0 ? max(b, l0) : b;       // first step of its sweep; the first pass also makes D
+    const int n_hc = (geo.hq + kDeltaHeads - 1) / kDeltaHeads;
+    const int h0 = (int)blockIdx.x % n_hc * kDeltaHeads;
+    const int rest = (int)blockIdx.x / n_hc;
+    const int js = rest % geo.n_steps, t0 = rest / geo.n_steps * kDeltaTokens;
+    const int j = geo.step_begin + js;
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-    const int64_t unit = (int64_t)((int)blockIdx.x % per_pass) * UPB + grp;
+    const T* go_base = static_cast<const T*>(a.d_o[j]) + sub * 8;
+    const T* oo_base = static_cast<const T*>(a.o[j]) + sub * 8;
+
+    frag go[NP], oo[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int r = p * RPP + grp;                                 // neighbouring rows are heads of one token
+        const int i = min(t0 + r / kDeltaHeads, geo.T - 1), h = min(h0 + r % kDeltaHeads, geo.hq - 1);
+        const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh;
+        go[p] = gload_frag<T>(go_base + off);
+        oo[p] = gload_frag<T>(oo_base + off);
+    }
+    const int wt = threadIdx.x % kDeltaTokens, wh = threadIdx.x / kDeltaTokens;   // what this thread writes
+    const bool writes = wh < kDeltaHeads && h0 + wh < geo.hq && t0 + wt < geo.T;
+    float lse = 0.f;
+    if (writes) lse = a.lse[j][(int64_t)(h0 + wh) * geo.lse_st + t0 + wt];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const float d = group_sum_dpp<LPR>(dot8(go[p], oo[p], 0.f));
+        const int r = p * RPP + grp;
+        if (sub == 0) sum[r % kDeltaHeads * kDeltaTokens + r / kDeltaHeads] = d;
+    }
+    __syncthreads();
+    if (writes) {
+        const int64_t at = ((int64_t)js * geo.hq + h0 + wh) * geo.T + t0 + wt;
+        a.delta[at] = sum[wh * kDeltaTokens + wt];
+        a.lse2[at] = lse * kLog2e;
+    }
+}
+
+// dK_l, dV_l of the later blocks for 16-bit types: the K_l, V_l rows of a (token, kv head) and their fp32 gradients stay
+// in registers while one sweep over (step, head of the group) feeds all of them (the suffix part of Alg. 2 read from
+// the key's side: key (l, i) is seen only by the queries (j >= l, i) of Sec. 2.4's unrolled steps).
+// kDiagRegBlocks blocks fit; with more steps the blocks are taken so many at a time by further workgroups, whose sweeps
+// start at the first step that sees one of theirs.  Either workgroups of the streaming launch, with D and LSE at hand,
+// or (MAKE_D) the preprocess launch, whose first pass makes these from O on the way.  Bound by memory; the rows of the
+// next two pairs are requested before a pair is worked on (4096 tokens, MAKE_D, 0.98 GB: none ahead 4.45 TB/s, one
+// 4.75, two 5.07; four, with two blocks fewer in registers, no more).
+template <typename T, int D, int THREADS, bool MAKE_D>
+TTT_DEV void diag_unit(const BwdArgs& a, const int wg) {
+    static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
+    using frag = typename Elem<T>::frag;
+    constexpr int NL = kDiagRegBlocks, PF = 2;
+    constexpr int LPR = D / 8;        // lanes that share one (token, kv head): 8 elements each
+    constexpr int UPB = THREADS / LPR;
+
+    const Geometry& geo = a.geo;
+    const int Tn = geo.T, G = geo.G, b = geo.step_begin, e = b + geo.n_steps;
+    const int per_pass = a.diag_units / a.diag_passes;
+    const int pass = wg / per_pass;
+    const int l0 = 1 + pass * NL;                                 // first block of this pass
+    const int j0 = MAKE_D && pass == 0 ? b : max(b, l0);          // first step of its sweep
+    const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
+    const int64_t unit = (int64_t)(wg % per_pass) * UPB + grp;
     if (unit >= (int64_t)Tn * geo.hkv) return;   // whole aligned lane groups leave together
     const int i = (int)(unit / geo.hkv);
     const int g = (int)(unit % geo.hkv);
     const int64_t kvoff = (int64_t)i * geo.kv_st + (int64_t)g * geo.kv_sh + sub * 8;
+    // this lane's place in a block of the carry: two quads D / 2 apart, so that a wave's 16-byte accesses are side by side
+    const int64_t coff = ((int64_t)i * geo.hkv + g) * D + sub * 4;
+    const int64_t cblk = (int64_t)Tn * geo.hkv * D;
 
+    const int n_pairs = (e - j0) * G;
+    frag qf[PF], go[PF], oo[PF];
+    float lse[PF], dl[PF];
+    auto request = [&](int n, int s) {
+        const int j = j0 + n / G, h = g * G + n % G;
+        const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh + sub * 8;
+        qf[s] = gload_frag<T>(static_cast<const T*>(a.q[j]) + off);
+        go[s] = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
+        if constexpr (MAKE_D) {
+            oo[s] = gload_frag<T>(static_cast<const T*>(a.o[j]) + off);
+            lse[s] = a.lse[j][(int64_t)h * geo.lse_st + i];
+        } else {
+            const int64_t at = ((int64_t)(j - b) * geo.hq + h) * Tn + i;
+            lse[s] = a.lse2[at];
+            dl[s] = a.delta[at];
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < PF; ++s)
+        if (s < n_pairs) request(s, s);
+
+    // the sums start from the carry of the later steps' calls: everything that a unit reads is in flight at once
     frag kf[NL], vf[NL];
     float dk[NL][8], dv[NL][8];
+    const bool carried = a.accumulate && !a.carry_reset;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
         if (l0 + l < e) {
             kf[l] = gload_frag<T>(static_cast<const T*>(a.k[l0 + l]) + kvoff);
             vf[l] = gload_frag<T>(static_cast<const T*>(a.v[l0 + l]) + kvoff);
         }
+    }
 #pragma unroll
-        for (int x = 0; x < 8; ++x) dk[l][x] = dv[l][x] = 0.f;
+    for (int l = 0; l < NL; ++l) {
+        if (carried && l0 + l < e) {
+            const float* ck = a.dkl_acc + (l0 + l - 1) * cblk + coff;
+            const float* cv = a.dvl_acc + (l0 + l - 1) * cblk + coff;
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const f32x4 k4 = gload_vec4<float>(ck + half * (D / 2)), v4 = gload_vec4<float>(cv + half * (D / 2));
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    dk[l][4 * half + x] = k4[x];
+                    dv[l][4 * half + x] = v4[x];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) dk[l][x] = dv[l][x] = 0.f;
+        }
     }
 
-    // One sweep over the (step, head of the group) pairs; the rows of the next PF pairs are requested
-    // before a pair is worked on, so that a lane group always has PF requests in flight beside the pair
-    // it works on (the kernel is bound by HBM; measured at 4096 tokens, 0.98 GB per launch: no request
-    // ahead 4.45 TB/s, one 4.75, two 5.07, four -- with one block fewer in registers -- 5.07).
-    const int n_pairs = (e - j0) * G;
-    frag qf[PF], go[PF], oo[PF];
-    float lse_raw[PF];
-    auto request = [&](int n, auto slot_c) {
-        constexpr int S = decltype(slot_c)::value;
-        const int j = j0 + n / G, h = g * G + n % G;
-        const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh + sub * 8;
-        qf[S] = gload_frag<T>(static_cast<const T*>(a.q[j]) + off);
-        go[S] = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
-        oo[S] = gload_frag<T>(static_cast<const T*>(a.o[j]) + off);
-        lse_raw[S] = a.lse[j][(int64_t)h * geo.lse_st + i];
-    };
-    if (n_pairs > 0) request(0, IntC<0>{});
-    if constexpr (PF > 1) if (n_pairs > 1) request(1, IntC<1>{});
-    if constexpr (PF > 2) if (n_pairs > 2) request(2, IntC<2>{});
-    if constexpr (PF > 3) if (n_pairs > 3) request(3, IntC<3>{});
-    static_assert(PF >= 1 && PF <= 4, "prefetch depth");
     for (int n = 0; n < n_pairs; ++n) {
-        const int j = j0 + n / G, h = g * G + n % G;
+        const int j = j0 + n / G;
         const frag cq = qf[0], cg = go[0], co = oo[0];
-        const float lse2 = lse_raw[0] * kLog2e;
+        const float lse2 = MAKE_D ? lse[0] * kLog2e : lse[0];
+        float dsum = dl[0];
 #pragma unroll
         for (int s = 0; s + 1 < PF; ++s) {
             qf[s] = qf[s + 1];
             go[s] = go[s + 1];
             oo[s] = oo[s + 1];
-            lse_raw[s] = lse_raw[s + 1];
+            lse[s] = lse[s + 1];
+            dl[s] = dl[s + 1];
         }
-        if (n + PF < n_pairs) request(n + PF, IntC<PF - 1>{});
-        const float dsum = group_sum_dpp<LPR>(dot8(cg, co, 0.f));
-        if (sub == 0 && pass == 0) {
-            const int64_t at = ((int64_t)(j - b) * geo.hq + h) * Tn + i;
-            a.delta[at] = dsum;
-            a.lse2[at] = lse2;
+        if (n + PF < n_pairs) request(n + PF, PF - 1);
+        if constexpr (MAKE_D) {
+            dsum = group_sum_dpp<LPR>(dot8(cg, co, 0.f));
+            if (sub == 0 && pass == 0) {
+                const int64_t at = ((int64_t)(j - b) * geo.hq + g * G + n % G) * Tn + i;
+                a.delta[at] = dsum;
+                a.lse2[at] = lse2;
+            }
         }
         float qx[8], gx[8];
 #pragma unroll
@@ -257,7 +339,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
             if (l0 + l > j) break;             // a block is visible from the step of its own number on
             const float s = group_sum_dpp<LPR>(dot8(cq, kf[l], 0.f));
             const float dp = group_sum_dpp<LPR>(dot8(cg, vf[l], 0.f));
-            const float p = fast_exp2(s * (geo.scale * kLog2e) - lse2);
+            const float p = fast_exp2(s * geo.scale_log2 - lse2);
             const float ds = p * (dp - dsum) * geo.scale;
 #pragma unroll
             for (int x = 0; x < 8; ++x) {
@@ -271,38 +353,31 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) 
     for (int l = 0; l < NL; ++l) {
         const int lb = l0 + l;
         if (lb >= e) break;
-        if (a.accumulate) {
-            // fp32 carry across the calls of a descending-step sweep; this group owns its slice
-            const int64_t coff = (((int64_t)(lb - 1) * Tn + i) * geo.hkv + g) * D + sub * 8;
-            f32x4* ck = reinterpret_cast<f32x4*>(a.dkl_acc + coff);
-            f32x4* cv = reinterpret_cast<f32x4*>(a.dvl_acc + coff);
-            if (!a.carry_reset) {
+        if (a.accumulate && lb < b) {   // not complete yet: earlier steps' calls have not run
+            float* ck = a.dkl_acc + (lb - 1) * cblk + coff;
+            float* cv = a.dvl_acc + (lb - 1) * cblk + coff;
 #pragma unroll
-                for (int v4 = 0; v4 < 2; ++v4) {
-                    const f32x4 pk = ck[v4], pv = cv[v4];
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        dk[l][4 * v4 + x] += pk[x];
-                        dv[l][4 * v4 + x] += pv[x];
-                    }
-                }
+            for (int half = 0; half < 2; ++half) {
+                gstore_vec4<float>(ck + half * (D / 2), dk[l][4 * half], dk[l][4 * half + 1], dk[l][4 * half + 2], dk[l][4 * half + 3]);
+                gstore_vec4<float>(cv + half * (D / 2), dv[l][4 * half], dv[l][4 * half + 1], dv[l][4 * half + 2], dv[l][4 * half + 3]);
             }
-            if (lb < b) {   // not complete yet: earlier steps' calls have not run
-#pragma unroll
-                for (int v4 = 0; v4 < 2; ++v4) {
-                    ck[v4] = f32x4{dk[l][4 * v4], dk[l][4 * v4 + 1], dk[l][4 * v4 + 2], dk[l][4 * v4 + 3]};
-                    cv[v4] = f32x4{dv[l][4 * v4], dv[l][4 * v4 + 1], dv[l][4 * v4 + 2], dv[l][4 * v4 + 3]};
-                }
-                continue;
-            }
+            continue;
         }
-        T* gk = static_cast<T*>(a.dk[lb]) + kvoff;
-        T* gv = static_cast<T*>(a.dv[lb]) + kvoff;
-        gstore_vec4<T>(gk, dk[l][0], dk[l][1], dk[l][2], dk[l][3]);
-        gstore_vec4<T>(gk + 4, dk[l][4], dk[l][5], dk[l][6], dk[l][7]);
-        gstore_vec4<T>(gv, dv[l][0], dv[l][1], dv[l][2], dv[l][3]);
-        gstore_vec4<T>(gv + 4, dv[l][4], dv[l][5], dv[l][6], dv[l][7]);
+        frag ok, ov;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            ok[x] = (T)dk[l][x];
+            ov[x] = (T)dv[l][x];
+        }
+        *reinterpret_cast<frag*>(static_cast<T*>(a.dk[lb]) + kvoff) = ok;
+        *reinterpret_cast<frag*>(static_cast<T*>(a.dv[lb]) + kvoff) = ov;
     }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) {
+    if ((int)blockIdx.x >= a.pre_blocks) bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
+    else diag_unit<T, D, 256, true>(a, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1392,14 +1467,18 @@ TTT_DEV void dkv_p8_unit(const BwdArgs& a, char* smem, const int wg) {
 // ------------------------------------------------------------------------------------------------
 // One launch for both streaming passes: the dK/dV units first (they are the longer ones), then the dQ
 // tiles in order of falling length.  Neither needs anything from the other, so what one pass leaves of
-// the device while its last units finish is filled by the other.
+// the device while its last units finish is filled by the other -- and, unless the preprocess launch has made them
+// (diag_blocks_apart), by the units of the later blocks' dK, dV, which are short and come last (spread over the
+// launch, or between its two parts, they keep the dK/dV units of an XCD from streaming the same rows together: one
+// step, 32/8 heads, 512 and 2048 tokens 66 and 227 us at the end, 83 and 232 elsewhere).
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D>
 __global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs a) {
     extern __shared__ __align__(16) char smem[];
     const int wg = blockIdx.x;
     if (wg < a.grid_kv) dkv_p8_unit<T, D>(a, smem, wg);
-    else dq_pipe_tile<T, D, 8>(a, smem, wg - a.grid_kv);
+    else if (wg < a.diag_first) dq_pipe_tile<T, D, 8>(a, smem, wg - a.grid_kv);
+    else diag_unit<T, D, 512, false>(a, wg - a.diag_first);
 }
 
 template <typename T, int D>
@@ -1451,30 +1530,46 @@ static void set_head_map(HeadMap& m, int hkv, int rest_count, int64_t& grid) {
     }
 }
 
-constexpr int kPreRegBlocks = 7;   // later blocks whose rows and gradients fit the registers of the preprocess kernel
-
 template <typename T, int D>
 static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
     const Geometry& geo = a.geo;
     hipError_t e;
     const int64_t acc_n4 = (int64_t)geo.T * geo.hkv * (D / 4);
 
-    // 1. D and the diagonal blocks, the tokens' document bounds, and cleared block-0 sums unless a carry from later
-    // steps is being continued
+    // 1. D and, here or beside the streaming passes, the diagonal blocks; the tokens' document bounds; and cleared block-0
+    // sums unless a carry from later steps is being continued
+    const int64_t kv_rows = (int64_t)geo.T * geo.hkv;
+    a.diag_units = 0;
+    a.diag_passes = 1;
+    int64_t units_beside = 0;   // diag_unit workgroups of the streaming launch
+    int n_cu = 0;
+    if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
     {
         constexpr int UPB = 256 / (D / 8);
-        const int64_t units = (int64_t)geo.T * geo.hkv;
-        a.pre_passes = 1;
-        if constexpr (sizeof(T) == 2) a.pre_passes = std::max(1, (geo.step_begin + geo.n_steps - 2 + kPreRegBlocks) / kPreRegBlocks);
-        const int64_t pre_blocks = (units + UPB - 1) / UPB * a.pre_passes;
+        int64_t pre_blocks = (kv_rows + UPB - 1) / UPB;
+        bool apart = true;
+        if constexpr (sizeof(T) == 2) {
+            const CallShape shape = call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base);
+            a.diag_passes = diag_passes(shape);
+            apart = diag_blocks_apart(shape, D, n_cu);
+            if (apart) {
+                pre_blocks *= a.diag_passes;
+                if (pre_blocks <= 0x7fffffffLL) a.diag_units = (int)pre_blocks;
+            } else {
+                constexpr int UPB2 = 512 / (D / 8);
+                if (geo.step_begin + geo.n_steps > 1) units_beside = (kv_rows + UPB2 - 1) / UPB2 * a.diag_passes;
+                pre_blocks = (int64_t)((geo.T + kDeltaTokens - 1) / kDeltaTokens) * geo.n_steps * ((geo.hq + kDeltaHeads - 1) / kDeltaHeads);
+            }
+        }
         a.bounds_blocks = (geo.T + 255) / 256;
         a.clear_n4 = !a.accumulate || a.carry_reset ? acc_n4 : 0;
         const int64_t grid = pre_blocks + a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
         if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
         a.pre_blocks = (int)pre_blocks;
         if constexpr (sizeof(T) == 2) {
-            ProfileScope prof("ttt_bwd_pre_regs_kernel", stream);
-            hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D, kPreRegBlocks, 2>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+            ProfileScope prof(apart ? "ttt_bwd_pre_regs_kernel" : "ttt_bwd_delta_kernel", stream);
+            if (apart) hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+            else hipLaunchKernelGGL((ttt_bwd_delta_kernel<T, D>), dim3((unsigned)grid), dim3(256), 0, stream, a);
         } else {
             auto kern = ttt_bwd_pre_kernel<T, D>;
             const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);   // D of a unit's (step, head) pairs
@@ -1514,8 +1609,6 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         a.q_split = 1;
         int64_t n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
         if constexpr (k16) {
-            int n_cu = 0;
-            if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
             const DkvPlan plan = plan_dkv_split(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), D, n_cu);
             a.chunk_blocks = plan.chunk_blocks;
             n_split = plan.n_split;
@@ -1523,8 +1616,6 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
             if (n_units * n_split > 0x7fffffffLL) return hipErrorInvalidValue;
             a.n_units = (int)n_units;
         } else {
-            int n_cu = 0;
-            if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
             const DkvPlanF32 plan = plan_dkv_split_f32(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), n_cu);
             n_split = plan.n_split;
             a.q_split = plan.q_split;
@@ -1535,11 +1626,14 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
         set_head_map(a.map_kv, geo.hkv, (int)(n_units * n_split), grid_kv);
         set_head_map(a.map_q, geo.hkv, a.n_tiles_q * geo.n_steps * geo.G, grid_q);
         grid_kv = (grid_kv + 7) / 8 * 8;   // workgroups go to the XCDs in turn: keep the dQ part's map in step with them
-        if (grid_kv + grid_q > 0x7fffffffLL) return hipErrorInvalidValue;
+        const int64_t grid = grid_kv + grid_q + units_beside;
+        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
         a.grid_kv = (int)grid_kv;
+        a.diag_first = (int)(grid_kv + grid_q);
+        if (units_beside > 0) a.diag_units = (int)units_beside;
         {
             ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : "ttt_bwd_main_f32_kernel", stream);
-            hipLaunchKernelGGL(kern, dim3((unsigned)(grid_kv + grid_q)), dim3(NW * 64), LDS, stream, a);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

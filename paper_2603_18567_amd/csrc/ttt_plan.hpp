@@ -286,6 +286,21 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
     return best;
 }
 
+// Where the later blocks' dK, dV of the 16-bit backward are made: in the preprocess launch, together with D (true), or as the
+// last workgroups of the streaming launch, whose tail they fill while the preprocess only makes D.  The second
+// way reads dO once more and is the better one (forward and backward, 256 ... 8192 tokens in one document or many, one
+// step a call: 2 to 27 % up to 2048 tokens, 0 to 2 % beyond; all steps in one call, up to 512 tokens: 3 to 40 %)
+// except for sweeps over many (step, head) pairs that also fill the device: there one unit is as long as a
+// dQ tile and leaves a tail of its own (all steps, 7 to 12 of 32/8 heads: 0 to 2.7 % slower from 1024 tokens on).
+constexpr int kDiagRegBlocks = 7;   // later blocks whose rows and gradients fit a lane's registers: one pass takes so many
+inline int diag_passes(const CallShape& a) { return std::max(1, (a.step_begin + a.n_steps - 2 + kDiagRegBlocks) / kDiagRegBlocks); }
+
+inline bool diag_blocks_apart(const CallShape& a, int head_dim, int n_cu) {
+    const int64_t n_pairs = (int64_t)a.n_steps * a.G;
+    const int64_t units = (int64_t)a.T * a.hkv * head_dim / (8 * 512) * diag_passes(a);   // 512 threads, 8 elements each
+    return n_pairs > 16 && units * n_pairs > 20 * (int64_t)n_cu && a.step_begin + a.n_steps > 1;
+}
+
 // The fp32 backward: ways to split the (step, head) list of a 128-key tile, and its query rows.
 struct DkvPlanF32 {
     int n_split, q_split;

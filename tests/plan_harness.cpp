@@ -18,6 +18,10 @@ void plan_backward(int T, int step_begin, int n_steps, int G, int hkv, int n_doc
     *n_split = p.n_split;
 }
 
+int plan_later_blocks(int T, int step_begin, int n_steps, int G, int hkv, int head_dim, int n_cu) {
+    return ttt::diag_blocks_apart(ttt::CallShape{T, step_begin, n_steps, G, hkv, 0, nullptr, 0}, head_dim, n_cu);
+}
+
 void plan_backward_f32(int T, int n_steps, int G, int hkv, int n_cu, int* n_split, int* q_split) {
     const ttt::DkvPlanF32 p = ttt::plan_dkv_split_f32(ttt::CallShape{T, 0, n_steps, G, hkv, 0, nullptr, 0}, n_cu);
     *n_split = p.n_split;

@@ -44,6 +44,11 @@ def backward_split(cu, hq, hkv, d, step_begin, n_steps, n_cu=256):
                  cu.ctypes.data_as(ctypes.c_void_p), d, n_cu)
 
 
+def later_blocks_apart(tokens, hq, hkv, d, step_begin, n_steps, n_cu=256):
+    """whether the preprocess launch makes the later blocks' dK, dV (16-bit)"""
+    return bool(_lib().plan_later_blocks(tokens, step_begin, n_steps, hq // hkv, hkv, d, n_cu))
+
+
 def backward_split_f32(tokens, hq, hkv, n_steps, n_cu=256):
     """(parts of the (step, head) list, parts of the query rows)"""
     return _call(_lib().plan_backward_f32, tokens, n_steps, hq // hkv, hkv, n_cu)
