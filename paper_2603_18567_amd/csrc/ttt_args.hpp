@@ -37,7 +37,8 @@ struct FwdArgs {
     int cu_base, n_docs;
     int n_tiles;            // query tiles over the packed token axis
     int pack_log2;          // log2 of the query heads (of one kv group) that share a workgroup
-    int diag_lds;           // 1: the rows of the diagonal keys are staged in LDS (64-row workgroups, 32 with two key groups)
+    int diag_rows;          // rows of a workgroup's diagonal keys that go through LDS, 0: straight from global memory
+    int diag_slots;         // blocks that have LDS for these rows behind the tile stages
     HeadMap map;
     // host side only (the launcher's choice of the work split reads the document structure from it)
     const int32_t* cu_host; // cu_seqlens of the documents of this call: n_docs + 1 entries, first entry = cu_base

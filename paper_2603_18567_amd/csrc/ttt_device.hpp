@@ -329,6 +329,11 @@ struct TileCopy {
         for (int it = 0; it < kIters; ++it)
             async_copy16(first_row + it * iter_stride, off, tile_lds + wave_dst + it * NTHREADS * 16);
     }
+    // so many rows, a multiple of kRowsPerIter
+    TTT_DEV void copy_rows(uint32_t tile_lds, const T* first_row, int rows) const {
+        for (int it = 0; it < rows / kRowsPerIter; ++it)
+            async_copy16(first_row + it * iter_stride, off, tile_lds + wave_dst + it * NTHREADS * 16);
+    }
 };
 
 // Workgroup barrier for data handed over through LDS only: this wave's LDS accesses are complete,

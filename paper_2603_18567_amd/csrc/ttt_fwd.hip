@@ -14,6 +14,7 @@
 // Tiles are cut over the packed token axis, not per document: a row's visible prefix is
 // [tok_start[i], i], so a wave visits the kv tiles that intersect [tok_start[first row], last row]
 // and nothing else; tiles strictly inside that range for every row skip the mask code.
+#include <algorithm>
 #include <type_traits>
 
 #include "ttt_args.hpp"
@@ -33,9 +34,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
     constexpr float kLazy = 8.f;          // log2 of the largest p tolerated before the reference max moves
-    constexpr bool kDiagLds = sizeof(T) == 2 && KT == 64;   // diagonal rows may be staged in LDS
-    constexpr int kDiagRows = KS == 2 && D == 64 ? 64 : 64 / KS;   // rows copied (the threads' pieces make whole rows)
-    constexpr int kDiagSlots = KS == 1 ? 3 : 2;   // blocks whose rows are staged at once
+    constexpr bool kDiagLds = sizeof(T) == 2;   // diagonal rows may go through LDS
 
     extern __shared__ __align__(16) char smem[];
     // LDS of a key group: K stage 0, K stage 1, V stage 0, V stage 1
@@ -169,14 +168,33 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         }
     };
 
-    // one kv tile (of each key group): wait for its copy, start the next one into the other stage, compute from this one
-    auto step = [&](auto stage_c, int u) {
+    // Diagonal keys whose rows go through LDS (the waves of a row block want the same K_l / V_l rows): a slot holds the
+    // workgroup's rows of one block; a.diag_slots of them lie behind the tile stages.
+    const int diag_bytes = a.diag_rows * (D * E::kBytes), slot_bytes = 2 * diag_bytes;
+    auto request_diag = [&](int lb, int n, int at) {   // blocks lb .. lb + n - 1 to the slots from byte `at` on
+        if constexpr (kDiagLds) {
+            for (int i = 0; i < n; ++i, at += slot_bytes) {
+                const T* Kl = static_cast<const T*>(a.k[lb + i]) + (int64_t)g * geo.kv_sh;
+                const T* Vl = static_cast<const T*>(a.v[lb + i]) + (int64_t)g * geo.kv_sh;
+                if (q_tile0 + a.diag_rows <= Tn) {
+                    const int64_t first = (int64_t)q_tile0 * geo.kv_st;
+                    tile_copy.copy_rows(lds_addr(smem) + at, Kl + first, a.diag_rows);
+                    tile_copy.copy_rows(lds_addr(smem) + at + diag_bytes, Vl + first, a.diag_rows);
+                } else {
+                    int tid_here = tid;
+                    asm volatile("" : "+v"(tid_here));   // computed here, not carried through the main loop
+                    for (int r = 0; r < a.diag_rows; r += tile_copy.kRowsPerIter) {
+                        tile_load_async<T, D, tile_copy.kRowsPerIter, NT>(smem + at + r * (D * E::kBytes), Kl, geo.kv_st, q_tile0 + r, Tn - 1, tid_here);
+                        tile_load_async<T, D, tile_copy.kRowsPerIter, NT>(smem + at + diag_bytes + r * (D * E::kBytes), Vl, geo.kv_st, q_tile0 + r, Tn - 1, tid_here);
+                    }
+                }
+            }
+        }
+    };
+
+    // scores, softmax and O of this wave's rows and the tile in stage ST
+    auto tile_work = [&](auto stage_c, const int kv0) {
         constexpr int ST = decltype(stage_c)::value;
-        wait_async_copies();
-        __syncthreads();   // tile u is in LDS for everyone; everyone is done with the other stage
-        if (u + KS <= u_hi) load_tile(ST ^ 1, u + KS);
-        const int kv0 = (u + kg) * KT;
-        if (!(active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w)) return;
         constexpr uint32_t tk = ST * TILE_BYTES, tv = (2 + ST) * TILE_BYTES;
         // S^T[kv, q] = K Q^T
         f32x16 sacc[KB][QB];
@@ -257,12 +275,22 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
             }
         }
     };
+    // one kv tile (of each key group), which is in LDS: start the copy of the next one into the other stage, compute from
+    // this one, wait for the copy
+    auto step = [&](auto stage_c, int u) {
+        constexpr int ST = decltype(stage_c)::value;
+        if (u + KS <= u_hi) load_tile(ST ^ 1, u + KS);
+        const int kv0 = (u + kg) * KT;
+        if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) tile_work(stage_c, kv0);
+        wait_async_copies();
+        __syncthreads();   // the next tile is in LDS for everyone; everyone is done with this stage
+    };
 
     load_tile(0, u_lo);
 
-    // Diagonal keys of blocks 1..j (suffix part of the mask): one key per block and row, taken first
-    // so that their global-memory latency overlaps the first tile copy.  Row-wise dot products on
-    // the vector ALU.
+    // Diagonal keys of blocks 1..j (suffix part of the mask): one key per block and row.  Row-wise dot products on
+    // the vector ALU; straight from global memory they are taken first, so that their latency overlaps the first
+    // tile copy.
     auto diag_key = [&](const frag (&dk)[QB][DC], const frag (&dv)[QB][DC]) {
         float s[QB];
         float vv[QB][DB][16];   // the key's value row in accumulator order
@@ -295,44 +323,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
                 for (int i = 0; i < 16; ++i) oacc[qb][db][i] = fmaf(p, vv[qb][db][i], oacc[qb][db][i]);
         }
     };
-    if (a.diag_lds) {
-        // Workgroups of 64 rows (packed heads: all waves of a row block want the same K_l / V_l rows):
-        // the rows of up to kDiagSlots blocks are copied into LDS at once, behind the tile stages, so
-        // their latency is paid once per group of blocks, not once per block, and once per kv group,
-        // not once per head.  j is the same for the whole workgroup: the barriers are uniform.
-        // (With two key groups: workgroups of 32 rows, and every second block goes to each group.)
-        if constexpr (kDiagLds) {
-            constexpr int DIAG_BYTES = kDiagRows * D * E::kBytes;
-            char* dbase = smem + KS * GROUP_BYTES;
-            for (int base = 1; base <= j; base += kDiagSlots) {
-                const int nb = min(kDiagSlots, j - base + 1);
-                if (base > 1) __syncthreads();   // the slots are free again
-                for (int i = 0; i < nb; ++i) {
-                    const T* Kl = static_cast<const T*>(a.k[base + i]) + (int64_t)g * geo.kv_sh;
-                    const T* Vl = static_cast<const T*>(a.v[base + i]) + (int64_t)g * geo.kv_sh;
-                    tile_load_async<T, D, kDiagRows, NT>(dbase + (2 * i) * DIAG_BYTES, Kl, geo.kv_st, q_tile0, Tn - 1, tid);
-                    tile_load_async<T, D, kDiagRows, NT>(dbase + (2 * i + 1) * DIAG_BYTES, Vl, geo.kv_st, q_tile0, Tn - 1, tid);
-                }
-                wait_async_copies();
-                __syncthreads();
-                if (active) {
-                    const int rb = (wq0 - q_tile0) / 32;   // this wave's first row block inside the workgroup's rows
-                    for (int i = kg; i < nb; i += KS) {
-                        const uint32_t drow = KS * GROUP_BYTES + (2 * i) * DIAG_BYTES - kg * GROUP_BYTES;
-                        frag dk[QB][DC], dv[QB][DC];
-#pragma unroll
-                        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                            for (int t = 0; t < DC; ++t) {
-                                dk[qb][t] = row_frag(drow, rb + qb, t);
-                                dv[qb][t] = row_frag(drow + DIAG_BYTES, rb + qb, t);
-                            }
-                        diag_key(dk, dv);
-                    }
-                }
-            }
-        }
-    } else if (active && j >= 1 + kg) {
+    if (!(kDiagLds && a.diag_rows > 0) && active && j >= 1 + kg) {
         // the fragments of block lb + 1 are requested from global memory before block lb is consumed
         frag dk[QB][DC], dv[QB][DC], nk[QB][DC], nv[QB][DC];
         auto request = [&](int lb, frag (&rk)[QB][DC], frag (&rv)[QB][DC]) {
@@ -363,15 +354,53 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         }
     }
 
+    wait_async_copies();
+    __syncthreads();   // the first tile is in LDS for everyone
+    // the diagonal rows of the first blocks are requested behind it and wait in LDS until the tiles are done
+    const int diag_first = kDiagLds && a.diag_rows > 0 ? min(j, a.diag_slots) : 0;
+    request_diag(1, diag_first, KS * GROUP_BYTES);
+
     for (int u = u_lo; u <= u_hi; u += 2 * KS) {
         step(IntC<0>{}, u);
         if (u + KS <= u_hi) step(IntC<1>{}, u + KS);
     }
 
+    if constexpr (kDiagLds) {
+        // The diagonal keys that wait in LDS; further blocks are requested into the free half -- the tile stages and
+        // the blocks' own slots in turn -- before those of the other half are worked on.  (Taken before the tiles,
+        // three blocks at a time, every group's copies were waited for: at 4096 tokens 3.4 us per group of a workgroup's
+        // 85.)  j is the same for the whole workgroup: the barriers are uniform.
+        const int rb = (wq0 - q_tile0) / 32;   // this wave's first row block inside the workgroup's rows
+        int base = 1, at = KS * GROUP_BYTES;
+        for (int nb = diag_first; nb > 0;) {
+            const int other = at == 0 ? KS * GROUP_BYTES : 0;
+            const int more = min(j + 1 - base - nb, at == 0 ? a.diag_slots : KS * GROUP_BYTES / slot_bytes);
+            request_diag(base + nb, more, other);
+            if (active) {
+                for (int i = kg; i < nb; i += KS) {
+                    const uint32_t drow = at + i * slot_bytes - kg * GROUP_BYTES;
+                    frag dk[QB][DC], dv[QB][DC];
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                        for (int t = 0; t < DC; ++t) {
+                            dk[qb][t] = row_frag(drow, rb + qb, t);
+                            dv[qb][t] = row_frag(drow + diag_bytes, rb + qb, t);
+                        }
+                    diag_key(dk, dv);
+                }
+            }
+            wait_async_copies();
+            __syncthreads();
+            base += nb;
+            nb = more;
+            at = other;
+        }
+    }
+
     // normalise; rows go through a wave-private LDS patch (carved out of the tile stages, which
-    // everybody has finished reading after this barrier) so that every global store is a full
-    // 16-byte piece of a row and a wave instruction covers whole rows
-    __syncthreads();
+    // everybody has finished reading) so that every global store is a full 16-byte piece of a row and a
+    // wave instruction covers whole rows
     if constexpr (KS == 2) {
         // The second key group's rows join the first one's: reference maximum, sum and O of the same lane of wave
         // gwave, as 16-byte pieces side by side.  A group that saw no key of a row brings m = -inf, l = 0, O = 0.
@@ -458,16 +487,23 @@ hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int
 
 template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
     constexpr int LDS_TILES = 4 * KS * 64 * D * (int)sizeof(T);   // two stages of K and V tiles
-    constexpr int DIAG_ROWS = KS == 2 && D == 64 ? 64 : 64 / KS;   // as in the kernel
-    constexpr int LDS_DIAG = (KS == 1 ? 3 : 2) * 2 * DIAG_ROWS * D * (int)sizeof(T);   // the rows of so many blocks' diagonal keys
+    constexpr int LDS_MAX = 160 * 1024 / (WPE * 4 / NW) / 1024 * 1024;   // of a workgroup, so many to a compute unit
+    constexpr int ROWS_PER_COPY = NW * 64 * 16 / (D * (int)sizeof(T));
     auto kern = ttt_fwd_kernel<T, D, QB, NW, KS, WPE>;
     static LdsOptIn lds_opt_in;
-    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS_TILES + (sizeof(T) == 2 ? LDS_DIAG : 0)); e != hipSuccess) return e;
+    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS_MAX); e != hipSuccess) return e;
     const Geometry& geo = a.geo;
     const int qt_rows = (NW / KS * QB * 32) >> a.pack_log2;
     a.n_tiles = (geo.T + qt_rows - 1) / qt_rows;
-    a.diag_lds = sizeof(T) == 2 && qt_rows == 64 / KS;
-    const int lds_bytes = LDS_TILES + (a.diag_lds ? LDS_DIAG : 0);
+    // Rows of the diagonal keys through LDS: up to three blocks behind the tile stages, if the LDS for one block at
+    // least is to be had without a workgroup less on the compute unit.  Fragment loads from global memory instead touch
+    // 32 rows each and wait (forward and backward of the last of twelve steps, 512 tokens: 12/2 heads, 64 or 128 rows
+    // 81.7 -> 69.0 us; 8/2 heads of 64, 32 rows 48.9 -> 44.3).
+    a.diag_rows = std::max(qt_rows, ROWS_PER_COPY);
+    const int slot_bytes = 2 * a.diag_rows * D * (int)sizeof(T);
+    a.diag_slots = sizeof(T) == 2 ? std::min(3, (LDS_MAX - LDS_TILES) / slot_bytes) : 0;
+    if (a.diag_slots == 0 || slot_bytes > LDS_TILES) a.diag_rows = a.diag_slots = 0;
+    const int lds_bytes = LDS_TILES + a.diag_slots * slot_bytes;
     a.map.hkv = geo.hkv;
     a.map.rest_count = a.n_tiles * geo.n_steps * (geo.G >> a.pack_log2);
     int64_t grid;
