@@ -35,11 +35,11 @@ template <int LPR> TTT_DEV float group_sum(float v) {
 // What the streaming passes need besides, done by further workgroups of the same launch (as launches of their own
 // these took longer to start than to run: three of the five or six launches of a short call): document bounds per
 // token, and cleared block-0 sums.
-TTT_DEV void bwd_pre_side_work(const BwdArgs& a, int blk) {
+TTT_DEV void bwd_pre_side_work(const BwdCommon& a, int blk) {
     const Geometry& geo = a.geo;
     if (blk < a.bounds_blocks) {
         const int i = blk * 256 + threadIdx.x;
-        if (i < geo.T) write_doc_bounds(a.cu, a.cu_base, a.n_docs, i, a.tok_start, a.tok_end);
+        if (i < geo.T) write_doc_bounds(a.cu, a.n_docs, i, a.tok_start, a.tok_end);
         return;
     }
     const int clear_blocks = (int)gridDim.x - a.pre_blocks - a.bounds_blocks;
@@ -49,8 +49,8 @@ TTT_DEV void bwd_pre_side_work(const BwdArgs& a, int blk) {
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs a) {
+template <typename T, int D, int N>
+__global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs<N> a) {
     if ((int)blockIdx.x >= a.pre_blocks) {
         bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
         return;
@@ -61,11 +61,12 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs a) {
     extern __shared__ float sD[];    // [UPB][n_steps*G]
 
     const Geometry& geo = a.geo;
-    const int Tn = geo.T, G = geo.G, ns = geo.n_steps, b = geo.step_begin, e = b + ns;
+    const BwdSlice& sl = slice_of(a, &BwdSlice::pre_first, blockIdx.x);
+    const int Tn = geo.T, G = geo.G, ns = sl.n_steps, b = geo.step_begin, e = b + ns;
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-    const int64_t unit = (int64_t)blockIdx.x * UPB + grp;
-    const bool valid = unit < (int64_t)Tn * geo.hkv;
-    const int i = valid ? (int)(unit / geo.hkv) : 0;
+    const int64_t unit = (int64_t)((int)blockIdx.x - sl.pre_first) * UPB + grp;
+    const bool valid = unit < (int64_t)(sl.t1 - sl.t0) * geo.hkv;
+    const int i = sl.t0 + (valid ? (int)(unit / geo.hkv) : 0);
     const int g = valid ? (int)(unit % geo.hkv) : 0;
     float* myD = sD + grp * (ns * G);
 
@@ -86,7 +87,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs a) {
                 if (valid) {
                     const int64_t at = ((int64_t)js * geo.hq + h) * Tn + i;
                     a.delta[at] = d;
-                    a.lse2[at] = a.lse[j][(int64_t)h * geo.lse_st + i] * kLog2e;
+                    a.lse2[at] = a.lse[j][(int64_t)h * geo.T + i] * kLog2e;
                 }
             }
         }
@@ -116,7 +117,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs a) {
                 }
                 s = group_sum<LPR>(s);
                 dp = group_sum<LPR>(dp);
-                const float lse = a.lse[j][(int64_t)h * geo.lse_st + i];
+                const float lse = a.lse[j][(int64_t)h * geo.T + i];
                 const float p = fast_exp2((s * geo.scale - lse) * kLog2e);
                 const float ds = p * (dp - myD[(j - b) * G + hg]) * geo.scale;
 #pragma unroll
@@ -172,8 +173,8 @@ template <int LPR> TTT_DEV float group_sum_dpp(float v) {
 // are all requested at once (whole rows of neighbouring heads), its results leave as runs of 32 tokens.
 constexpr int kDeltaTokens = 32, kDeltaHeads = 4;
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs a) {
+template <typename T, int D, int N>
+__global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs<N> a) {
     static_assert(sizeof(T) == 2, "16-bit elements");
     if ((int)blockIdx.x >= a.pre_blocks) {
         bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
@@ -186,10 +187,12 @@ __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs a) {
     __shared__ float sum[kDeltaHeads * kDeltaTokens];
 
     const Geometry& geo = a.geo;
+    const BwdSlice& sl = slice_of(a, &BwdSlice::pre_first, blockIdx.x);
     const int n_hc = (geo.hq + kDeltaHeads - 1) / kDeltaHeads;
-    const int h0 = (int)blockIdx.x % n_hc * kDeltaHeads;
-    const int rest = (int)blockIdx.x / n_hc;
-    const int js = rest % geo.n_steps, t0 = rest / geo.n_steps * kDeltaTokens;
+    const int wg = (int)blockIdx.x - sl.pre_first;
+    const int h0 = wg % n_hc * kDeltaHeads;
+    const int rest = wg / n_hc;
+    const int js = rest % sl.n_steps, t0 = sl.t0 + rest / sl.n_steps * kDeltaTokens;
     const int j = geo.step_begin + js;
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
     const T* go_base = static_cast<const T*>(a.d_o[j]) + sub * 8;
@@ -199,15 +202,15 @@ __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs a) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const int r = p * RPP + grp;                                 // neighbouring rows are heads of one token
-        const int i = min(t0 + r / kDeltaHeads, geo.T - 1), h = min(h0 + r % kDeltaHeads, geo.hq - 1);
+        const int i = min(t0 + r / kDeltaHeads, sl.t1 - 1), h = min(h0 + r % kDeltaHeads, geo.hq - 1);
         const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh;
         go[p] = gload_frag<T>(go_base + off);
         oo[p] = gload_frag<T>(oo_base + off);
     }
     const int wt = threadIdx.x % kDeltaTokens, wh = threadIdx.x / kDeltaTokens;   // what this thread writes
-    const bool writes = wh < kDeltaHeads && h0 + wh < geo.hq && t0 + wt < geo.T;
+    const bool writes = wh < kDeltaHeads && h0 + wh < geo.hq && t0 + wt < sl.t1;
     float lse = 0.f;
-    if (writes) lse = a.lse[j][(int64_t)(h0 + wh) * geo.lse_st + t0 + wt];
+    if (writes) lse = a.lse[j][(int64_t)(h0 + wh) * geo.T + t0 + wt];
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
         const float d = group_sum_dpp<LPR>(dot8(go[p], oo[p], 0.f));
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs a) {
 // next two pairs are requested before a pair is worked on (4096 tokens, MAKE_D, 0.98 GB: none ahead 4.45 TB/s, one
 // 4.75, two 5.07; four, with two blocks fewer in registers, no more).
 template <typename T, int D, int THREADS, bool MAKE_D>
-TTT_DEV void diag_unit(const BwdArgs& a, const int wg) {
+TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
     static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
     using frag = typename Elem<T>::frag;
     constexpr int NL = kDiagRegBlocks, PF = 2;
@@ -239,15 +242,15 @@ TTT_DEV void diag_unit(const BwdArgs& a, const int wg) {
     constexpr int UPB = THREADS / LPR;
 
     const Geometry& geo = a.geo;
-    const int Tn = geo.T, G = geo.G, b = geo.step_begin, e = b + geo.n_steps;
-    const int per_pass = a.diag_units / a.diag_passes;
+    const int Tn = geo.T, G = geo.G, b = geo.step_begin, e = b + sl.n_steps;
+    const int per_pass = sl.diag_units / sl.diag_passes;
     const int pass = wg / per_pass;
     const int l0 = 1 + pass * NL;                                 // first block of this pass
     const int j0 = MAKE_D && pass == 0 ? b : max(b, l0);          // first step of its sweep
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
     const int64_t unit = (int64_t)(wg % per_pass) * UPB + grp;
-    if (unit >= (int64_t)Tn * geo.hkv) return;   // whole aligned lane groups leave together
-    const int i = (int)(unit / geo.hkv);
+    if (unit >= (int64_t)(sl.t1 - sl.t0) * geo.hkv) return;   // whole aligned lane groups leave together
+    const int i = sl.t0 + (int)(unit / geo.hkv);
     const int g = (int)(unit % geo.hkv);
     const int64_t kvoff = (int64_t)i * geo.kv_st + (int64_t)g * geo.kv_sh + sub * 8;
     // this lane's place in a block of the carry: two quads D / 2 apart, so that a wave's 16-byte accesses are side by side
@@ -264,7 +267,7 @@ TTT_DEV void diag_unit(const BwdArgs& a, const int wg) {
         go[s] = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
         if constexpr (MAKE_D) {
             oo[s] = gload_frag<T>(static_cast<const T*>(a.o[j]) + off);
-            lse[s] = a.lse[j][(int64_t)h * geo.lse_st + i];
+            lse[s] = a.lse[j][(int64_t)h * geo.T + i];
         } else {
             const int64_t at = ((int64_t)(j - b) * geo.hq + h) * Tn + i;
             lse[s] = a.lse2[at];
@@ -374,17 +377,21 @@ TTT_DEV void diag_unit(const BwdArgs& a, const int wg) {
     }
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs a) {
-    if ((int)blockIdx.x >= a.pre_blocks) bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
-    else diag_unit<T, D, 256, true>(a, (int)blockIdx.x);
+template <typename T, int D, int N>
+__global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs<N> a) {
+    if ((int)blockIdx.x >= a.pre_blocks) {
+        bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
+        return;
+    }
+    const BwdSlice& sl = slice_of(a, &BwdSlice::pre_first, blockIdx.x);
+    diag_unit<T, D, 256, true>(a, sl, (int)blockIdx.x - sl.pre_first);
 }
 
 // ------------------------------------------------------------------------------------------------
 // dQ: query-stationary
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int QB, int NW>
-TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
+TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;
@@ -400,18 +407,18 @@ TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map_q, wg, g, rest)) return;
+    if (!decode_block(a.map, sl.q_rest, wg, g, rest)) return;
     const int hg = rest % geo.G;
     rest /= geo.G;
-    const int js = rest % geo.n_steps;
+    const int js = rest % sl.n_steps;
     const int j = geo.step_begin + js;
-    const int tile = a.n_tiles_q - 1 - rest / geo.n_steps;
+    const int t0 = sl.t0, Tn = sl.t1;   // first token of the slice, one past its last
+    const int tile = (Tn - t0 + QT - 1) / QT - 1 - rest / sl.n_steps;
     const int h = g * geo.G + hg;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
-    const int Tn = geo.T;
-    const int q_tile0 = tile * QT;
+    const int q_tile0 = t0 + tile * QT;
     const int wq0 = q_tile0 + wave * (QB * 32);
     const bool active = wq0 < Tn;
 
@@ -427,15 +434,15 @@ TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
         qi[qb] = wq0 + 32 * qb + n;
         qc[qb] = qi[qb] < Tn ? qi[qb] : Tn - 1;
         st[qb] = a.tok_start[qc[qb]];
-        lse2[qb] = a.lse[j][(int64_t)h * geo.lse_st + qc[qb]] * kLog2e;
-        dl[qb] = a.delta[((int64_t)js * geo.hq + h) * Tn + qc[qb]];
+        lse2[qb] = a.lse[j][(int64_t)h * geo.T + qc[qb]] * kLog2e;
+        dl[qb] = a.delta[((int64_t)js * geo.hq + h) * geo.T + qc[qb]];
     }
     const int hi_w = min(wq0 + QB * 32 - 1, Tn - 1);
     const int lo_w = active ? __builtin_amdgcn_readfirstlane(a.tok_start[min(wq0, Tn - 1)]) : 0;
     const int st_hi = active ? __builtin_amdgcn_readfirstlane(a.tok_start[hi_w]) : 0;
     const int lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
     const int hi = min(q_tile0 + QT - 1, Tn - 1);
-    const int u_lo = lo / KT, u_hi = hi / KT;
+    const int u_lo = (lo - t0) / KT, u_hi = (hi - t0) / KT;   // key tiles, counted from t0
 
     frag qf[QB][DC], gof[QB][DC];
 #pragma unroll
@@ -455,17 +462,17 @@ TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
             for (int i = 0; i < 16; ++i) dqacc[qb][db][i] = 0.f;
     const float c = geo.scale_log2;
 
-    tile_load_async<T, D, KT, NT>(sK(0), K0, geo.kv_st, u_lo * KT, Tn - 1, tid);
-    tile_load_async<T, D, KT, NT>(sV(0), V0, geo.kv_st, u_lo * KT, Tn - 1, tid);
+    tile_load_async<T, D, KT, NT>(sK(0), K0, geo.kv_st, t0 + u_lo * KT, Tn - 1, tid);
+    tile_load_async<T, D, KT, NT>(sV(0), V0, geo.kv_st, t0 + u_lo * KT, Tn - 1, tid);
     int stage = 0;
     for (int u = u_lo; u <= u_hi; ++u) {
         wait_async_copies();
         __syncthreads();
         if (u < u_hi) {
-            tile_load_async<T, D, KT, NT>(sK(stage ^ 1), K0, geo.kv_st, (u + 1) * KT, Tn - 1, tid);
-            tile_load_async<T, D, KT, NT>(sV(stage ^ 1), V0, geo.kv_st, (u + 1) * KT, Tn - 1, tid);
+            tile_load_async<T, D, KT, NT>(sK(stage ^ 1), K0, geo.kv_st, t0 + (u + 1) * KT, Tn - 1, tid);
+            tile_load_async<T, D, KT, NT>(sV(stage ^ 1), V0, geo.kv_st, t0 + (u + 1) * KT, Tn - 1, tid);
         }
-        const int kv0 = u * KT;
+        const int kv0 = t0 + u * KT;
         if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) {
             const char* tk = sK(stage);
             const char* tv = sV(stage);
@@ -582,7 +589,7 @@ TTT_DEV void dq_tile(const BwdArgs& a, char* smem, const int wg) {
 // LDS: two stages of [K tile | V tile], which differ in one bit of the per-lane addresses.
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int NW>
-TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
+TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     static_assert(sizeof(T) == 2, "this dQ kernel is for 16-bit elements");
     static_assert(NW == 8, "two waves per SIMD supply the overlap; no other wave count is built");
     using E = Elem<T>;
@@ -606,18 +613,18 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map_q, wg, g, rest)) return;
+    if (!decode_block(a.map, sl.q_rest, wg, g, rest)) return;
     const int hg = rest % geo.G;
     rest /= geo.G;
-    const int js = rest % geo.n_steps;
+    const int js = rest % sl.n_steps;
     const int j = geo.step_begin + js;
-    const int tile = a.n_tiles_q - 1 - rest / geo.n_steps;
+    const int t0 = sl.t0, Tn = sl.t1;   // first token of the slice, one past its last
+    const int tile = (Tn - t0 + QT - 1) / QT - 1 - rest / sl.n_steps;
     const int h = g * geo.G + hg;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
-    const int Tn = geo.T;
-    const int q_tile0 = tile * QT;
+    const int q_tile0 = t0 + tile * QT;
     const int wq0 = q_tile0 + wave * 32;
     const bool active = wq0 < Tn;
 
@@ -629,7 +636,7 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
     const int qi = wq0 + n;
     const int qc = qi < Tn ? qi : Tn - 1;
     const int st = a.tok_start[qc];
-    const int64_t at = ((int64_t)js * geo.hq + h) * Tn + qc;
+    const int64_t at = ((int64_t)js * geo.hq + h) * geo.T + qc;
     const float lse2 = a.lse2[at];
     const float dl = a.delta[at];
     const int hi_w = min(wq0 + 31, Tn - 1);
@@ -637,7 +644,7 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
     const int st_hi = active ? __builtin_amdgcn_readfirstlane(a.tok_start[hi_w]) : 0;
     const int lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
     const int hi = min(q_tile0 + QT - 1, Tn - 1);
-    const int u_lo = lo / KT, u_hi = hi / KT;
+    const int u_lo = (lo - t0) / KT, u_hi = (hi - t0) / KT;   // key tiles, counted from t0
 
     frag qf[DC], gof[DC];
 #pragma unroll
@@ -680,14 +687,14 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
     TileCopy<T, D, KT, NT> tile_copy;
     tile_copy.init(geo.kv_st, tid);
     auto issue = [&](int u, int s) {
-        if ((u + 1) * KT <= Tn) {
-            const int64_t first = (int64_t)u * KT * geo.kv_st;
+        if (t0 + (u + 1) * KT <= Tn) {
+            const int64_t first = (int64_t)(t0 + u * KT) * geo.kv_st;
             tile_copy.copy(lds0 + s * STAGE_BYTES, K0 + first);
             tile_copy.copy(lds0 + s * STAGE_BYTES + TILE_BYTES, V0 + first);
         } else {
             char* stg = smem + s * STAGE_BYTES;
-            tile_load_async<T, D, KT, NT>(stg, K0, geo.kv_st, u * KT, Tn - 1, tid);
-            tile_load_async<T, D, KT, NT>(stg + TILE_BYTES, V0, geo.kv_st, u * KT, Tn - 1, tid);
+            tile_load_async<T, D, KT, NT>(stg, K0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
+            tile_load_async<T, D, KT, NT>(stg + TILE_BYTES, V0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
         }
     };
 
@@ -697,7 +704,7 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
         wait_async_copies();
         __syncthreads();
         if (u < u_hi) issue(u + 1, stage ^ 1);
-        const int kv0 = u * KT;
+        const int kv0 = t0 + u * KT;
         if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) {
             frag ka[DC], va[DC];   // row-wise K / V fragments of the block being scored
             frag tfr[NE];          // K^T fragments of the block being accumulated
@@ -890,7 +897,7 @@ TTT_DEV void dq_pipe_tile(const BwdArgs& a, char* smem, const int wg) {
 // dK_0, dV_0: key-stationary
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int NW>
-TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
+TTT_DEV void dkv_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KVT = NW * 32;   // kv rows per workgroup, 32 per wave
@@ -910,28 +917,28 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
 
     const Geometry& geo = a.geo;
     int g, rest;
-    if (!decode_block(a.map_kv, wg, g, rest)) return;
-    const int sp = rest % a.n_split;
-    rest /= a.n_split;
-    const int part = rest % a.q_split;
-    const int tile = rest / a.q_split;   // low tiles of a document have the longest query range: first
+    if (!decode_block(a.map, sl.kv_rest, wg, g, rest)) return;
+    const int sp = rest % sl.n_split;
+    rest /= sl.n_split;
+    const int part = rest % sl.q_split;
+    const int tile = rest / sl.q_split;   // low tiles of a document have the longest query range: first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
-    const int Tn = geo.T;
-    const int kv_tile0 = tile * KVT;
+    const int t0 = sl.t0, Tn = sl.t1;   // first token of the slice, one past its last
+    const int kv_tile0 = t0 + tile * KVT;
     const int wk0 = kv_tile0 + wave * 32;          // first kv row of this wave
     const bool active = wk0 < Tn;
     const int wk_hi = min(wk0 + 31, Tn - 1);
     // query rows that can see this workgroup's / this wave's keys
     const int q_end = __builtin_amdgcn_readfirstlane(a.tok_end[min(kv_tile0 + KVT - 1, Tn - 1)]);
     const int wq_end = active ? __builtin_amdgcn_readfirstlane(a.tok_end[wk_hi]) : 0;
-    const int qt_first = kv_tile0 / QTL, qt_all = (q_end - 1) / QTL - qt_first + 1;
-    const int qt_lo = qt_first + qt_all * part / a.q_split;   // this workgroup's part of them
-    const int nqt = qt_first + qt_all * (part + 1) / a.q_split - qt_lo;
+    const int qt_first = tile * (KVT / QTL), qt_all = (q_end - 1 - t0) / QTL - qt_first + 1;   // query tiles, counted from t0
+    const int qt_lo = qt_first + qt_all * part / sl.q_split;   // this workgroup's part of them
+    const int nqt = qt_first + qt_all * (part + 1) / sl.q_split - qt_lo;
     if (nqt <= 0) return;
-    const int n_jh = geo.n_steps * geo.G;
-    const int n_c = (n_jh - sp + a.n_split - 1) / a.n_split;   // (step, head) pairs of this split
+    const int n_jh = sl.n_steps * geo.G;
+    const int n_c = (n_jh - sp + sl.n_split - 1) / sl.n_split;   // (step, head) pairs of this split
     const int n_it = n_c * nqt;
 
     const T* K0 = static_cast<const T*>(a.k[0]) + (int64_t)g * geo.kv_sh;
@@ -955,20 +962,20 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
     // stage loader: query tile `qt` of (step, head) pair number `ci` of this split
     auto issue = [&](int it, int s) {
         const int ci = it / nqt, qt = qt_lo + it % nqt;
-        const int jh = sp + ci * a.n_split;
+        const int jh = sp + ci * sl.n_split;
         const int js = jh / geo.G, h = g * geo.G + jh % geo.G;
         const int j = geo.step_begin + js;
         const T* Qj = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
         const T* dOj = static_cast<const T*>(a.d_o[j]) + (int64_t)h * geo.q_sh;
-        tile_load_async<T, D, QTL, NT>(sQ(s), Qj, geo.q_st, qt * QTL, Tn - 1, tid);
-        tile_load_async<T, D, QTL, NT>(sG(s), dOj, geo.q_st, qt * QTL, Tn - 1, tid);
+        tile_load_async<T, D, QTL, NT>(sQ(s), Qj, geo.q_st, t0 + qt * QTL, Tn - 1, tid);
+        tile_load_async<T, D, QTL, NT>(sG(s), dOj, geo.q_st, t0 + qt * QTL, Tn - 1, tid);
         if (tid < QTL) {
-            const int q = qt * QTL + tid;
+            const int q = t0 + qt * QTL + tid;
             const bool in = q < Tn;
             const int qq = in ? q : Tn - 1;
             // rows past the end get LSE = +inf so that p = 0
-            sLse(s)[tid] = in ? a.lse[j][(int64_t)h * geo.lse_st + qq] * kLog2e : INFINITY;
-            sDl(s)[tid] = in ? a.delta[((int64_t)js * geo.hq + h) * Tn + qq] : 0.f;
+            sLse(s)[tid] = in ? a.lse[j][(int64_t)h * geo.T + qq] * kLog2e : INFINITY;
+            sDl(s)[tid] = in ? a.delta[((int64_t)js * geo.hq + h) * geo.T + qq] : 0.f;
             sSt(s)[tid] = a.tok_start[qq];
         }
     };
@@ -979,7 +986,7 @@ TTT_DEV void dkv_tile(const BwdArgs& a, char* smem, const int wg) {
         wait_async_copies();
         __syncthreads();
         if (it + 1 < n_it) issue(it + 1, stage ^ 1);
-        const int q0 = (qt_lo + it % nqt) * QTL;
+        const int q0 = t0 + (qt_lo + it % nqt) * QTL;
         // this wave's keys are seen by query rows [wk0, wq_end)
         if (active && q0 + QTL - 1 >= wk0 && q0 < wq_end) {
             const char* tq = sQ(stage);
@@ -1092,8 +1099,8 @@ template <typename T, int D> struct DkvP8 {
 };
 
 template <typename T, int D>
-__device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const int g, const int sp, const int tile,
-                                            const int chunk) {
+__device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int g, const int sp,
+                                            const int tile, const int chunk) {
     static_assert(sizeof(T) == 2, "this dK/dV kernel is for 16-bit elements");
     using E = Elem<T>;
     using frag = typename E::frag;
@@ -1113,8 +1120,8 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pair = wave & 3, grp = wave >> 2;
     const int n = lane & 31, hh = lane >> 5;
-    const int Tn = geo.T;
-    const int kv_tile0 = tile * KVT;
+    const int t0 = sl.t0, Tn = sl.t1;   // first token of the slice, one past its last
+    const int kv_tile0 = t0 + tile * KVT;
     const int wk0 = kv_tile0 + pair * 32;
     const bool active = wk0 < Tn;
     const int wk_hi = min(wk0 + 31, Tn - 1);
@@ -1122,13 +1129,14 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
     const int wq_end = active ? __builtin_amdgcn_readfirstlane(a.tok_end[wk_hi]) : 0;
     const bool wave_split = active && __builtin_amdgcn_readfirstlane(a.tok_start[wk_hi]) > wk0;
     const int kvi = wk0 + n;
-    // query blocks of this chunk that see a key of this tile
-    const int qb_lo = max(kv_tile0 / 32, chunk * a.chunk_blocks);
-    const int nqb = min((q_end - 1) / 32, (chunk + 1) * a.chunk_blocks - 1) - qb_lo + 1;
+    // query blocks of this chunk that see a key of this tile, counted from t0
+    const int qb_lo = max(tile * (KVT / 32), chunk * sl.chunk_blocks);
+    const int nqb = min((q_end - 1 - t0) / 32, (chunk + 1) * sl.chunk_blocks - 1) - qb_lo + 1;
     if (nqb <= 0) return;
-    const int wq_lim = min(wq_end, (qb_lo + nqb) * 32);   // blocks from here on are not this unit's
-    const int n_jh = geo.n_steps * geo.G;
-    const int n_c = (n_jh - sp + a.n_split - 1) / a.n_split;
+    const int wq_lim = min(wq_end, t0 + (qb_lo + nqb) * 32);   // blocks from here on are not this unit's
+    const int n_split = sl.n_split;
+    const int n_jh = sl.n_steps * geo.G;
+    const int n_c = (n_jh - sp + n_split - 1) / n_split;
     const int nqb2 = (nqb + 1) / 2;           // steps per (step, head) pair: one block per wave group
     const int n_steps2 = n_c * nqb2;
     const float c = geo.scale_log2;
@@ -1198,7 +1206,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
     const uint32_t dst0 = __builtin_amdgcn_readfirstlane(lds0 + grp * C::kSlot + gw * 1024);
     const uint32_t vdst0 = __builtin_amdgcn_readfirstlane(lds0 + C::kVecBase + grp * C::kVecSlot);
     const int64_t blk2_stride = (int64_t)64 * geo.q_st;       // two blocks, in elements
-    const int qb_top = qb_lo + 2 * nqb2 - 1 - grp;            // this group's first block: the sweep runs downwards
+    const int row_top = t0 + (qb_lo + 2 * nqb2 - 1 - grp) * 32;   // this group's first block: the sweep runs downwards
     struct Pos {
         int i, ci;             // block 2 i + grp of (step, head) pair number ci of this split
         const T *q, *g;        // first row of the block in Q_j and dO_j of that head
@@ -1206,15 +1214,15 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
     const T *head_q = nullptr, *head_g = nullptr;             // of the pair the next request is in
     const float *head_l = nullptr, *head_d = nullptr;
     auto enter_pair = [&](Pos& ps) {
-        const int jh = sp + ps.ci * a.n_split;
+        const int jh = sp + ps.ci * n_split;
         const int js = jh / geo.G, h = g * geo.G + jh % geo.G;
         const int j = geo.step_begin + js;
         head_q = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
         head_g = static_cast<const T*>(a.d_o[j]) + (int64_t)h * geo.q_sh;
-        const int64_t at = ((int64_t)js * geo.hq + h) * Tn;
+        const int64_t at = ((int64_t)js * geo.hq + h) * geo.T;
         head_l = a.lse2 + at;
         head_d = a.delta + at;
-        const int64_t first = (int64_t)qb_top * 32 * geo.q_st;
+        const int64_t first = (int64_t)row_top * geo.q_st;
         ps.q = head_q + first;
         ps.g = head_g + first;
     };
@@ -1232,7 +1240,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
         constexpr int ST = decltype(stage_c)::value;
         const uint32_t st = dst0 + ST * C::kStage;
         const uint32_t vec = vdst0 + ST * C::kVecStage;
-        const int row0 = (qb_top - 2 * ps.i) * 32;
+        const int row0 = row_top - 64 * ps.i;
         if (row0 + 32 <= Tn) {
 #pragma unroll
             for (int i = 0; i < NLD; ++i) {
@@ -1289,7 +1297,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
         constexpr int ST = decltype(stage_c)::value;
         constexpr uint32_t SO = ST * C::kStage;
         constexpr uint32_t VO = ST * C::kVecStage;
-        const int q0 = (qb_top - 2 * nxt.i) * 32;
+        const int q0 = row_top - 64 * nxt.i;
         if (more) {
             advance(nxt);
             request(nxt, IntC<1 - ST>{});
@@ -1450,18 +1458,19 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdArgs& a, char* smem, const 
 // number of blocks -- except the few tiles on the chunk's diagonal -- so they stay together and the
 // rows are read from HBM once per XCD, not once per workgroup.
 template <typename T, int D>
-TTT_DEV void dkv_p8_unit(const BwdArgs& a, char* smem, const int wg) {
+TTT_DEV void dkv_p8_unit(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     int g, rest;
-    if (!decode_block(a.map_kv, wg, g, rest)) return;
-    const int sp = rest / a.n_units;
-    int r = rest % a.n_units;
+    if (!decode_block(a.map, sl.kv_rest, wg, g, rest)) return;
+    const int sp = rest / sl.n_units;
+    int r = rest % sl.n_units;
+    const int n_tiles = (sl.t1 - sl.t0 + 127) / 128;
     int chunk = 0;
     for (;; ++chunk) {
-        const int tiles = min(a.n_tiles_kv, (chunk + 1) * a.chunk_blocks / 4);   // 128-key tiles = 4 blocks
+        const int tiles = min(n_tiles, (chunk + 1) * sl.chunk_blocks / 4);   // 128-key tiles = 4 blocks
         if (r < tiles) break;
         r -= tiles;
     }
-    dkv_p8_tile<T, D>(a, smem, g, sp, r, chunk);
+    dkv_p8_tile<T, D>(a, sl, smem, g, sp, r, chunk);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1472,32 +1481,39 @@ TTT_DEV void dkv_p8_unit(const BwdArgs& a, char* smem, const int wg) {
 // launch, or between its two parts, they keep the dK/dV units of an XCD from streaming the same rows together: one
 // step, 32/8 heads, 512 and 2048 tokens 66 and 227 us at the end, 83 and 232 elsewhere).
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs a) {
+template <typename T, int D, int N>
+__global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs<N> a) {
     extern __shared__ __align__(16) char smem[];
     const int wg = blockIdx.x;
-    if (wg < a.grid_kv) dkv_p8_unit<T, D>(a, smem, wg);
-    else if (wg < a.diag_first) dq_pipe_tile<T, D, 8>(a, smem, wg - a.grid_kv);
-    else diag_unit<T, D, 512, false>(a, wg - a.diag_first);
+    if (wg >= a.grid_stream) {
+        const BwdSlice& sl = slice_of(a, &BwdSlice::diag_first, wg);
+        diag_unit<T, D, 512, false>(a, sl, wg - sl.diag_first);
+        return;
+    }
+    const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
+    if (wg < sl.q_first) dkv_p8_unit<T, D>(a, sl, smem, wg - sl.kv_first);
+    else dq_pipe_tile<T, D, 8>(a, sl, smem, wg - sl.q_first);
 }
 
-template <typename T, int D>
-__global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs a) {
+template <typename T, int D, int N>
+__global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs<N> a) {
     extern __shared__ __align__(16) char smem[];
     const int wg = blockIdx.x;
-    if (wg < a.grid_kv) dkv_tile<T, D, 4>(a, smem, wg);
-    else dq_tile<T, D, 1, 4>(a, smem, wg - a.grid_kv);
+    const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
+    if (wg < sl.q_first) dkv_tile<T, D, 4>(a, sl, smem, wg - sl.kv_first);
+    else dq_tile<T, D, 1, 4>(a, sl, smem, wg - sl.q_first);
 }
 
 // ------------------------------------------------------------------------------------------------
 // small helper: the block-0 sums in the output dtype
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D>
-__global__ void ttt_bwd_finish_kernel(const BwdArgs a) {
+template <typename T, int D, int N>
+__global__ void ttt_bwd_finish_kernel(const BwdArgs<N> a) {
     const Geometry& geo = a.geo;
-    const int64_t n4 = (int64_t)geo.T * geo.hkv * (D / 4);
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < n4; x += stride) {
+    const BwdSlice& sl = slice_of(a, &BwdSlice::finish_first, blockIdx.x);
+    const int64_t row4 = (int64_t)geo.hkv * (D / 4), end4 = sl.t1 * row4;
+    const int64_t stride = (int64_t)sl.finish_blocks * blockDim.x;
+    for (int64_t x = sl.t0 * row4 + (int64_t)((int)blockIdx.x - sl.finish_first) * blockDim.x + threadIdx.x; x < end4; x += stride) {
         const int d4 = (int)(x % (D / 4));
         const int64_t tg = x / (D / 4);
         const int g = (int)(tg % geo.hkv);
@@ -1514,65 +1530,63 @@ __global__ void ttt_bwd_finish_kernel(const BwdArgs a) {
 // ------------------------------------------------------------------------------------------------
 // launch sequence
 // ------------------------------------------------------------------------------------------------
-static void set_head_map(HeadMap& m, int hkv, int rest_count, int64_t& grid) {
-    m.hkv = hkv;
-    m.rest_count = rest_count;
-    if (hkv % 8 == 0) {
-        m.mode = 1;
-        grid = (int64_t)hkv * rest_count;
-    } else if (8 % hkv == 0) {
-        m.mode = 2;
-        const int xp = 8 / hkv;
-        grid = 8 * (int64_t)((rest_count + xp - 1) / xp);
-    } else {
-        m.mode = 0;
-        grid = (int64_t)hkv * rest_count;
-    }
-}
-
-template <typename T, int D>
-static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
+template <typename T, int D, int N>
+static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int n_slices, hipStream_t stream) {
+    constexpr bool k16 = sizeof(T) == 2;      // streaming launch: eight waves; fp32: four
+    constexpr int kMaxGrid = 0x7fffffff;
+    BwdArgs<N> a;
+    static_cast<BwdCommon&>(a) = common;
     const Geometry& geo = a.geo;
     hipError_t e;
-    const int64_t acc_n4 = (int64_t)geo.T * geo.hkv * (D / 4);
+    int n_cu = 0;
+    if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
+    a.map = head_map(geo.hkv);
+    CallShape shapes[kMaxSlices];
+    int max_steps = 0;
+    for (int i = 0; i < n_slices; ++i) {
+        shapes[i] = slices[i].shape;
+        BwdSlice& sl = a.slices[i];
+        sl.t0 = slices[i].t0;
+        sl.t1 = sl.t0 + shapes[i].T;
+        sl.n_steps = shapes[i].n_steps;
+        sl.diag_units = 0;
+        sl.diag_passes = 1;
+        max_steps = std::max(max_steps, sl.n_steps);
+    }
+    a.n_slices = n_slices;
 
     // 1. D and, here or beside the streaming passes, the diagonal blocks; the tokens' document bounds; and cleared block-0
     // sums unless a carry from later steps is being continued
-    const int64_t kv_rows = (int64_t)geo.T * geo.hkv;
-    a.diag_units = 0;
-    a.diag_passes = 1;
-    int64_t units_beside = 0;   // diag_unit workgroups of the streaming launch
-    int n_cu = 0;
-    if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
+    const bool apart = !k16 || diag_blocks_apart(shapes, n_slices, D, n_cu);
     {
         constexpr int UPB = 256 / (D / 8);
-        int64_t pre_blocks = (kv_rows + UPB - 1) / UPB;
-        bool apart = true;
-        if constexpr (sizeof(T) == 2) {
-            const CallShape shape = call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base);
-            a.diag_passes = diag_passes(shape);
-            apart = diag_blocks_apart(shape, D, n_cu);
-            if (apart) {
-                pre_blocks *= a.diag_passes;
-                if (pre_blocks <= 0x7fffffffLL) a.diag_units = (int)pre_blocks;
-            } else {
-                constexpr int UPB2 = 512 / (D / 8);
-                if (geo.step_begin + geo.n_steps > 1) units_beside = (kv_rows + UPB2 - 1) / UPB2 * a.diag_passes;
-                pre_blocks = (int64_t)((geo.T + kDeltaTokens - 1) / kDeltaTokens) * geo.n_steps * ((geo.hq + kDeltaHeads - 1) / kDeltaHeads);
+        int64_t grid = 0;
+        for (int i = 0; i < n_slices; ++i) {
+            BwdSlice& sl = a.slices[i];
+            const int64_t tokens = shapes[i].T;
+            int64_t blocks = (tokens * geo.hkv + UPB - 1) / UPB;
+            sl.pre_first = (int)grid;
+            if constexpr (k16) {
+                sl.diag_passes = diag_passes(shapes[i]);
+                if (apart) {
+                    blocks *= sl.diag_passes;
+                    if (blocks <= kMaxGrid) sl.diag_units = (int)blocks;
+                } else {
+                    blocks = (tokens + kDeltaTokens - 1) / kDeltaTokens * sl.n_steps * ((geo.hq + kDeltaHeads - 1) / kDeltaHeads);
+                }
             }
+            if ((grid += blocks) > kMaxGrid) return hipErrorInvalidValue;
         }
-        a.bounds_blocks = (geo.T + 255) / 256;
-        a.clear_n4 = !a.accumulate || a.carry_reset ? acc_n4 : 0;
-        const int64_t grid = pre_blocks + a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        a.pre_blocks = (int)pre_blocks;
-        if constexpr (sizeof(T) == 2) {
+        a.pre_blocks = (int)grid;
+        grid += a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
+        if (grid > kMaxGrid) return hipErrorInvalidValue;
+        if constexpr (k16) {
             ProfileScope prof(apart ? "ttt_bwd_pre_regs_kernel" : "ttt_bwd_delta_kernel", stream);
-            if (apart) hipLaunchKernelGGL((ttt_bwd_pre_regs_kernel<T, D>), dim3((unsigned)grid), dim3(256), 0, stream, a);
-            else hipLaunchKernelGGL((ttt_bwd_delta_kernel<T, D>), dim3((unsigned)grid), dim3(256), 0, stream, a);
+            auto kern = apart ? ttt_bwd_pre_regs_kernel<T, D, N> : ttt_bwd_delta_kernel<T, D, N>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, stream, a);
         } else {
-            auto kern = ttt_bwd_pre_kernel<T, D>;
-            const size_t lds = (size_t)UPB * geo.n_steps * geo.G * sizeof(float);   // D of a unit's (step, head) pairs
+            auto kern = ttt_bwd_pre_kernel<T, D, N>;
+            const size_t lds = (size_t)UPB * max_steps * geo.G * sizeof(float);   // D of a unit's (step, head) pairs
             if (lds > 160 * 1024) return hipErrorInvalidValue;
             if (lds > 48 * 1024) {
                 e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1586,51 +1600,62 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
 
     // 2. dQ and block 0's dK, dV in one launch
     {
-        constexpr bool k16 = sizeof(T) == 2;      // eight waves; fp32: four
         constexpr int NW = k16 ? 8 : 4;
         constexpr int QT = NW * 32, KVT = 128;
         constexpr int LDS_Q = k16 ? 2 * 2 * 128 * D * (int)sizeof(T) : 4 * 64 * D * (int)sizeof(T);
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
-        void (*kern)(BwdArgs);
-        if constexpr (k16) kern = ttt_bwd_main_kernel<T, D>;
-        else kern = ttt_bwd_main_f32_kernel<T, D>;
+        void (*kern)(BwdArgs<N>);
+        if constexpr (k16) kern = ttt_bwd_main_kernel<T, D, N>;
+        else kern = ttt_bwd_main_f32_kernel<T, D, N>;
         static LdsOptIn lds_opt_in;
         if ((e = lds_opt_in.ensure((const void*)kern, LDS)) != hipSuccess) return e;
         // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
         // 32-bit byte offsets
         if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
-        a.n_tiles_q = (geo.T + QT - 1) / QT;
-        a.n_tiles_kv = (geo.T + KVT - 1) / KVT;
-        // split the (step, head) list of a dK/dV unit so that the grid fills the device evenly
-        const int n_jh = geo.n_steps * geo.G;
-        int n_split = 1;
-        a.q_split = 1;
-        int64_t n_units = a.n_tiles_kv;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
-        if constexpr (k16) {
-            const DkvPlan plan = plan_dkv_split(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), D, n_cu);
-            a.chunk_blocks = plan.chunk_blocks;
-            n_split = plan.n_split;
-            n_units = dkv_units_of(geo.T, a.n_tiles_kv, a.chunk_blocks);
-            if (n_units * n_split > 0x7fffffffLL) return hipErrorInvalidValue;
-            a.n_units = (int)n_units;
-        } else {
-            const DkvPlanF32 plan = plan_dkv_split_f32(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), n_cu);
-            n_split = plan.n_split;
-            a.q_split = plan.q_split;
-            n_units *= a.q_split;
+        // dK/dV: split the (step, head) list of a unit so that the grid fills the device evenly
+        int64_t grid = 0;
+        double slice_us[N] = {}, all_us = 0.;
+        if constexpr (N > 1)
+            for (int i = 0; i < n_slices; ++i) all_us += slice_us[i] = bwd_slice_us(shapes[i], D);
+        for (int i = 0; i < n_slices; ++i) {
+            BwdSlice& sl = a.slices[i];
+            const int n_tiles = (shapes[i].T + KVT - 1) / KVT;
+            int64_t n_units = n_tiles;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
+            sl.q_split = 1;
+            if constexpr (k16) {
+                const DkvPlan plan = plan_dkv_split(shapes[i], D, n_cu, all_us - slice_us[i]);
+                sl.chunk_blocks = plan.chunk_blocks;
+                sl.n_split = plan.n_split;
+                n_units = dkv_units_of(shapes[i].T, n_tiles, sl.chunk_blocks);
+            } else {
+                const DkvPlanF32 plan = plan_dkv_split_f32(shapes[i], n_cu);
+                sl.n_split = plan.n_split;
+                sl.q_split = plan.q_split;
+                n_units *= sl.q_split;
+            }
+            if (n_units * sl.n_split > kMaxGrid) return hipErrorInvalidValue;
+            sl.n_units = (int)n_units;
+            sl.kv_rest = (int)(n_units * sl.n_split);
+            sl.kv_first = (int)grid;
+            if ((grid += head_map_grid(a.map, sl.kv_rest)) > kMaxGrid) return hipErrorInvalidValue;
+            const int64_t rest = (int64_t)((shapes[i].T + QT - 1) / QT) * sl.n_steps * geo.G;
+            sl.q_first = (int)grid;
+            if ((grid += head_map_grid(a.map, rest)) > kMaxGrid) return hipErrorInvalidValue;
+            sl.q_rest = (int)rest;
         }
-        a.n_split = n_split;
-        int64_t grid_kv, grid_q;
-        set_head_map(a.map_kv, geo.hkv, (int)(n_units * n_split), grid_kv);
-        set_head_map(a.map_q, geo.hkv, a.n_tiles_q * geo.n_steps * geo.G, grid_q);
-        grid_kv = (grid_kv + 7) / 8 * 8;   // workgroups go to the XCDs in turn: keep the dQ part's map in step with them
-        const int64_t grid = grid_kv + grid_q + units_beside;
-        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-        a.grid_kv = (int)grid_kv;
-        a.diag_first = (int)(grid_kv + grid_q);
-        if (units_beside > 0) a.diag_units = (int)units_beside;
+        a.grid_stream = (int)grid;
+        if (!apart) {
+            constexpr int UPB = 512 / (D / 8);
+            for (int i = 0; i < n_slices; ++i) {
+                BwdSlice& sl = a.slices[i];
+                const int64_t units = geo.step_begin + sl.n_steps > 1 ? ((int64_t)shapes[i].T * geo.hkv + UPB - 1) / UPB * sl.diag_passes : 0;
+                sl.diag_first = (int)grid;
+                if ((grid += units) > kMaxGrid) return hipErrorInvalidValue;
+                sl.diag_units = (int)units;
+            }
+        }
         {
             ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : "ttt_bwd_main_f32_kernel", stream);
             hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS, stream, a);
@@ -1640,21 +1665,43 @@ static hipError_t launch_bwd_t(BwdArgs& a, hipStream_t stream) {
 
     // 3. block-0 sums -> output dtype, once the sweep has covered step 0
     if (!a.accumulate || geo.step_begin == 0) {
-        const int blocks = (int)((acc_n4 + 255) / 256 < 4096 ? (acc_n4 + 255) / 256 : 4096);
+        int blocks = 0;
+        for (int i = 0; i < n_slices; ++i) {
+            BwdSlice& sl = a.slices[i];
+            sl.finish_first = blocks;
+            sl.finish_blocks = (int)std::min<int64_t>(((int64_t)shapes[i].T * geo.hkv * (D / 4) + 255) / 256, 4096);
+            blocks += sl.finish_blocks;
+        }
         {
             ProfileScope prof("ttt_bwd_finish_kernel", stream);
-            hipLaunchKernelGGL((ttt_bwd_finish_kernel<T, D>), dim3(blocks), dim3(256), 0, stream, a);
+            hipLaunchKernelGGL((ttt_bwd_finish_kernel<T, D, N>), dim3(blocks), dim3(256), 0, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t launch_bwd(int dtype, int head_dim, BwdArgs& a, hipStream_t stream) {
-    if (dtype == 1 && head_dim == 128) return launch_bwd_t<__bf16, 128>(a, stream);
-    if (dtype == 1 && head_dim == 64) return launch_bwd_t<__bf16, 64>(a, stream);
-    if (dtype == 0 && head_dim == 128) return launch_bwd_t<float, 128>(a, stream);
-    if (dtype == 0 && head_dim == 64) return launch_bwd_t<float, 64>(a, stream);
+// the slices (those with the longest work first) in launches of one or of many
+template <typename T, int D> static hipError_t launch_bwd_slices(BwdCommon a, const Slice* slices, int n_slices, hipStream_t stream) {
+    int n_cu = 0;
+    if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
+    for (int i = 0, n; i < n_slices; i += n) {
+        n = 1;
+        if (sizeof(T) == 4 || !bwd_slice_alone(slices[i].shape, D, n_cu))
+            while (n < kMaxSlices && i + n < n_slices && (sizeof(T) == 4 || !bwd_slice_alone(slices[i + n].shape, D, n_cu))) ++n;
+        const hipError_t e = n > 1 ? launch_bwd_n<T, D, kMaxSlices>(a, slices + i, n, stream) : launch_bwd_n<T, D, 1>(a, slices + i, n, stream);
+        if (e != hipSuccess) return e;
+        a.bounds_blocks = 0;   // the first launch wrote and cleared them for the whole batch
+        a.clear_n4 = 0;
+    }
+    return hipSuccess;
+}
+
+hipError_t launch_bwd(int dtype, int head_dim, const BwdCommon& a, const Slice* slices, int n_slices, hipStream_t stream) {
+    if (dtype == 1 && head_dim == 128) return launch_bwd_slices<__bf16, 128>(a, slices, n_slices, stream);
+    if (dtype == 1 && head_dim == 64) return launch_bwd_slices<__bf16, 64>(a, slices, n_slices, stream);
+    if (dtype == 0 && head_dim == 128) return launch_bwd_slices<float, 128>(a, slices, n_slices, stream);
+    if (dtype == 0 && head_dim == 64) return launch_bwd_slices<float, 64>(a, slices, n_slices, stream);
     return hipErrorInvalidValue;
 }
 

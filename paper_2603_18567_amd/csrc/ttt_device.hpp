@@ -460,17 +460,15 @@ template <> TTT_DEV void gstore_vec4<__bf16>(__bf16* p, float a, float b, float 
     *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
 }
 
-// bounds of token i's document, by binary search in cu_seqlens (`cu` may be a slice of a longer array: `base` = its
-// first entry, subtracted so that the bounds count from the slice's first token)
-TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int base, int n_docs, int i, int* __restrict__ tok_start,
-                              int* __restrict__ tok_end) {
+// bounds of token i's document, by binary search in cu_seqlens
+TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int n_docs, int i, int* __restrict__ tok_start, int* __restrict__ tok_end) {
     int lo = 0, hi = n_docs;   // find the largest r with cu[r] <= i (then cu[r+1] > i)
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (cu[mid] - base <= i) lo = mid; else hi = mid;
+        if (cu[mid] <= i) lo = mid; else hi = mid;
     }
-    tok_start[i] = cu[lo] - base;
-    tok_end[i] = cu[lo + 1] - base;
+    tok_start[i] = cu[lo];
+    tok_end[i] = cu[lo + 1];
 }
 
 // Workgroup index -> (kv head, remaining index) so that workgroups that share one kv head's K_0/V_0
@@ -479,9 +477,14 @@ TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int base, int n_docs, 
 struct HeadMap {
     int mode;        // 0: no remap, 1: hkv multiple of 8, 2: hkv divides 8
     int hkv;
-    int rest_count;
 };
-TTT_DEV bool decode_block(const HeadMap& m, int id, int& g, int& rest) {
+inline HeadMap head_map(int hkv) { return HeadMap{hkv % 8 == 0 ? 1 : 8 % hkv == 0 ? 2 : 0, hkv}; }
+// workgroups of a part with `rest_count` items per kv head, a multiple of 8: the next part's map stays in step with the XCDs
+inline int64_t head_map_grid(const HeadMap& m, int64_t rest_count) {
+    const int xp = m.mode == 2 ? 8 / m.hkv : 1;
+    return m.mode == 2 ? 8 * ((rest_count + xp - 1) / xp) : (m.hkv * rest_count + 7) / 8 * 8;
+}
+TTT_DEV bool decode_block(const HeadMap& m, int rest_count, int id, int& g, int& rest) {
     if (m.mode == 1) {
         const int hp = m.hkv >> 3;
         const int xcd = id & 7, slot = id >> 3;
@@ -496,7 +499,7 @@ TTT_DEV bool decode_block(const HeadMap& m, int id, int& g, int& rest) {
         g = id % m.hkv;
         rest = id / m.hkv;
     }
-    return rest < m.rest_count;
+    return rest < rest_count;
 }
 
 }  // namespace ttt

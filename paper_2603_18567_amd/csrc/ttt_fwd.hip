@@ -21,8 +21,8 @@
 
 namespace ttt {
 
-template <typename T, int D, int QB, int NW, int KS, int WPE>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void ttt_fwd_kernel(const FwdArgs a) {
+template <typename T, int D, int QB, int NW, int KS, int WPE, int N>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) void ttt_fwd_kernel(const FwdArgs<N> a) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;                // kv rows per LDS tile
@@ -43,8 +43,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     auto sV = [&](int s) -> char* { return smem + (2 + s) * TILE_BYTES; };
 
     const Geometry& geo = a.geo;
+    const FwdSlice& sl = slice_of(a, &FwdSlice::first, blockIdx.x);
     int g, rest;
-    if (!decode_block(a.map, blockIdx.x, g, rest)) return;
+    if (!decode_block(a.map, sl.rest_count, blockIdx.x - sl.first, g, rest)) return;
     // The waves of a workgroup are 2^pack_log2 query heads of the kv group x NW >> pack_log2 blocks of
     // rows: heads that share K_0 / V_0 also share the key range, so all waves of a workgroup see
     // (almost) the same number of key tiles and none idles while the tile on the diagonal is finished.
@@ -52,16 +53,16 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     const int n_hgrp = geo.G >> pk;
     const int hgrp = rest % n_hgrp;
     rest /= n_hgrp;
-    const int j = geo.step_begin + rest % geo.n_steps;
-    const int tile = a.n_tiles - 1 - rest / geo.n_steps;   // long-prefix tiles first
+    const int j = geo.step_begin + rest % sl.n_steps;
+    const int tile = sl.n_tiles - 1 - rest / sl.n_steps;   // long-prefix tiles first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = KS == 1 ? 0 : wave / NWG, gwave = wave % NWG;   // key group, wave within it
     const int h = g * geo.G + (hgrp << pk) + (gwave & ((1 << pk) - 1));
     const int n = lane & 31, hh = lane >> 5;
-    const int Tn = geo.T;   // packed tokens
+    const int t0 = sl.t0, Tn = sl.t1;   // first token of the slice, one past its last
     const int qt_rows = QT >> pk;   // rows of a workgroup
-    const int q_tile0 = tile * qt_rows;
+    const int q_tile0 = t0 + tile * qt_rows;
     const int wq0 = q_tile0 + (gwave >> pk) * (QB * 32);
     const bool active = wq0 < Tn;
 
@@ -87,12 +88,12 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
     } else {
         // one document start per lane: the last one at or before the workgroup's first row, then those inside its rows
-        const int starts = a.cu[min(lane, a.n_docs - 1)] - a.cu_base;
-        int r = __popcll(__ballot(lane < a.n_docs && starts <= q_tile0)) - 1;
+        const int starts = a.cu[sl.doc0 + min(lane, sl.n_docs - 1)];
+        int r = __popcll(__ballot(lane < sl.n_docs && starts <= q_tile0)) - 1;
         lo = lo_w = st_hi = __builtin_amdgcn_readlane(starts, r);
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) st[qb] = lo;
-        for (++r; r < a.n_docs; ++r) {
+        for (++r; r < sl.n_docs; ++r) {
             const int s = __builtin_amdgcn_readlane(starts, r);
             if (s > hi) break;
 #pragma unroll
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
             st_hi = s <= hi_w ? s : st_hi;
         }
     }
-    const int u_lo = lo / KT, u_hi = hi / KT;
+    const int u_lo = (lo - t0) / KT, u_hi = (hi - t0) / KT;   // key tiles, counted from t0
 
     // Q as the stationary B operand: lane (n,hh) holds Q[row n][16t + 8hh .. +8]
     frag qf[QB][DC];
@@ -154,8 +155,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
             char* const tk = sK(s) + x * GROUP_BYTES;
             char* const tv = sV(s) + x * GROUP_BYTES;
             if constexpr (kFastCopy) {
-                if ((u + 1) * KT <= Tn) {
-                    const int64_t first = (int64_t)u * KT * geo.kv_st;
+                if (t0 + (u + 1) * KT <= Tn) {
+                    const int64_t first = (int64_t)(t0 + u * KT) * geo.kv_st;
                     tile_copy.copy(lds_addr(tk), K0 + first);
                     tile_copy.copy(lds_addr(tv), V0 + first);
                     continue;
@@ -163,8 +164,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
             }
             int tid_here = tid;
             if constexpr (KS > 1) asm volatile("" : "+v"(tid_here));   // computed here, not carried through the main loop
-            tile_load_async<T, D, KT, NT>(tk, K0, geo.kv_st, u * KT, Tn - 1, tid_here);
-            tile_load_async<T, D, KT, NT>(tv, V0, geo.kv_st, u * KT, Tn - 1, tid_here);
+            tile_load_async<T, D, KT, NT>(tk, K0, geo.kv_st, t0 + u * KT, Tn - 1, tid_here);
+            tile_load_async<T, D, KT, NT>(tv, V0, geo.kv_st, t0 + u * KT, Tn - 1, tid_here);
         }
     };
 
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     auto step = [&](auto stage_c, int u) {
         constexpr int ST = decltype(stage_c)::value;
         if (u + KS <= u_hi) load_tile(ST ^ 1, u + KS);
-        const int kv0 = (u + kg) * KT;
+        const int kv0 = t0 + (u + kg) * KT;
         if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) tile_work(stage_c, kv0);
         wait_async_copies();
         __syncthreads();   // the next tile is in LDS for everyone; everyone is done with this stage
@@ -445,7 +446,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     for (int qb = 0; qb < QB; ++qb) {
         const float lt = half_sum(l[qb]);
         const float inv = 1.f / lt;
-        if (hh == 0 && qi[qb] < Tn) a.lse[j][(int64_t)h * geo.lse_st + qi[qb]] = m[qb] * geo.scale + __logf(lt);
+        if (hh == 0 && qi[qb] < Tn) a.lse[j][(int64_t)h * geo.T + qi[qb]] = m[qb] * geo.scale + __logf(lt);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -471,30 +472,31 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 }
 
 // first / one-past-last token of each token's document
-__global__ void ttt_tok_bounds_kernel(const int* __restrict__ cu, int base, int n_docs, int T, int* __restrict__ tok_start,
+__global__ void ttt_tok_bounds_kernel(const int* __restrict__ cu, int n_docs, int T, int* __restrict__ tok_start,
                                       int* __restrict__ tok_end) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < T) write_doc_bounds(cu, base, n_docs, i, tok_start, tok_end);
+    if (i < T) write_doc_bounds(cu, n_docs, i, tok_start, tok_end);
 }
 
-hipError_t launch_tok_bounds(const int* cu_dev, int base, int n_docs, int T, int* tok_start, int* tok_end, hipStream_t stream) {
+hipError_t launch_tok_bounds(const int* cu_dev, int n_docs, int T, int* tok_start, int* tok_end, hipStream_t stream) {
     if (T <= 0) return hipSuccess;
     ProfileScope prof("ttt_tok_bounds_kernel", stream);
-    hipLaunchKernelGGL(ttt_tok_bounds_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, cu_dev, base, n_docs, T,
-                       tok_start, tok_end);
+    hipLaunchKernelGGL(ttt_tok_bounds_kernel, dim3((T + 255) / 256), dim3(256), 0, stream, cu_dev, n_docs, T, tok_start, tok_end);
     return hipGetLastError();
 }
 
-template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hipError_t launch_fwd_t(FwdArgs& a, hipStream_t stream) {
+template <typename T, int D, int QB, int NW, int KS, int WPE, int N>
+static hipError_t launch_fwd_n(const FwdCommon& common, const Slice* slices, int n_slices, hipStream_t stream) {
     constexpr int LDS_TILES = 4 * KS * 64 * D * (int)sizeof(T);   // two stages of K and V tiles
     constexpr int LDS_MAX = 160 * 1024 / (WPE * 4 / NW) / 1024 * 1024;   // of a workgroup, so many to a compute unit
     constexpr int ROWS_PER_COPY = NW * 64 * 16 / (D * (int)sizeof(T));
-    auto kern = ttt_fwd_kernel<T, D, QB, NW, KS, WPE>;
+    auto kern = ttt_fwd_kernel<T, D, QB, NW, KS, WPE, N>;
     static LdsOptIn lds_opt_in;
     if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS_MAX); e != hipSuccess) return e;
+    FwdArgs<N> a;
+    static_cast<FwdCommon&>(a) = common;
     const Geometry& geo = a.geo;
     const int qt_rows = (NW / KS * QB * 32) >> a.pack_log2;
-    a.n_tiles = (geo.T + qt_rows - 1) / qt_rows;
     // Rows of the diagonal keys through LDS: up to three blocks behind the tile stages, if the LDS for one block at
     // least is to be had without a workgroup less on the compute unit.  Fragment loads from global memory instead touch
     // 32 rows each and wait (forward and backward of the last of twelve steps, 512 tokens: 12/2 heads, 64 or 128 rows
@@ -504,22 +506,24 @@ template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hi
     a.diag_slots = sizeof(T) == 2 ? std::min(3, (LDS_MAX - LDS_TILES) / slot_bytes) : 0;
     if (a.diag_slots == 0 || slot_bytes > LDS_TILES) a.diag_rows = a.diag_slots = 0;
     const int lds_bytes = LDS_TILES + a.diag_slots * slot_bytes;
-    a.map.hkv = geo.hkv;
-    a.map.rest_count = a.n_tiles * geo.n_steps * (geo.G >> a.pack_log2);
-    int64_t grid;
-    if (geo.hkv % 8 == 0) {
-        a.map.mode = 1;
-        grid = (int64_t)geo.hkv * a.map.rest_count;
-    } else if (8 % geo.hkv == 0) {
-        a.map.mode = 2;
-        const int xp = 8 / geo.hkv;
-        grid = 8 * (int64_t)((a.map.rest_count + xp - 1) / xp);
-    } else {
-        a.map.mode = 0;
-        grid = (int64_t)geo.hkv * a.map.rest_count;
+    a.map = head_map(geo.hkv);
+    int64_t grid = 0;
+    for (int i = 0; i < n_slices; ++i) {
+        const CallShape& shape = slices[i].shape;
+        FwdSlice& sl = a.slices[i];
+        sl.first = (int)grid;
+        sl.t0 = slices[i].t0;
+        sl.t1 = sl.t0 + shape.T;
+        sl.n_steps = shape.n_steps;
+        sl.doc0 = slices[i].doc0;
+        sl.n_docs = shape.n_docs;
+        sl.n_tiles = (shape.T + qt_rows - 1) / qt_rows;
+        const int64_t rest = (int64_t)sl.n_tiles * shape.n_steps * (geo.G >> a.pack_log2);
+        grid += head_map_grid(a.map, rest);
+        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+        sl.rest_count = (int)rest;
     }
-    if (grid <= 0) return hipSuccess;
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    a.n_slices = n_slices;
     // the 16-bit kernels address the pieces of up to 64 rows of K or V with 32-bit byte offsets
     if (sizeof(T) == 2 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
     ProfileScope prof("ttt_fwd_kernel", stream);
@@ -527,22 +531,31 @@ template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4> static hi
     return hipGetLastError();
 }
 
-hipError_t launch_fwd(int dtype, int head_dim, FwdArgs& a, hipStream_t stream) {
+template <typename T, int D, int QB, int NW, int KS, int WPE = NW / 4>
+static hipError_t launch_fwd_t(const FwdCommon& a, const Slice* slices, int n_slices, hipStream_t stream) {
+    return n_slices > 1 ? launch_fwd_n<T, D, QB, NW, KS, WPE, kMaxSlices>(a, slices, n_slices, stream)
+                        : launch_fwd_n<T, D, QB, NW, KS, WPE, 1>(a, slices, n_slices, stream);
+}
+
+hipError_t launch_fwd(int dtype, int head_dim, const FwdCommon& common, const Slice* slices, int n_slices, hipStream_t stream) {
     int n_cu = 0;
     if (hipError_t e = current_device_cu_count(n_cu); e != hipSuccess) return e;
-    const FwdPlan plan = plan_fwd(call_shape(a.geo, a.n_docs, a.cu_host, a.cu_base), dtype == 1, head_dim, n_cu);
+    CallShape shapes[kMaxSlices];
+    for (int i = 0; i < n_slices; ++i) shapes[i] = slices[i].shape;
+    const FwdPlan plan = plan_fwd(shapes, n_slices, dtype == 1, head_dim, n_cu);
+    FwdCommon a = common;
     a.pack_log2 = plan.pack_log2;
     const bool two_groups = plan.split == kFwdTwoKeyGroups;
     if (dtype == 1 && head_dim == 128)
-        return two_groups ? launch_fwd_t<__bf16, 128, 1, 8, 2>(a, stream) : launch_fwd_t<__bf16, 128, 1, 8, 1>(a, stream);
+        return two_groups ? launch_fwd_t<__bf16, 128, 1, 8, 2>(a, slices, n_slices, stream) : launch_fwd_t<__bf16, 128, 1, 8, 1>(a, slices, n_slices, stream);
     if (dtype == 1 && head_dim == 64) {
-        if (two_groups) return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, stream);
-        if (plan.split == kFwdFourWaves) return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, stream);
-        return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, stream);
+        if (two_groups) return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, slices, n_slices, stream);
+        if (plan.split == kFwdFourWaves) return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, slices, n_slices, stream);
+        return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, slices, n_slices, stream);
     }
-    if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, stream);
+    if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, slices, n_slices, stream);
     if (dtype == 0 && head_dim == 64)
-        return two_groups ? launch_fwd_t<float, 64, 1, 4, 2>(a, stream) : launch_fwd_t<float, 64, 1, 4, 1>(a, stream);
+        return two_groups ? launch_fwd_t<float, 64, 1, 4, 2>(a, slices, n_slices, stream) : launch_fwd_t<float, 64, 1, 4, 1>(a, slices, n_slices, stream);
     return hipErrorInvalidValue;
 }
 

@@ -34,26 +34,32 @@ enum FwdSplit { kFwdEightWaves, kFwdFourWaves, kFwdTwoKeyGroups };
 // full and 1.85 when it is, a tile pair 2.0 and 2.2, a diagonal key 2.0 and 1.3 through LDS and twice that
 // otherwise.  One step, 32/8 heads: 1024 tokens 40 -> 29 us, 2048 70 -> 59, 3000 98 (114 with two groups); all
 // seven steps at 2048 293 (373).
-inline bool two_key_groups_end_first(const CallShape& a, int pack_log2, int n_cu) {
+inline bool two_key_groups_end_first(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
     const int rows = (8 * 32) >> pack_log2;      // of a workgroup with one key group
-    const int64_t per_tile = (int64_t)a.hkv * (a.G >> pack_log2) * a.n_steps;
-    if ((int64_t)(a.T + rows - 1) / rows * per_tile > 6 * n_cu) return false;   // many rounds: the work decides
-    const double j_mean = a.step_begin + 0.5 * (a.n_steps - 1), j_max = a.step_begin + a.n_steps - 1;
+    auto per_tile = [&](const CallShape& a) { return (int64_t)a.hkv * (a.G >> pack_log2) * a.n_steps; };
+    int64_t tiles_all = 0;
+    for (int i = 0; i < n_calls; ++i) tiles_all += (int64_t)(calls[i].T + rows - 1) / rows * per_tile(calls[i]);
+    if (tiles_all > 6 * n_cu) return false;   // many rounds: the work decides
     double est[2];
     for (int ks = 1; ks <= 2; ++ks) {
         const int r = rows / ks;
         const double diag = (ks == 1 ? 2.0 : 1.3) * (r * ks == 64 ? 1. : 2.);
-        int doc = 0;
-        int64_t steps = 0, n = 0, most = 0;
-        for (int row = 0; row < a.T; row += r, ++n) {
-            while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
-            const int64_t tiles = std::min(row + r - 1, a.T - 1) / 64 - (a.cu_host[doc] - a.cu_base) / 64 + 1;
-            const int64_t s = (tiles + ks - 1) / ks;
-            steps += s;
-            most = std::max(most, s);
+        double longest = 0., work = 0.;
+        for (int i = 0; i < n_calls; ++i) {
+            const CallShape& a = calls[i];
+            const double j_mean = a.step_begin + 0.5 * (a.n_steps - 1), j_max = a.step_begin + a.n_steps - 1;
+            int doc = 0;
+            int64_t steps = 0, n = 0, most = 0;
+            for (int row = 0; row < a.T; row += r, ++n) {
+                while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
+                const int64_t tiles = std::min(row + r - 1, a.T - 1) / 64 - (a.cu_host[doc] - a.cu_base) / 64 + 1;
+                const int64_t s = (tiles + ks - 1) / ks;
+                steps += s;
+                most = std::max(most, s);
+            }
+            longest = std::max(longest, 3. + most * (ks == 1 ? 1.55 : 2.0) + j_max * diag);
+            work += (n * (3. + j_mean * diag) + steps * (ks == 1 ? 1.85 : 2.2)) * (double)per_tile(a) / n_cu;
         }
-        const double longest = 3. + most * (ks == 1 ? 1.55 : 2.0) + j_max * diag;
-        const double work = (n * (3. + j_mean * diag) + steps * (ks == 1 ? 1.85 : 2.2)) * (double)per_tile / n_cu;
         est[ks - 1] = std::max(longest, work);
     }
     return est[1] < 0.97 * est[0];
@@ -68,11 +74,15 @@ inline bool two_key_groups_end_first(const CallShape& a, int pack_log2, int n_cu
 //   4096 tokens in nine documents, 32/8, one step: 23 / 26 / 34 (43)
 // Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest passes over
 // the keys.
-inline FwdSplit work_split_64(const CallShape& a, int pack_log2, int n_cu) {
+inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
     const int rows = (8 * 32) >> pack_log2;
-    const int64_t n = (int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack_log2) * a.n_steps;
+    int64_t n = 0;
     int longest = 0;
-    for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+    for (int i = 0; i < n_calls; ++i) {
+        const CallShape& a = calls[i];
+        n += (int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack_log2) * a.n_steps;
+        for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+    }
     const bool is_long = longest >= 16 * 64;
     if (is_long && n <= n_cu) return kFwdTwoKeyGroups;
     return n <= n_cu || (is_long && n <= 3 * (int64_t)n_cu) ? kFwdFourWaves : kFwdEightWaves;
@@ -84,23 +94,29 @@ struct FwdPlan {
     int pack_log2;
 };
 
-inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu) {
+// One launch serves `n_calls` slices of a batch, all of one head geometry.
+inline FwdPlan plan_fwd(const CallShape* calls, int n_calls, bool is_bf16, int head_dim, int n_cu) {
+    const int G = calls[0].G;
     // as many heads of a kv group per workgroup as divide the group, at most 4
     int pack_log2 = 0;
-    while ((2 << pack_log2) <= 4 && a.G % (2 << pack_log2) == 0) ++pack_log2;
+    while ((2 << pack_log2) <= 4 && G % (2 << pack_log2) == 0) ++pack_log2;
     if (is_bf16 && head_dim == 128)
-        return FwdPlan{two_key_groups_end_first(a, pack_log2, n_cu) ? kFwdTwoKeyGroups : kFwdEightWaves, pack_log2};
-    if (is_bf16) return FwdPlan{work_split_64(a, pack_log2, n_cu), pack_log2};
+        return FwdPlan{two_key_groups_end_first(calls, n_calls, pack_log2, n_cu) ? kFwdTwoKeyGroups : kFwdEightWaves, pack_log2};
+    if (is_bf16) return FwdPlan{work_split_64(calls, n_calls, pack_log2, n_cu), pack_log2};
     if (head_dim == 64) {
         // fp32 matrix instructions are slow and a short launch lasts as long as one wave's key tiles: two key groups
         // (LDS for one workgroup per compute unit) while every workgroup still gets a unit of its own (128 tokens, 4/4
         // heads, three steps 20 -> 13 us; 700 tokens, 8/1 heads, one step 56 -> 37)
         const int pack = std::min(pack_log2, 1);   // two waves per key group
         const int rows = (2 * 32) >> pack;
-        if ((int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack) * a.n_steps <= n_cu) return FwdPlan{kFwdTwoKeyGroups, pack};
+        int64_t n = 0;
+        for (int i = 0; i < n_calls; ++i)
+            n += (int64_t)((calls[i].T + rows - 1) / rows) * calls[i].hkv * (G >> pack) * calls[i].n_steps;
+        if (n <= n_cu) return FwdPlan{kFwdTwoKeyGroups, pack};
     }
     return FwdPlan{kFwdFourWaves, pack_log2};
 }
+inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu) { return plan_fwd(&a, 1, is_bf16, head_dim, n_cu); }
 
 // ------------------------------------------------------------------------------------------------
 // Work split of the 16-bit backward launch: 32-row query blocks per dK/dV chunk and ways to split the
@@ -160,7 +176,9 @@ template <typename F> void for_units_of_an_xcd(int hkv, int64_t n_units, F&& f) 
 // those of dealing every option, up to 131072 tokens within 0.04 % by the model).  Seven calls of one step each,
 // fresh layout of documents of 256 ... 4096 tokens, 32/8 heads: 16384 tokens 0.17 ms, 65536 1.1, 524288 1.3 (lists of
 // all units per call: 0.36, 5.2 and 590).
-inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
+//
+// other_us: what the other slices of the same launch take of an XCD's compute units, in all; it is taken to fill them evenly.
+inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double other_us = 0.) {
     const int T = a.T, n_jh = a.n_steps * a.G;
     const int n_tiles = (T + 127) / 128, n_tiles_q = (T + 255) / 256;
     const float stream = head_dim == 64 ? 0.6f : 1.f;
@@ -171,14 +189,15 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
     struct Key {
         int T, n_docs, step_begin, n_steps, G, hkv, head_dim, n_cu;
         uint64_t cu_hash;
+        double other_us;
         bool operator==(const Key& o) const {
             return T == o.T && n_docs == o.n_docs && step_begin == o.step_begin && n_steps == o.n_steps && G == o.G &&
-                   hkv == o.hkv && head_dim == o.head_dim && n_cu == o.n_cu && cu_hash == o.cu_hash;
+                   hkv == o.hkv && head_dim == o.head_dim && n_cu == o.n_cu && cu_hash == o.cu_hash && other_us == o.other_us;
         }
     };
     uint64_t h = 1469598103934665603ull;
     for (int r = 0; r <= a.n_docs; ++r) h = (h ^ (uint64_t)(uint32_t)(a.cu_host[r] - a.cu_base)) * 1099511628211ull;
-    const Key key{T, a.n_docs, a.step_begin, a.n_steps, a.G, a.hkv, head_dim, n_cu, h};
+    const Key key{T, a.n_docs, a.step_begin, a.n_steps, a.G, a.hkv, head_dim, n_cu, h, other_us};
     static std::mutex mu;
     static std::vector<std::pair<Key, DkvPlan>> cache;
     {
@@ -239,7 +258,7 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
             if (ns > n_jh || units * ns * a.hkv > 0x7fffffff) break;   // (more workgroups than a grid has)
             const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((double)units - used) * kEmptyUs));
             const double longest = (double)((n_jh + ns - 1) / ns) * most * kStepUs + kUnitUs;
-            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work) / cus), share * (double)units * ns + n_dq});
+            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work + other_us) / cus), share * (double)units * ns + n_dq});
         }
     }
     std::sort(options.begin(), options.end(), [](const Option& x, const Option& y) { return x.bound < y.bound; });
@@ -255,7 +274,7 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
         const int n_chunks = (T + o.cb * 32 - 1) / (o.cb * 32);
         for (int ch = 0; ch < n_chunks; ++ch)
             for (int t = 0; t < std::min(n_tiles, (ch + 1) * o.cb / 4); ++t) steps.push_back(dkv_unit_steps(t, q_end[t], ch, o.cb));
-        free_at.assign(cus, 0.f);
+        free_at.assign(cus, (float)(other_us / cus));
         float finish = 0.f;
         auto deal = [&](float us) {   // to the compute unit that frees up first: the root of a heap, which then sinks
             const float t = free_at[0] + us;
@@ -295,10 +314,40 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu) {
 constexpr int kDiagRegBlocks = 7;   // later blocks whose rows and gradients fit a lane's registers: one pass takes so many
 inline int diag_passes(const CallShape& a) { return std::max(1, (a.step_begin + a.n_steps - 2 + kDiagRegBlocks) / kDiagRegBlocks); }
 
-inline bool diag_blocks_apart(const CallShape& a, int head_dim, int n_cu) {
-    const int64_t n_pairs = (int64_t)a.n_steps * a.G;
-    const int64_t units = (int64_t)a.T * a.hkv * head_dim / (8 * 512) * diag_passes(a);   // 512 threads, 8 elements each
-    return n_pairs > 16 && units * n_pairs > 20 * (int64_t)n_cu && a.step_begin + a.n_steps > 1;
+inline bool diag_blocks_apart(const CallShape* calls, int n_calls, int head_dim, int n_cu) {
+    int64_t all = 0;
+    for (int i = 0; i < n_calls; ++i) {
+        const CallShape& a = calls[i];
+        const int64_t n_pairs = (int64_t)a.n_steps * a.G;
+        const int64_t units = (int64_t)a.T * a.hkv * head_dim / (8 * 512) * diag_passes(a);   // 512 threads, 8 elements each
+        if (n_pairs > 16 && a.step_begin + a.n_steps > 1) all += units * n_pairs;
+    }
+    return all > 20 * (int64_t)n_cu;
+}
+inline bool diag_blocks_apart(const CallShape& a, int head_dim, int n_cu) { return diag_blocks_apart(&a, 1, head_dim, n_cu); }
+
+// What a slice takes of one XCD's compute units by the model above, us in all: its documents one by one, half of each key
+// tile's rows below the diagonal.
+inline double bwd_slice_us(const CallShape& a, int head_dim) {
+    const double stream = head_dim == 64 ? 0.6 : 1., pairs = (double)a.n_steps * a.G;
+    double units = 0., steps = 0., keys = 0.;
+    for (int r = 0; r < a.n_docs; ++r) {
+        const double n = a.cu_host[r + 1] - a.cu_host[r], tiles = n / 128. + 0.5;
+        units += tiles * (n / 2048. + 1.);
+        steps += tiles * (n / 128. + 0.5);
+        keys += (n / 256. + 0.5) * (n / 256. + 1.);
+    }
+    return a.hkv / 8. * (steps * pairs * 1.9 * stream + units * 13. + keys * pairs * 5. * stream +
+                         ((double)a.T / 256. + 1.) * pairs * (8. + 1.7 * stream * (a.step_begin + 0.5 * (a.n_steps - 1))));
+}
+
+// Whether a slice has a backward launch of its own.  Slices that share a launch fill each other's tails and save launches, but
+// workgroups that start one by one, as others end, no longer stream the same Q / dO rows together.  So a slice that takes the
+// device more than a millisecond is alone (forward and backward, 16384 tokens in nine slices of up to twelve steps,
+// 32/8 heads: 12133 us with a launch per slice, 11965 so, 12300 at 0.2 ms, 12030 at 2; all in one 12450; 8192
+// tokens in documents of 100 to 500, up to seven steps 2171 -> 1461, 8/2 heads of 64 1321 -> 471 at any of these lines).
+inline bool bwd_slice_alone(const CallShape& a, int head_dim, int n_cu) {
+    return bwd_slice_us(a, head_dim) > 1000. * std::max(1, n_cu / 8);
 }
 
 // The fp32 backward: ways to split the (step, head) list of a 128-key tile, and its query rows.
