@@ -108,11 +108,14 @@ def ttt_attn_profile_totals(capacity: int = 16) -> dict:
     return {names[i].decode(): float(ms[i]) for i in range(n)}
 
 
-def _ptr_array(tensors, k):
+def _ptr_array(tensors, k, first=0, end=None):
+    """Device pointers of the steps [first, end) that the call reads or writes; NULL for the others (asking a tensor for
+    its pointer is most of what a call costs here: a one-step backward of seven steps needs 8 to 20 of 63)."""
     arr = (ctypes.c_void_p * k)()
-    for i in range(k):
-        t = tensors[i] if tensors is not None and i < len(tensors) else None
-        arr[i] = None if t is None else t.data_ptr()
+    for i in range(first, min(k if end is None else end, 0 if tensors is None else len(tensors))):
+        t = tensors[i]
+        if t is not None:
+            arr[i] = t.data_ptr()
     return arr
 
 
@@ -136,8 +139,11 @@ def ttt_attn_workspace_bytes(params: TttAttnParams, which_pass: int) -> int:
 
 
 def _stream_ptr(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    if stream is None:
+        if torch.cuda.is_initialized():   # the handle alone: no Stream object is made (3 us a call)
+            return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def _cu_host_array(cu_seqlens_host):
@@ -148,10 +154,10 @@ def _cu_host_array(cu_seqlens_host):
 def ttt_attn_fwd(params, q, k, v, cu_seqlens_dev, cu_seqlens_host, o, lse, workspace, stream=None):
     """q,k,v,o,lse: lists (length params.k; None where a step is not needed) of device tensors."""
     lib = load_library()
-    K = params.k
-    rc = lib.ttt_attn_fwd(ctypes.byref(params), _ptr_array(q, K), _ptr_array(k, K), _ptr_array(v, K),
+    K, b, e = params.k, params.step_begin, params.step_end
+    rc = lib.ttt_attn_fwd(ctypes.byref(params), _ptr_array(q, K, b, e), _ptr_array(k, K, 0, e), _ptr_array(v, K, 0, e),
                           ctypes.c_void_p(cu_seqlens_dev.data_ptr()), _cu_host_array(cu_seqlens_host),
-                          _ptr_array(o, K), _ptr_array(lse, K),
+                          _ptr_array(o, K, b, e), _ptr_array(lse, K, b, e),
                           ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
                           _stream_ptr(stream))
     if rc != TTT_OK:
@@ -161,10 +167,10 @@ def ttt_attn_fwd(params, q, k, v, cu_seqlens_dev, cu_seqlens_host, o, lse, works
 def ttt_attn_fwd_static(params, q, k, v, cu_seqlens_dev, cu_seqlens_host, o, lse, stream=None):
     """ttt_attn_fwd without a workspace (the library's built-in scratch; at most TTT_STATIC_MAX_TOKENS tokens)."""
     lib = load_library()
-    K = params.k
-    rc = lib.ttt_attn_fwd_static(ctypes.byref(params), _ptr_array(q, K), _ptr_array(k, K), _ptr_array(v, K),
+    K, b, e = params.k, params.step_begin, params.step_end
+    rc = lib.ttt_attn_fwd_static(ctypes.byref(params), _ptr_array(q, K, b, e), _ptr_array(k, K, 0, e), _ptr_array(v, K, 0, e),
                                  ctypes.c_void_p(cu_seqlens_dev.data_ptr()), _cu_host_array(cu_seqlens_host),
-                                 _ptr_array(o, K), _ptr_array(lse, K), _stream_ptr(stream))
+                                 _ptr_array(o, K, b, e), _ptr_array(lse, K, b, e), _stream_ptr(stream))
     if rc != TTT_OK:
         raise TttAttnError(rc, ttt_attn_last_error())
 
@@ -207,11 +213,12 @@ def ttt_attn_bwd_docsteps(params, doc_steps, q, k, v, o, lse, d_o, cu_seqlens_de
 def ttt_attn_bwd(params, q, k, v, o, lse, d_o, cu_seqlens_dev, cu_seqlens_host, dq, dk, dv,
                  accumulate_dkv, workspace, stream=None):
     lib = load_library()
-    K = params.k
-    rc = lib.ttt_attn_bwd(ctypes.byref(params), _ptr_array(q, K), _ptr_array(k, K), _ptr_array(v, K),
-                          _ptr_array(o, K), _ptr_array(lse, K), _ptr_array(d_o, K),
+    K, b, e = params.k, params.step_begin, params.step_end
+    written = b if accumulate_dkv else 0   # first cache block whose gradient this call completes
+    rc = lib.ttt_attn_bwd(ctypes.byref(params), _ptr_array(q, K, b, e), _ptr_array(k, K, 0, e), _ptr_array(v, K, 0, e),
+                          _ptr_array(o, K, b, e), _ptr_array(lse, K, b, e), _ptr_array(d_o, K, b, e),
                           ctypes.c_void_p(cu_seqlens_dev.data_ptr()), _cu_host_array(cu_seqlens_host),
-                          _ptr_array(dq, K), _ptr_array(dk, K), _ptr_array(dv, K), int(accumulate_dkv),
+                          _ptr_array(dq, K, b, e), _ptr_array(dk, K, written, e), _ptr_array(dv, K, written, e), int(accumulate_dkv),
                           ctypes.c_void_p(workspace.data_ptr()), workspace.numel() * workspace.element_size(),
                           _stream_ptr(stream))
     if rc != TTT_OK:
