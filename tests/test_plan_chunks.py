@@ -1,0 +1,18 @@
+"""The chunk limits of the 16-bit backward's work split (CPU only): with few kv heads and a long (step, head) list the choice
+is the best one by the model up to 512-row chunks, on either side of the line up to 1024."""
+import numpy as np
+import pytest
+
+from plan_lib import backward_split
+from test_plan_backward import model
+
+
+@pytest.mark.parametrize("tokens,hq,hkv,d,n,limit", [(4096, 64, 4, 128, 7, 16), (2048, 12, 2, 128, 3, 16), (2047, 64, 4, 128, 7, 32),
+                                                     (4096, 64, 4, 128, 1, 32), (4096, 32, 8, 128, 7, 32), (4096, 24, 1, 64, 1, 32)])
+def test_chunk_limit(tokens, hq, hkv, d, n, limit):
+    cu = np.array([0, tokens], dtype=np.int32)
+    cb, ns = backward_split(cu, hq, hkv, d, 0, n)
+    n_jh = n * (hq // hkv)
+    options = {(c, s): model(cu, hq, hkv, d, 0, n, c, s) for c in (8, 16, 32) for s in (1, 2, 3, 4, 6, 8)
+               if s <= n_jh and c <= limit and (c == 8 or c * 16 < tokens)}
+    assert options[cb, ns] <= min(options.values()) * (1 + 1e-4), (cb, ns, options)
