@@ -2,17 +2,16 @@
 // (Sec. 4.2.1), so every kernel here recomputes p = exp(s - LSE) from Q and K tile by tile and
 // applies the softmax-attention VJP:  D = <dO,O>, dp = <dO,V>, ds = p (dp - D).
 //
-//   ttt_bwd_pre_kernel     D for every (step, head, token); and the complete dK_l, dV_l of the later
-//                          cache blocks l >= 1, which are only ever read on the diagonal (suffix part
-//                          of Alg. 2), so one small group of lanes owns each (token, kv head) -- no atomics
-//                          (16-bit types: ttt_bwd_pre_regs_kernel; or ttt_bwd_delta_kernel for D, and the later
-//                          blocks as diag_unit workgroups of the next launch)
+//   ttt_bwd_delta_kernel   D for every (step, head, token)
+//   ttt_bwd_pre_regs_kernel  the same and the complete dK_l, dV_l of the later blocks (16-bit, by a rule on sizes)
 //   ttt_bwd_main_kernel    both streaming passes in one launch (ttt_bwd_main_f32_kernel for fp32):
 //     dkv_p8_tile, dkv_tile   key-stationary over block 0: dK, dV accumulators of 32 keys per wave in registers
 //                          while every (step, head of the group, query block at or below the diagonal) streams
 //                          past through LDS; partial sums of the splits meet in fp32 atomics
 //     dq_pipe_tile, dq_tile   query-stationary, same streaming structure as the forward: dQ_j
-//     diag_unit            (16-bit) dK_l, dV_l of the later blocks
+//     diag_unit            the complete dK_l, dV_l of the later cache blocks l >= 1, which are only ever read on the
+//                          diagonal (suffix part of Alg. 2), so one small group of lanes owns each (token, kv
+//                          head) -- no atomics
 //   ttt_bwd_finish_kernel  fp32 block-0 sums -> dK_0, dV_0 in the tensor dtype
 
 #include <algorithm>
@@ -26,12 +25,6 @@ constexpr float kLog2e = 1.44269504088896340736f;
 // ------------------------------------------------------------------------------------------------
 // D and the diagonal blocks' dK_l, dV_l
 // ------------------------------------------------------------------------------------------------
-template <int LPR> TTT_DEV float group_sum(float v) {
-#pragma unroll
-    for (int s = 1; s < LPR; s <<= 1) v += __shfl_xor(v, s, 64);
-    return v;
-}
-
 // What the streaming passes need besides, done by further workgroups of the same launch (as launches of their own
 // these took longer to start than to run: three of the five or six launches of a short call): document bounds per
 // token, and cleared block-0 sums.
@@ -49,112 +42,6 @@ TTT_DEV void bwd_pre_side_work(const BwdCommon& a, int blk) {
     }
 }
 
-template <typename T, int D, int N>
-__global__ __launch_bounds__(256) void ttt_bwd_pre_kernel(const BwdArgs<N> a) {
-    if ((int)blockIdx.x >= a.pre_blocks) {
-        bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
-        return;
-    }
-    using frag = typename Elem<T>::frag;
-    constexpr int LPR = D / 8;       // lanes that share one (token, kv head): 8 elements each
-    constexpr int UPB = 256 / LPR;   // (token, kv head) units per workgroup
-    extern __shared__ float sD[];    // [UPB][n_steps*G]
-
-    const Geometry& geo = a.geo;
-    const BwdSlice& sl = slice_of(a, &BwdSlice::pre_first, blockIdx.x);
-    const int Tn = geo.T, G = geo.G, ns = sl.n_steps, b = geo.step_begin, e = b + ns;
-    const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
-    const int64_t unit = (int64_t)((int)blockIdx.x - sl.pre_first) * UPB + grp;
-    const bool valid = unit < (int64_t)(sl.t1 - sl.t0) * geo.hkv;
-    const int i = sl.t0 + (valid ? (int)(unit / geo.hkv) : 0);
-    const int g = valid ? (int)(unit % geo.hkv) : 0;
-    float* myD = sD + grp * (ns * G);
-
-    // phase 1: D_j[h,i] = <dO_j[i,h], O_j[i,h]>
-    for (int js = 0; js < ns; ++js) {
-        const int j = b + js;
-        for (int hg = 0; hg < G; ++hg) {
-            const int h = g * G + hg;
-            const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh + sub * 8;
-            const frag go = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
-            const frag oo = gload_frag<T>(static_cast<const T*>(a.o[j]) + off);
-            float d = 0.f;
-#pragma unroll
-            for (int x = 0; x < 8; ++x) d = fmaf(to_f32<T>(go[x]), to_f32<T>(oo[x]), d);
-            d = group_sum<LPR>(d);
-            if (sub == 0) {
-                myD[js * G + hg] = d;
-                if (valid) {
-                    const int64_t at = ((int64_t)js * geo.hq + h) * Tn + i;
-                    a.delta[at] = d;
-                    a.lse2[at] = a.lse[j][(int64_t)h * geo.T + i] * kLog2e;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    if (!valid) return;
-
-    // phase 2: blocks l >= 1 see only the queries at their own token, steps j >= l
-    for (int lb = 1; lb < e; ++lb) {
-        const int64_t kvoff = (int64_t)i * geo.kv_st + (int64_t)g * geo.kv_sh + sub * 8;
-        const frag kf = gload_frag<T>(static_cast<const T*>(a.k[lb]) + kvoff);
-        const frag vf = gload_frag<T>(static_cast<const T*>(a.v[lb]) + kvoff);
-        float dk[8], dv[8];
-#pragma unroll
-        for (int x = 0; x < 8; ++x) dk[x] = dv[x] = 0.f;
-        for (int j = (lb > b ? lb : b); j < e; ++j) {
-            for (int hg = 0; hg < G; ++hg) {
-                const int h = g * G + hg;
-                const int64_t off = (int64_t)i * geo.q_st + (int64_t)h * geo.q_sh + sub * 8;
-                const frag qf = gload_frag<T>(static_cast<const T*>(a.q[j]) + off);
-                const frag go = gload_frag<T>(static_cast<const T*>(a.d_o[j]) + off);
-                float s = 0.f, dp = 0.f;
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    s = fmaf(to_f32<T>(qf[x]), to_f32<T>(kf[x]), s);
-                    dp = fmaf(to_f32<T>(go[x]), to_f32<T>(vf[x]), dp);
-                }
-                s = group_sum<LPR>(s);
-                dp = group_sum<LPR>(dp);
-                const float lse = a.lse[j][(int64_t)h * geo.T + i];
-                const float p = fast_exp2((s * geo.scale - lse) * kLog2e);
-                const float ds = p * (dp - myD[(j - b) * G + hg]) * geo.scale;
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    dk[x] = fmaf(ds, to_f32<T>(qf[x]), dk[x]);
-                    dv[x] = fmaf(p, to_f32<T>(go[x]), dv[x]);
-                }
-            }
-        }
-        if (a.accumulate) {
-            // fp32 carry across the calls of a descending-step sweep; this group owns its slice
-            const int64_t coff = (((int64_t)(lb - 1) * Tn + i) * geo.hkv + g) * D + sub * 8;
-            float* ck = a.dkl_acc + coff;
-            float* cv = a.dvl_acc + coff;
-            if (!a.carry_reset) {
-#pragma unroll
-                for (int x = 0; x < 8; ++x) {
-                    dk[x] += ck[x];
-                    dv[x] += cv[x];
-                }
-            }
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                ck[x] = dk[x];
-                cv[x] = dv[x];
-            }
-            if (lb < b) continue;   // not complete yet: earlier steps' calls have not run
-        }
-        T* gk = static_cast<T*>(a.dk[lb]) + kvoff;
-        T* gv = static_cast<T*>(a.dv[lb]) + kvoff;
-        gstore_vec4<T>(gk, dk[0], dk[1], dk[2], dk[3]);
-        gstore_vec4<T>(gk + 4, dk[4], dk[5], dk[6], dk[7]);
-        gstore_vec4<T>(gv, dv[0], dv[1], dv[2], dv[3]);
-        gstore_vec4<T>(gv + 4, dv[4], dv[5], dv[6], dv[7]);
-    }
-}
-
 // Sum over an aligned group of LPR (4, 8 or 16) lanes with DPP moves only (no LDS traffic):
 // quad butterflies, then the half-row and the row mirror pair up quads and half-rows.
 template <int LPR> TTT_DEV float group_sum_dpp(float v) {
@@ -168,14 +55,13 @@ template <int LPR> TTT_DEV float group_sum_dpp(float v) {
     return v;
 }
 
-// 16-bit types: D and LSE * log2(e) alone, which is all that the streaming passes wait for.  Bound by memory (16384
+// D and LSE * log2(e) alone, which is all that the streaming passes wait for.  Bound by memory (16-bit, 16384
 // tokens, 32 heads, one step: 52 us, 5.2 TB/s); one workgroup takes 32 tokens x kDeltaHeads heads of one step: its loads
 // are all requested at once (whole rows of neighbouring heads), its results leave as runs of 32 tokens.
 constexpr int kDeltaTokens = 32, kDeltaHeads = 4;
 
 template <typename T, int D, int N>
 __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs<N> a) {
-    static_assert(sizeof(T) == 2, "16-bit elements");
     if ((int)blockIdx.x >= a.pre_blocks) {
         bwd_pre_side_work(a, (int)blockIdx.x - a.pre_blocks);
         return;
@@ -225,19 +111,19 @@ __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs<N> a) 
     }
 }
 
-// dK_l, dV_l of the later blocks for 16-bit types: the K_l, V_l rows of a (token, kv head) and their fp32 gradients stay
+// dK_l, dV_l of the later blocks: the K_l, V_l rows of a (token, kv head) and their fp32 gradients stay
 // in registers while one sweep over (step, head of the group) feeds all of them (the suffix part of Alg. 2 read from
 // the key's side: key (l, i) is seen only by the queries (j >= l, i) of Sec. 2.4's unrolled steps).
-// kDiagRegBlocks blocks fit; with more steps the blocks are taken so many at a time by further workgroups, whose sweeps
+// kDiagRegBlocks blocks fit (fp32: kDiagRegBlocksF32); with more steps the blocks are taken so many at a time by further workgroups, whose sweeps
 // start at the first step that sees one of theirs.  Either workgroups of the streaming launch, with D and LSE at hand,
 // or (MAKE_D) the preprocess launch, whose first pass makes these from O on the way.  Bound by memory; the rows of the
 // next two pairs are requested before a pair is worked on (4096 tokens, MAKE_D, 0.98 GB: none ahead 4.45 TB/s, one
 // 4.75, two 5.07; four, with two blocks fewer in registers, no more).
 template <typename T, int D, int THREADS, bool MAKE_D>
 TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
-    static_assert(sizeof(T) == 2, "register budget sized for 16-bit elements");
     using frag = typename Elem<T>::frag;
-    constexpr int NL = kDiagRegBlocks, PF = 2;
+    constexpr int NL = sizeof(T) == 2 ? kDiagRegBlocks : kDiagRegBlocksF32, PF = 2;
+    constexpr bool kExactLse = sizeof(T) == 4;   // fp32: the difference to the LSE before the factor log2(e), which is the more exact
     constexpr int LPR = D / 8;        // lanes that share one (token, kv head): 8 elements each
     constexpr int UPB = THREADS / LPR;
 
@@ -270,7 +156,7 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
             lse[s] = a.lse[j][(int64_t)h * geo.T + i];
         } else {
             const int64_t at = ((int64_t)(j - b) * geo.hq + h) * Tn + i;
-            lse[s] = a.lse2[at];
+            lse[s] = kExactLse ? a.lse[j][(int64_t)h * geo.T + i] : a.lse2[at];
             dl[s] = a.delta[at];
         }
     };
@@ -278,20 +164,23 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
     for (int s = 0; s < PF; ++s)
         if (s < n_pairs) request(s, s);
 
-    // the sums start from the carry of the later steps' calls: everything that a unit reads is in flight at once
     frag kf[NL], vf[NL];
     float dk[NL][8], dv[NL][8];
-    const bool carried = a.accumulate && !a.carry_reset;
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
         if (l0 + l < e) {
             kf[l] = gload_frag<T>(static_cast<const T*>(a.k[l0 + l]) + kvoff);
             vf[l] = gload_frag<T>(static_cast<const T*>(a.v[l0 + l]) + kvoff);
         }
-    }
 #pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        if (carried && l0 + l < e) {
+        for (int x = 0; x < 8; ++x) dk[l][x] = dv[l][x] = 0.f;
+    }
+    // The carry of the later steps' calls.  16-bit: the sums start from it, so that everything that a unit reads is in flight at
+    // once; fp32: it is added to this call's sums, which is the more exact by 1 %.
+    auto add_carry = [&]() {
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            if (!a.accumulate || a.carry_reset || l0 + l >= e) break;
             const float* ck = a.dkl_acc + (l0 + l - 1) * cblk + coff;
             const float* cv = a.dvl_acc + (l0 + l - 1) * cblk + coff;
 #pragma unroll
@@ -299,15 +188,13 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
                 const f32x4 k4 = gload_vec4<float>(ck + half * (D / 2)), v4 = gload_vec4<float>(cv + half * (D / 2));
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    dk[l][4 * half + x] = k4[x];
-                    dv[l][4 * half + x] = v4[x];
+                    dk[l][4 * half + x] += k4[x];
+                    dv[l][4 * half + x] += v4[x];
                 }
             }
-        } else {
-#pragma unroll
-            for (int x = 0; x < 8; ++x) dk[l][x] = dv[l][x] = 0.f;
         }
-    }
+    };
+    if constexpr (sizeof(T) == 2) add_carry();
 
     for (int n = 0; n < n_pairs; ++n) {
         const int j = j0 + n / G;
@@ -342,7 +229,7 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
             if (l0 + l > j) break;             // a block is visible from the step of its own number on
             const float s = group_sum_dpp<LPR>(dot8(cq, kf[l], 0.f));
             const float dp = group_sum_dpp<LPR>(dot8(cg, vf[l], 0.f));
-            const float p = fast_exp2(s * geo.scale_log2 - lse2);
+            const float p = fast_exp2(kExactLse ? (s * geo.scale - lse2) * kLog2e : s * geo.scale_log2 - lse2);
             const float ds = p * (dp - dsum) * geo.scale;
 #pragma unroll
             for (int x = 0; x < 8; ++x) {
@@ -352,6 +239,7 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
         }
     }
 
+    if constexpr (sizeof(T) == 4) add_carry();
 #pragma unroll
     for (int l = 0; l < NL; ++l) {
         const int lb = l0 + l;
@@ -366,14 +254,8 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
             }
             continue;
         }
-        frag ok, ov;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            ok[x] = (T)dk[l][x];
-            ov[x] = (T)dv[l][x];
-        }
-        *reinterpret_cast<frag*>(static_cast<T*>(a.dk[lb]) + kvoff) = ok;
-        *reinterpret_cast<frag*>(static_cast<T*>(a.dv[lb]) + kvoff) = ov;
+        gstore_frag<T>(static_cast<T*>(a.dk[lb]) + kvoff, dk[l]);
+        gstore_frag<T>(static_cast<T*>(a.dv[lb]) + kvoff, dv[l]);
     }
 }
 
@@ -390,20 +272,26 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs<N> 
 // ------------------------------------------------------------------------------------------------
 // dQ: query-stationary
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, int QB, int NW>
+// fp32.  With two key groups (KS = 2) the halves of a workgroup take every second key tile (and diagonal key) of the same
+// rows and add up in LDS: fp32 matrix instructions are slow, and a short launch lasts as long as one wave's tiles
+// (dq_two_key_groups).
+template <typename T, int D, int QB, int NW, int KS>
 TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;
     constexpr int KB = KT / 32;
-    constexpr int QT = NW * QB * 32;
+    constexpr int NWG = NW / KS;   // waves of a key group
+    constexpr int QT = NWG * QB * 32;
     constexpr int DC = D / 16;
     constexpr int DB = D / 32;
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
 
-    auto sK = [&](int s) -> char* { return smem + s * TILE_BYTES; };
-    auto sV = [&](int s) -> char* { return smem + (2 + s) * TILE_BYTES; };
+    // LDS of a key group: K stage 0, K stage 1, V stage 0, V stage 1
+    constexpr int GROUP_BYTES = 4 * TILE_BYTES;
+    auto sK = [&](int s, int group) -> char* { return smem + group * GROUP_BYTES + s * TILE_BYTES; };
+    auto sV = [&](int s, int group) -> char* { return smem + group * GROUP_BYTES + (2 + s) * TILE_BYTES; };
 
     const Geometry& geo = a.geo;
     int g, rest;
@@ -419,7 +307,8 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
     const int q_tile0 = t0 + tile * QT;
-    const int wq0 = q_tile0 + wave * (QB * 32);
+    const int kg = KS == 1 ? 0 : wave / NWG, gwave = wave % NWG;   // key group, wave within it
+    const int wq0 = q_tile0 + gwave * (QB * 32);
     const bool active = wq0 < Tn;
 
     const T* Qj = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
@@ -462,20 +351,24 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
             for (int i = 0; i < 16; ++i) dqacc[qb][db][i] = 0.f;
     const float c = geo.scale_log2;
 
-    tile_load_async<T, D, KT, NT>(sK(0), K0, geo.kv_st, t0 + u_lo * KT, Tn - 1, tid);
-    tile_load_async<T, D, KT, NT>(sV(0), V0, geo.kv_st, t0 + u_lo * KT, Tn - 1, tid);
+    auto load = [&](int s, int u0) {   // tiles u0 ... of the key groups
+#pragma unroll
+        for (int x = 0; x < KS; ++x) {
+            if (KS > 1 && u0 + x > u_hi) break;
+            tile_load_async<T, D, KT, NT>(sK(s, x), K0, geo.kv_st, t0 + (u0 + x) * KT, Tn - 1, tid);
+            tile_load_async<T, D, KT, NT>(sV(s, x), V0, geo.kv_st, t0 + (u0 + x) * KT, Tn - 1, tid);
+        }
+    };
+    load(0, u_lo);
     int stage = 0;
-    for (int u = u_lo; u <= u_hi; ++u) {
+    for (int u = u_lo; u <= u_hi; u += KS) {
         wait_async_copies();
         __syncthreads();
-        if (u < u_hi) {
-            tile_load_async<T, D, KT, NT>(sK(stage ^ 1), K0, geo.kv_st, t0 + (u + 1) * KT, Tn - 1, tid);
-            tile_load_async<T, D, KT, NT>(sV(stage ^ 1), V0, geo.kv_st, t0 + (u + 1) * KT, Tn - 1, tid);
-        }
-        const int kv0 = t0 + u * KT;
+        if (u + KS <= u_hi) load(stage ^ 1, u + KS);
+        const int kv0 = t0 + (u + kg) * KT;
         if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) {
-            const char* tk = sK(stage);
-            const char* tv = sV(stage);
+            const char* tk = sK(stage, kg);
+            const char* tv = sV(stage, kg);
             f32x16 sacc[KB][QB], pacc[KB][QB];
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -527,10 +420,10 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
         }
         stage ^= 1;
     }
-    if (!active) return;
+    if (KS == 1 && !active) return;
 
     // diagonal keys of blocks 1..j
-    for (int lb = 1; lb <= j; ++lb) {
+    for (int lb = 1 + kg; lb <= j; lb += KS) {
         const T* Kl = static_cast<const T*>(a.k[lb]) + (int64_t)g * geo.kv_sh;
         const T* Vl = static_cast<const T*>(a.v[lb]) + (int64_t)g * geo.kv_sh;
 #pragma unroll
@@ -562,6 +455,35 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
                         dqacc[qb][db][i4 * 4 + x] = fmaf(ds, to_f32<T>(kk[x]), dqacc[qb][db][i4 * 4 + x]);
                 }
         }
+    }
+
+    if constexpr (KS == 2) {
+        // the second group's rows join the first one's: 16-byte pieces of the same lane of wave gwave
+        static_assert(NWG * QB * DB * 4 * 1024 <= KS * GROUP_BYTES, "one group's rows fit in the tile stages");
+        f32x4* piece = reinterpret_cast<f32x4*>(smem) + gwave * (QB * DB * 4 * 64) + lane;
+        __syncthreads();   // everybody is done with the tile stages
+        if (kg == 1) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int db = 0; db < DB; ++db)
+#pragma unroll
+                    for (int i4 = 0; i4 < 4; ++i4)
+                        piece[((qb * DB + db) * 4 + i4) * 64] = f32x4{dqacc[qb][db][4 * i4], dqacc[qb][db][4 * i4 + 1],
+                                                                      dqacc[qb][db][4 * i4 + 2], dqacc[qb][db][4 * i4 + 3]};
+        }
+        __syncthreads();
+        if (kg == 1 || !active) return;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x4 o4 = piece[((qb * DB + db) * 4 + i4) * 64];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) dqacc[qb][db][4 * i4 + x] += o4[x];
+                }
     }
 
 #pragma unroll
@@ -1499,9 +1421,22 @@ template <typename T, int D, int N>
 __global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs<N> a) {
     extern __shared__ __align__(16) char smem[];
     const int wg = blockIdx.x;
+    if (wg >= a.grid_stream) {
+        const BwdSlice& sl = slice_of(a, &BwdSlice::diag_first, wg);
+        diag_unit<T, D, 256, false>(a, sl, wg - sl.diag_first);
+        return;
+    }
     const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
-    if (wg < sl.q_first) dkv_tile<T, D, 4>(a, sl, smem, wg - sl.kv_first);
-    else dq_tile<T, D, 1, 4>(a, sl, smem, wg - sl.q_first);
+    if (wg < sl.q_first) {
+        dkv_tile<T, D, 4>(a, sl, smem, wg - sl.kv_first);
+        return;
+    }
+    if constexpr (D == 64)
+        if (a.dq_key_groups == 2) {
+            dq_tile<T, D, 1, 4, 2>(a, sl, smem, wg - sl.q_first);
+            return;
+        }
+    dq_tile<T, D, 1, 4, 1>(a, sl, smem, wg - sl.q_first);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1542,7 +1477,6 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
     if ((e = current_device_cu_count(n_cu)) != hipSuccess) return e;
     a.map = head_map(geo.hkv);
     CallShape shapes[kMaxSlices];
-    int max_steps = 0;
     for (int i = 0; i < n_slices; ++i) {
         shapes[i] = slices[i].shape;
         BwdSlice& sl = a.slices[i];
@@ -1551,70 +1485,62 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         sl.n_steps = shapes[i].n_steps;
         sl.diag_units = 0;
         sl.diag_passes = 1;
-        max_steps = std::max(max_steps, sl.n_steps);
     }
     a.n_slices = n_slices;
 
+    // fp32 calls of more (step, head) pairs have always been refused
+    for (int i = 0; i < n_slices; ++i)
+        if (!k16 && shapes[i].n_steps * geo.G > 20 * D) return hipErrorInvalidValue;
+
     // 1. D and, here or beside the streaming passes, the diagonal blocks; the tokens' document bounds; and cleared block-0
     // sums unless a carry from later steps is being continued
-    const bool apart = !k16 || diag_blocks_apart(shapes, n_slices, D, n_cu);
+    const bool apart = k16 && diag_blocks_apart(shapes, n_slices, D, n_cu);
     {
         constexpr int UPB = 256 / (D / 8);
         int64_t grid = 0;
         for (int i = 0; i < n_slices; ++i) {
             BwdSlice& sl = a.slices[i];
             const int64_t tokens = shapes[i].T;
-            int64_t blocks = (tokens * geo.hkv + UPB - 1) / UPB;
             sl.pre_first = (int)grid;
-            if constexpr (k16) {
-                sl.diag_passes = diag_passes(shapes[i]);
-                if (apart) {
-                    blocks *= sl.diag_passes;
-                    if (blocks <= kMaxGrid) sl.diag_units = (int)blocks;
-                } else {
-                    blocks = (tokens + kDeltaTokens - 1) / kDeltaTokens * sl.n_steps * ((geo.hq + kDeltaHeads - 1) / kDeltaHeads);
-                }
+            sl.diag_passes = diag_passes(shapes[i], k16 ? kDiagRegBlocks : kDiagRegBlocksF32);
+            int64_t blocks = (tokens + kDeltaTokens - 1) / kDeltaTokens * sl.n_steps * ((geo.hq + kDeltaHeads - 1) / kDeltaHeads);
+            if (apart) {
+                blocks = (tokens * geo.hkv + UPB - 1) / UPB * sl.diag_passes;
+                if (blocks <= kMaxGrid) sl.diag_units = (int)blocks;
             }
             if ((grid += blocks) > kMaxGrid) return hipErrorInvalidValue;
         }
         a.pre_blocks = (int)grid;
         grid += a.bounds_blocks + std::min<int64_t>((a.clear_n4 + 1023) / 1024, 2048);
         if (grid > kMaxGrid) return hipErrorInvalidValue;
-        if constexpr (k16) {
-            ProfileScope prof(apart ? "ttt_bwd_pre_regs_kernel" : "ttt_bwd_delta_kernel", stream);
-            auto kern = apart ? ttt_bwd_pre_regs_kernel<T, D, N> : ttt_bwd_delta_kernel<T, D, N>;
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, stream, a);
-        } else {
-            auto kern = ttt_bwd_pre_kernel<T, D, N>;
-            const size_t lds = (size_t)UPB * max_steps * geo.G * sizeof(float);   // D of a unit's (step, head) pairs
-            if (lds > 160 * 1024) return hipErrorInvalidValue;
-            if (lds > 48 * 1024) {
-                e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return e;
-            }
-            ProfileScope prof("ttt_bwd_pre_kernel", stream);
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, stream, a);
-        }
+        ProfileScope prof(apart ? "ttt_bwd_pre_regs_kernel" : "ttt_bwd_delta_kernel", stream);
+        auto kern = ttt_bwd_delta_kernel<T, D, N>;
+        if constexpr (k16)
+            if (apart) kern = ttt_bwd_pre_regs_kernel<T, D, N>;
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), 0, stream, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
 
     // 2. dQ and block 0's dK, dV in one launch
     {
         constexpr int NW = k16 ? 8 : 4;
-        constexpr int QT = NW * 32, KVT = 128;
+        constexpr int KVT = 128;
         constexpr int LDS_Q = k16 ? 2 * 2 * 128 * D * (int)sizeof(T) : 4 * 64 * D * (int)sizeof(T);
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
+        constexpr int LDS_KEY_GROUPS = !k16 && D == 64 ? 2 * LDS_Q : LDS;   // fp32 dQ tiles with two key groups
         void (*kern)(BwdArgs<N>);
         if constexpr (k16) kern = ttt_bwd_main_kernel<T, D, N>;
         else kern = ttt_bwd_main_f32_kernel<T, D, N>;
         static LdsOptIn lds_opt_in;
-        if ((e = lds_opt_in.ensure((const void*)kern, LDS)) != hipSuccess) return e;
+        if ((e = lds_opt_in.ensure((const void*)kern, LDS_KEY_GROUPS)) != hipSuccess) return e;
         // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
         // 32-bit byte offsets
         if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         // dK/dV: split the (step, head) list of a unit so that the grid fills the device evenly
+        a.dq_key_groups = !k16 && D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
+        const int q_rows = NW * 32 / a.dq_key_groups;
         int64_t grid = 0;
         double slice_us[N] = {}, all_us = 0.;
         if constexpr (N > 1)
@@ -1640,14 +1566,14 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
             sl.kv_rest = (int)(n_units * sl.n_split);
             sl.kv_first = (int)grid;
             if ((grid += head_map_grid(a.map, sl.kv_rest)) > kMaxGrid) return hipErrorInvalidValue;
-            const int64_t rest = (int64_t)((shapes[i].T + QT - 1) / QT) * sl.n_steps * geo.G;
+            const int64_t rest = (int64_t)((shapes[i].T + q_rows - 1) / q_rows) * sl.n_steps * geo.G;
             sl.q_first = (int)grid;
             if ((grid += head_map_grid(a.map, rest)) > kMaxGrid) return hipErrorInvalidValue;
             sl.q_rest = (int)rest;
         }
         a.grid_stream = (int)grid;
         if (!apart) {
-            constexpr int UPB = 512 / (D / 8);
+            constexpr int UPB = NW * 64 / (D / 8);
             for (int i = 0; i < n_slices; ++i) {
                 BwdSlice& sl = a.slices[i];
                 const int64_t units = geo.step_begin + sl.n_steps > 1 ? ((int64_t)shapes[i].T * geo.hkv + UPB - 1) / UPB * sl.diag_passes : 0;
@@ -1658,7 +1584,7 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         }
         {
             ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : "ttt_bwd_main_f32_kernel", stream);
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), LDS, stream, a);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), a.dq_key_groups == 2 ? LDS_KEY_GROUPS : LDS, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

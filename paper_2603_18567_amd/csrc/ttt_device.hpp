@@ -460,6 +460,19 @@ template <> TTT_DEV void gstore_vec4<__bf16>(__bf16* p, float a, float b, float 
     *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
 }
 
+// 8 consecutive elements to global memory, 16 bytes a store
+template <typename T> TTT_DEV void gstore_frag(T* p, const float (&v)[8]);
+template <> TTT_DEV void gstore_frag<float>(float* p, const float (&v)[8]) {
+    gstore_vec4<float>(p, v[0], v[1], v[2], v[3]);
+    gstore_vec4<float>(p + 4, v[4], v[5], v[6], v[7]);
+}
+template <> TTT_DEV void gstore_frag<__bf16>(__bf16* p, const float (&v)[8]) {
+    bf16x8 r;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = (__bf16)v[e];
+    *reinterpret_cast<bf16x8*>(p) = r;
+}
+
 // bounds of token i's document, by binary search in cu_seqlens
 TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int n_docs, int i, int* __restrict__ tok_start, int* __restrict__ tok_end) {
     int lo = 0, hi = n_docs;   // find the largest r with cu[r] <= i (then cu[r+1] > i)

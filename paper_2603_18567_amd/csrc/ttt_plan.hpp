@@ -316,15 +316,15 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
 // step a call: 2 to 27 % up to 2048 tokens, 0 to 2 % beyond; all steps in one call, up to 512 tokens: 3 to 40 %)
 // except for sweeps over many (step, head) pairs that also fill the device: there one unit is as long as a
 // dQ tile and leaves a tail of its own (all steps, 7 to 12 of 32/8 heads: 0 to 2.7 % slower from 1024 tokens on).
-constexpr int kDiagRegBlocks = 7;   // later blocks whose rows and gradients fit a lane's registers: one pass takes so many
-inline int diag_passes(const CallShape& a) { return std::max(1, (a.step_begin + a.n_steps - 2 + kDiagRegBlocks) / kDiagRegBlocks); }
+constexpr int kDiagRegBlocks = 7, kDiagRegBlocksF32 = 3;   // later blocks whose rows and gradients fit a lane's registers
+inline int diag_passes(const CallShape& a, int per_pass) { return std::max(1, (a.step_begin + a.n_steps - 2 + per_pass) / per_pass); }
 
 inline bool diag_blocks_apart(const CallShape* calls, int n_calls, int head_dim, int n_cu) {
     int64_t all = 0;
     for (int i = 0; i < n_calls; ++i) {
         const CallShape& a = calls[i];
         const int64_t n_pairs = (int64_t)a.n_steps * a.G;
-        const int64_t units = (int64_t)a.T * a.hkv * head_dim / (8 * 512) * diag_passes(a);   // 512 threads, 8 elements each
+        const int64_t units = (int64_t)a.T * a.hkv * head_dim / (8 * 512) * diag_passes(a, kDiagRegBlocks);   // 512 threads, 8 elements each
         if (n_pairs > 16 && a.step_begin + a.n_steps > 1) all += units * n_pairs;
     }
     return all > 20 * (int64_t)n_cu;
@@ -369,6 +369,19 @@ inline DkvPlanF32 plan_dkv_split_f32(const CallShape& a, int n_cu) {
     while (p.n_split == n_jh && p.q_split < (a.T + 63) / 64 && (int64_t)n_tiles * a.hkv * p.n_split * (p.q_split + 1) <= n_cu)
         ++p.q_split;
     return p;
+}
+
+// The fp32 dQ tiles of head_dim 64 (LDS for one workgroup per compute unit): two key groups and 64 rows while all of them
+// together with the dK/dV units have a compute unit each (the streaming launch of three steps on 128 tokens, 4/4 heads 23.2 ->
+// 18.1 us; forward and backward, 128 tokens, 12/2 heads, one step a call of six 328 -> 218 with the later blocks beside).
+inline bool dq_two_key_groups(const CallShape* calls, int n_calls, int n_cu) {
+    int64_t n = 0;
+    for (int i = 0; i < n_calls; ++i) {
+        const CallShape& a = calls[i];
+        const DkvPlanF32 kv = plan_dkv_split_f32(a, n_cu);
+        n += (int64_t)a.hkv * ((a.T + 127) / 128 * kv.n_split * kv.q_split + (a.T + 63) / 64 * a.n_steps * a.G);
+    }
+    return n <= n_cu;
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -28,6 +28,11 @@ void plan_backward_f32(int T, int n_steps, int G, int hkv, int n_cu, int* n_spli
     *q_split = p.q_split;
 }
 
+int plan_dq_key_groups(int T, int n_steps, int G, int hkv, int n_cu) {
+    const ttt::CallShape shape{T, 0, n_steps, G, hkv, 0, nullptr, 0};
+    return ttt::dq_two_key_groups(&shape, 1, n_cu);
+}
+
 // tile sizes and workgroups per compute unit of the launches of a projection; returns how many there are
 int plan_projection(int64_t tokens, int hidden_in, int features, int largest_fits, int n_cu, int* mt_nt_per_cu, int* f_first) {
     const ttt::QkvPlan p = ttt::plan_qkv(tokens, hidden_in, features, largest_fits != 0, n_cu);

@@ -54,6 +54,11 @@ def backward_split_f32(tokens, hq, hkv, n_steps, n_cu=256):
     return _call(_lib().plan_backward_f32, tokens, n_steps, hq // hkv, hkv, n_cu)
 
 
+def dq_key_groups_f32(tokens, hq, hkv, n_steps, n_cu=256):
+    """key groups of the dQ tiles (head_dim 64)"""
+    return 2 if _lib().plan_dq_key_groups(tokens, n_steps, hq // hkv, hkv, n_cu) else 1
+
+
 def projection_tiles(tokens, hidden_in, features, n_cu=256, largest_fits=True):
     """[(tokens, features, workgroups per compute unit) of a tile] of the launches"""
     tiles, f_first = (ctypes.c_int * 6)(), ctypes.c_int()

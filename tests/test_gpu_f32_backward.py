@@ -1,0 +1,37 @@
+"""GPU parity of the fp32 backward: dQ tiles with two key groups (one tile, odd and even numbers of tiles, documents that begin
+inside a tile pair, rows whose keys all lie in one group) and with one, and the later blocks in one, two and three passes, all
+steps in one call or one step a call with the carry.  Every case asserts the key groups that the launch rules choose."""
+import pytest
+import torch
+
+from paper_2603_18567_amd.workloads import custom_workload
+from plan_lib import dq_key_groups_f32
+from ttt_testlib import Case, compare_full
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # documents, hq, hkv, head_dim, k, steps per backward call, key groups
+    ([1], 2, 1, 64, 1, 1, 2),
+    ([65], 4, 4, 64, 2, 2, 2),
+    ([100, 1, 60], 8, 2, 64, 4, 1, 2),
+    ([193], 2, 2, 64, 8, 8, 2),
+    ([70, 130], 3, 1, 64, 5, 1, 2),
+    ([90, 200], 16, 16, 64, 4, 4, 1),
+    ([33, 40], 4, 2, 128, 8, 1, 1),
+    ([129], 6, 3, 128, 5, 5, 1),
+]
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,steps,groups", CASES, ids=[f"{sum(c[0])}_{c[1]}_{c[2]}_{c[3]}_{c[4]}_{c[5]}" for c in CASES])
+def test_f32_backward_matches_oracle(docs, hq, hkv, d, k, steps, groups):
+    print(f"documents={docs} heads={hq}/{hkv} head_dim={d} k={k} steps={steps}", flush=True)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert (dq_key_groups_f32(sum(docs), hq, hkv, steps, n_cu) if d == 64 else 1) == groups
+    case = Case(custom_workload(f"f32_bwd_{sum(docs)}_{d}", "f32", docs, hq, hkv, d, k, seed=hq + k), "cuda:0")
+    case.run.forward()
+    for j in reversed(range(0, k, steps)):
+        case.run.backward(case.d_o, j, j + steps, accumulate=steps < k)
+    torch.cuda.synchronize()
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
