@@ -390,26 +390,53 @@ inline bool dq_two_key_groups(const CallShape* calls, int n_calls, int n_cu) {
 // The tiles a call can be cut into, and what they were measured to take (us; sweeps over 16 to 8192 tokens, hidden_in
 // 64 to 8192, 2048 to 9216 features): `round` once per round of the device (first copies, epilogue), and per
 // 64-column slice `t1` with one workgroup on every compute unit, `lo` in the limit of few workgroups (copies and
-// clock are shared), and `t2` with two side by side on one unit.  Model and measurement agree within 8 %.
+// clock are shared), and `t2` with two side by side on one unit.  With weights that are in no cache model and measurement
+// differ by 5 % (256 x 256) to 15 % (64 x 64; rms over 120 shapes).
 struct QkvTile {
     int mt, nt, per_cu;
+    int max_group;     // token tiles of one feature tile that are dealt to an XCD together, at most
+    bool by_xcd;       // long workgroups, one to a compute unit: the XCD that gets the most tiles sets the rounds
     double round, lo, t1, t2;
 };
 constexpr QkvTile kQkvTiles[] = {
-    {256, 256, 1, 8., 0.95, 1.55, 0.},
-    {128, 128, 2, 5., 0.57, 0.57, 1.03},
-    {128, 128, 1, 4., 0.44, 0.55, 0.},
-    {128, 64, 1, 3., 0.30, 0.37, 0.},
-    {64, 64, 2, 3., 0.18, 0.18, 0.36},
-    {64, 32, 2, 2., 0.17, 0.17, 0.28},
-    {32, 32, 2, 2., 0.14, 0.14, 0.22},
+    {256, 256, 1, 4, true, 8., 0.95, 1.55, 0.},
+    {128, 128, 2, 8, false, 5., 0.57, 0.57, 1.03},
+    {128, 128, 1, 8, true, 4., 0.44, 0.55, 0.},
+    {128, 64, 1, 8, false, 3., 0.30, 0.37, 0.},
+    {64, 64, 2, 8, false, 3., 0.18, 0.18, 0.36},
+    {64, 32, 2, 8, false, 2., 0.17, 0.17, 0.28},
+    {32, 32, 2, 8, false, 2., 0.14, 0.14, 0.22},
 };
 constexpr int kQkvTileKinds = sizeof(kQkvTiles) / sizeof(kQkvTiles[0]);
 constexpr double kQkvLaunchUs = 3.;
 
-// estimated time of `tiles` tiles: full rounds of the device and a last one, as full as it is
-inline double qkv_cost(const QkvTile& v, int64_t tiles, int n_cu, int slices) {
-    const int64_t slots = (int64_t)n_cu * v.per_cu, rest = tiles % slots;
+// Tiles of the XCD that gets the most: groups of m_per token tiles (the last of a feature tile is smaller) go to the eight
+// XCDs in turn.
+inline int64_t qkv_xcd_tiles(int64_t m, int64_t n, int m_per) {
+    const int64_t groups = (m + m_per - 1) / m_per, most = (groups * n + 7) / 8;
+    // an odd number of groups brings every XCD its share of the smaller ones
+    return most * m_per - (groups % 2 ? most / groups * (groups * m_per - m) : 0);
+}
+
+// How many token tiles go together: as many as the kind allows in equal groups; fewer of the largest tiles where that saves
+// a round of the device (253 of them in groups of four are 36 on one XCD of 32 compute units: 2772 tokens, hidden_in 7040,
+// 5888 features took two rounds for one).  Smaller tiles lose more by sharing less of an L2 (539 tokens, hidden_in 2304,
+// 7168 features 39 us in groups of five, 47 in groups of three).
+inline int qkv_group(const QkvTile& v, int64_t m, int64_t n, int n_cu) {
+    const int64_t slots = std::max(1, n_cu / 8);
+    auto rounds = [&](int per) { return (qkv_xcd_tiles(m, n, per) + slots - 1) / slots; };
+    const int64_t groups = (m + v.max_group - 1) / v.max_group;
+    int best = (int)((m + groups - 1) / groups);
+    if (v.mt == 256)
+        for (int per = best - 1; per >= 1; --per)
+            if (rounds(per) < rounds(best)) best = per;
+    return best;
+}
+
+// estimated time of m x n tiles: full rounds of the device and a last one, as full as it is
+inline double qkv_cost(const QkvTile& v, int64_t m, int64_t n, int n_cu, int slices) {
+    const int64_t slots = (int64_t)n_cu * v.per_cu;
+    const int64_t tiles = v.by_xcd ? 8 * qkv_xcd_tiles(m, n, qkv_group(v, m, n, n_cu)) : m * n, rest = tiles % slots;
     const double full = v.round + slices * (v.per_cu == 2 ? v.t2 : v.t1);
     double us = kQkvLaunchUs + (double)(tiles / slots) * full;
     if (rest > n_cu) us += full;
@@ -429,7 +456,7 @@ struct QkvPlan {
 inline QkvPlan plan_qkv(int64_t tokens, int hidden_in, int features, bool largest_fits, int n_cu) {
     const int slices = hidden_in / 64, kinds = largest_fits ? 0 : 1;
     auto row_tiles = [&](const QkvTile& t) { return (tokens + t.mt - 1) / t.mt; };
-    auto cost = [&](const QkvTile& t, int f) { return qkv_cost(t, row_tiles(t) * ((f + t.nt - 1) / t.nt), n_cu, slices); };
+    auto cost = [&](const QkvTile& t, int f) { return qkv_cost(t, row_tiles(t), (f + t.nt - 1) / t.nt, n_cu, slices); };
     QkvPlan plan{-1, -1, features};
     double best = 0.;
     for (int t = kinds; t < kQkvTileKinds; ++t) {
@@ -443,10 +470,13 @@ inline QkvPlan plan_qkv(int64_t tokens, int hidden_in, int features, bool larges
         const QkvTile& large = kQkvTiles[t];
         const int64_t slots = (int64_t)n_cu * large.per_cu, m = row_tiles(large);
         const int64_t rounds = m * ((features + large.nt - 1) / large.nt) / slots;
-        const int64_t f = rounds * slots / m * large.nt;
+        int64_t n = rounds * slots / m;
+        while (n > 0 && qkv_xcd_tiles(m, n, qkv_group(large, m, n, n_cu)) > rounds * slots / 8) --n;   // the fullest XCD, too
+        const int64_t f = n * large.nt;
         if (f <= 0 || f >= features) continue;
         const double head = cost(large, (int)f);
         for (int u = kinds; u < kQkvTileKinds; ++u) {
+            if (u == t) continue;   // two launches of one kind gain nothing (6322 tokens, hidden_in 5376, 7040 features 495 us, 507)
             const double c = head + cost(kQkvTiles[u], features - (int)f);
             if (c < best) {
                 best = c;

@@ -38,6 +38,7 @@ struct QkvArgs {
     int n_q, n_k, n_v;    // heads written to q (rotated), k (rotated), v (as they are); weight rows in this order
     int64_t x_st, w_st;   // row strides in elements
     int m_tiles, n_tiles;
+    int m_per;            // token tiles of one feature tile that go to one XCD together
     int f_first, f_count; // features of this launch (a call may be carried out as two launches)
 };
 
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
 
     // groups of up to 4 token tiles of one feature tile on one XCD, as in the kernel below
     const int slot = blockIdx.x >> 3;
-    const int m_groups = (a.m_tiles + 3) / 4, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int m_per = a.m_per, m_groups = (a.m_tiles + m_per - 1) / m_per;
     const int grp = slot / m_per * 8 + (blockIdx.x & 7);
     const int tm = grp % m_groups * m_per + slot % m_per, tn = grp / m_groups;
     if (tm >= a.m_tiles || tn >= a.n_tiles) return;
@@ -304,7 +305,7 @@ __global__ __launch_bounds__(512) void ttt_qkv_rope_splitk_kernel(const QkvArgs 
     // round-robin over the 8): with few tokens its weight rows enter that L2 once; with many the groups are
     // dealt out token group by token group, so that an XCD keeps to the same x rows.
     const int slot = blockIdx.x >> 3;
-    const int m_groups = (a.m_tiles + 7) / 8, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int m_per = a.m_per, m_groups = (a.m_tiles + m_per - 1) / m_per;
     const int grp = slot / m_per * 8 + (blockIdx.x & 7);
     const int tm = grp % m_groups * m_per + slot % m_per, tn = grp / m_groups;
     if (tm >= a.m_tiles || tn >= a.n_tiles) return;
@@ -495,7 +496,7 @@ static hipError_t launch_qkv_rope_splitk(QkvArgs& a, hipStream_t stream) {
     if (hipError_t e = lds_opt_in.ensure((const void*)kern, C::LDS); e != hipSuccess) return e;
     a.m_tiles = (a.T + MT - 1) / MT;
     a.n_tiles = a.f_count / NT;
-    const int64_t m_groups = (a.m_tiles + 7) / 8, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int64_t m_per = a.m_per, m_groups = (a.m_tiles + m_per - 1) / m_per;
     const int64_t grid = 8 * m_per * ((m_groups * a.n_tiles + 7) / 8);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     ProfileScope prof("ttt_qkv_rope_kernel", stream);
@@ -510,7 +511,7 @@ static hipError_t launch_qkv_rope_256(QkvArgs& a, hipStream_t stream) {
     if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS); e != hipSuccess) return e;
     a.m_tiles = (a.T + 255) / 256;
     a.n_tiles = (a.f_count + 255) / 256;
-    const int64_t m_groups = (a.m_tiles + 3) / 4, m_per = (a.m_tiles + m_groups - 1) / m_groups;
+    const int64_t m_per = a.m_per, m_groups = (a.m_tiles + m_per - 1) / m_per;
     const int64_t grid = 8 * m_per * ((m_groups * a.n_tiles + 7) / 8);
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
     ProfileScope prof("ttt_qkv_rope_kernel", stream);
@@ -558,12 +559,15 @@ hipError_t launch_qkv_rope(const void* x, const void* w, const float* cos_tab, c
     const bool largest_fits = x_st < (int64_t)1 << 23 && w_st < (int64_t)1 << 23;
     const int features = (n_q + n_k + n_v) * 128;
     const QkvPlan plan = plan_qkv(tokens, hidden_in, features, largest_fits, n_cu);
-    a.f_first = 0;
-    a.f_count = plan.f_first;
-    if (hipError_t e = kQkvLaunchers[plan.first](a, stream); e != hipSuccess || plan.second < 0) return e;
-    a.f_first = plan.f_first;
-    a.f_count = features - plan.f_first;
-    return kQkvLaunchers[plan.second](a, stream);
+    auto launch = [&](int kind, int f_first, int f_count) {
+        const QkvTile& t = kQkvTiles[kind];
+        a.f_first = f_first;
+        a.f_count = f_count;
+        a.m_per = qkv_group(t, (a.T + t.mt - 1) / t.mt, (f_count + t.nt - 1) / t.nt, n_cu);
+        return kQkvLaunchers[kind](a, stream);
+    };
+    if (hipError_t e = launch(plan.first, 0, plan.f_first); e != hipSuccess || plan.second < 0) return e;
+    return launch(plan.second, plan.f_first, features - plan.f_first);
 }
 
 }  // namespace ttt

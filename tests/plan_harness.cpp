@@ -48,4 +48,11 @@ int plan_projection(int64_t tokens, int hidden_in, int features, int largest_fit
     *f_first = p.f_first;
     return n;
 }
+
+// token tiles of one feature tile that a launch of tiles of `kind` deals to an XCD together
+int plan_projection_group(int64_t tokens, int kind, int features, int n_cu) {
+    const ttt::QkvTile& t = ttt::kQkvTiles[kind];
+    return ttt::qkv_group(t, (tokens + t.mt - 1) / t.mt, (features + t.nt - 1) / t.nt, n_cu);
+}
+
 }

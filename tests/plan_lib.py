@@ -64,3 +64,15 @@ def projection_tiles(tokens, hidden_in, features, n_cu=256, largest_fits=True):
     tiles, f_first = (ctypes.c_int * 6)(), ctypes.c_int()
     n = _lib().plan_projection(ctypes.c_int64(tokens), hidden_in, features, int(largest_fits), n_cu, tiles, ctypes.byref(f_first))
     return [tuple(tiles[3 * i:3 * i + 3]) for i in range(n)]
+
+
+def projection_first_features(tokens, hidden_in, features, n_cu=256):
+    """features of the first launch"""
+    tiles, f_first = (ctypes.c_int * 6)(), ctypes.c_int()
+    _lib().plan_projection(ctypes.c_int64(tokens), hidden_in, features, 1, n_cu, tiles, ctypes.byref(f_first))
+    return f_first.value
+
+
+def projection_group(tokens, kind, features, n_cu=256):
+    """token tiles of one feature tile that are dealt to an XCD together (kind: place in the table of tiles)"""
+    return _lib().plan_projection_group(ctypes.c_int64(tokens), kind, features, n_cu)
