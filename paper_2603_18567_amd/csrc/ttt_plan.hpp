@@ -420,7 +420,9 @@ inline int64_t qkv_xcd_tiles(int64_t m, int64_t n, int m_per) {
 
 // How many token tiles go together: as many as the kind allows in equal groups; fewer of the largest tiles where that saves
 // a round of the device (253 of them in groups of four are 36 on one XCD of 32 compute units: 2772 tokens, hidden_in 7040,
-// 5888 features took two rounds for one).  Smaller tiles lose more by sharing less of an L2 (539 tokens, hidden_in 2304,
+// 5888 features took two rounds for one).  Groups without a remainder only: the empty workgroups of the others take a
+// compute unit each before the last tiles of an XCD get one (2283 tokens, hidden_in 2752, 6912 features, 243 tiles: groups
+// of three, 33 on one XCD, 131 us, of two 142, one by one 87).  Smaller tiles lose more by sharing less of an L2 (539 tokens, hidden_in 2304,
 // 7168 features 39 us in groups of five, 47 in groups of three).
 inline int qkv_group(const QkvTile& v, int64_t m, int64_t n, int n_cu) {
     const int64_t slots = std::max(1, n_cu / 8);
@@ -429,7 +431,7 @@ inline int qkv_group(const QkvTile& v, int64_t m, int64_t n, int n_cu) {
     int best = (int)((m + groups - 1) / groups);
     if (v.mt == 256)
         for (int per = best - 1; per >= 1; --per)
-            if (rounds(per) < rounds(best)) best = per;
+            if (m % per == 0 && rounds(per) < rounds(best)) best = per;
     return best;
 }
 
