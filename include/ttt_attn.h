@@ -143,10 +143,10 @@ int ttt_attn_bwd(const ttt_attn_params* params,
  * of TTT steps of document r: its tokens take part in steps j < doc_steps_host[r] only and own the
  * cache blocks l < doc_steps_host[r] only.  For the other (step, document) combinations nothing is
  * read and nothing is written: the rows of such a document in O_j, LSE_j, dQ_j, dK_l, dV_l keep
- * their contents.  Documents are independent, so the call is carried out as one pass per run of
- * consecutive documents with equal step count, one after the other on the stream, sharing the
- * workspace (sized by ttt_attn_workspace_bytes for the whole batch as before); group documents by
- * step count for the fewest passes.  The backward variant has no carry mode (accumulate_dkv = 0).
+ * their contents.  Documents are independent: a launch takes up to 16 runs of consecutive documents with
+ * equal step count (the backward gives a run that takes the device long a launch of its own), in the
+ * workspace sized by ttt_attn_workspace_bytes for the whole batch; group documents by step count for
+ * the fewest runs.  The backward variant has no carry mode (accumulate_dkv = 0).
  * All other arguments, layouts and errors are those of ttt_attn_fwd / ttt_attn_bwd.
  */
 int ttt_attn_fwd_docsteps(const ttt_attn_params* params, const int32_t* doc_steps_host, const void* const* q,
