@@ -1335,42 +1335,49 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
         step(s + 1 < n_steps2, IntC<0>{});
         if (s + 1 < n_steps2) step(s + 2 < n_steps2, IntC<1>{});
     }
-    // The two waves of a key range first add their sums in LDS (the last barrier of the loop has
-    // freed all of it): half as many atomics.  Quad q of a lane's accumulators sits at
-    // (q * 256 + pair * 64 + lane) * 16 bytes.
-    static_assert(2 * DB * 4 * 256 * 16 <= C::kLds, "the sums of one wave group fit in LDS");
+    // The two waves of a key range add their sums in LDS (the last barrier of the loop has freed all of it): group 0 hands
+    // its dV over and ends with the sums of dK, group 1 the other way round, so that eight waves request the atomics
+    // (from four waves, each row's address worked out per lane: 5.1 us of a unit's end, 2.3 so; 128 tokens, 32/8 heads, a
+    // pass of seven steps one by one 216 -> 210 us).  Quad q of what a lane hands over sits at
+    // (q * 256 + pair * 64 + lane) * 16 bytes of its group's half.
+    constexpr int HALF_BYTES = DB * 4 * 256 * 16;
+    static_assert(2 * HALF_BYTES <= C::kLds, "the sums that change hands fit in LDS");
     typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
     const uint32_t sum_addr = lds0 + (pair * 64 + lane) * 16;
     if (grp == 1) {
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int i4 = 0; i4 < 4; ++i4) {
-                *(lds_f32x4*)(uintptr_t)(sum_addr + ((db * 4 + i4) * 2 + 0) * 4096) =
-                    f32x4{dkacc[db][4 * i4], dkacc[db][4 * i4 + 1], dkacc[db][4 * i4 + 2], dkacc[db][4 * i4 + 3]};
-                *(lds_f32x4*)(uintptr_t)(sum_addr + ((db * 4 + i4) * 2 + 1) * 4096) =
-                    f32x4{dvacc[db][4 * i4], dvacc[db][4 * i4 + 1], dvacc[db][4 * i4 + 2], dvacc[db][4 * i4 + 3]};
-            }
+        for (int db = 0; db < DB; ++db) {
+            const f32x16 t = dkacc[db];
+            dkacc[db] = dvacc[db];
+            dvacc[db] = t;
+        }
     }
-    __syncthreads();
-    if (!active || grp == 1) return;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-            const f32x4 k4 = *(const lds_f32x4*)(uintptr_t)(sum_addr + ((db * 4 + i4) * 2 + 0) * 4096);
-            const f32x4 v4 = *(const lds_f32x4*)(uintptr_t)(sum_addr + ((db * 4 + i4) * 2 + 1) * 4096);
+        for (int i4 = 0; i4 < 4; ++i4)
+            *(lds_f32x4*)(uintptr_t)(sum_addr + grp * HALF_BYTES + (db * 4 + i4) * 4096) =
+                f32x4{dvacc[db][4 * i4], dvacc[db][4 * i4 + 1], dvacc[db][4 * i4 + 2], dvacc[db][4 * i4 + 3]};
+    __syncthreads();
+    if (!active) return;
+    // rows of the block-0 sums: a uniform base per row and a lane's place in it
+    float* const acc = (grp == 0 ? a.dk0_acc : a.dv0_acc) + ((int64_t)wk0 * geo.hkv + g) * D;
+    const int64_t row = (int64_t)geo.hkv * D;
+    const uint32_t lane_at = (uint32_t)(4 * hh) * (uint32_t)row + n;
+    auto flush = [&](auto whole) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int i = 4 * i4 + e;
-                const int kv = wk0 + acc_row(i, hh);
-                if (kv < Tn) {
-                    const int64_t off = ((int64_t)kv * geo.hkv + g) * D + db * 32 + n;
-                    atomicAdd(a.dk0_acc + off, dkacc[db][i] + k4[e]);
-                    atomicAdd(a.dv0_acc + off, dvacc[db][i] + v4[e]);
-                }
+        for (int i4 = 0; i4 < 4; ++i4)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                const f32x4 s4 = *(const lds_f32x4*)(uintptr_t)(sum_addr + (grp ^ 1) * HALF_BYTES + (db * 4 + i4) * 4096);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (decltype(whole)::value || wk0 + acc_row(4 * i4 + e, hh) < Tn)
+                        atomicAdd(acc + (8 * i4 + e) * row + lane_at + db * 32, dkacc[db][4 * i4 + e] + s4[e]);
             }
-        }
+    };
+    if (wk0 + 32 <= Tn) flush(IntC<1>{});
+    else flush(IntC<0>{});
 }
 
 // One workgroup = one key tile x one chunk of `chunk_blocks` query blocks x one split of the
