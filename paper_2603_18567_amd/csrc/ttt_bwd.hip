@@ -562,18 +562,14 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
     const float lse2 = a.lse2[at];
     const float dl = a.delta[at];
     const int hi_w = min(wq0 + 31, Tn - 1);
-    const int lo_w = active ? __builtin_amdgcn_readfirstlane(a.tok_start[min(wq0, Tn - 1)]) : 0;
-    const int st_hi = active ? __builtin_amdgcn_readfirstlane(a.tok_start[hi_w]) : 0;
-    const int lo = __builtin_amdgcn_readfirstlane(a.tok_start[q_tile0]);
+    const int first_row = __builtin_amdgcn_readfirstlane(min(wq0, Tn - 1));
+    int lo_w = uniform_load(a.tok_start + first_row);
+    int st_hi = uniform_load(a.tok_start + max(__builtin_amdgcn_readfirstlane(hi_w), first_row));
+    asm volatile("" : "+v"(lo_w), "+v"(st_hi));
+    const int lo = uniform_load(a.tok_start + q_tile0);
     const int hi = min(q_tile0 + QT - 1, Tn - 1);
     const int u_lo = (lo - t0) / KT, u_hi = (hi - t0) / KT;   // key tiles, counted from t0
 
-    frag qf[DC], gof[DC];
-#pragma unroll
-    for (int t = 0; t < DC; ++t) {
-        qf[t] = gload_frag<T>(Qj + (int64_t)qc * geo.q_st + t * 16 + hh * 8);
-        gof[t] = gload_frag<T>(dOj + (int64_t)qc * geo.q_st + t * 16 + hh * 8);
-    }
     f32x16 dqacc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
@@ -615,12 +611,50 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
             tile_copy.copy(lds0 + s * STAGE_BYTES + TILE_BYTES, V0 + first);
         } else {
             char* stg = smem + s * STAGE_BYTES;
-            tile_load_async<T, D, KT, NT>(stg, K0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
-            tile_load_async<T, D, KT, NT>(stg + TILE_BYTES, V0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
+            int tid_here = tid;
+            asm volatile("" : "+v"(tid_here));   // computed here, not carried through the main loop
+            tile_load_async<T, D, KT, NT>(stg, K0, geo.kv_st, t0 + u * KT, Tn - 1, tid_here);
+            tile_load_async<T, D, KT, NT>(stg + TILE_BYTES, V0, geo.kv_st, t0 + u * KT, Tn - 1, tid_here);
         }
     };
 
-    issue(u_lo, 0);
+    // The wave's Q rows, and then its dO rows, come through a region of the stage that the second tile will take, as
+    // whole rows: loaded as fragments from global memory they touch 32 rows per instruction and hold up the
+    // copies of the first tile behind them (start of a workgroup to its first scores, one step: 128 tokens 4.4 -> 3.5 us,
+    // 1024 tokens 6.7 -> 4.5; all seven steps at 4096 tokens, forward and backward 0.5 % less).
+    frag qf[DC], gof[DC];
+    {
+        constexpr int NCP = 32 * TL::kPieces / 64;
+        constexpr int ROWS_BYTES = 32 * TL::kRowBytes;
+        static_assert(NW * ROWS_BYTES <= STAGE_BYTES, "one region per wave");
+        const uint32_t region = __builtin_amdgcn_readfirstlane(lds0 + STAGE_BYTES + wave * ROWS_BYTES);
+        int lane_here = lane;
+        asm volatile("" : "+v"(lane_here));   // computed here, not carried through the main loop
+        uint32_t roff[NCP];
+#pragma unroll
+        for (int it = 0; it < NCP; ++it) {
+            const int pidx = it * 64 + lane_here;
+            const int r = pidx / TL::kPieces, pos = pidx % TL::kPieces;   // rows past the end repeat the last one
+            roff[it] = (uint32_t)((min(r, Tn - 1 - first_row) * geo.q_st + (pos ^ TL::swz(r)) * TL::kElemsPerPiece) * (int64_t)sizeof(T));
+        }
+        auto request = [&](const T* base) {
+#pragma unroll
+            for (int it = 0; it < NCP; ++it) async_copy16(base + (int64_t)first_row * geo.q_st, roff[it], region + it * 1024);
+        };
+        LaneFrags<T, D> lf;
+        lf.init(lane_here);
+        const char* rows = smem + STAGE_BYTES + wave * ROWS_BYTES;
+        request(Qj);
+        issue(u_lo, 0);
+        wait_copies_but(IntC<2 * TILE_BYTES / (NT * 16)>{});
+#pragma unroll
+        for (int t = 0; t < DC; ++t) qf[t] = lf.rowwise(rows, 0, t);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the region is read out: refill it
+        request(dOj);
+        wait_async_copies();
+#pragma unroll
+        for (int t = 0; t < DC; ++t) gof[t] = lf.rowwise(rows, 0, t);
+    }
     int stage = 0;
     for (int u = u_lo; u <= u_hi; ++u) {
         wait_async_copies();
@@ -1047,9 +1081,9 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
     const int wk0 = kv_tile0 + pair * 32;
     const bool active = wk0 < Tn;
     const int wk_hi = min(wk0 + 31, Tn - 1);
-    const int q_end = __builtin_amdgcn_readfirstlane(a.tok_end[min(kv_tile0 + KVT - 1, Tn - 1)]);
-    const int wq_end = active ? __builtin_amdgcn_readfirstlane(a.tok_end[wk_hi]) : 0;
-    const bool wave_split = active && __builtin_amdgcn_readfirstlane(a.tok_start[wk_hi]) > wk0;
+    const int q_end = uniform_load(a.tok_end + min(kv_tile0 + KVT - 1, Tn - 1));
+    const int wq_end = active ? uniform_load(a.tok_end + wk_hi) : 0;
+    const bool wave_split = active && uniform_load(a.tok_start + wk_hi) > wk0;
     const int kvi = wk0 + n;
     // query blocks of this chunk that see a key of this tile, counted from t0
     const int qb_lo = max(tile * (KVT / 32), chunk * sl.chunk_blocks);

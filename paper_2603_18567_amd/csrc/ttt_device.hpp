@@ -473,6 +473,12 @@ template <> TTT_DEV void gstore_frag<__bf16>(__bf16* p, const float (&v)[8]) {
     *reinterpret_cast<bf16x8*>(p) = r;
 }
 
+// an entry of a table that an earlier launch wrote, at a wave-uniform place: through the scalar cache, so that it neither
+// waits for vector memory requests in flight nor makes them wait
+TTT_DEV int uniform_load(const int* p) {
+    return *reinterpret_cast<const __attribute__((address_space(4))) int*>(reinterpret_cast<uintptr_t>(p));
+}
+
 // bounds of token i's document, by binary search in cu_seqlens
 TTT_DEV void write_doc_bounds(const int* __restrict__ cu, int n_docs, int i, int* __restrict__ tok_start, int* __restrict__ tok_end) {
     int lo = 0, hi = n_docs;   // find the largest r with cu[r] <= i (then cu[r+1] > i)
