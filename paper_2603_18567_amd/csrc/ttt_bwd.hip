@@ -1051,7 +1051,9 @@ template <typename T, int D> struct DkvP8 {
     static constexpr int kVecSlot = 3 * 32 * 4;               // LSE*log2e, D, first token of the document
     static constexpr int kVecStage = 2 * kVecSlot;
     static constexpr int kLds = kVecBase + kStages * kVecStage;
-    static constexpr int kChunk = kKeys * 32;                 // 16 columns of all keys, operand-major
+    // K and V rows, operand-major: [32 columns][16 keys][16-byte piece of the columns][key].  Where the row fragment of
+    // chunk t (16 columns) starts, from a lane's place on:
+    static constexpr int chunk_at(int t) { return (t >> 1) * kKeys * 64 + (t & 1) * 512; }
 };
 
 template <typename T, int D>
@@ -1082,13 +1084,34 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
     const bool active = wk0 < Tn;
     const int wk_hi = min(wk0 + 31, Tn - 1);
     const int q_end = uniform_load(a.tok_end + min(kv_tile0 + KVT - 1, Tn - 1));
-    const int wq_end = active ? uniform_load(a.tok_end + wk_hi) : 0;
-    const bool wave_split = active && uniform_load(a.tok_start + wk_hi) > wk0;
+    const int wk_end = uniform_load(a.tok_end + wk_hi), wk_start = uniform_load(a.tok_start + wk_hi);   // of the last key's document
     const int kvi = wk0 + n;
+    // K_0, V_0 rows of the tile -> LDS, while the document bounds are on their way.  The layout gives a lane one address
+    // register for all its row fragments of K and V, consecutive lanes consecutive 16-byte pieces, and a copy
+    // instruction 64 bytes of each of 16 rows (after the bounds, with 32 bytes of 32 rows, the requests end 2.1 us after the
+    // workgroup's start, 1.4 so; 128 tokens, 32/8 heads, a pass of seven steps one by one 208 -> 204 us).
+    {
+        const int row = min(kv_tile0 + wave * 16 + (lane & 15), Tn - 1);
+        const int64_t off = (int64_t)row * geo.kv_st + (int64_t)g * geo.kv_sh + (lane >> 4) * 8;
+        const T* K0 = static_cast<const T*>(a.k[0]) + off;
+        const T* V0 = static_cast<const T*>(a.v[0]) + off;
+        const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + wave * 1024);
+#pragma unroll
+        for (int t = 0; t < DC; t += 2) {
+            async_copy16(K0 + t * 16, dst + C::kKBase + C::chunk_at(t));
+            async_copy16(V0 + t * 16, dst + C::kVBase + C::chunk_at(t));
+        }
+    }
+
+    const int wq_end = active ? wk_end : 0;
+    const bool wave_split = active && wk_start > wk0;
     // query blocks of this chunk that see a key of this tile, counted from t0
     const int qb_lo = max(tile * (KVT / 32), chunk * sl.chunk_blocks);
     const int nqb = min((q_end - 1 - t0) / 32, (chunk + 1) * sl.chunk_blocks - 1) - qb_lo + 1;
-    if (nqb <= 0) return;
+    if (nqb <= 0) {
+        wait_async_copies();   // nothing may land in LDS that is the next workgroup's
+        return;
+    }
     const int wq_lim = min(wq_end, t0 + (qb_lo + nqb) * 32);   // blocks from here on are not this unit's
     const int n_split = sl.n_split;
     const int n_jh = sl.n_steps * geo.G;
@@ -1097,27 +1120,10 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
     const int n_steps2 = n_c * nqb2;
     const float c = geo.scale_log2;
 
-    // K_0, V_0 rows of the tile -> LDS
-    {
-        const T* K0 = static_cast<const T*>(a.k[0]) + (int64_t)g * geo.kv_sh;
-        const T* V0 = static_cast<const T*>(a.v[0]) + (int64_t)g * geo.kv_sh;
-        // operand-major layout [chunk of 16 columns][32-key pair][column half][key]: a lane's row
-        // fragment of chunk t is at (its own 16 bytes) + t * kChunk, so one address register serves
-        // all chunks of K and V, and consecutive lanes read consecutive 16-byte pieces
-        for (int u = wave; u < DC * 4; u += 8) {
-            const int t = u >> 2, rg = u & 3;
-            const int row = min(kv_tile0 + rg * 32 + n, Tn - 1);
-            const int64_t off = (int64_t)row * geo.kv_st + (2 * t + hh) * 8;
-            const uint32_t dst = lds0 + t * C::kChunk + rg * 1024;
-            async_copy16(K0 + off, dst + C::kKBase);
-            async_copy16(V0 + off, dst + C::kVBase);
-        }
-    }
-
     // per-lane LDS addresses: query-block fragments (this group's slot of stage 0), the pair's K rows
     uint32_t ra[DC], ta[DB][2];
-    const uint32_t ka = lds0 + C::kKBase + pair * 1024 + lane * 16;
-    static_assert((DC - 1) * C::kChunk + C::kVBase - C::kKBase < 65536, "LDS offsets are 16-bit immediates");
+    const uint32_t ka = lds0 + C::kKBase + pair * 2048 + (n >> 4) * 1024 + hh * 256 + (n & 15) * 16;
+    static_assert(C::chunk_at(DC - 1) + C::kVBase - C::kKBase < 65536, "LDS offsets are 16-bit immediates");
     {
         LaneFrags<T, D> lf;
         lf.init(lane);
@@ -1245,7 +1251,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
     constexpr int KR = DC < 6 ? DC : 6;
     frag kreg[KR];
 #pragma unroll
-    for (int t = 0; t < KR; ++t) kreg[t] = ld(ka + t * C::kChunk);
+    for (int t = 0; t < KR; ++t) kreg[t] = ld(ka + C::chunk_at(t));
 
     // One step: request the blocks of the next step into the other stage, then this wave's block from
     // stage ST (a compile-time constant, so that every LDS address is a register plus an immediate).
@@ -1266,7 +1272,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     qa[t] = ld(ra[t] + SO);
-                    kf[t] = t < KR ? kreg[t < KR ? t : 0] : ld(ka + t * C::kChunk);
+                    kf[t] = t < KR ? kreg[t < KR ? t : 0] : ld(ka + C::chunk_at(t));
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
@@ -1276,7 +1282,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
 #pragma unroll
                         for (int u = t + 2; u < t + 4; ++u) {
                             qa[u] = ld(ra[u] + SO);
-                            kf[u] = u < KR ? kreg[u < KR ? u : 0] : ld(ka + u * C::kChunk);
+                            kf[u] = u < KR ? kreg[u < KR ? u : 0] : ld(ka + C::chunk_at(u));
                         }
                     }
                     issue_fence();
@@ -1289,7 +1295,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     ga[t] = ld(ra[t] + SO + C::kBlk);
-                    vf[t] = ld(ka + t * C::kChunk + (C::kVBase - C::kKBase));
+                    vf[t] = ld(ka + C::chunk_at(t) + (C::kVBase - C::kKBase));
                 }
 #pragma unroll
                 for (int i = 0; i < 16; ++i) pacc[i] = 0.f;
@@ -1299,7 +1305,7 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
 #pragma unroll
                         for (int u = t + 2; u < t + 4; ++u) {
                             ga[u] = ld(ra[u] + SO + C::kBlk);
-                            vf[u] = ld(ka + u * C::kChunk + (C::kVBase - C::kKBase));
+                            vf[u] = ld(ka + C::chunk_at(u) + (C::kVBase - C::kKBase));
                         }
                     }
                     issue_fence();
