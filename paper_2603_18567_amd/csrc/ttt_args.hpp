@@ -79,7 +79,7 @@ struct BwdCommon {
     int pre_blocks;         // workgroups of the preprocess launch that do its main work; after them:
     int bounds_blocks;      // those that write tok_start, tok_end; and the rest clear the block-0 sums
     int64_t clear_n4;       // 16-byte pieces of each block-0 sum to clear
-    int dq_key_groups;      // (fp32, head_dim 64) key groups of a dQ tile: 1 or 2
+    int dq_key_groups;      // key groups of a dQ tile, 1 or 2 (fp32: head_dim 64 only)
     int accumulate;         // 0/1
     int carry_reset;        // accumulate mode: this call starts the sweep (carry is overwritten, not read)
     int* tok_start;         // [T] first token of each token's document

@@ -508,9 +508,12 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
 // blocks of 32, each taken through S^T, dP^T, dS^T and the dQ^T update in turn, with the LDS
 // fragments of the next matrix instructions requested ahead.  Eight waves (two per SIMD) overlap
 // one wave's vector work with the other's matrix work.
+// With two key groups (KS = 2, short launches: plan_short_bwd) a workgroup has 128 rows and its halves take the two halves of
+// every key tile and every second diagonal key, and add up in LDS: a chain half as long for a launch that lasts as long as
+// its longest tile (493 tokens, 12/2 heads, the fifth of five steps: backward 34.4 -> 26.5 us).
 // LDS: two stages of [K tile | V tile], which differ in one bit of the per-lane addresses.
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, int NW>
+template <typename T, int D, int NW, int KS>
 TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     static_assert(sizeof(T) == 2, "this dQ kernel is for 16-bit elements");
     static_assert(NW == 8, "two waves per SIMD supply the overlap; no other wave count is built");
@@ -518,8 +521,10 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
     using frag = typename E::frag;
     using TL = Tile<T, D>;
     constexpr int KT = 128;
-    constexpr int NB = KT / 32;
-    constexpr int QT = NW * 32;
+    constexpr int KW = KT / KS;       // keys of a tile that a wave works on
+    constexpr int NB = KW / 32;
+    constexpr int NWG = NW / KS;      // waves of a key group
+    constexpr int QT = NWG * 32;
     constexpr int DC = D / 16;
     constexpr int DB = D / 32;
     constexpr int NT = NW * 64;
@@ -547,7 +552,9 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
     const int q_tile0 = t0 + tile * QT;
-    const int wq0 = q_tile0 + wave * 32;
+    // key group, wave within it
+    const int kg = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / NWG), gwave = KS == 1 ? wave : wave % NWG;
+    const int wq0 = q_tile0 + gwave * 32;
     const bool active = wq0 < Tn;
 
     const T* Qj = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
@@ -582,11 +589,11 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
         LaneFrags<T, D> lf;
         lf.init(lane);
 #pragma unroll
-        for (int t = 0; t < DC; ++t) ra[t] = lds0 + lf.row[t];
+        for (int t = 0; t < DC; ++t) ra[t] = lds0 + lf.row[t] + kg * (KW * TL::kRowBytes);
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
-            ta[db][0] = lds0 + lf.tr[db][0];
-            ta[db][1] = lds0 + lf.tr[db][1];
+            ta[db][0] = lds0 + lf.tr[db][0] + kg * (KW * TL::kRowBytes);
+            ta[db][1] = lds0 + lf.tr[db][1] + kg * (KW * TL::kRowBytes);
         }
     }
     auto ld_row = [&](int which, int kb, int t) -> frag {   // which: 0 = K tile, 1 = V tile
@@ -660,8 +667,8 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
         wait_async_copies();
         __syncthreads();
         if (u < u_hi) issue(u + 1, stage ^ 1);
-        const int kv0 = t0 + u * KT;
-        if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) {
+        const int kv0 = t0 + u * KT + kg * KW;
+        if (active && kv0 <= hi_w && kv0 + KW - 1 >= lo_w) {
             frag ka[DC], va[DC];   // row-wise K / V fragments of the block being scored
             frag tfr[NE];          // K^T fragments of the block being accumulated
             frag sfr[2];           // dS^T operands of the previous block
@@ -742,7 +749,7 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
         stage ^= 1;
     }
     __syncthreads();   // everybody is done with the tile stages: they become the store patches
-    if (!active) return;
+    if (KS == 1 && !active) return;
 
     // Diagonal keys of blocks 1..j.  The workgroup's LDS is free now and every wave has 16 KB of it to
     // itself (its store patch lies inside): the K_l / V_l rows of the wave's 32 tokens are copied there
@@ -752,7 +759,7 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
     constexpr int WAVE_LDS = 2 * 32 * D * E::kBytes;
     static_assert(NW * WAVE_LDS <= 2 * STAGE_BYTES, "one region per wave");
     char* wbuf = smem + wave * WAVE_LDS;
-    if (j >= 1) {
+    if (active && j >= 1 + kg) {
         frag dk[DC], dv[DC];
         auto request = [&](int lb) {   // straight from global memory (rows past the end clamped)
             const T* krow = static_cast<const T*>(a.k[lb]) + (int64_t)g * geo.kv_sh + (int64_t)qc * geo.kv_st;
@@ -805,26 +812,50 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
             };
             LaneFrags<T, D> lf;
             lf.init(lane_here);
-            copy(1);
-            for (int lb = 1; lb <= j; ++lb) {
+            copy(1 + kg);
+            for (int lb = 1 + kg; lb <= j; lb += KS) {
                 wait_async_copies();
 #pragma unroll
                 for (int t = 0; t < DC; ++t) {
                     dk[t] = lf.rowwise(wbuf, 0, t);
                     dv[t] = lf.rowwise(wbuf + WAVE_LDS / 2, 0, t);
                 }
-                if (lb < j) {
+                if (lb + KS <= j) {
                     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the region is read out: refill it
-                    copy(lb + 1);
+                    copy(lb + KS);
                 }
                 apply();
             }
         } else {
-            for (int lb = 1; lb <= j; ++lb) {
+            for (int lb = 1 + kg; lb <= j; lb += KS) {
                 request(lb);
                 apply();
             }
         }
+    }
+
+    if constexpr (KS == 2) {
+        // the second group's rows join the first one's: 16-byte pieces of the same lane of wave gwave
+        static_assert(DB * 4 * 1024 <= WAVE_LDS, "a wave's rows fit in its region");
+        f32x4* piece = reinterpret_cast<f32x4*>(smem + gwave * WAVE_LDS) + lane;
+        __syncthreads();   // everybody is done with the diagonal keys
+        if (kg == 1) {
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4)
+                    piece[(db * 4 + i4) * 64] = f32x4{dqacc[db][4 * i4], dqacc[db][4 * i4 + 1], dqacc[db][4 * i4 + 2], dqacc[db][4 * i4 + 3]};
+        }
+        __syncthreads();
+        if (kg == 1 || !active) return;
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const f32x4 o4 = piece[(db * 4 + i4) * 64];
+#pragma unroll
+                for (int x = 0; x < 4; ++x) dqacc[db][4 * i4 + x] += o4[x];
+            }
     }
 
     // scaled rows go through a wave-private LDS patch so that global stores are whole 16-byte pieces
@@ -1450,7 +1481,7 @@ TTT_DEV void dkv_p8_unit(const BwdCommon& a, const BwdSlice& sl, char* smem, con
 // launch, or between its two parts, they keep the dK/dV units of an XCD from streaming the same rows together: one
 // step, 32/8 heads, 512 and 2048 tokens 66 and 227 us at the end, 83 and 232 elsewhere).
 // ------------------------------------------------------------------------------------------------
-template <typename T, int D, int N>
+template <typename T, int D, int N, int KS>
 __global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs<N> a) {
     extern __shared__ __align__(16) char smem[];
     const int wg = blockIdx.x;
@@ -1461,7 +1492,7 @@ __global__ __launch_bounds__(512) void ttt_bwd_main_kernel(const BwdArgs<N> a) {
     }
     const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
     if (wg < sl.q_first) dkv_p8_unit<T, D>(a, sl, smem, wg - sl.kv_first);
-    else dq_pipe_tile<T, D, 8>(a, sl, smem, wg - sl.q_first);
+    else dq_pipe_tile<T, D, 8, KS>(a, sl, smem, wg - sl.q_first);
 }
 
 template <typename T, int D, int N>
@@ -1572,21 +1603,22 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
         constexpr int LDS_KEY_GROUPS = !k16 && D == 64 ? 2 * LDS_Q : LDS;   // fp32 dQ tiles with two key groups
+        DkvPlan plans[N];
+        if constexpr (k16) a.dq_key_groups = plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
+        else a.dq_key_groups = D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
         void (*kern)(BwdArgs<N>);
-        if constexpr (k16) kern = ttt_bwd_main_kernel<T, D, N>;
-        else kern = ttt_bwd_main_f32_kernel<T, D, N>;
-        static LdsOptIn lds_opt_in;
-        if ((e = lds_opt_in.ensure((const void*)kern, LDS_KEY_GROUPS)) != hipSuccess) return e;
+        if constexpr (!k16) kern = ttt_bwd_main_f32_kernel<T, D, N>;
+        else if constexpr (N == 1) kern = a.dq_key_groups == 2 ? ttt_bwd_main_kernel<T, D, N, 2> : ttt_bwd_main_kernel<T, D, N, 1>;
+        else kern = ttt_bwd_main_kernel<T, D, N, 1>;   // (several slices: one key group)
+        static LdsOptIn lds_opt_in[2];   // one per kernel
+        if ((e = lds_opt_in[k16 ? a.dq_key_groups - 1 : 0].ensure((const void*)kern, LDS_KEY_GROUPS)) != hipSuccess) return e;
         // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
         // 32-bit byte offsets
         if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         // dK/dV: split the (step, head) list of a unit so that the grid fills the device evenly
-        a.dq_key_groups = !k16 && D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
         const int q_rows = NW * 32 / a.dq_key_groups;
         int64_t grid = 0;
-        DkvPlan plans[N];
-        if constexpr (k16) plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
         for (int i = 0; i < n_slices; ++i) {
             BwdSlice& sl = a.slices[i];
             const int n_tiles = (shapes[i].T + KVT - 1) / KVT;

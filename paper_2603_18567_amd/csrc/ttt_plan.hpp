@@ -205,13 +205,26 @@ template <typename F> void for_units_of_an_xcd(int hkv, int64_t n_units, F&& f) 
 // all units per call: 0.36, 5.2 and 590).
 //
 // other_us: what the other slices of the same launch take of an XCD's compute units, in all; it is taken to fill them evenly.
-inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double other_us = 0.) {
+struct BwdPrices {   // us
+    float step, unit, empty;        // of a dK/dV unit: per step, of its own; one that no row sees
+    float tile, diag, own;          // of a dQ tile: per 128-key tile, per diagonal key, of its own
+    float later, later_pair;        // of a workgroup of the later blocks: of its own, per (step, head) pair; 0: not counted
+    float flush;                    // of 256 units' sums: the rate of the atomics, all compute units together
+};
+struct BwdDeal {
+    DkvPlan plan;
+    double us;   // when the last compute unit ends, by the prices; < 0: no option ends before `limit`
+};
+constexpr int kDiagRegBlocks = 7, kDiagRegBlocksF32 = 3;   // later blocks whose rows and gradients fit a lane's registers
+inline int diag_passes(const CallShape& a, int per_pass) { return std::max(1, (a.step_begin + a.n_steps - 2 + per_pass) / per_pass); }
+
+inline BwdDeal deal_bwd(const CallShape& a, int n_cu, double other_us, const BwdPrices& price, int q_rows, bool short_launch,
+                        int later_rows = 1, double limit = -1.) {
     const int T = a.T, n_jh = a.n_steps * a.G;
-    const int n_tiles = (T + 127) / 128, n_tiles_q = (T + 255) / 256;
-    const float stream = head_dim == 64 ? 0.6f : 1.f;
-    const float kStepUs = 1.9f * stream, kUnitUs = 13.f, kEmptyUs = 1.f;
-    const float kTileUs = 5.f * stream, kDiagUs = 1.7f * stream, kQUs = 8.f;
-    constexpr int kMaxDealt = 12288;
+    const int n_tiles = (T + 127) / 128, n_tiles_q = (T + q_rows - 1) / q_rows;
+    const float kStepUs = price.step, kUnitUs = price.unit, kEmptyUs = price.empty;
+    const float kTileUs = price.tile, kDiagUs = price.diag, kQUs = price.own;
+    const int kMaxDealt = short_launch ? 6144 : 12288;
     const int cus = std::max(1, n_cu / 8);
     const double share = (double)a.hkv / 8.;   // heads per XCD
     // document of token i, asked for rising i
@@ -226,7 +239,7 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
     doc = 0;
     double keys = 0.;
     for (int t = 0; t < n_tiles_q; ++t) {
-        q_keys[t] = std::min(t * 256 + 255, T - 1) / 128 - (a.cu_host[doc_of(t * 256)] - a.cu_base) / 128 + 1;
+        q_keys[t] = std::min((t + 1) * q_rows - 1, T - 1) / 128 - (a.cu_host[doc_of(t * q_rows)] - a.cu_base) / 128 + 1;
         keys += q_keys[t];
     }
     // the dQ tiles of one XCD in launch order
@@ -238,14 +251,18 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
             const int u = (int)unit, js = u / a.G % a.n_steps, t = n_tiles_q - 1 - u / n_jh;
             dq.push_back(kQUs + q_keys[t] * kTileUs + (a.step_begin + js) * kDiagUs);
         });
+    const bool later = price.later > 0.f && a.step_begin + a.n_steps > 1;   // the later blocks' workgroups of one XCD
+    const int n_later = later ? (int)(((int64_t)T * a.hkv + later_rows - 1) / later_rows * diag_passes(a, kDiagRegBlocks) + 7) / 8 : 0;
+    const float later_us = price.later + price.later_pair * (float)n_jh;
     struct Option {
         int cb, ns;
+        double flush;   // the atomics of all units
         double bound;   // about when the best schedule ends: the longest unit, or the work over the compute units
         double dealt;   // units and dQ tiles of one XCD
     };
     int longest_doc = 0;
     for (int r = 0; r < a.n_docs; ++r) longest_doc = std::max(longest_doc, a.cu_host[r + 1] - a.cu_host[r]);
-    const bool few_heads = n_jh > 16 && a.hkv > 1 && a.hkv < 5 && T >= 2048 && longest_doc >= 1280;
+    const bool few_heads = !short_launch && n_jh > 16 && a.hkv > 1 && a.hkv < 5 && T >= 2048 && longest_doc >= 1280;
     std::vector<Option> options;
     for (int log2_cb = 3; log2_cb <= 7; ++log2_cb) {
         const int cb = 1 << log2_cb;
@@ -265,22 +282,32 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
             most = std::max({most, s0, s1, whole > 0 ? cb / 2 : 0});
         }
         const int64_t units = dkv_units_of(T, n_tiles, cb);
-        for (int ns : {1, 2, 3, 4, 6, 8}) {
+        for (int ns : {1, 2, 3, 4, 6, 8, 12, 16, 24}) {
+            if (ns > 8 && !short_launch) break;
             if (ns > n_jh || units * ns * a.hkv > 0x7fffffff) break;   // (more workgroups than a grid has)
             const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((double)units - used) * kEmptyUs));
             const double longest = (double)((n_jh + ns - 1) / ns) * most * kStepUs + kUnitUs;
-            options.push_back(Option{cb, ns, std::max(longest, (work + dq_work + other_us) / cus), share * (double)units * ns + n_dq});
+            const double flush = price.flush * used * ns * a.hkv / 256.;
+            options.push_back(Option{cb, ns, flush, flush + std::max(longest, (work + dq_work + other_us + n_later * later_us) / cus),
+                                     share * (double)units * ns + n_dq + n_later});
         }
     }
     std::sort(options.begin(), options.end(), [](const Option& x, const Option& y) { return x.bound < y.bound; });
     DkvPlan best{16, 1};
     if (!options.empty()) best = DkvPlan{options[0].cb, options[0].ns};
     double best_us = -1., dealt = 0.;
+    if (limit >= 0.) {   // only options that end sooner count
+        best_us = limit;
+        best = DkvPlan{0, 0};
+    }
     std::vector<float> free_at;
     std::vector<int> steps;
     for (const Option& o : options) {
         if (best_us >= 0. && o.bound >= best_us) break;
-        if ((dealt += o.dealt) > kMaxDealt) break;
+        if ((dealt += o.dealt) > kMaxDealt) {
+            if (best_us < 0.) best_us = o.bound;
+            break;
+        }
         steps.clear();
         const int n_chunks = (T + o.cb * 32 - 1) / (o.cb * 32);
         for (int ch = 0; ch < n_chunks; ++ch)
@@ -305,12 +332,18 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
             deal(n2 > 0 ? (float)((n_jh - sp + o.ns - 1) / o.ns * n2) * kStepUs + kUnitUs : kEmptyUs);
         });
         for (float us : dq) deal(us);
-        if (best_us < 0. || finish < best_us) {
-            best_us = finish;
+        for (int i = 0; i < n_later; ++i) deal(later_us);
+        if (best_us < 0. || finish + o.flush < best_us) {
+            best_us = finish + o.flush;
             best = DkvPlan{o.cb, o.ns};
         }
     }
-    return best;
+    return BwdDeal{best, best.n_split > 0 ? best_us : -1.};
+}
+
+inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double other_us = 0.) {
+    const float stream = head_dim == 64 ? 0.6f : 1.f;
+    return deal_bwd(a, n_cu, other_us, BwdPrices{1.9f * stream, 13.f, 1.f, 5.f * stream, 1.7f * stream, 8.f, 0.f, 0.f, 0.f}, 256, false).plan;
 }
 
 // Where the later blocks' dK, dV of the 16-bit backward are made: in the preprocess launch, together with D (true), or as the
@@ -319,9 +352,6 @@ inline DkvPlan plan_dkv_split(const CallShape& a, int head_dim, int n_cu, double
 // step a call: 2 to 27 % up to 2048 tokens, 0 to 2 % beyond; all steps in one call, up to 512 tokens: 3 to 40 %)
 // except for sweeps over many (step, head) pairs that also fill the device: there one unit is as long as a
 // dQ tile and leaves a tail of its own (all steps, 7 to 12 of 32/8 heads: 0 to 2.7 % slower from 1024 tokens on).
-constexpr int kDiagRegBlocks = 7, kDiagRegBlocksF32 = 3;   // later blocks whose rows and gradients fit a lane's registers
-inline int diag_passes(const CallShape& a, int per_pass) { return std::max(1, (a.step_begin + a.n_steps - 2 + per_pass) / per_pass); }
-
 inline bool diag_blocks_apart(const CallShape* calls, int n_calls, int head_dim, int n_cu) {
     int64_t all = 0;
     for (int i = 0; i < n_calls; ++i) {
@@ -349,11 +379,43 @@ inline double bwd_slice_us(const CallShape& a, int head_dim) {
                          ((double)a.T / 256. + 1.) * pairs * (8. + 1.7 * stream * (a.step_begin + 0.5 * (a.n_steps - 1))));
 }
 
-// The plans of the slices that share a launch.  They depend on the document structure, the steps, the heads and the device, and
-// are kept for the last 64 launches: a batch of more runs of documents than that would push out its own entries, and those of
-// every other call, if each slice had one (153 runs of documents of 20 to 200 tokens, 32/8 heads, up to
+// Short launches of one slice: prices of their own, and dQ tiles of 256 rows or of 128 whose keys two halves of the workgroup share
+// (two key groups: half as long a chain of key tiles and diagonal keys).  A launch that leaves compute units idle, or ends with
+// a few long tiles, gains from them; the work of all is less without.
+// The prices are fitted to all splits (chunk size, list split up to 24, key groups) of 2097 launches of up to 1600 dQ tiles: 64 ...
+// 4096 tokens in one document or many, seven head geometries, one step a call (the first to the ninth) or two to eight at once.
+// Whole backward over the best split of each, in the mean, head_dim 128 / 64: 1.023 / 1.027; with the prices above and one key group 1.128 / 1.105,
+// with the best split of one key group 1.047 / 1.038.  Four in a hundred are more than 3 % slower than with the prices above (1.24 at
+// most).  1320 tokens, 8/1 heads of 64, the last of eight steps, forward and backward 63.9 -> 50.9 us; 493 tokens, 12/2 heads, five steps one
+// by one 200 -> 179.  Launches of several slices keep the prices above (1154 tokens in eight slices: 3 % slower with these).
+constexpr int kShortLaunchTiles = 1600, kShortLaunchTokens = 4096;
+inline BwdPrices short_launch_prices(int head_dim, int dq_groups) {
+    if (head_dim == 64)
+        return dq_groups == 2 ? BwdPrices{1.19f, 8.7f, 1.05f, 1.15f, 0.30f, 9.6f, 7.2f, 0.08f, 0.3f} : BwdPrices{1.19f, 8.7f, 1.05f, 2.65f, 0.85f, 5.1f, 7.2f, 0.08f, 0.3f};
+    return dq_groups == 2 ? BwdPrices{1.59f, 11.5f, 2.5f, 2.17f, 0.81f, 8.7f, 8.4f, 0.33f, 3.1f} : BwdPrices{1.59f, 11.5f, 2.5f, 4.16f, 1.64f, 5.5f, 8.4f, 0.33f, 3.1f};
+}
+struct ShortPlan {
+    int dq_groups;   // 0: not a short launch
+    DkvPlan kv;
+};
+inline ShortPlan plan_short_bwd(const CallShape& a, int head_dim, int n_cu) {
+    ShortPlan best{0, {}};
+    if (a.T > kShortLaunchTokens || (int64_t)((a.T + 255) / 256) * a.n_steps * a.G * a.hkv > kShortLaunchTiles) return best;
+    double best_us = -1.;
+    for (int groups = 1; groups <= 2; ++groups) {
+        const BwdDeal d = deal_bwd(a, n_cu, 0., short_launch_prices(head_dim, groups), 256 / groups, true, 512 / (head_dim / 8), best_us);
+        if (d.us < 0.) continue;
+        best_us = d.us;
+        best = ShortPlan{groups, d.plan};
+    }
+    return best;
+}
+
+// The plans of the slices that share a launch; returns the key groups of its dQ tiles.  They depend on the document structure, the
+// steps, the heads and the device, and are kept for the last 64 launches: a batch of more runs of documents than that would push out its own
+// entries, and those of every other call, if each slice had one (153 runs of documents of 20 to 200 tokens, 32/8 heads, up to
 // seven steps: 0.5 ms of planning in each call with the same batch, 0.07 so, most of it the caller's).
-inline void plan_dkv_launch(const CallShape* calls, int n_calls, int head_dim, int n_cu, DkvPlan* plans) {
+inline int plan_dkv_launch(const CallShape* calls, int n_calls, int head_dim, int n_cu, DkvPlan* plans) {
     struct Key {
         int64_t tokens;
         int n_calls, n_docs, step_begin, n_steps, G, hkv, head_dim, n_cu;   // (documents and steps of all slices together)
@@ -374,23 +436,35 @@ inline void plan_dkv_launch(const CallShape* calls, int n_calls, int head_dim, i
         for (int r = 0; r <= a.n_docs; ++r) add(a.cu_host[r] - a.cu_base);
     }
     static std::mutex mu;
-    static std::vector<std::pair<Key, std::vector<DkvPlan>>> cache;
+    struct Made {
+        Key key;
+        int dq_groups;
+        std::vector<DkvPlan> kv;
+    };
+    static std::vector<Made> cache;
     {
         std::lock_guard<std::mutex> lock(mu);
-        for (const auto& e : cache)
-            if (e.first == key) {
-                std::copy(e.second.begin(), e.second.end(), plans);
-                return;
+        for (const Made& e : cache)
+            if (e.key == key) {
+                std::copy(e.kv.begin(), e.kv.end(), plans);
+                return e.dq_groups;
             }
     }
-    std::vector<double> us(n_calls, 0.);
-    double all_us = 0.;
-    for (int i = 0; n_calls > 1 && i < n_calls; ++i) all_us += us[i] = bwd_slice_us(calls[i], head_dim);
-    for (int i = 0; i < n_calls; ++i) plans[i] = plan_dkv_split(calls[i], head_dim, n_cu, all_us - us[i]);
-    std::vector<DkvPlan> made(plans, plans + n_calls);
+    const ShortPlan one = n_calls == 1 ? plan_short_bwd(calls[0], head_dim, n_cu) : ShortPlan{0, {}};
+    const int dq_groups = std::max(1, one.dq_groups);
+    if (one.dq_groups > 0) {
+        plans[0] = one.kv;
+    } else {
+        std::vector<double> us(n_calls, 0.);
+        double all_us = 0.;
+        for (int i = 0; n_calls > 1 && i < n_calls; ++i) all_us += us[i] = bwd_slice_us(calls[i], head_dim);
+        for (int i = 0; i < n_calls; ++i) plans[i] = plan_dkv_split(calls[i], head_dim, n_cu, all_us - us[i]);
+    }
+    Made made{key, dq_groups, std::vector<DkvPlan>(plans, plans + n_calls)};
     std::lock_guard<std::mutex> lock(mu);
     if (cache.size() >= 64) cache.erase(cache.begin());
-    cache.emplace_back(key, std::move(made));
+    cache.push_back(std::move(made));
+    return dq_groups;
 }
 
 // Whether a slice has a backward launch of its own.  Slices that share a launch fill each other's tails and save launches, but

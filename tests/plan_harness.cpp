@@ -37,6 +37,16 @@ void plan_backward_runs(int n_runs, const int* first, const int* n_docs, const i
     }
 }
 
+// the work split and the key groups of the dQ tiles of a launch of one run of documents
+void plan_backward_launch(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int head_dim, int n_cu,
+                          int* chunk_blocks, int* n_split, int* dq_groups) {
+    const ttt::CallShape call{T, step_begin, n_steps, G, hkv, n_docs, cu, cu[0]};
+    ttt::DkvPlan p;
+    *dq_groups = ttt::plan_dkv_launch(&call, 1, head_dim, n_cu, &p);
+    *chunk_blocks = p.chunk_blocks;
+    *n_split = p.n_split;
+}
+
 int plan_later_blocks(int T, int step_begin, int n_steps, int G, int hkv, int head_dim, int n_cu) {
     return ttt::diag_blocks_apart(ttt::CallShape{T, step_begin, n_steps, G, hkv, 0, nullptr, 0}, head_dim, n_cu);
 }

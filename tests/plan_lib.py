@@ -44,6 +44,13 @@ def backward_split(cu, hq, hkv, d, step_begin, n_steps, n_cu=256):
                  cu.ctypes.data_as(ctypes.c_void_p), d, n_cu)
 
 
+def backward_launch(docs, hq, hkv, d, step_begin, n_steps, n_cu=256):
+    """(32-row query blocks per chunk, parts of the (step, head) list, key groups of a dQ tile) of a launch of one run of documents"""
+    cu = _cu(docs)
+    return _call(_lib().plan_backward_launch, int(cu[-1]), step_begin, n_steps, hq // hkv, hkv, len(docs),
+                 cu.ctypes.data_as(ctypes.c_void_p), d, n_cu, n_out=3)
+
+
 def backward_splits_of_runs(cu, first, n_docs, n_steps, hq, hkv, d, n_cu=256):
     """[(32-row query blocks per chunk, parts of the list)] of runs of documents, 16 to a launch"""
     ints = [np.ascontiguousarray(x, dtype=np.int32) for x in (first, n_docs, n_steps, cu)]
