@@ -1518,6 +1518,290 @@ __global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs<N> 
 }
 
 // ------------------------------------------------------------------------------------------------
+// fp32: operands straight from memory
+// ------------------------------------------------------------------------------------------------
+// As in the forward, fp32 matrix instructions are slow enough for operands that come from memory, and without tiles to share
+// a workgroup's four waves need no barrier until their sums meet in LDS.  A dQ tile is 32 rows of one (step, head)
+// whose key blocks (and diagonal keys) the waves take in turn; a dK/dV unit 32 keys of a kv head whose (step, head, query
+// block) items are dealt to the waves of all its splits.  A wave has a part of LDS to itself, into which the next block's rows are
+// copied once the operands of this one are in registers: they arrive under its last matrix instructions, half of all (read as
+// fragments from global memory instead, an item of head_dim 128 took 12.4 us, so 8.5, 7.0 of them matrix instructions).  Whole backward, tiles
+// shared in LDS -> so: 247 tokens, 8/1 heads of 128, one step 67 -> 38 us; 444 tokens, 8/2 of 128, the last of seven 129 -> 63; 128
+// tokens, 4/4 heads of 64, three steps 24.2 -> 18.7.  Errors against 64 bits are smaller too (dQ 4.6e-7, 4.8e-7 before; dK, dV as before or less).
+template <int D> struct BwdF32 {
+    static constexpr int kRows = 32, kWaves = 4;
+    static constexpr int kVec = 3 * 32 * 4;                                   // LSE*log2e, D, first token of the document of 32 rows
+    static constexpr int kPieces = 2 * (D / 8);                               // 16-byte pieces of a lane's dK and dV
+    static constexpr int kLds = kWaves * (kPieces * 1024 + kVec);
+};
+
+template <int D>
+TTT_DEV void dq_f32_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
+    constexpr int NW = BwdF32<D>::kWaves;
+    constexpr int DC = D / 16, DB = D / 32;
+    const Geometry& geo = a.geo;
+    int g, rest;
+    if (!decode_block(a.map, sl.q_rest, wg, g, rest)) return;
+    const int h = g * geo.G + rest % geo.G;
+    rest /= geo.G;
+    const int js = rest % sl.n_steps, j = geo.step_begin + js;
+    const int t0 = sl.t0, Tn = sl.t1;
+    const int tile = (Tn - t0 + 31) / 32 - 1 - rest / sl.n_steps;   // long-prefix tiles first
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hh = lane >> 5;
+    const int q0 = t0 + tile * 32, hi = min(q0 + 31, Tn - 1);
+    const int qi = q0 + n, qc = min(qi, Tn - 1);
+    const int lo = uniform_load(a.tok_start + q0), st_hi = uniform_load(a.tok_start + hi);
+
+    const int64_t qoff = (int64_t)h * geo.q_sh + (int64_t)qc * geo.q_st + hh * 8;
+    const float *qrow = static_cast<const float*>(a.q[j]) + qoff, *grow = static_cast<const float*>(a.d_o[j]) + qoff;
+    f32x8 qf[DC], gof[DC];
+#pragma unroll
+    for (int t = 0; t < DC; ++t) {
+        qf[t] = gload_frag<float>(qrow + t * 16);
+        gof[t] = gload_frag<float>(grow + t * 16);
+    }
+    const int st = a.tok_start[qc];
+    const float lse2 = a.lse[j][(int64_t)h * geo.T + qc] * kLog2e;
+    const float dl = a.delta[((int64_t)js * geo.hq + h) * geo.T + qc];
+    const float c = geo.scale_log2;
+    f32x16 dqacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dqacc[db][i] = 0.f;
+
+    const float* K0 = static_cast<const float*>(a.k[0]) + (int64_t)g * geo.kv_sh;
+    const float* V0 = static_cast<const float*>(a.v[0]) + (int64_t)g * geo.kv_sh;
+    char* const tk = smem + wave * (BwdF32<D>::kPieces * 1024);
+    char* const tv = tk + 32 * D * 4;
+    const uint32_t lds = lds_addr(smem) + wave * (BwdF32<D>::kPieces * 1024);
+    auto request = [&](int kv0) {   // K and V rows of a block
+        const int last = min(31, Tn - 1 - kv0);
+        wave_rows_async<D>(lds, K0 + (int64_t)kv0 * geo.kv_st, geo.kv_st, last, lane);
+        wave_rows_async<D>(lds + 32 * D * 4, V0 + (int64_t)kv0 * geo.kv_st, geo.kv_st, last, lane);
+    };
+    const int kv_first = t0 + ((lo - t0) / 32 + wave) * 32;
+    if (kv_first <= hi) request(kv_first);
+    for (int kv0 = kv_first; kv0 <= hi; kv0 += NW * 32) {
+        wait_async_copies();
+        // S^T = K Q^T and dP^T = V dO^T
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < DC; ++t) {
+            s = mma(frag_rowwise<float, D>(tk, n, t * 16 + hh * 8), qf[t], s);
+            dp = mma(frag_rowwise<float, D>(tv, n, t * 16 + hh * 8), gof[t], dp);
+        }
+        f32x8 kt[2][DB];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) kt[x][db] = frag_transposed<float, D>(tk, x * 16, db * 32, lane);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the block is read out: the next one arrives under what follows
+        if (kv0 + NW * 32 <= hi) request(kv0 + NW * 32);
+        const bool need_mask = kv0 + 31 > q0 || kv0 < st_hi;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            float p = fast_exp2(fmaf(s[i], c, -lse2));
+            if (need_mask) {
+                const int kv = kv0 + acc_row(i, hh);
+                p = kv <= qi && kv >= st ? p : 0.f;
+            }
+            dp[i] = p * (dp[i] - dl);   // dS^T
+        }
+        // dQ^T[d, q] += K^T dS^T
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const f32x8 sf = acc_chunk<float>(dp, x);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) dqacc[db] = mma(kt[x][db], sf, dqacc[db]);
+        }
+    }
+    for (int lb = 1 + wave; lb <= j; lb += NW) {
+        const int64_t at = (int64_t)g * geo.kv_sh + (int64_t)qc * geo.kv_st;
+        const float *krow = static_cast<const float*>(a.k[lb]) + at, *vrow = static_cast<const float*>(a.v[lb]) + at;
+        float s = 0.f, dp = 0.f;
+#pragma unroll
+        for (int t = 0; t < DC; ++t) {
+            s = dot8(qf[t], gload_frag<float>(krow + t * 16 + hh * 8), s);
+            dp = dot8(gof[t], gload_frag<float>(vrow + t * 16 + hh * 8), dp);
+        }
+        s = half_sum(s);
+        dp = half_sum(dp);
+        const float p = fast_exp2(fmaf(s, c, -lse2));
+        const float ds = p * (dp - dl);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const f32x4 kk = gload_vec4<float>(krow + db * 32 + i4 * 8 + hh * 4);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) dqacc[db][i4 * 4 + x] = fmaf(ds, kk[x], dqacc[db][i4 * 4 + x]);
+            }
+    }
+
+    // the waves meet: piece p of a lane's row is added up by wave p % 4
+    f32x4* const mine = reinterpret_cast<f32x4*>(tk) + lane;   // each in its own part of LDS: the others may still read theirs
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+            mine[(db * 4 + i4) * 64] = f32x4{dqacc[db][4 * i4], dqacc[db][4 * i4 + 1], dqacc[db][4 * i4 + 2], dqacc[db][4 * i4 + 3]};
+    __syncthreads();
+    if (qi >= Tn) return;
+    const f32x4* const all = reinterpret_cast<const f32x4*>(smem) + lane;
+    float* row = static_cast<float*>(a.dq[j]) + (int64_t)h * geo.q_sh + (int64_t)qi * geo.q_st + hh * 4;
+    for (int p = wave; p < DB * 4; p += NW) {
+        f32x4 sum = all[p * 64];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += all[(w * BwdF32<D>::kPieces + p) * 64];
+        *reinterpret_cast<f32x4*>(row + p * 8) = sum * geo.scale;
+    }
+}
+
+template <int D>
+TTT_DEV void dkv_f32_unit(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
+    using C = BwdF32<D>;
+    constexpr int NW = C::kWaves;
+    constexpr int DC = D / 16, DB = D / 32;
+    const Geometry& geo = a.geo;
+    int g, rest;
+    if (!decode_block(a.map, sl.kv_rest, wg, g, rest)) return;
+    const int sp = rest % sl.n_split, tile = rest / sl.n_split;   // low tiles of a document have the longest query range: first
+    const int t0 = sl.t0, Tn = sl.t1;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hh = lane >> 5;
+    const int wk0 = t0 + tile * 32, kvi = wk0 + n;
+    const int nqb = (uniform_load(a.tok_end + min(wk0 + 31, Tn - 1)) - 1 - t0) / 32 - tile + 1;   // query blocks that see a key
+    const int n_items = sl.n_steps * geo.G * nqb;
+
+    const int64_t kvoff = (int64_t)g * geo.kv_sh + (int64_t)min(kvi, Tn - 1) * geo.kv_st + hh * 8;
+    f32x8 kf[DC], vf[DC];
+#pragma unroll
+    for (int t = 0; t < DC; ++t) {
+        kf[t] = gload_frag<float>(static_cast<const float*>(a.k[0]) + kvoff + t * 16);
+        vf[t] = gload_frag<float>(static_cast<const float*>(a.v[0]) + kvoff + t * 16);
+    }
+    f32x16 dkacc[DB], dvacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dkacc[db][i] = dvacc[db][i] = 0.f;
+    const float c = geo.scale_log2;
+    float* const vec = reinterpret_cast<float*>(smem + NW * C::kPieces * 1024 + wave * C::kVec);
+
+    char* const tq = smem + wave * (C::kPieces * 1024);
+    char* const tg = tq + 32 * D * 4;
+    const uint32_t lds = lds_addr(smem) + wave * (C::kPieces * 1024);
+    float lse2_n = 0.f, dl_n = 0.f;   // of the item requested last, one row per lane
+    int st_n = 0;
+    auto request = [&](int it) {      // Q and dO rows of an item
+        const int jh = it / nqb, qb = tile + it % nqb;
+        const int js = jh / geo.G, j = geo.step_begin + js, h = g * geo.G + jh % geo.G;
+        const int q0 = t0 + qb * 32, last = min(31, Tn - 1 - q0), qq = q0 + min(n, last);
+        const int64_t first = (int64_t)h * geo.q_sh + (int64_t)q0 * geo.q_st;
+        const float l = a.lse[j][(int64_t)h * geo.T + qq];
+        dl_n = a.delta[((int64_t)js * geo.hq + h) * geo.T + qq];
+        st_n = a.tok_start[qq];
+        wave_rows_async<D>(lds, static_cast<const float*>(a.q[j]) + first, geo.q_st, last, lane);
+        wave_rows_async<D>(lds + 32 * D * 4, static_cast<const float*>(a.d_o[j]) + first, geo.q_st, last, lane);
+        lse2_n = n <= last ? l * kLog2e : INFINITY;   // rows past the end: p = 0
+    };
+    const int stride = sl.n_split * NW;
+    int it = sp * NW + wave;
+    if (it < n_items) request(it);
+    for (; it < n_items; it += stride) {
+        const int q0 = t0 + (tile + it % nqb) * 32;
+        wait_async_copies();
+        __builtin_amdgcn_wave_barrier();
+        vec[n] = lse2_n;   // to be read by accumulator row
+        vec[32 + n] = dl_n;
+        vec[64 + n] = __int_as_float(st_n);
+        __builtin_amdgcn_wave_barrier();
+        // S[q, kv] = Q K^T and dP[q, kv] = dO V^T: lane = key
+        f32x16 s, dp;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = dp[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < DC; ++t) {
+            s = mma(frag_rowwise<float, D>(tq, n, t * 16 + hh * 8), kf[t], s);
+            dp = mma(frag_rowwise<float, D>(tg, n, t * 16 + hh * 8), vf[t], dp);
+        }
+        f32x8 gt[2][DB], qt[2][DB];
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                gt[x][db] = frag_transposed<float, D>(tg, x * 16, db * 32, lane);
+                qt[x][db] = frag_transposed<float, D>(tq, x * 16, db * 32, lane);
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // the item is read out: the next one arrives under what follows
+        if (it + stride < n_items) request(it + stride);
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            const int r = 8 * i4 + 4 * hh;
+            const f32x4 l4 = *reinterpret_cast<const f32x4*>(vec + r), d4 = *reinterpret_cast<const f32x4*>(vec + 32 + r);
+            const f32x4 s4 = *reinterpret_cast<const f32x4*>(vec + 64 + r);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int i = i4 * 4 + x;
+                const float p = fast_exp2(fmaf(s[i], c, -l4[x]));
+                s[i] = kvi <= q0 + r + x && kvi >= __float_as_int(s4[x]) ? p : 0.f;   // P
+                dp[i] = s[i] * (dp[i] - d4[x]);                                       // dS
+            }
+        }
+        // dV[kv, d] += P^T dO;  dK[kv, d] += dS^T Q
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const f32x8 pf = acc_chunk<float>(s, x), sf = acc_chunk<float>(dp, x);
+#pragma unroll
+            for (int db = 0; db < DB; ++db) {
+                dvacc[db] = mma(pf, gt[x][db], dvacc[db]);
+                dkacc[db] = mma(sf, qt[x][db], dkacc[db]);
+            }
+        }
+    }
+
+    // the waves meet: piece p of a lane's sums (dK's first) is added up by wave p % 4 and joins the block-0 sums
+    f32x4* const mine = reinterpret_cast<f32x4*>(tq) + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+            mine[(db * 4 + i4) * 64] = f32x4{dkacc[db][4 * i4], dkacc[db][4 * i4 + 1], dkacc[db][4 * i4 + 2], dkacc[db][4 * i4 + 3]};
+            mine[(DB * 4 + db * 4 + i4) * 64] = f32x4{dvacc[db][4 * i4], dvacc[db][4 * i4 + 1], dvacc[db][4 * i4 + 2], dvacc[db][4 * i4 + 3]};
+        }
+    __syncthreads();
+    const f32x4* const all = reinterpret_cast<const f32x4*>(smem) + lane;
+    for (int p = wave; p < C::kPieces; p += NW) {
+        f32x4 sum = all[p * 64];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += all[(w * C::kPieces + p) * 64];
+        float* const acc = p < DB * 4 ? a.dk0_acc : a.dv0_acc;
+        const int db = p % (DB * 4) / 4, row0 = wk0 + 8 * (p % 4) + 4 * hh;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (row0 + e < Tn) atomicAdd(acc + ((int64_t)(row0 + e) * geo.hkv + g) * D + db * 32 + n, sum[e]);
+    }
+}
+
+template <int D, int N>
+__global__ __launch_bounds__(256) void ttt_bwd_f32_kernel(const BwdArgs<N> a) {
+    extern __shared__ __align__(16) char smem[];
+    const int wg = blockIdx.x;
+    if (wg >= a.grid_stream) {
+        const BwdSlice& sl = slice_of(a, &BwdSlice::diag_first, wg);
+        diag_unit<float, D, 256, false>(a, sl, wg - sl.diag_first);
+        return;
+    }
+    const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
+    if (wg < sl.q_first) dkv_f32_unit<D>(a, sl, smem, wg - sl.kv_first);
+    else dq_f32_tile<D>(a, sl, smem, wg - sl.q_first);
+}
+
+// ------------------------------------------------------------------------------------------------
 // small helper: the block-0 sums in the output dtype
 // ------------------------------------------------------------------------------------------------
 template <typename T, int D, int N>
@@ -1597,37 +1881,46 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
 
     // 2. dQ and block 0's dK, dV in one launch
     {
+        // fp32: operands straight from memory (rows of a block are told apart by 32-bit offsets), or tiles in LDS
+        const bool direct = !k16 && std::max(geo.q_st, geo.kv_st) < (int64_t)1 << 25 && bwd_f32_direct(shapes, n_slices, D);
         constexpr int NW = k16 ? 8 : 4;
         constexpr int KVT = 128;
         constexpr int LDS_Q = k16 ? 2 * 2 * 128 * D * (int)sizeof(T) : 4 * 64 * D * (int)sizeof(T);
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
+        constexpr int LDS_DIRECT = BwdF32<D>::kLds;
         constexpr int LDS_KEY_GROUPS = !k16 && D == 64 ? 2 * LDS_Q : LDS;   // fp32 dQ tiles with two key groups
         DkvPlan plans[N];
         if constexpr (k16) a.dq_key_groups = plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
-        else a.dq_key_groups = D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
+        else a.dq_key_groups = !direct && D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
         void (*kern)(BwdArgs<N>);
-        if constexpr (!k16) kern = ttt_bwd_main_f32_kernel<T, D, N>;
+        if constexpr (!k16) kern = direct ? ttt_bwd_f32_kernel<D, N> : ttt_bwd_main_f32_kernel<T, D, N>;
         else if constexpr (N == 1) kern = a.dq_key_groups == 2 ? ttt_bwd_main_kernel<T, D, N, 2> : ttt_bwd_main_kernel<T, D, N, 1>;
         else kern = ttt_bwd_main_kernel<T, D, N, 1>;   // (several slices: one key group)
+        const int lds_most = direct ? LDS_DIRECT : LDS_KEY_GROUPS;
         static LdsOptIn lds_opt_in[2];   // one per kernel
-        if ((e = lds_opt_in[k16 ? a.dq_key_groups - 1 : 0].ensure((const void*)kern, LDS_KEY_GROUPS)) != hipSuccess) return e;
+        if ((e = lds_opt_in[k16 ? a.dq_key_groups - 1 : direct ? 1 : 0].ensure((const void*)kern, lds_most)) != hipSuccess) return e;
         // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
         // 32-bit byte offsets
         if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         // dK/dV: split the (step, head) list of a unit so that the grid fills the device evenly
-        const int q_rows = NW * 32 / a.dq_key_groups;
+        const int q_rows = direct ? 32 : NW * 32 / a.dq_key_groups, kv_rows = direct ? 32 : KVT;
         int64_t grid = 0;
         for (int i = 0; i < n_slices; ++i) {
             BwdSlice& sl = a.slices[i];
-            const int n_tiles = (shapes[i].T + KVT - 1) / KVT;
+            const int n_tiles = (shapes[i].T + kv_rows - 1) / kv_rows;
             int64_t n_units = n_tiles;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
             sl.q_split = 1;
             if constexpr (k16) {
                 sl.chunk_blocks = plans[i].chunk_blocks;
                 sl.n_split = plans[i].n_split;
                 n_units = dkv_units_of(shapes[i].T, n_tiles, sl.chunk_blocks);
+            } else if (direct) {
+                double other = 0.;
+                for (int o = 0; o < n_slices; ++o)
+                    if (o != i) other += f32_bwd_dq_work(shapes[o], D, count_keys(shapes[o], 32, 32, 4));
+                sl.n_split = plan_dkv_f32_direct(shapes[i], D, n_cu, other);
             } else {
                 const DkvPlanF32 plan = plan_dkv_split_f32(shapes[i], n_cu);
                 sl.n_split = plan.n_split;
@@ -1656,8 +1949,8 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
             }
         }
         {
-            ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : "ttt_bwd_main_f32_kernel", stream);
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), a.dq_key_groups == 2 ? LDS_KEY_GROUPS : LDS, stream, a);
+            ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : direct ? "ttt_bwd_f32_kernel" : "ttt_bwd_main_f32_kernel", stream);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), direct ? LDS_DIRECT : a.dq_key_groups == 2 ? LDS_KEY_GROUPS : LDS, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

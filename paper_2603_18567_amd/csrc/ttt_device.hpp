@@ -460,6 +460,32 @@ template <> TTT_DEV void gstore_vec4<__bf16>(__bf16* p, float a, float b, float 
     *reinterpret_cast<bf16x4*>(p) = bf16x4{(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
 }
 
+// The transposed fragment (frag_transposed) of a 32-row block straight from memory, fp32: chunk c of 16 rows, 32-column block
+// db.  `base` is the block's first row, wave-uniform; rows past number `last` repeat it.  4 * stride must stay below 2^30.
+TTT_DEV f32x8 gload_cols(const float* base, int64_t stride, int last, int c, int db, int n, int hh) {
+    f32x8 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int r = 16 * c + 8 * (e / 4) + e % 4, r0 = min(r, last), r1 = min(r + 4, last);   // row of the lower and of the upper lane half
+        const char* row = reinterpret_cast<const char*>(base + r0 * stride);
+        const uint32_t off = n * 4 + (hh ? (uint32_t)((r1 - r0) * stride) * 4u : 0u);
+        v[e] = *reinterpret_cast<const float*>(row + off + db * 128);
+    }
+    return v;
+}
+
+// Rows 0 ... 31 from `base` on (wave-uniform; rows past number `last` repeat it) to a tile of this wave's own, requested by the
+// wave alone.  32 * stride must stay below 2^30 elements.
+template <int D> TTT_DEV void wave_rows_async(uint32_t tile_lds, const float* base, int64_t stride, int last, int lane) {
+    using TL = Tile<float, D>;
+#pragma unroll
+    for (int it = 0; it < 32 * TL::kPieces / 64; ++it) {
+        const int p = it * 64 + lane, r = p / TL::kPieces, pos = p % TL::kPieces;
+        const uint32_t off = ((uint32_t)min(r, last) * (uint32_t)stride + (pos ^ TL::swz(r)) * TL::kElemsPerPiece) * 4u;
+        async_copy16(base, off, tile_lds + it * 1024);
+    }
+}
+
 // 8 consecutive elements to global memory, 16 bytes a store
 template <typename T> TTT_DEV void gstore_frag(T* p, const float (&v)[8]);
 template <> TTT_DEV void gstore_frag<float>(float* p, const float (&v)[8]) {

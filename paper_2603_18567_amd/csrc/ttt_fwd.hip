@@ -471,6 +471,220 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// fp32: operands straight from memory
+// ------------------------------------------------------------------------------------------------
+// One workgroup = 32 tokens x one query head x one step; its eight waves take every eighth block of 32 keys (and every
+// eighth diagonal key) and meet once, in LDS.  fp32 matrix instructions are a sixteenth as fast as 16-bit ones, so a block's
+// operands (32 KB at head_dim 128) need no LDS to keep up with them, and without tiles to share the waves need no
+// barrier before the end: what bounds a short call is one wave's chain of matrix instructions, and this split makes it
+// as short as the keys allow (us, tiles in LDS -> so: 128 tokens, 4/4 heads of 64, three steps 13.7 -> 10.2; 247 tokens, 8/1 heads
+// of 128, one step 56 -> 21; 444 tokens, 8/2 of 128 113 -> 37).  fwd_f32_direct has the rule.
+template <int D, int N>
+__global__ __launch_bounds__(512) void ttt_fwd_f32_kernel(const FwdArgs<N> a) {
+    constexpr int NW = 8;
+    constexpr int DC = D / 16, DB = D / 32;
+    constexpr float kLazy = 8.f;                     // as in ttt_fwd_kernel
+    constexpr int WAVE_PIECES = DB * 4 + 1;          // 16-byte pieces of a lane: O, and reference maximum and sum
+    extern __shared__ __align__(16) char smem[];
+
+    const Geometry& geo = a.geo;
+    const FwdSlice& sl = slice_of(a, &FwdSlice::first, blockIdx.x);
+    int g, rest;
+    if (!decode_block(a.map, sl.rest_count, blockIdx.x - sl.first, g, rest)) return;
+    const int h = g * geo.G + rest % geo.G;
+    rest /= geo.G;
+    const int j = geo.step_begin + rest % sl.n_steps;
+    const int tile = sl.n_tiles - 1 - rest / sl.n_steps;   // long-prefix tiles first
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 31, hh = lane >> 5;
+    const int t0 = sl.t0, Tn = sl.t1;
+    const int q0 = t0 + tile * 32, hi = min(q0 + 31, Tn - 1);
+    const int qi = q0 + n, qc = min(qi, Tn - 1);
+
+    // document starts of the first row, of the last one and of this lane's
+    int lo, st_hi, st;
+    if (a.tok_start) {
+        st = a.tok_start[qc];
+        lo = uniform_load(a.tok_start + q0);
+        st_hi = uniform_load(a.tok_start + hi);
+    } else {
+        const int starts = a.cu[sl.doc0 + min(lane, sl.n_docs - 1)];   // one per lane
+        int r = __popcll(__ballot(lane < sl.n_docs && starts <= q0)) - 1;
+        lo = st = st_hi = __builtin_amdgcn_readlane(starts, r);
+        for (++r; r < sl.n_docs; ++r) {
+            const int s = __builtin_amdgcn_readlane(starts, r);
+            if (s > hi) break;
+            st = s <= qc ? s : st;
+            st_hi = s;
+        }
+    }
+
+    const float* qrow = static_cast<const float*>(a.q[j]) + (int64_t)h * geo.q_sh + (int64_t)qc * geo.q_st + hh * 8;
+    f32x8 qf[DC];
+#pragma unroll
+    for (int t = 0; t < DC; ++t) qf[t] = gload_frag<float>(qrow + t * 16);
+    f32x16 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+    float m = -INFINITY, l = 0.f;
+    const float c = geo.scale_log2;
+    auto raise = [&](float mx) {   // the reference maximum moves when it is exceeded by 2^kLazy
+        const bool grow = (mx - m) * c > kLazy;
+        if (__any(grow)) {
+            const float m_new = grow ? mx : m;
+            const float alpha = grow ? fast_exp2((m - m_new) * c) : 1.f;
+            m = m_new;
+            l *= alpha;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+        }
+    };
+
+    const float* K0 = static_cast<const float*>(a.k[0]) + (int64_t)g * geo.kv_sh;
+    const float* V0 = static_cast<const float*>(a.v[0]) + (int64_t)g * geo.kv_sh;
+    for (int kv0 = t0 + ((lo - t0) / 32 + wave) * 32; kv0 <= hi; kv0 += NW * 32) {
+        const int last = min(31, Tn - 1 - kv0);
+        const float* krow = K0 + (int64_t)(kv0 + min(n, last)) * geo.kv_st + hh * 8;
+        const float* v0 = V0 + (int64_t)kv0 * geo.kv_st;
+        // S^T[kv, q] = K Q^T; the first half of V is requested behind K and arrives under it
+        f32x8 kf[DC], vf[DB];
+#pragma unroll
+        for (int t = 0; t < DC; ++t) kf[t] = gload_frag<float>(krow + t * 16);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) vf[db] = gload_cols(v0, geo.kv_st, last, 0, db, n, hh);
+        issue_fence();
+        f32x16 s;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) s[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < DC; ++t) s = mma(kf[t], qf[t], s);
+        f32x8 vg[DB];
+#pragma unroll
+        for (int db = 0; db < DB; ++db) vg[db] = gload_cols(v0, geo.kv_st, last, 1, db, n, hh);
+        issue_fence();
+        if (kv0 + 31 > q0 || kv0 < st_hi) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int kv = kv0 + acc_row(i, hh);
+                s[i] = kv <= qi && kv >= st ? s[i] : -INFINITY;
+            }
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s[i]);
+        raise(half_max(mx));
+        const float mc = m == -INFINITY ? 0.f : m * c;
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            s[i] = fast_exp2(fmaf(s[i], c, -mc));
+            sum += s[i];
+        }
+        l += sum;
+        // O^T[d, q] += V^T P^T
+        const f32x8 p0 = acc_chunk<float>(s, 0), p1 = acc_chunk<float>(s, 1);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) oacc[db] = mma(vf[db], p0, oacc[db]);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) oacc[db] = mma(vg[db], p1, oacc[db]);
+    }
+    for (int lb = 1 + wave; lb <= j; lb += NW) {
+        const int64_t at = (int64_t)g * geo.kv_sh + (int64_t)qc * geo.kv_st + hh * 8;
+        const float *krow = static_cast<const float*>(a.k[lb]) + at, *vrow = static_cast<const float*>(a.v[lb]) + at;
+        f32x8 vf[DC];
+        float s = 0.f, vv[DB][16];
+#pragma unroll
+        for (int t = 0; t < DC; ++t) vf[t] = gload_frag<float>(vrow + t * 16);
+#pragma unroll
+        for (int t = 0; t < DC; ++t) s = dot8(qf[t], gload_frag<float>(krow + t * 16), s);
+        frags_to_acc_order<float, DC>(vf, vv);
+        s = half_sum(s);
+        raise(s);
+        const float p = fast_exp2((s - m) * c);
+        l += 0.5f * p;   // the two lane halves are added at the end
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) oacc[db][i] = fmaf(p, vv[db][i], oacc[db][i]);
+    }
+
+    // The waves meet: what each has of a row is scaled to the row's maximum and added, wave w doing pieces w, w + 8, ... of O.
+    // A wave that saw no key of a row brings m = -inf, l = 0, O = 0.
+    f32x4* const mine = reinterpret_cast<f32x4*>(smem) + wave * (WAVE_PIECES * 64) + lane;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4)
+            mine[(db * 4 + i4) * 64] = f32x4{oacc[db][4 * i4], oacc[db][4 * i4 + 1], oacc[db][4 * i4 + 2], oacc[db][4 * i4 + 3]};
+    mine[DB * 4 * 64] = f32x4{m, half_sum(l), 0.f, 0.f};
+    __syncthreads();
+    const f32x4* const all = reinterpret_cast<const f32x4*>(smem) + lane;
+    float wm[NW], wl[NW];
+    float m_all = -INFINITY, lt = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const f32x4 ml = all[(w * WAVE_PIECES + DB * 4) * 64];
+        wm[w] = ml[0];
+        wl[w] = ml[1];
+        m_all = fmaxf(m_all, wm[w]);   // finite: a row sees its own key
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        wm[w] = fast_exp2((wm[w] - m_all) * c);
+        lt += wl[w] * wm[w];
+    }
+    if (qi >= Tn) return;
+    const float inv = 1.f / lt;
+    if (wave == 0 && hh == 0) a.lse[j][(int64_t)h * geo.T + qi] = m_all * geo.scale + __logf(lt);
+    float* orow = static_cast<float*>(a.o[j]) + (int64_t)h * geo.q_sh + (int64_t)qi * geo.q_st + hh * 4;
+    for (int p = wave; p < DB * 4; p += NW) {
+        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const f32x4 x = all[(w * WAVE_PIECES + p) * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = fmaf(x[e], wm[w], o[e]);
+        }
+        *reinterpret_cast<f32x4*>(orow + p * 8) = o * inv;
+    }
+}
+
+template <int D, int N>
+static hipError_t launch_fwd_f32_n(const FwdCommon& common, const Slice* slices, int n_slices, hipStream_t stream) {
+    constexpr int LDS = 8 * (D / 8 + 1) * 1024;
+    auto kern = ttt_fwd_f32_kernel<D, N>;
+    static LdsOptIn lds_opt_in;
+    if (hipError_t e = lds_opt_in.ensure((const void*)kern, LDS); e != hipSuccess) return e;
+    FwdArgs<N> a;
+    static_cast<FwdCommon&>(a) = common;
+    a.map = head_map(a.geo.hkv);
+    int64_t grid = 0;
+    for (int i = 0; i < n_slices; ++i) {
+        const CallShape& shape = slices[i].shape;
+        FwdSlice& sl = a.slices[i];
+        sl.first = (int)grid;
+        sl.t0 = slices[i].t0;
+        sl.t1 = sl.t0 + shape.T;
+        sl.n_steps = shape.n_steps;
+        sl.doc0 = slices[i].doc0;
+        sl.n_docs = shape.n_docs;
+        sl.n_tiles = (shape.T + 31) / 32;
+        const int64_t rest = (int64_t)sl.n_tiles * shape.n_steps * a.geo.G;
+        grid += head_map_grid(a.map, rest);
+        if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+        sl.rest_count = (int)rest;
+    }
+    a.n_slices = n_slices;
+    ProfileScope prof("ttt_fwd_f32_kernel", stream);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), LDS, stream, a);
+    return hipGetLastError();
+}
+
 // first / one-past-last token of each token's document
 __global__ void ttt_tok_bounds_kernel(const int* __restrict__ cu, int n_docs, int T, int* __restrict__ tok_start,
                                       int* __restrict__ tok_end) {
@@ -546,6 +760,11 @@ hipError_t launch_fwd(int dtype, int head_dim, const FwdCommon& common, const Sl
         if (two_groups) return launch_fwd_t<__bf16, 64, 1, 8, 2>(a, slices, n_slices, stream);
         if (plan.split == kFwdFourWaves) return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, slices, n_slices, stream);
         return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, slices, n_slices, stream);
+    }
+    // operands straight from memory: rows are told apart by 32-bit offsets of up to four strides
+    if (dtype == 0 && a.geo.kv_st < (int64_t)1 << 28 && fwd_f32_direct(shapes, n_slices, head_dim, n_cu, plan)) {
+        if (head_dim == 128) return n_slices > 1 ? launch_fwd_f32_n<128, kMaxSlices>(a, slices, n_slices, stream) : launch_fwd_f32_n<128, 1>(a, slices, n_slices, stream);
+        return n_slices > 1 ? launch_fwd_f32_n<64, kMaxSlices>(a, slices, n_slices, stream) : launch_fwd_f32_n<64, 1>(a, slices, n_slices, stream);
     }
     if (dtype == 0 && head_dim == 128) return launch_fwd_t<float, 128, 1, 4, 1>(a, slices, n_slices, stream);
     if (dtype == 0 && head_dim == 64)

@@ -140,6 +140,52 @@ inline FwdPlan plan_fwd(const CallShape* calls, int n_calls, bool is_bf16, int h
 }
 inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu) { return plan_fwd(&a, 1, is_bf16, head_dim, n_cu); }
 
+// The longest and all of what the tiles of `rows` rows of a slice see, in groups of `per` key blocks of `keys` keys.
+struct KeyCount {
+    int64_t tiles = 0, blocks = 0, groups = 0, longest = 0;   // longest: groups of one tile
+};
+inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
+    KeyCount n;
+    int doc = 0;
+    for (int row = 0; row < a.T; row += rows) {
+        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
+        const int64_t blocks = std::min(row + rows - 1, a.T - 1) / keys - (a.cu_host[doc] - a.cu_base) / keys + 1, groups = (blocks + per - 1) / per;
+        ++n.tiles;
+        n.blocks += blocks;
+        n.groups += groups;
+        n.longest = std::max(n.longest, groups);
+    }
+    return n;
+}
+
+struct F32FwdPrices {
+    double own, chain, diag;                  // the longest workgroup: of its own, per group of key blocks, per diagonal key
+    double base, tile, block, tile_diag;      // the work: of the launch, per row tile, per key block, per diagonal key of a tile
+};
+
+// Whether an fp32 forward takes its operands straight from memory (ttt_fwd_f32_kernel: 32 rows of one head per workgroup, eight waves
+// that take the key blocks in turn) or through LDS tiles, as `tiled` says.  Each is estimated as its longest workgroup, or
+// the work of all over the compute units, by prices (us) fitted to 2863 launches of 32 ... 2500 tokens, eight head geometries, one step or up to
+// eight at once: in the mean the choice takes 1.003 / 1.002 of the better one (head_dim 64 / 128), tiles alone 1.35 / 1.96,
+// memory alone 1.030 / 1.013.  Few or long workgroups want the first, many rounds of the device with four heads to a tile the second.
+inline bool fwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int n_cu, const FwdPlan& tiled) {
+    const bool d64 = head_dim == 64;
+    const F32FwdPrices m = d64 ? F32FwdPrices{5.2, 5.0, 0.19, 6.0, 5.2, 0.62, 0.33} : F32FwdPrices{3.2, 11.7, 0.54, 10.2, 8.3, 1.43, 0.87};
+    const F32FwdPrices t = d64 ? F32FwdPrices{6.4, 5.1, 1.08, 8.3, 5.8, 5.26, 2.1} : F32FwdPrices{9.5, 11.8, 3.4, 19.8, 9.6, 12.3, 4.6};
+    const int groups = tiled.split == kFwdTwoKeyGroups ? 2 : 1, rows = (128 / groups) >> tiled.pack_log2;
+    double m_long = 0., m_work = 0., t_long = 0., t_work = 0.;
+    for (int i = 0; i < n_calls; ++i) {
+        const CallShape& a = calls[i];
+        const double heads = (double)a.hkv * a.G * a.n_steps, j_max = a.step_begin + a.n_steps - 1, j_mean = a.step_begin + 0.5 * (a.n_steps - 1);
+        const KeyCount nm = count_keys(a, 32, 32, 8), nt = count_keys(a, rows, 64, groups);
+        m_long = std::max(m_long, m.own + m.chain * nm.longest + m.diag * j_max);
+        m_work += heads * (nm.tiles * (m.tile + m.tile_diag * j_mean) + nm.blocks * m.block);
+        t_long = std::max(t_long, t.own + t.chain * nt.longest + t.diag * j_max);
+        t_work += heads / (1 << tiled.pack_log2) * (nt.tiles * (t.tile + t.tile_diag * j_mean) + (groups == 1 ? nt.groups * t.block : 0.));
+    }
+    return std::max(m_long, m.base + m_work / n_cu) < std::max(t_long, t.base + t_work / n_cu);
+}
+
 // ------------------------------------------------------------------------------------------------
 // Work split of the 16-bit backward launch: 32-row query blocks per dK/dV chunk and ways to split the
 // (step, head) list, chosen by a model of the launch.
@@ -476,7 +522,74 @@ inline bool bwd_slice_alone(const CallShape& a, int head_dim, int n_cu) {
     return bwd_slice_us(a, head_dim) > 1000. * std::max(1, n_cu / 8);
 }
 
-// The fp32 backward: ways to split the (step, head) list of a 128-key tile, and its query rows.
+// The fp32 backward with operands straight from memory (ttt_bwd_f32_kernel): ways to split the (step, head, query block) items of a
+// 32-key unit.  Estimated as the longest chain of a wave, or the work of all over the compute units and 0.15 of that chain (how
+// unevenly they end), by prices (us) fitted to all splits of the 2863 launches of fwd_f32_direct: 1.013 / 1.011 of the best split in the mean
+// (head_dim 64 / 128).  `other`: the work of the other slices of the launch.
+struct F32BwdPrices {
+    double unit, step, tile, group, diag;                        // the chains: a unit and four of its items, a dQ tile, four of its key blocks, a diagonal key
+    double later, unit_work, step_work, tile_work, group_work, diag_work;
+};
+inline F32BwdPrices f32_bwd_prices(int head_dim) {
+    return head_dim == 64 ? F32BwdPrices{1.35, 5.1, 1.45, 3.75, 0.31, 0.91, 4.9, 0.25, 2.9, 8.05, 0.78}
+                          : F32BwdPrices{0.95, 11.5, 0.82, 9.3, 0.68, 2.0, 8.8, 0.1, 1.1, 18.2, 1.8};
+}
+// per key tile of 32: the query blocks that see it
+inline std::vector<int> f32_query_blocks(const CallShape& a) {
+    std::vector<int> n((a.T + 31) / 32);
+    int doc = 0;
+    for (int t = 0; t < (int)n.size(); ++t) {
+        const int last = std::min(t * 32 + 31, a.T - 1);
+        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= last) ++doc;
+        n[t] = (a.cu_host[doc + 1] - a.cu_base - 1) / 32 - t + 1;
+    }
+    return n;
+}
+inline double f32_bwd_dq_work(const CallShape& a, int head_dim, const KeyCount& n) {
+    const F32BwdPrices p = f32_bwd_prices(head_dim);
+    const double heads = (double)a.hkv * a.G * a.n_steps, later = a.step_begin + a.n_steps > 1 ? (double)a.T * a.hkv * head_dim / 2048. * a.n_steps * a.G : 0.;
+    return heads * (n.tiles * (p.tile_work + p.diag_work * (a.step_begin + 0.5 * (a.n_steps - 1))) + n.groups * p.group_work) + later * p.later;
+}
+inline int plan_dkv_f32_direct(const CallShape& a, int head_dim, int n_cu, double other) {
+    const F32BwdPrices p = f32_bwd_prices(head_dim);
+    const KeyCount keys = count_keys(a, 32, 32, 4);
+    const std::vector<int> blocks = f32_query_blocks(a);
+    const int64_t n_jh = (int64_t)a.n_steps * a.G;
+    const double dq_chain = p.tile + p.group * keys.longest + p.diag * (a.step_begin + a.n_steps - 1), dq_work = other + f32_bwd_dq_work(a, head_dim, keys);
+    int best = 1;
+    double best_us = -1.;
+    for (int ns : {1, 2, 3, 4, 6, 8, 12, 16, 24}) {
+        if (ns > 4 * n_jh || (int64_t)blocks.size() * ns * a.hkv > 0x7fffffff) break;
+        int64_t steps = 0, longest = 0;
+        for (int b : blocks) {
+            const int64_t s = (n_jh * b + 4 * ns - 1) / (4 * ns);
+            steps += s;
+            longest = std::max(longest, s);
+        }
+        const double work = ((double)blocks.size() * p.unit_work + steps * p.step_work) * ns * a.hkv + dq_work;
+        const double chain = std::max(p.unit + p.step * longest, dq_chain), us = std::max(chain, work / n_cu + 0.15 * chain);
+        if (best_us < 0. || us < best_us) {
+            best_us = us;
+            best = ns;
+        }
+    }
+    return best;
+}
+// Tiles through LDS (ttt_bwd_main_f32_kernel) are 0 to 6 % faster in the mean with head_dim 128, 512 tokens or more in a document and
+// work for many rounds of the device (99 of those launches; 2000 tokens, 32/8 heads, two steps 2391 against 2610 us); elsewhere operands
+// from memory take 0.64 of their time in the mean with head_dim 128, 0.75 with 64 (444 tokens, 8/2 heads, the last of seven steps 129 -> 63).
+inline bool bwd_f32_direct(const CallShape* calls, int n_calls, int head_dim) {
+    int64_t tiles = 0;
+    int longest = 0;
+    for (int i = 0; i < n_calls; ++i) {
+        const CallShape& a = calls[i];
+        tiles += (int64_t)((a.T + 31) / 32) * a.hkv * a.G * a.n_steps;
+        for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+    }
+    return head_dim == 64 || tiles < 1500 || longest < 512;
+}
+
+// The fp32 backward with tiles in LDS: ways to split the (step, head) list of a 128-key tile, and its query rows.
 struct DkvPlanF32 {
     int n_split, q_split;
 };

@@ -75,6 +75,13 @@ def dq_key_groups_f32(tokens, hq, hkv, n_steps, n_cu=256):
     return 2 if _lib().plan_dq_key_groups(tokens, n_steps, hq // hkv, hkv, n_cu) else 1
 
 
+def f32_direct(docs, hq, hkv, d, step_begin, n_steps, n_cu=256):
+    """whether the fp32 forward and backward take their operands straight from memory"""
+    cu = _cu(docs)
+    return tuple(map(bool, _call(_lib().plan_f32_direct, int(cu[-1]), step_begin, n_steps, hq // hkv, hkv, len(docs),
+                                 cu.ctypes.data_as(ctypes.c_void_p), d, n_cu)))
+
+
 def projection_tiles(tokens, hidden_in, features, n_cu=256, largest_fits=True):
     """[(tokens, features, workgroups per compute unit) of a tile] of the launches"""
     tiles, f_first = (ctypes.c_int * 6)(), ctypes.c_int()

@@ -1,0 +1,78 @@
+"""GPU parity of the fp32 passes with operands straight from memory (rows, keys and documents that end inside a block of 32, more key
+blocks and diagonal keys than waves, more than 64 documents, strided views) and of the tiles in LDS that large launches and rows
+2^25 elements apart take.  Every case asserts the way that the launch rules choose for its passes."""
+import pytest
+import torch
+
+from paper_2603_18567_amd import TttAttnRunner
+from paper_2603_18567_amd.workloads import custom_workload
+from plan_lib import f32_direct
+from ttt_testlib import Case, compare_full
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # documents, hq, hkv, head_dim, k, steps per call, (forward, backward) straight from memory
+    ([1], 2, 1, 64, 3, 1, (True, True)),
+    ([32], 3, 1, 128, 2, 2, (True, True)),
+    ([31, 1, 33], 4, 2, 64, 3, 3, (True, True)),
+    ([300, 0, 65], 4, 2, 128, 2, 1, (True, True)),        # ten key blocks: some waves have two
+    ([70], 4, 4, 128, 12, 12, (True, True)),              # eleven diagonal keys
+    ([33, 40], 8, 1, 64, 11, 1, (True, True)),
+    ([20, 30] * 35, 4, 1, 128, 2, 1, (True, True)),       # bounds per token
+    ([700], 4, 1, 64, 2, 2, (True, True)),
+    ([40] * 40, 64, 4, 64, 2, 2, (False, True)),
+    ([512, 40], 16, 16, 128, 6, 6, (True, False)),
+    ([530], 32, 8, 128, 3, 3, (False, False)),
+]
+
+
+def passes(run, d_o, k, steps):
+    for j in range(0, k, steps):
+        run.forward(j, j + steps)
+    for j in reversed(range(0, k, steps)):
+        run.backward(d_o, j, j + steps, accumulate=steps < k)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,steps,direct", CASES, ids=[f"{sum(c[0])}_{len(c[0])}_{c[1]}_{c[2]}_{c[3]}_{c[4]}" for c in CASES])
+def test_f32_matches_oracle(docs, hq, hkv, d, k, steps, direct):
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    print(f"documents={docs} heads={hq}/{hkv} head_dim={d} k={k} steps={steps}", flush=True)
+    assert all(f32_direct(docs, hq, hkv, d, j, steps, n_cu) == direct for j in range(0, k, steps))
+    case = Case(custom_workload(f"f32_direct_{sum(docs)}_{d}", "f32", docs, hq, hkv, d, k, seed=sum(docs) + k), "cuda:0")
+    for t in case.run.o + case.run.lse:
+        t.fill_(float("nan"))
+    passes(case.run, case.d_o, k, steps)
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,row,head", [([45, 50], 4, 2, 64, 3, 4 * 72 + 40, 72), ([66], 2, 2, 128, 2, 2 * 136, 136),
+                                                       ([3], 2, 1, 64, 1, 1 << 25, 64), ([2], 2, 1, 128, 2, 1 << 25, 128)],
+                         ids=["strided_64", "strided_128", "far_rows_64", "far_rows_128"])
+def test_f32_strided_views_match_oracle(docs, hq, hkv, d, k, row, head):
+    """Rows `row` elements apart, heads `head`: what lies between keeps a sentinel."""
+    print(f"documents={docs} heads={hq}/{hkv} head_dim={d} k={k} strides={row},{head}", flush=True)
+    case = Case(custom_workload(f"f32_strided_{sum(docs)}_{d}", "f32", docs, hq, hkv, d, k, seed=k + d), "cuda:0")
+    sentinel, bufs = 77.0, []
+
+    def wide(t, copy=True):
+        buf = torch.full(((t.shape[0] - 1) * row + t.shape[1] * head,), sentinel, device=t.device)
+        view = buf.as_strided(t.shape, (row, head, 1))
+        if copy:
+            view.copy_(t)
+        bufs.append((buf, view))
+        return view
+
+    run = TttAttnRunner([wide(t) for t in case.q], [wide(t) for t in case.k], [wide(t) for t in case.v], case.wl.cu_seqlens, case.wl.scale, "cuda:0")
+    d_o = [wide(t) for t in case.d_o]
+    run.o, run.dq = [wide(t, False) for t in case.q], [wide(t, False) for t in case.q]
+    run.dk, run.dv = [wide(t, False) for t in case.k], [wide(t, False) for t in case.v]
+    passes(run, d_o, k, k)
+    case.run = run
+    for key, (err, bound) in compare_full(case).items():
+        assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
+    for buf, view in bufs:
+        view.fill_(sentinel)
+        assert bool((buf == sentinel).all())
