@@ -84,7 +84,7 @@ struct BwdCommon {
     int carry_reset;        // accumulate mode: this call starts the sweep (carry is overwritten, not read)
     int* tok_start;         // [T] first token of each token's document
     int* tok_end;           // [T] one past its last token
-    float* delta;           // [steps][hq][T]  D = <dO, O>
+    float* delta;           // [steps][hq][T]  D = <dO, O>; 16-bit: -D
     float* lse2;            // [steps][hq][T]  LSE * log2(e), the exponent offset of the 16-bit kernels
     float* dk0_acc;         // [T][hkv][d] fp32, block-0 partial sums (atomics)
     float* dv0_acc;

@@ -2,7 +2,7 @@
 // (Sec. 4.2.1), so every kernel here recomputes p = exp(s - LSE) from Q and K tile by tile and
 // applies the softmax-attention VJP:  D = <dO,O>, dp = <dO,V>, ds = p (dp - D).
 //
-//   ttt_bwd_delta_kernel   D for every (step, head, token)
+//   ttt_bwd_delta_kernel   D for every (step, head, token); 16-bit: -D, from which the dP sums start
 //   ttt_bwd_pre_regs_kernel  the same and the complete dK_l, dV_l of the later blocks (16-bit, by a rule on sizes)
 //   ttt_bwd_main_kernel    both streaming passes in one launch (ttt_bwd_main_f32_kernel for fp32):
 //     dkv_p8_tile, dkv_tile   key-stationary over block 0: dK, dV accumulators of 32 keys per wave in registers
@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void ttt_bwd_delta_kernel(const BwdArgs<N> a) 
     __syncthreads();
     if (writes) {
         const int64_t at = ((int64_t)js * geo.hq + h0 + wh) * geo.T + t0 + wt;
-        a.delta[at] = sum[wh * kDeltaTokens + wt];
+        a.delta[at] = sizeof(T) == 2 ? -sum[wh * kDeltaTokens + wt] : sum[wh * kDeltaTokens + wt];
         if constexpr (sizeof(T) == 2) a.lse2[at] = lse * kLog2e;
     }
 }
@@ -200,7 +200,7 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
         const int j = j0 + n / G;
         const frag cq = qf[0], cg = go[0], co = oo[0];
         const float lse2 = MAKE_D ? lse[0] * kLog2e : lse[0];
-        float dsum = dl[0];
+        float dsum = sizeof(T) == 2 ? -dl[0] : dl[0];
 #pragma unroll
         for (int s = 0; s + 1 < PF; ++s) {
             qf[s] = qf[s + 1];
@@ -214,7 +214,7 @@ TTT_DEV void diag_unit(const BwdCommon& a, const BwdSlice& sl, const int wg) {
             dsum = group_sum_dpp<LPR>(dot8(cg, co, 0.f));
             if (sub == 0 && pass == 0) {
                 const int64_t at = ((int64_t)(j - b) * geo.hq + g * G + n % G) * Tn + i;
-                a.delta[at] = dsum;
+                a.delta[at] = -dsum;
                 a.lse2[at] = lse2;
             }
         }
@@ -567,7 +567,7 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
     const int st = a.tok_start[qc];
     const int64_t at = ((int64_t)js * geo.hq + h) * geo.T + qc;
     const float lse2 = a.lse2[at];
-    const float dl = a.delta[at];
+    const float ndl = a.delta[at];   // -D
     const int hi_w = min(wq0 + 31, Tn - 1);
     const int first_row = __builtin_amdgcn_readfirstlane(min(wq0, Tn - 1));
     int lo_w = uniform_load(a.tok_start + first_row);
@@ -583,6 +583,12 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
 #pragma unroll
         for (int i = 0; i < 16; ++i) dqacc[db][i] = 0.f;
     const float c = geo.scale_log2;
+    // The dP sums start from -D, which has registers of its own for that: sixteen vector instructions less per block (4096 tokens, 32/8
+    // heads, seven steps 4161 -> 4120 us; head_dim 64, 8192 tokens, four steps 5114 -> 5077).
+    f32x16 minus_d;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) minus_d[i] = ndl;
+    asm volatile("" : "+v"(minus_d));
 
     uint32_t ra[DC], ta[DB][2];
     {
@@ -683,7 +689,8 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
             // S^T[kv, q] = K Q^T and dP^T[kv, q] = V dO^T (lane = query row)
             auto score = [&](int kb) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) sacc[i] = pacc[i] = 0.f;
+                for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+                pacc = minus_d;
 #pragma unroll
                 for (int t = 0; t < DC; ++t) {
                     if (t + PDR < DC) {
@@ -722,11 +729,11 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
                             const int kv = kb0 + acc_row(x, hh);
                             float p = fast_exp2(fmaf(sacc[x], c, -lse2));
                             p = (kv <= qi && kv >= st) ? p : 0.f;
-                            pacc[x] = p * (pacc[x] - dl);   // dS^T
+                            pacc[x] *= p;   // dS^T
                         }
                     } else {
 #pragma unroll
-                        for (int x = 0; x < 16; ++x) pacc[x] = fast_exp2(fmaf(sacc[x], c, -lse2)) * (pacc[x] - dl);
+                        for (int x = 0; x < 16; ++x) pacc[x] *= fast_exp2(fmaf(sacc[x], c, -lse2));
                     }
                     sfr[0] = acc_chunk<T>(pacc, 0);
                     sfr[1] = acc_chunk<T>(pacc, 1);
@@ -782,7 +789,7 @@ TTT_DEV void dq_pipe_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, co
             s = half_sum(s);
             dp = half_sum(dp);
             const float p = fast_exp2(fmaf(s, c, -lse2));
-            const float ds = p * (dp - dl);
+            const float ds = p * (dp + ndl);
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -1277,9 +1284,10 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
     __syncthreads();
 
     // KR of the pair's K row fragments stay in registers, as many as there is room for: the scores' operand reads
-    // are what loads LDS most (1.5 KB per matrix instruction, 1.3 with these; with all eight one register
-    // spills and the backward is 5 % slower instead of 2 % faster: 4096 tokens, seven steps 3480 -> 3415 us)
-    constexpr int KR = DC < 6 ? DC : 6;
+    // are what loads LDS most (1.5 KB per matrix instruction, 1.34 with these: 4096 tokens, seven steps, six of them 3480 -> 3415 us;
+    // with six beside the dP sums that start from -D four registers spill and everything is 3 to 5 % slower, with five or four
+    // none does and they are equal)
+    constexpr int KR = DC < 5 ? DC : 5;
     frag kreg[KR];
 #pragma unroll
     for (int t = 0; t < KR; ++t) kreg[t] = ld(ka + C::chunk_at(t));
@@ -1296,8 +1304,17 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
             request(nxt, IntC<1 - ST>{});
         }
         if (active && q0 + 31 >= wk0 && q0 < wq_lim) {
-            // ---- S = Q K^T, dP = dO V^T for the pair's 32 keys, two contraction chunks at a time
+            // ---- S = Q K^T, dP - D = dO V^T - D for the pair's 32 keys, two contraction chunks at a time.  The dP sums start
+            // from -D, read before the scores: read where dP begins it is waited for (the backward 3 % slower than with the
+            // subtraction), so it takes the place of sixteen vector instructions a block (forward and backward of 4096 tokens, 32/8
+            // heads, one step a call 0.5 % faster; head_dim 64, 4431 tokens, eight steps 3768 -> 3683 us).
             f32x16 sacc, pacc;
+#pragma unroll
+            for (int i4 = 0; i4 < 4; ++i4) {
+                const f32x4 d4 = ld_vec(VO + 128, i4);
+#pragma unroll
+                for (int x = 0; x < 4; ++x) pacc[4 * i4 + x] = d4[x];
+            }
             {
                 frag qa[DC], kf[DC];
 #pragma unroll
@@ -1328,8 +1345,6 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
                     ga[t] = ld(ra[t] + SO + C::kBlk);
                     vf[t] = ld(ka + C::chunk_at(t) + (C::kVBase - C::kKBase));
                 }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) pacc[i] = 0.f;
 #pragma unroll
                 for (int t = 0; t < DC; t += 2) {
                     if (t + 2 < DC) {
@@ -1372,13 +1387,8 @@ __device__ __forceinline__ void dkv_p8_tile(const BwdCommon& a, const BwdSlice& 
             frag tfr[NE];
 #pragma unroll
             for (int x = 0; x < 2; ++x) tfr[x] = ld_tr(SO, 1 - (x & 1), (x >> 1) / DB, (x >> 1) % DB);
-            {
-                f32x4 d4[4];
 #pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) d4[i4] = ld_vec(VO + 128, i4);
-#pragma unroll
-                for (int x = 0; x < 16; ++x) pacc[x] = sacc[x] * (pacc[x] - d4[x / 4][x % 4]);
-            }
+            for (int x = 0; x < 16; ++x) pacc[x] *= sacc[x];
             // ---- dV += P^T dO, dK += dS^T Q: the accumulator chunks are the A operands as they are
             frag pfr[2], sfr[2];
 #pragma unroll
