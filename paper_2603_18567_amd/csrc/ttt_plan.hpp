@@ -85,29 +85,73 @@ inline bool two_key_groups_end_first(const CallShape* calls, int n_calls, int pa
     return est[1] < 0.97 * est[0];
 }
 
+// The longest and all of what the tiles of `rows` rows of a slice see, in groups of `per` key blocks of `keys` keys.
+struct KeyCount {
+    int64_t tiles = 0, blocks = 0, groups = 0, longest = 0;   // longest: groups of one tile
+};
+inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
+    KeyCount n;
+    int doc = 0;
+    for (int row = 0; row < a.T; row += rows) {
+        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
+        const int64_t blocks = std::min(row + rows - 1, a.T - 1) / keys - (a.cu_host[doc] - a.cu_base) / keys + 1, groups = (blocks + per - 1) / per;
+        ++n.tiles;
+        n.blocks += blocks;
+        n.groups += groups;
+        n.longest = std::max(n.longest, groups);
+    }
+    return n;
+}
+
 // The same choice for head_dim 64, whose workgroups leave room for others on their compute unit: eight waves in 128
 // registers (two workgroups per unit), four waves and half the rows (three per unit), or two key groups
-// (one per unit).  Measured (us, in that order; last, what four waves of 64 rows took before):
-//   32/8 heads, one step: 1024 tokens 25 / 17 / 15 (30), 2048 45 / 32 / 31 (53), 4096 96 / 85 / 97 (111)
-//   32/8, seven steps: 4096 tokens 534 / 549 / 731 (790);  64/4, 8192 tokens 3988 / 4110 / 4986 (5774)
-//   4096 tokens in seven documents of up to 764, 32/8, one step: 32 / 29 / 37
-// Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest passes over
-// the keys.  The lines were drawn when the diagonal keys still came before the tiles.  Over 706 shapes of 128 ... 8192
-// tokens (seven head geometries, first step 0 to 11, one to seven steps, one document or many) the choice took 1.074 of the best
-// of the three in the mean then, and takes 1.057 now, at most 1.19 in nine of ten: four waves for two groups, which would be 11 %
-// faster there, in 273 of them, eight for four (8 %) in 144.
+// (one per unit).  Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest
+// passes over the keys.  Each split is estimated as its longest workgroup, or the work of all over the compute units and a part
+// of the longest one (how unevenly they end), whichever is more, by prices (us) fitted to 4000 launches of 64 ... 9000 tokens (seven
+// head geometries, one document or many, first step 0 to 10, one to nine steps): the choice takes 1.005 of the best of the three in
+// the mean; two lines at one and three workgroups per unit and 1024-token documents, drawn for a sample of sizes, took 1.068, and
+// one launch in twenty is more than 3 % slower than with them.  Packed batches of fewer than 640 tokens keep the first of those lines (the
+// parity tests of the three splits rest on it), where it takes 1.10.  725 tokens, 32/8 heads, ten steps one by one: forward and backward 453 -> 437
+// us; 579 tokens, 24/8 heads, the last of three steps: 38.1 -> 36.1.  Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys, as before.
+struct Fwd64Prices {
+    double own, tile, diag;                  // the longest workgroup: of its own, per key tile (or pair of them), per diagonal key
+    double wg, wg_tile, wg_diag;             // the work: per workgroup, its tiles, its diagonal keys
+    double base, uneven;
+};
 inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
-    const int rows = (8 * 32) >> pack_log2;
-    int64_t n = 0;
-    int longest = 0;
+    constexpr Fwd64Prices kPrices[] = {   // in the order of FwdSplit
+        {0.33, 1.38, 0.81, 3.02, 0.90, 0.64, 7.6, 0.54},
+        {0.08, 0.72, 0.54, 1.53, 0.48, 0.32, 7.7, 0.43},
+        {0.22, 1.17, 0.48, 4.19, 1.33, 0.48, 6.2, 0.},
+    };
+    int64_t tokens = 0, docs = 0, n_wgs = 0;
     for (int i = 0; i < n_calls; ++i) {
         const CallShape& a = calls[i];
-        n += (int64_t)((a.T + rows - 1) / rows) * a.hkv * (a.G >> pack_log2) * a.n_steps;
-        for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
+        tokens += a.T;
+        n_wgs += (int64_t)((a.T + (256 >> pack_log2) - 1) / (256 >> pack_log2)) * a.hkv * (a.G >> pack_log2) * a.n_steps;
+        docs += a.n_docs;
     }
-    const bool is_long = longest >= 16 * 64;
-    if (is_long && n <= n_cu) return kFwdTwoKeyGroups;
-    return n <= n_cu || (is_long && n <= 3 * (int64_t)n_cu) ? kFwdFourWaves : kFwdEightWaves;
+    if (n_wgs > 16 * (int64_t)n_cu) return kFwdEightWaves;
+    if (tokens < 640 && docs > 1) return n_wgs <= n_cu ? kFwdFourWaves : kFwdEightWaves;
+    FwdSplit best = kFwdEightWaves;
+    double best_us = -1.;
+    for (FwdSplit split : {kFwdEightWaves, kFwdFourWaves, kFwdTwoKeyGroups}) {
+        const Fwd64Prices& p = kPrices[split];
+        const int rows = (split == kFwdEightWaves ? 256 : 128) >> pack_log2;
+        double longest = 0., work = 0.;
+        for (int i = 0; i < n_calls; ++i) {
+            const CallShape& a = calls[i];
+            const KeyCount n = count_keys(a, rows, 64, split == kFwdTwoKeyGroups ? 2 : 1);
+            longest = std::max(longest, p.own + p.tile * n.longest + p.diag * (a.step_begin + a.n_steps - 1));
+            work += (double)a.hkv * (a.G >> pack_log2) * a.n_steps * (n.tiles * (p.wg + p.wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1))) + n.groups * p.wg_tile);
+        }
+        const double us = p.base + std::max(longest, p.uneven * longest + work / n_cu);
+        if (best_us < 0. || us < best_us) {
+            best_us = us;
+            best = split;
+        }
+    }
+    return best;
 }
 
 // The forward's split, and how many heads of a kv group share a workgroup (its log2).
@@ -139,24 +183,6 @@ inline FwdPlan plan_fwd(const CallShape* calls, int n_calls, bool is_bf16, int h
     return FwdPlan{kFwdFourWaves, pack_log2};
 }
 inline FwdPlan plan_fwd(const CallShape& a, bool is_bf16, int head_dim, int n_cu) { return plan_fwd(&a, 1, is_bf16, head_dim, n_cu); }
-
-// The longest and all of what the tiles of `rows` rows of a slice see, in groups of `per` key blocks of `keys` keys.
-struct KeyCount {
-    int64_t tiles = 0, blocks = 0, groups = 0, longest = 0;   // longest: groups of one tile
-};
-inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
-    KeyCount n;
-    int doc = 0;
-    for (int row = 0; row < a.T; row += rows) {
-        while (doc + 1 < a.n_docs && a.cu_host[doc + 1] - a.cu_base <= row) ++doc;
-        const int64_t blocks = std::min(row + rows - 1, a.T - 1) / keys - (a.cu_host[doc] - a.cu_base) / keys + 1, groups = (blocks + per - 1) / per;
-        ++n.tiles;
-        n.blocks += blocks;
-        n.groups += groups;
-        n.longest = std::max(n.longest, groups);
-    }
-    return n;
-}
 
 struct F32FwdPrices {
     double own, chain, diag;                  // the longest workgroup: of its own, per group of key blocks, per diagonal key
