@@ -76,3 +76,26 @@ def test_f32_strided_views_match_oracle(docs, hq, hkv, d, k, row, head):
     for buf, view in bufs:
         view.fill_(sentinel)
         assert bool((buf == sentinel).all())
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_f32_diagonal_scores_of_minus_infinity(d):
+    """A diagonal key of score -inf has no weight, also where it is the first key that its wave sees: the same as a score too low to count."""
+    print(f"head_dim={d}", flush=True)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert f32_direct([40], 2, 1, d, 0, 3, n_cu)[0]
+    case = Case(custom_workload(f"f32_minus_inf_{d}", "f32", [40], 2, 1, d, 3, seed=d), "cuda:0")
+    for t in case.q:
+        t[..., 0].abs_().add_(0.1)
+    outputs = []
+    for low in (-1e30, float("-inf")):
+        for t in case.k[1:]:
+            t[::3, :, 0] = low
+        for t in case.run.o + case.run.lse:
+            t.fill_(float("nan"))
+        case.run.forward(0, 3)
+        torch.cuda.synchronize()
+        outputs.append([t.clone() for t in case.run.o + case.run.lse])
+    for finite, infinite in zip(*outputs):
+        assert bool(finite.isfinite().all())
+        assert torch.equal(finite, infinite)
