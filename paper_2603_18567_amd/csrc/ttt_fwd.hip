@@ -605,7 +605,7 @@ __global__ __launch_bounds__(512) void ttt_fwd_f32_kernel(const FwdArgs<N> a) {
         frags_to_acc_order<float, DC>(vf, vv);
         s = half_sum(s);
         raise(s);
-        const float p = m == -INFINITY ? 0.f : fast_exp2((s - m) * c);   // (a score of -inf, and no key of the row before it in this wave)
+        const float p = fast_exp2((s - (m == -INFINITY ? 0.f : m)) * c);   // m = -inf: no key of the row yet but of score -inf (p = 0) or NaN
         l += 0.5f * p;   // the two lane halves are added at the end
 #pragma unroll
         for (int db = 0; db < DB; ++db)

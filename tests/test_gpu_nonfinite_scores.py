@@ -1,0 +1,58 @@
+"""GPU: scores that are not finite.  A NaN reaches exactly the rows that see its key.
+Every case asserts the way that the launch rules choose."""
+import pytest
+import torch
+
+from paper_2603_18567_amd.workloads import custom_workload
+from plan_lib import f32_direct, forward_split
+from ttt_testlib import Case
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # dtype, documents, hq, hkv, head_dim, k, steps per call, way
+    ("f32", [40], 2, 1, 64, 4, 4, "direct"),
+    ("f32", [40], 2, 1, 128, 4, 4, "direct"),
+    ("f32", [40] * 40, 64, 4, 64, 2, 2, "four_waves"),
+    ("f32", [530], 32, 8, 128, 3, 3, "four_waves"),
+]
+
+
+def way_of(dtype, docs, hq, hkv, d, step, steps):
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    if dtype == "f32" and f32_direct(docs, hq, hkv, d, step, steps, n_cu)[0]:
+        return "direct"
+    return forward_split(docs, hq, hkv, d, dtype, step, steps, n_cu)[0]
+
+
+def prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=0):
+    print(f"{dtype} documents={docs} heads={hq}/{hkv} head_dim={d} k={k} steps={steps}", flush=True)
+    assert all(way_of(dtype, docs, hq, hkv, d, j, steps) == way for j in range(from_step, k, steps))
+    return Case(custom_workload(f"nonfinite_{dtype}_{d}_{way}", dtype, docs, hq, hkv, d, k, seed=d + len(docs)), "cuda:0")
+
+
+def forward(run, steps):
+    for t in run.o + run.lse:
+        t.fill_(77.0)
+    for j in range(0, run.K, steps):
+        run.forward(j, j + steps)
+    torch.cuda.synchronize()
+    return [t.clone() for t in run.o], [t.clone() for t in run.lse]
+
+
+@pytest.mark.parametrize("dtype,docs,hq,hkv,d,k,steps,way", CASES, ids=[f"{c[0]}_{c[4]}_{c[7]}" for c in CASES])
+def test_a_nan_in_a_later_block_reaches_its_row(dtype, docs, hq, hkv, d, k, steps, way):
+    """A diagonal key with a NaN, in each later block in turn: O and LSE of its token are NaN from that step on, in the heads of
+    its group, and nothing else is, also where it is the first key of the row that its wave sees."""
+    case = prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=steps if way == "two_key_groups" else 0)
+    G, row, g = hq // hkv, 5, hkv - 1
+    for block in range(1, k):
+        was = case.run.k[block][row, g, 3].clone()
+        case.run.k[block][row, g, 3] = float("nan")
+        o, lse = forward(case.run, steps)
+        case.run.k[block][row, g, 3] = was
+        for j in range(k):
+            hit = torch.zeros(hq, sum(docs), dtype=torch.bool, device="cuda:0")
+            hit[g * G:(g + 1) * G, row] = j >= block
+            assert torch.equal(lse[j].isnan(), hit), f"LSE[{j}], NaN in block {block}"
+            assert torch.equal(o[j].isnan(), hit.T[..., None].expand_as(o[j])), f"O[{j}], NaN in block {block}"
