@@ -316,7 +316,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
                     for (int i = 0; i < 16; ++i) oacc[qb][db][i] *= alpha;
             }
-            const float p = fast_exp2((sc - m[qb]) * c);
+            const float p = fast_exp2((sc - (m[qb] == -INFINITY ? 0.f : m[qb])) * c);   // m = -inf: no key of the row yet but of score -inf (p = 0) or NaN
             l[qb] += 0.5f * p;   // the two lane halves are added at the end
 #pragma unroll
             for (int db = 0; db < DB; ++db)

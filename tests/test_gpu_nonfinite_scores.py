@@ -15,6 +15,11 @@ CASES = [
     ("f32", [40], 2, 1, 128, 4, 4, "direct"),
     ("f32", [40] * 40, 64, 4, 64, 2, 2, "four_waves"),
     ("f32", [530], 32, 8, 128, 3, 3, "four_waves"),
+    ("bf16", [300], 8, 2, 128, 4, 1, "two_key_groups"),
+    ("bf16", [300, 70, 1, 29, 49], 64, 16, 128, 12, 12, "eight_waves"),
+    ("bf16", [500], 32, 8, 64, 4, 1, "two_key_groups"),
+    ("bf16", [33, 1, 130, 64], 4, 2, 64, 4, 1, "four_waves"),
+    ("bf16", [63, 200, 1, 336], 32, 8, 64, 4, 4, "eight_waves"),
 ]
 
 
@@ -44,9 +49,9 @@ def forward(run, steps):
 def test_a_nan_in_a_later_block_reaches_its_row(dtype, docs, hq, hkv, d, k, steps, way):
     """A diagonal key with a NaN, in each later block in turn: O and LSE of its token are NaN from that step on, in the heads of
     its group, and nothing else is, also where it is the first key of the row that its wave sees."""
-    case = prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=steps if way == "two_key_groups" else 0)
+    case = prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=1 if way == "two_key_groups" else 0)   # (step 0 has no diagonal key)
     G, row, g = hq // hkv, 5, hkv - 1
-    for block in range(1, k):
+    for block in range(1, min(k, 4)):
         was = case.run.k[block][row, g, 3].clone()
         case.run.k[block][row, g, 3] = float("nan")
         o, lse = forward(case.run, steps)
@@ -56,3 +61,19 @@ def test_a_nan_in_a_later_block_reaches_its_row(dtype, docs, hq, hkv, d, k, step
             hit[g * G:(g + 1) * G, row] = j >= block
             assert torch.equal(lse[j].isnan(), hit), f"LSE[{j}], NaN in block {block}"
             assert torch.equal(o[j].isnan(), hit.T[..., None].expand_as(o[j])), f"O[{j}], NaN in block {block}"
+
+
+@pytest.mark.parametrize("dtype,docs,hq,hkv,d,k,steps,way", CASES, ids=[f"{c[0]}_{c[4]}_{c[7]}" for c in CASES])
+def test_a_later_block_s_score_of_minus_infinity_has_no_weight(dtype, docs, hq, hkv, d, k, steps, way):
+    """The same O and LSE as with a score too low to count, also where it is the first key of the row that its wave sees."""
+    case = prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=1 if way == "two_key_groups" else 0)
+    for t in case.q:
+        t[..., 0].abs_().add_(0.1)
+    outputs = []
+    for low in (-1e30, float("-inf")):
+        for t in case.k[1:]:
+            t[::3, :, 0] = low
+        outputs.append(sum(forward(case.run, steps), []))
+    for finite, infinite in zip(*outputs):
+        assert bool(finite.isfinite().all())
+        assert torch.equal(finite, infinite)
