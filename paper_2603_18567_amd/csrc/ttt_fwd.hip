@@ -425,8 +425,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 const f32x4 ml = piece[(qb * (DB * 4 + 1) + DB * 4) * 64];
-                const float m_new = fmaxf(m[qb], ml[0]);   // one of them is finite: a row sees its own key
-                const float a0 = fast_exp2((m[qb] - m_new) * c), a1 = fast_exp2((ml[0] - m_new) * c);
+                const float m_new = fmaxf(m[qb], ml[0]), off = m_new == -INFINITY ? 0.f : m_new;   // (-inf: every score of the row is)
+                const float a0 = fast_exp2((m[qb] - off) * c), a1 = fast_exp2((ml[0] - off) * c);
                 m[qb] = m_new;
                 l[qb] = l[qb] * a0 + ml[1] * a1;
 #pragma unroll
@@ -631,11 +631,12 @@ __global__ __launch_bounds__(512) void ttt_fwd_f32_kernel(const FwdArgs<N> a) {
         const f32x4 ml = all[(w * WAVE_PIECES + DB * 4) * 64];
         wm[w] = ml[0];
         wl[w] = ml[1];
-        m_all = fmaxf(m_all, wm[w]);   // finite: a row sees its own key
+        m_all = fmaxf(m_all, wm[w]);
     }
+    const float off = m_all == -INFINITY ? 0.f : m_all;   // (-inf: every score of the row is)
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        wm[w] = fast_exp2((wm[w] - m_all) * c);
+        wm[w] = fast_exp2((wm[w] - off) * c);
         lt += wl[w] * wm[w];
     }
     if (qi >= Tn) return;

@@ -77,3 +77,17 @@ def test_a_later_block_s_score_of_minus_infinity_has_no_weight(dtype, docs, hq, 
     for finite, infinite in zip(*outputs):
         assert bool(finite.isfinite().all())
         assert torch.equal(finite, infinite)
+
+
+@pytest.mark.parametrize("dtype,docs,hq,hkv,d,k,steps,way", CASES, ids=[f"{c[0]}_{c[4]}_{c[7]}" for c in CASES])
+def test_a_row_whose_scores_are_all_minus_infinity(dtype, docs, hq, hkv, d, k, steps, way):
+    """The sum of its weights is 0: LSE is -inf and O is 0 / 0, in every split.  The rows that see other keys as well are finite."""
+    case = prepare(dtype, docs, hq, hkv, d, k, steps, way, from_step=1 if way == "two_key_groups" else 0)
+    for t in case.q:
+        t[..., 0].abs_().add_(0.1)
+    for t in case.k:
+        t[0, :, 0] = float("-inf")
+    o, lse = forward(case.run, steps)
+    for j in range(k):
+        assert bool((lse[j][:, 0] == float("-inf")).all()) and bool(lse[j][:, 1:].isfinite().all()), f"LSE[{j}]"
+        assert bool(o[j][0].isnan().all()) and bool(o[j][1:].isfinite().all()), f"O[{j}]"
