@@ -1891,8 +1891,7 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
 
     // 2. dQ and block 0's dK, dV in one launch
     {
-        // fp32: operands straight from memory (rows of a block are told apart by 32-bit offsets), or tiles in LDS
-        const bool direct = !k16 && std::max(geo.q_st, geo.kv_st) < (int64_t)1 << 25 && bwd_f32_direct(shapes, n_slices, D);
+        const bool direct = !k16 && bwd_f32_direct(shapes, n_slices, D, geo.q_st, geo.kv_st);   // fp32: operands straight from memory, or tiles in LDS
         constexpr int NW = k16 ? 8 : 4;
         constexpr int KVT = 128;
         constexpr int LDS_Q = k16 ? 2 * 2 * 128 * D * (int)sizeof(T) : 4 * 64 * D * (int)sizeof(T);

@@ -461,7 +461,8 @@ template <> TTT_DEV void gstore_vec4<__bf16>(__bf16* p, float a, float b, float 
 }
 
 // The transposed fragment (frag_transposed) of a 32-row block straight from memory, fp32: chunk c of 16 rows, 32-column block
-// db.  `base` is the block's first row, wave-uniform; rows past number `last` repeat it.  4 * stride must stay below 2^30.
+// db.  `base` is the block's first row, wave-uniform; rows past number `last` repeat it.  16 * stride + 124
+// must stay below 2^32 (stride: a multiple of 8 below 2^28).
 TTT_DEV f32x8 gload_cols(const float* base, int64_t stride, int last, int c, int db, int n, int hh) {
     f32x8 v;
 #pragma unroll

@@ -762,8 +762,7 @@ hipError_t launch_fwd(int dtype, int head_dim, const FwdCommon& common, const Sl
         if (plan.split == kFwdFourWaves) return launch_fwd_t<__bf16, 64, 1, 4, 1, 3>(a, slices, n_slices, stream);
         return launch_fwd_t<__bf16, 64, 1, 8, 1, 4>(a, slices, n_slices, stream);
     }
-    // operands straight from memory: rows are told apart by 32-bit offsets of up to four strides
-    if (dtype == 0 && a.geo.kv_st < (int64_t)1 << 28 && fwd_f32_direct(shapes, n_slices, head_dim, n_cu, plan)) {
+    if (dtype == 0 && fwd_f32_direct(shapes, n_slices, head_dim, n_cu, plan, a.geo.kv_st)) {   // operands straight from memory
         if (head_dim == 128) return n_slices > 1 ? launch_fwd_f32_n<128, kMaxSlices>(a, slices, n_slices, stream) : launch_fwd_f32_n<128, 1>(a, slices, n_slices, stream);
         return n_slices > 1 ? launch_fwd_f32_n<64, kMaxSlices>(a, slices, n_slices, stream) : launch_fwd_f32_n<64, 1>(a, slices, n_slices, stream);
     }

@@ -194,7 +194,9 @@ struct F32FwdPrices {
 // the work of all over the compute units, by prices (us) fitted to 2863 launches of 32 ... 2500 tokens, eight head geometries, one step or up to
 // eight at once: in the mean the choice takes 1.003 / 1.002 of the better one (head_dim 64 / 128), tiles alone 1.35 / 1.96,
 // memory alone 1.030 / 1.013.  Few or long workgroups want the first, many rounds of the device with four heads to a tile the second.
-inline bool fwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int n_cu, const FwdPlan& tiled) {
+// kv_st: elements from row to row, a multiple of 8; a lane's place in a row or the fourth after it is a 32-bit byte offset.
+inline bool fwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int n_cu, const FwdPlan& tiled, int64_t kv_st) {
+    if (kv_st >= (int64_t)1 << 28) return false;
     const bool d64 = head_dim == 64;
     const F32FwdPrices m = d64 ? F32FwdPrices{5.2, 5.0, 0.19, 6.0, 5.2, 0.62, 0.33} : F32FwdPrices{3.2, 11.7, 0.54, 10.2, 8.3, 1.43, 0.87};
     const F32FwdPrices t = d64 ? F32FwdPrices{6.4, 5.1, 1.08, 8.3, 5.8, 5.26, 2.1} : F32FwdPrices{9.5, 11.8, 3.4, 19.8, 9.6, 12.3, 4.6};
@@ -604,7 +606,9 @@ inline int plan_dkv_f32_direct(const CallShape& a, int head_dim, int n_cu, doubl
 // Tiles through LDS (ttt_bwd_main_f32_kernel) are 0 to 6 % faster in the mean with head_dim 128, 512 tokens or more in a document and
 // work for many rounds of the device (99 of those launches; 2000 tokens, 32/8 heads, two steps 2391 against 2610 us); elsewhere operands
 // from memory take 0.64 of their time in the mean with head_dim 128, 0.75 with 64 (444 tokens, 8/2 heads, the last of seven steps 129 -> 63).
-inline bool bwd_f32_direct(const CallShape* calls, int n_calls, int head_dim) {
+// q_st, kv_st: elements from row to row; the 32 rows of a block are told apart by 32-bit byte offsets.
+inline bool bwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int64_t q_st, int64_t kv_st) {
+    if (std::max(q_st, kv_st) >= (int64_t)1 << 25) return false;
     int64_t tiles = 0;
     int longest = 0;
     for (int i = 0; i < n_calls; ++i) {

@@ -62,11 +62,12 @@ int plan_dq_key_groups(int T, int n_steps, int G, int hkv, int n_cu) {
     return ttt::dq_two_key_groups(&shape, 1, n_cu);
 }
 
-// whether the fp32 passes take their operands straight from memory (rows at most 2^25 elements apart)
-void plan_f32_direct(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int head_dim, int n_cu, int* fwd, int* bwd) {
+// whether the fp32 passes take their operands straight from memory (q_st, kv_st: elements from row to row)
+void plan_f32_direct(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int head_dim, int n_cu, int64_t q_st,
+                     int64_t kv_st, int* fwd, int* bwd) {
     const ttt::CallShape call{T, step_begin, n_steps, G, hkv, n_docs, cu, cu[0]};
-    *fwd = ttt::fwd_f32_direct(&call, 1, head_dim, n_cu, ttt::plan_fwd(call, false, head_dim, n_cu));
-    *bwd = ttt::bwd_f32_direct(&call, 1, head_dim);
+    *fwd = ttt::fwd_f32_direct(&call, 1, head_dim, n_cu, ttt::plan_fwd(call, false, head_dim, n_cu), kv_st);
+    *bwd = ttt::bwd_f32_direct(&call, 1, head_dim, q_st, kv_st);
 }
 
 // tile sizes and workgroups per compute unit of the launches of a projection; returns how many there are

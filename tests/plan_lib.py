@@ -75,11 +75,12 @@ def dq_key_groups_f32(tokens, hq, hkv, n_steps, n_cu=256):
     return 2 if _lib().plan_dq_key_groups(tokens, n_steps, hq // hkv, hkv, n_cu) else 1
 
 
-def f32_direct(docs, hq, hkv, d, step_begin, n_steps, n_cu=256):
-    """whether the fp32 forward and backward take their operands straight from memory"""
+def f32_direct(docs, hq, hkv, d, step_begin, n_steps, n_cu=256, q_st=None, kv_st=None):
+    """whether the fp32 forward and backward take their operands straight from memory; q_st, kv_st: elements from row to row"""
     cu = _cu(docs)
+    strides = [ctypes.c_int64(heads * d if st is None else st) for heads, st in ((hq, q_st), (hkv, kv_st))]
     return tuple(map(bool, _call(_lib().plan_f32_direct, int(cu[-1]), step_begin, n_steps, hq // hkv, hkv, len(docs),
-                                 cu.ctypes.data_as(ctypes.c_void_p), d, n_cu)))
+                                 cu.ctypes.data_as(ctypes.c_void_p), d, n_cu, *strides)))
 
 
 def projection_tiles(tokens, hidden_in, features, n_cu=256, largest_fits=True):

@@ -1,6 +1,6 @@
 """GPU parity of the fp32 passes with operands straight from memory (rows, keys and documents that end inside a block of 32, more key
-blocks and diagonal keys than waves, more than 64 documents, strided views) and of the tiles in LDS that large launches and rows
-2^25 elements apart take.  Every case asserts the way that the launch rules choose for its passes."""
+blocks and diagonal keys than waves, more than 64 documents, strided views) and of the tiles in LDS that large launches, the backward of
+rows 2^25 elements apart and the forward of rows 2^28 apart take.  Every case asserts the way that the launch rules choose for its passes."""
 import pytest
 import torch
 
@@ -48,12 +48,16 @@ def test_f32_matches_oracle(docs, hq, hkv, d, k, steps, direct):
         assert err <= bound, f"{key}: {err:.3e} > {bound:.3e}"
 
 
-@pytest.mark.parametrize("docs,hq,hkv,d,k,row,head", [([45, 50], 4, 2, 64, 3, 4 * 72 + 40, 72), ([66], 2, 2, 128, 2, 2 * 136, 136),
-                                                       ([3], 2, 1, 64, 1, 1 << 25, 64), ([2], 2, 1, 128, 2, 1 << 25, 128)],
-                         ids=["strided_64", "strided_128", "far_rows_64", "far_rows_128"])
-def test_f32_strided_views_match_oracle(docs, hq, hkv, d, k, row, head):
+@pytest.mark.parametrize("docs,hq,hkv,d,k,row,head,direct", [
+    ([45, 50], 4, 2, 64, 3, 4 * 72 + 40, 72, (True, True)), ([66], 2, 2, 128, 2, 2 * 136, 136, (True, True)),
+    ([40] * 40, 64, 4, 64, 2, 64 * 72, 72, (False, True)), ([530], 32, 8, 128, 3, 32 * 136, 136, (False, False)),
+    ([31, 6], 2, 1, 64, 1, 1 << 25, 64, (True, False)), ([34], 2, 1, 128, 1, 1 << 25, 128, (True, False))],
+    ids=["strided_64", "strided_128", "strided_tiles_64", "strided_tiles_128", "far_rows_64", "far_rows_128"])
+def test_f32_strided_views_match_oracle(docs, hq, hkv, d, k, row, head, direct):
     """Rows `row` elements apart, heads `head`: what lies between keeps a sentinel."""
     print(f"documents={docs} heads={hq}/{hkv} head_dim={d} k={k} strides={row},{head}", flush=True)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert f32_direct(docs, hq, hkv, d, 0, k, n_cu, row, row) == direct
     case = Case(custom_workload(f"f32_strided_{sum(docs)}_{d}", "f32", docs, hq, hkv, d, k, seed=k + d), "cuda:0")
     sentinel, bufs = 77.0, []
 
@@ -76,6 +80,29 @@ def test_f32_strided_views_match_oracle(docs, hq, hkv, d, k, row, head):
     for buf, view in bufs:
         view.fill_(sentinel)
         assert bool((buf == sentinel).all())
+
+
+@pytest.mark.parametrize("row,direct", [((1 << 28) - 8, True), (1 << 28, False)])
+def test_f32_forward_with_rows_a_gibibyte_apart(row, direct):
+    """K and V rows as far apart as the forward's 32-bit offsets can tell, and farther: the same O and LSE as with rows that
+    follow each other."""
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    assert f32_direct([6], 2, 1, 64, 0, 1, n_cu, kv_st=row) == (direct, False)
+    print(f"kv row stride={row}", flush=True)
+    case = Case(custom_workload("f32_gibibyte", "f32", [6], 2, 1, 64, 1, seed=9), "cuda:0")
+    case.run.forward()
+
+    def far(t):
+        buf = torch.full((5 * row + 64,), 77.0, device=t.device)
+        view = buf.as_strided(t.shape, (row, 64, 1))
+        view.copy_(t)
+        return view
+
+    run = TttAttnRunner(case.q, [far(t) for t in case.k], [far(t) for t in case.v], case.wl.cu_seqlens, case.wl.scale, "cuda:0")
+    run.forward()
+    torch.cuda.synchronize()
+    for got, ref in zip(run.o + run.lse, case.run.o + case.run.lse):
+        torch.testing.assert_close(got, ref, rtol=1e-5, atol=1e-5)   # (sums of six terms, in another order with tiles)
 
 
 @pytest.mark.parametrize("d", [64, 128])
