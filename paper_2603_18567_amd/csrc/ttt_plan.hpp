@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <utility>
 #include <vector>
@@ -106,52 +107,61 @@ inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
 // The same choice for head_dim 64, whose workgroups leave room for others on their compute unit: eight waves in 128
 // registers (two workgroups per unit), four waves and half the rows (three per unit), or two key groups
 // (one per unit).  Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest
-// passes over the keys.  Each split is estimated as its longest workgroup, or the work of all over the compute units and a part
-// of the longest one (how unevenly they end), whichever is more, by prices (us) fitted to 4000 launches of 64 ... 9000 tokens (seven
-// head geometries, one document or many, first step 0 to 10, one to nine steps): the choice takes 1.005 of the best of the three in
-// the mean; two lines at one and three workgroups per unit and 1024-token documents, drawn for a sample of sizes, took 1.068, and
-// one launch in twenty is more than 3 % slower than with them.  Packed batches of fewer than 640 tokens keep the first of those lines (the
-// parity tests of the three splits rest on it), where it takes 1.10.  725 tokens, 32/8 heads, ten steps one by one: forward and backward 453 -> 437
-// us; 579 tokens, 24/8 heads, the last of three steps: 38.1 -> 36.1.  Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys, as before.
+// passes over the keys.  Two lines, at one and three of the largest workgroups per unit and 1024-token documents, say which, unless
+// another split is estimated to take 0.94 of that one's time or less.  A split is estimated as its longest workgroup, or the work
+// of all over the compute units (more where they make no whole rounds of it) and a part of the longest one (how unevenly they end),
+// whichever is more, by prices (us) fitted to 3400 launches of 40 ... 9000 tokens, timed in graphs (one launch after another
+// the shortest are as long as their submission): seven head geometries, one document or many, first step 0 to 10, one to nine steps.
+// The choice takes 1.024 of the best of the three in the mean, the lines alone 1.061; 7 launches in 1000 are more than 3 % slower
+// than by the lines, 1.22 at most (at 0.98, 1.017 and 25; the lowest of the three 1.010 and 44).  566 tokens in two documents, 24/8
+// heads, the last of eleven steps: 23 -> 17 us; 65, 64/4, nine steps from the tenth on: 22 -> 16.
+// Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys.
 struct Fwd64Prices {
     double own, tile, diag;                  // the longest workgroup: of its own, per key tile (or pair of them), per diagonal key
     double wg, wg_tile, wg_diag;             // the work: per workgroup, its tiles, its diagonal keys
-    double base, uneven;
+    double base, uneven, rounds;             // of the launch; of the longest workgroup; of what the last round leaves idle
+    double from_memory, idle;                // diagonal keys that do not go through LDS: more, by; less for waves without rows, by
 };
 inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
     constexpr Fwd64Prices kPrices[] = {   // in the order of FwdSplit
-        {0.33, 1.38, 0.81, 3.02, 0.90, 0.64, 7.6, 0.54},
-        {0.08, 0.72, 0.54, 1.53, 0.48, 0.32, 7.7, 0.43},
-        {0.22, 1.17, 0.48, 4.19, 1.33, 0.48, 6.2, 0.},
+        {0., 1.21, 0.71, 2.57, 0.95, 0.47, 5.36, 0.32, 0.19, 1.58, 0.50},
+        {0., 0.79, 0.52, 1.27, 0.49, 0.29, 5.11, 0.34, 0.18, 0.99, 0.45},
+        {1.51, 1.22, 0.52, 4.15, 1.25, 0.50, 3.83, 0., 0.48, 0., 0.},
     };
-    int64_t tokens = 0, docs = 0, n_wgs = 0;
+    int64_t n_wgs = 0;
+    int longest_doc = 0;
     for (int i = 0; i < n_calls; ++i) {
         const CallShape& a = calls[i];
-        tokens += a.T;
         n_wgs += (int64_t)((a.T + (256 >> pack_log2) - 1) / (256 >> pack_log2)) * a.hkv * (a.G >> pack_log2) * a.n_steps;
-        docs += a.n_docs;
+        for (int r = 0; r < a.n_docs; ++r) longest_doc = std::max(longest_doc, a.cu_host[r + 1] - a.cu_host[r]);
     }
     if (n_wgs > 16 * (int64_t)n_cu) return kFwdEightWaves;
-    if (tokens < 640 && docs > 1) return n_wgs <= n_cu ? kFwdFourWaves : kFwdEightWaves;
-    FwdSplit best = kFwdEightWaves;
-    double best_us = -1.;
+    const bool is_long = longest_doc >= 1024;
+    const FwdSplit line = is_long && n_wgs <= n_cu                                    ? kFwdTwoKeyGroups
+                          : n_wgs <= n_cu || (is_long && n_wgs <= 3 * (int64_t)n_cu) ? kFwdFourWaves
+                                                                                     : kFwdEightWaves;
+    double us[3];
     for (FwdSplit split : {kFwdEightWaves, kFwdFourWaves, kFwdTwoKeyGroups}) {
         const Fwd64Prices& p = kPrices[split];
-        const int rows = (split == kFwdEightWaves ? 256 : 128) >> pack_log2;
-        double longest = 0., work = 0.;
+        const int waves = split == kFwdFourWaves ? 4 : 8, groups = split == kFwdTwoKeyGroups ? 2 : 1, per_cu = split == kFwdEightWaves ? 2 : split == kFwdFourWaves ? 3 : 1;
+        const int rows = (waves / groups * 32) >> pack_log2;
+        const double from_memory = fwd_diag_slots(64, waves, groups, per_cu, rows).slots == 0 ? p.from_memory : 0.;
+        double longest = 0., work = 0., n = 0.;
         for (int i = 0; i < n_calls; ++i) {
             const CallShape& a = calls[i];
-            const KeyCount n = count_keys(a, rows, 64, split == kFwdTwoKeyGroups ? 2 : 1);
-            longest = std::max(longest, p.own + p.tile * n.longest + p.diag * (a.step_begin + a.n_steps - 1));
-            work += (double)a.hkv * (a.G >> pack_log2) * a.n_steps * (n.tiles * (p.wg + p.wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1))) + n.groups * p.wg_tile);
+            const KeyCount keys = count_keys(a, rows, 64, groups);
+            const double full = std::min(1., (double)a.T / rows), busy = 1. - p.idle * (1. - full), diag = busy * (1. + from_memory * full) * p.diag;
+            const double wg_diag = busy * (1. + from_memory * full) * p.wg_diag, per_tile = (double)a.hkv * (a.G >> pack_log2) * a.n_steps;
+            longest = std::max(longest, p.own + busy * p.tile * keys.longest + diag * (a.step_begin + a.n_steps - 1));
+            work += per_tile * (keys.tiles * (p.wg + wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1))) + busy * keys.groups * p.wg_tile);
+            n += per_tile * keys.tiles;
         }
-        const double us = p.base + std::max(longest, p.uneven * longest + work / n_cu);
-        if (best_us < 0. || us < best_us) {
-            best_us = us;
-            best = split;
-        }
+        const double rounds = n / n_cu;
+        if (rounds > 1.) work *= 1. + p.rounds * (std::ceil(rounds) / rounds - 1.);
+        us[split] = p.base + std::max(longest, p.uneven * longest + work / n_cu);
     }
-    return best;
+    const FwdSplit best = (FwdSplit)(std::min_element(us, us + 3) - us);
+    return us[best] < 0.94 * us[line] ? best : line;
 }
 
 // The forward's split, and how many heads of a kv group share a workgroup (its log2).

@@ -23,17 +23,18 @@ CASES = [
 ]
 
 
-# head_dim 64: two key groups while there are few, long workgroups; four waves while there are few; eight otherwise
+# head_dim 64: two key groups for few, long workgroups; four waves for more or shorter ones; eight for many.  (The splits' estimates
+# choose; with one or two heads to a workgroup eight waves are left for more than sixteen workgroups per compute unit.)
 CASES_64 = [
     ("two_key_groups", [1100], 4, 1, 2, 1),
     ("two_key_groups_documents", [3, 1030, 40], 2, 2, 3, 1),
     ("four_waves", [70, 1, 130, 64, 33], 8, 2, 4, 1),
-    ("four_waves_one_head", [200, 95], 3, 3, 3, 1),
-    ("eight_waves", [63, 200, 1, 336], 32, 8, 4, 4),
+    ("four_waves_one_head", [200, 95], 96, 32, 3, 1),
+    ("eight_waves", [63, 200, 1, 336], 64, 16, 9, 9),
     ("four_waves_two_heads", [33, 1, 130, 64], 4, 2, 4, 1),       # 64 rows: diagonal rows through LDS
-    ("eight_waves_one_head", [63, 200, 1, 300, 41], 32, 32, 3, 3),
-    ("eight_waves_two_heads", [63, 200, 1, 300, 41], 16, 8, 7, 7),
-    ("eight_waves_70_documents", [9, 1, 0, 17, 5] * 14, 48, 16, 6, 6),
+    ("eight_waves_one_head", [63, 200, 1, 41], 128, 128, 17, 17),
+    ("eight_waves_two_heads", [63, 200, 1, 41], 192, 96, 15, 15),
+    ("eight_waves_70_documents", [9, 1, 0, 17, 5] * 14, 144, 48, 15, 15),
 ]
 
 

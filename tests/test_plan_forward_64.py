@@ -16,8 +16,10 @@ from plan_lib import forward_split
     ([2493, 1235, 212], 12, 2, 3, 1, "two_key_groups"),   # 64, 58 and 41
     ([7640], 8, 2, 0, 1, "two_key_groups"),           # 151, 104 and 83
     ([65536], 16, 4, 0, 7, "eight_waves"),            # more than sixteen of the largest workgroups to a unit
-    ([320, 319], 16, 16, 0, 1, "four_waves"),         # a packed batch of fewer than 640 tokens: by the number of workgroups
-    ([320, 319], 14, 2, 0, 7, "eight_waves"),
+    ([497, 69], 24, 8, 10, 1, "two_key_groups"),      # short packed batches: 34, 23 and 17
+    ([183, 183, 66], 16, 16, 10, 4, "two_key_groups"),    # 34, 22 and 16
+    ([86, 145, 88], 32, 8, 3, 4, "four_waves"),       # 14, 11 and 17
+    ([91, 146, 79], 64, 4, 10, 6, "eight_waves"),     # 27, 29 and 47
 ])
 def test_the_split_that_was_measured_shortest(docs, hq, hkv, step, steps, split):
     assert forward_split(docs, hq, hkv, 64, "bf16", step, steps)[0] == split
