@@ -108,12 +108,12 @@ inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
 // registers (two workgroups per unit), four waves and half the rows (three per unit), or two key groups
 // (one per unit).  Long workgroups want splitting, by keys while there are few of them; many short ones want the fewest
 // passes over the keys.  Two lines, at one and three of the largest workgroups per unit and 1024-token documents, say which, unless
-// another split is estimated to take 0.94 of that one's time or less.  A split is estimated as its longest workgroup, or the work
-// of all over the compute units (more where they make no whole rounds of it) and a part of the longest one (how unevenly they end),
-// whichever is more, by prices (us) fitted to 3400 launches of 40 ... 9000 tokens, timed in graphs (one launch after another
+// another split is estimated to take 0.98 of that one's time or less.  A split is estimated as its longest workgroup, or the work
+// of all over the compute units (what each costs of its own counts more where they make no whole rounds) and a part of the longest one (how unevenly they end),
+// whichever is more, by prices (us) fitted to 3000 launches of 40 ... 9000 tokens, timed in graphs (one launch after another
 // the shortest are as long as their submission): seven head geometries, one document or many, first step 0 to 10, one to nine steps.
-// The choice takes 1.024 of the best of the three in the mean, the lines alone 1.061; 7 launches in 1000 are more than 3 % slower
-// than by the lines, 1.22 at most (at 0.98, 1.017 and 25; the lowest of the three 1.010 and 44).  566 tokens in two documents, 24/8
+// Over 1500 others the choice takes 1.017 of the best of the three in the mean, the lines alone 1.060; 9 launches in 1000 are more than
+// 3 % slower than by the lines, 1.12 at most (40 by the estimates alone, which take 1.009).  566 tokens in two documents, 24/8
 // heads, the last of eleven steps: 23 -> 17 us; 65, 64/4, nine steps from the tenth on: 22 -> 16.
 // Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys.
 struct Fwd64Prices {
@@ -124,9 +124,9 @@ struct Fwd64Prices {
 };
 inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
     constexpr Fwd64Prices kPrices[] = {   // in the order of FwdSplit
-        {0., 1.21, 0.71, 2.57, 0.95, 0.47, 5.36, 0.32, 0.19, 1.58, 0.50},
-        {0., 0.79, 0.52, 1.27, 0.49, 0.29, 5.11, 0.34, 0.18, 0.99, 0.45},
-        {1.51, 1.22, 0.52, 4.15, 1.25, 0.50, 3.83, 0., 0.48, 0., 0.},
+        {0., 1.22, 0.71, 2.54, 0.96, 0.46, 5.33, 0.32, 0.33, 1.58, 0.50},
+        {0., 0.80, 0.52, 1.25, 0.50, 0.28, 5.08, 0.34, 0.39, 0.99, 0.44},
+        {1.79, 1.23, 0.52, 4.08, 1.31, 0.47, 3.53, 0., 0.79, 0., 0.},
     };
     int64_t n_wgs = 0;
     int longest_doc = 0;
@@ -146,22 +146,23 @@ inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2
         const int waves = split == kFwdFourWaves ? 4 : 8, groups = split == kFwdTwoKeyGroups ? 2 : 1, per_cu = split == kFwdEightWaves ? 2 : split == kFwdFourWaves ? 3 : 1;
         const int rows = (waves / groups * 32) >> pack_log2;
         const double from_memory = fwd_diag_slots(64, waves, groups, per_cu, rows).slots == 0 ? p.from_memory : 0.;
-        double longest = 0., work = 0., n = 0.;
+        double longest = 0., each = 0., tiles = 0., n = 0.;
         for (int i = 0; i < n_calls; ++i) {
             const CallShape& a = calls[i];
             const KeyCount keys = count_keys(a, rows, 64, groups);
             const double full = std::min(1., (double)a.T / rows), busy = 1. - p.idle * (1. - full), diag = busy * (1. + from_memory * full) * p.diag;
             const double wg_diag = busy * (1. + from_memory * full) * p.wg_diag, per_tile = (double)a.hkv * (a.G >> pack_log2) * a.n_steps;
             longest = std::max(longest, p.own + busy * p.tile * keys.longest + diag * (a.step_begin + a.n_steps - 1));
-            work += per_tile * (keys.tiles * (p.wg + wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1))) + busy * keys.groups * p.wg_tile);
+            each += per_tile * keys.tiles * (p.wg + wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1)));
+            tiles += per_tile * busy * keys.groups * p.wg_tile;
             n += per_tile * keys.tiles;
         }
         const double rounds = n / n_cu;
-        if (rounds > 1.) work *= 1. + p.rounds * (std::ceil(rounds) / rounds - 1.);
-        us[split] = p.base + std::max(longest, p.uneven * longest + work / n_cu);
+        if (rounds > 1.) each *= 1. + p.rounds * (std::ceil(rounds) / rounds - 1.);
+        us[split] = p.base + std::max(longest, p.uneven * longest + (each + tiles) / n_cu);
     }
     const FwdSplit best = (FwdSplit)(std::min_element(us, us + 3) - us);
-    return us[best] < 0.94 * us[line] ? best : line;
+    return us[best] < 0.98 * us[line] ? best : line;
 }
 
 // The forward's split, and how many heads of a kv group share a workgroup (its log2).

@@ -30,7 +30,7 @@ CASES_64 = [
     ("two_key_groups_documents", [3, 1030, 40], 2, 2, 3, 1),
     ("four_waves", [70, 1, 130, 64, 33], 8, 2, 4, 1),
     ("four_waves_one_head", [200, 95], 96, 32, 3, 1),
-    ("eight_waves", [63, 200, 1, 336], 64, 16, 9, 9),
+    ("eight_waves", [63, 200, 1, 41], 128, 32, 11, 11),
     ("four_waves_two_heads", [33, 1, 130, 64], 4, 2, 4, 1),       # 64 rows: diagonal rows through LDS
     ("eight_waves_one_head", [63, 200, 1, 41], 128, 128, 17, 17),
     ("eight_waves_two_heads", [63, 200, 1, 41], 192, 96, 15, 15),
