@@ -290,6 +290,7 @@ template <typename F> void for_units_of_an_xcd(int hkv, int64_t n_units, F&& f) 
 // all units per call: 0.36, 5.2 and 590).
 //
 // other_us: what the other slices of the same launch take of an XCD's compute units, in all; it is taken to fill them evenly.
+// limit: only options that end sooner count.  only: this one counts.
 struct BwdPrices {   // us
     float step, unit, empty;        // of a dK/dV unit: per step, of its own; one that no row sees
     float tile, diag, own;          // of a dQ tile: per 128-key tile, per diagonal key, of its own
@@ -304,7 +305,7 @@ constexpr int kDiagRegBlocks = 7, kDiagRegBlocksF32 = 3;   // later blocks whose
 inline int diag_passes(const CallShape& a, int per_pass) { return std::max(1, (a.step_begin + a.n_steps - 2 + per_pass) / per_pass); }
 
 inline BwdDeal deal_bwd(const CallShape& a, int n_cu, double other_us, const BwdPrices& price, int q_rows, bool short_launch,
-                        int later_rows = 1, double limit = -1.) {
+                        int later_rows = 1, double limit = -1., const DkvPlan* only = nullptr) {
     const int T = a.T, n_jh = a.n_steps * a.G;
     const int n_tiles = (T + 127) / 128, n_tiles_q = (T + q_rows - 1) / q_rows;
     const float kStepUs = price.step, kUnitUs = price.unit, kEmptyUs = price.empty;
@@ -351,6 +352,7 @@ inline BwdDeal deal_bwd(const CallShape& a, int n_cu, double other_us, const Bwd
     std::vector<Option> options;
     for (int log2_cb = 3; log2_cb <= 7; ++log2_cb) {
         const int cb = 1 << log2_cb;
+        if (only && cb != only->chunk_blocks) continue;
         if (cb > 32 && n_jh > 8) break;
         if (cb > 16 && few_heads) break;
         if (cb > 8 && cb * 16 >= T) break;    // one chunk covers everything already
@@ -368,6 +370,7 @@ inline BwdDeal deal_bwd(const CallShape& a, int n_cu, double other_us, const Bwd
         }
         const int64_t units = dkv_units_of(T, n_tiles, cb);
         for (int ns : {1, 2, 3, 4, 6, 8, 12, 16, 24}) {
+            if (only && ns != only->n_split) continue;
             if (ns > 8 && !short_launch) break;
             if (ns > n_jh || units * ns * a.hkv > 0x7fffffff) break;   // (more workgroups than a grid has)
             const double work = share * (blocks * n_jh * kStepUs + ns * (used * kUnitUs + ((double)units - used) * kEmptyUs));
@@ -381,7 +384,7 @@ inline BwdDeal deal_bwd(const CallShape& a, int n_cu, double other_us, const Bwd
     DkvPlan best{16, 1};
     if (!options.empty()) best = DkvPlan{options[0].cb, options[0].ns};
     double best_us = -1., dealt = 0.;
-    if (limit >= 0.) {   // only options that end sooner count
+    if (limit >= 0.) {
         best_us = limit;
         best = DkvPlan{0, 0};
     }
@@ -470,8 +473,12 @@ inline double bwd_slice_us(const CallShape& a, int head_dim) {
 // The prices are fitted to all splits (chunk size, list split up to 24, key groups) of 2097 launches of up to 1600 dQ tiles: 64 ...
 // 4096 tokens in one document or many, seven head geometries, one step a call (the first to the ninth) or two to eight at once.
 // Whole backward over the best split of each, in the mean, head_dim 128 / 64: 1.023 / 1.027; with the prices above and one key group 1.128 / 1.105,
-// with the best split of one key group 1.047 / 1.038.  Four in a hundred are more than 3 % slower than with the prices above (1.24 at
-// most).  1320 tokens, 8/1 heads of 64, the last of eight steps, forward and backward 63.9 -> 50.9 us; 493 tokens, 12/2 heads, five steps one
+// with the best split of one key group 1.047 / 1.038.  The best one by these prices was 0.95 of the split by the prices above in the mean,
+// and more than 3 % slower in seven launches of a hundred, mostly with several steps (fewer rounds of longer units, and closer to each other).
+// There the split by the prices above stays unless two key groups, or with head_dim 128 another split with one, are estimated at 0.91
+// of it.  1500 other launches, timed in graphs, take 0.938 / 0.959 of the time by the prices above in the mean (head_dim 128 / 64);
+// 20 and 23 in a thousand are more than 3 % slower, 1.17 and 1.15 at most.
+// 1320 tokens, 8/1 heads of 64, the last of eight steps, forward and backward 63.9 -> 50.9 us; 493 tokens, 12/2 heads, five steps one
 // by one 200 -> 179.  Launches of several slices keep the prices above (1154 tokens in eight slices: 3 % slower with these).
 constexpr int kShortLaunchTiles = 1600, kShortLaunchTokens = 4096;
 inline BwdPrices short_launch_prices(int head_dim, int dq_groups) {
@@ -486,11 +493,26 @@ struct ShortPlan {
 inline ShortPlan plan_short_bwd(const CallShape& a, int head_dim, int n_cu) {
     ShortPlan best{0, {}};
     if (a.T > kShortLaunchTokens || (int64_t)((a.T + 255) / 256) * a.n_steps * a.G * a.hkv > kShortLaunchTiles) return best;
-    double best_us = -1.;
-    for (int groups = 1; groups <= 2; ++groups) {
-        const BwdDeal d = deal_bwd(a, n_cu, 0., short_launch_prices(head_dim, groups), 256 / groups, true, 512 / (head_dim / 8), best_us);
-        if (d.us < 0.) continue;
-        best_us = d.us;
+    const int later_rows = 512 / (head_dim / 8);
+    double limit = -1.;
+    int64_t most = INT64_MAX;   // workgroups of the launch
+    auto workgroups = [&](const DkvPlan& p, int q_rows) {
+        const int64_t later = ((int64_t)a.T * a.hkv + later_rows - 1) / later_rows * diag_passes(a, kDiagRegBlocks);
+        return later + dkv_units_of(a.T, (a.T + 127) / 128, p.chunk_blocks) * p.n_split * a.hkv + (int64_t)((a.T + q_rows - 1) / q_rows) * a.n_steps * a.G * a.hkv;
+    };
+    if (a.n_steps > 1) {
+        const DkvPlan first = plan_dkv_split(a, head_dim, n_cu);   // the split that another one has to beat
+        limit = 0.91 * deal_bwd(a, n_cu, 0., short_launch_prices(head_dim, 1), 256, true, later_rows, -1., &first).us;
+        // While it has a compute unit for every workgroup, so has the other one: a second round starts when all of the first one end,
+        // which the prices do not tell (666 tokens, 8/1 heads, four steps 45 -> 61 us; such launches 1.11 of the time in the mean, with one step 0.86)
+        if (workgroups(first, 256) <= n_cu) most = n_cu;
+        best = ShortPlan{1, first};
+        if (limit < 0.) return best;
+    }
+    for (int groups = a.n_steps > 1 && head_dim == 64 ? 2 : 1; groups <= 2; ++groups) {
+        const BwdDeal d = deal_bwd(a, n_cu, 0., short_launch_prices(head_dim, groups), 256 / groups, true, later_rows, limit);
+        if (d.us < 0. || workgroups(d.plan, 256 / groups) > most) continue;
+        limit = d.us;
         best = ShortPlan{groups, d.plan};
     }
     return best;

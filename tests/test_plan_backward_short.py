@@ -17,7 +17,6 @@ from plan_lib import _cu, backward_launch, backward_split
     ([403, 227], 32, 8, 128, 3, 7, 1),      # 147 and 159
     ([168], 24, 8, 128, 0, 5, 1),           # 28 and 30
     ([666], 8, 1, 128, 4, 4, 1),            # 45 and 61
-    ([283], 8, 1, 64, 0, 8, 1),             # 51 and 59
 ])
 def test_another_split_only_where_it_gains(docs, hq, hkv, d, step, steps, groups):
     *split, dq_groups = backward_launch(docs, hq, hkv, d, step, steps)
