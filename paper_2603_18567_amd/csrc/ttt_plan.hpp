@@ -203,8 +203,11 @@ struct F32FwdPrices {
 // Whether an fp32 forward takes its operands straight from memory (ttt_fwd_f32_kernel: 32 rows of one head per workgroup, eight waves
 // that take the key blocks in turn) or through LDS tiles, as `tiled` says.  Each is estimated as its longest workgroup, or
 // the work of all over the compute units, by prices (us) fitted to 2863 launches of 32 ... 2500 tokens, eight head geometries, one step or up to
-// eight at once: in the mean the choice takes 1.003 / 1.002 of the better one (head_dim 64 / 128), tiles alone 1.35 / 1.96,
+// eight at once: in the mean the lower estimate takes 1.003 / 1.002 of the better one (head_dim 64 / 128), tiles alone 1.35 / 1.96,
 // memory alone 1.030 / 1.013.  Few or long workgroups want the first, many rounds of the device with four heads to a tile the second.
+// Beyond those sizes tiles are better than estimated by a few percent (8963 tokens, 64/4 heads of 64, one step 5995 against 6393 us), so
+// memory has to be estimated at 0.95: over 1100 launches of 150 ... 16384 tokens 0.878 / 0.767 of the time of tiles in the mean, 11 of them more than
+// 3 % slower (0.876 / 0.762 and 87 by the lower estimate).
 // kv_st: elements from row to row, a multiple of 8; a lane's place in a row or the fourth after it is a 32-bit byte offset.
 inline bool fwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int n_cu, const FwdPlan& tiled, int64_t kv_st) {
     if (kv_st >= (int64_t)1 << 28) return false;
@@ -222,7 +225,7 @@ inline bool fwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, in
         t_long = std::max(t_long, t.own + t.chain * nt.longest + t.diag * j_max);
         t_work += heads / (1 << tiled.pack_log2) * (nt.tiles * (t.tile + t.tile_diag * j_mean) + (groups == 1 ? nt.groups * t.block : 0.));
     }
-    return std::max(m_long, m.base + m_work / n_cu) < std::max(t_long, t.base + t_work / n_cu);
+    return std::max(m_long, m.base + m_work / n_cu) < 0.95 * std::max(t_long, t.base + t_work / n_cu);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -22,7 +22,7 @@ CASES = [
     ([20, 30] * 35, 4, 1, 128, 2, 1, (True, True)),       # bounds per token
     ([700], 4, 1, 64, 2, 2, (True, True)),
     ([40] * 40, 64, 4, 64, 2, 2, (False, True)),
-    ([512, 40], 16, 16, 128, 6, 6, (True, False)),
+    ([512, 8], 16, 16, 128, 6, 6, (True, False)),
     ([530], 32, 8, 128, 3, 3, (False, False)),
 ]
 
@@ -39,7 +39,8 @@ def passes(run, d_o, k, steps):
 def test_f32_matches_oracle(docs, hq, hkv, d, k, steps, direct):
     n_cu = torch.cuda.get_device_properties(0).multi_processor_count
     print(f"documents={docs} heads={hq}/{hkv} head_dim={d} k={k} steps={steps}", flush=True)
-    assert all(f32_direct(docs, hq, hkv, d, j, steps, n_cu) == direct for j in range(0, k, steps))
+    ways = [f32_direct(docs, hq, hkv, d, j, steps, n_cu) for j in range(0, k, steps)]
+    assert ways == (direct if isinstance(direct, list) else [direct] * len(ways))
     case = Case(custom_workload(f"f32_direct_{sum(docs)}_{d}", "f32", docs, hq, hkv, d, k, seed=sum(docs) + k), "cuda:0")
     for t in case.run.o + case.run.lse:
         t.fill_(float("nan"))

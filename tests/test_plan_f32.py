@@ -14,3 +14,15 @@ def test_offsets_hold_in_32_bits(d):
         assert not forward or 4 * st * 4 + 31 * 4 < 1 << 32
         assert not backward or 31 * st * 4 + d * 4 <= 1 << 32
     assert f32_direct([40], 2, 1, d, 0, 1, q_st=1 << 28) == (True, False)   # (the forward reads rows of Q at 64-bit addresses)
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,step,steps,forward", [
+    ([476], 8, 1, 64, 2, 1, True),
+    ([444], 8, 2, 128, 6, 1, True),         # tiles 113 us, memory 37
+    ([8963], 64, 4, 64, 1, 1, False),       # 5995 and 6393
+    ([4824], 64, 4, 64, 3, 1, False),       # 1822 and 1962
+    ([3811], 32, 8, 64, 6, 5, False),       # 3059 and 3263
+    ([5450], 32, 8, 64, 4, 3, False),       # 3514 and 3726
+])
+def test_forward_s_way_that_was_measured_shorter(docs, hq, hkv, d, step, steps, forward):
+    assert f32_direct(docs, hq, hkv, d, step, steps)[0] == forward
