@@ -639,19 +639,27 @@ inline int plan_dkv_f32_direct(const CallShape& a, int head_dim, int n_cu, doubl
     }
     return best;
 }
-// Tiles through LDS (ttt_bwd_main_f32_kernel) are 0 to 6 % faster in the mean with head_dim 128, 512 tokens or more in a document and
-// work for many rounds of the device (99 of those launches; 2000 tokens, 32/8 heads, two steps 2391 against 2610 us); elsewhere operands
-// from memory take 0.64 of their time in the mean with head_dim 128, 0.75 with 64 (444 tokens, 8/2 heads, the last of seven steps 129 -> 63).
+// Over 1100 launches of 150 ... 16384 tokens operands from memory take 0.863 / 0.855 of the time of tiles through LDS
+// (ttt_bwd_main_f32_kernel) in the mean (head_dim 64 / 128; 444 tokens, 8/2 heads of 128, the last of seven steps 129 -> 63 us), but tiles are
+//  - 5 to 13 % faster with head_dim 128, 512 tokens or more in a document and work for many rounds of the device (2000 tokens, 32/8 heads,
+//    two steps 2391 against 2610 us);
+//  - 3 to 14 % faster where a unit of 32 keys has one (step, head) pair and diagonal keys beside, and there are many units: few
+//    items share what a unit costs of its own (head_dim 64, 16/16 heads, a later step: 7658 tokens in documents of 114 in the mean 363 against
+//    394 us; with documents of 3000 and more the items of a unit are many, and 0.98).
+// Elsewhere 20 of the launches are more than 3 % slower than with tiles, 1.15 at most.
 // q_st, kv_st: elements from row to row; the 32 rows of a block are told apart by 32-bit byte offsets.
 inline bool bwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, int64_t q_st, int64_t kv_st) {
     if (std::max(q_st, kv_st) >= (int64_t)1 << 25) return false;
     int64_t tiles = 0;
     int longest = 0;
+    bool one_pair = calls[0].step_begin > 0;
     for (int i = 0; i < n_calls; ++i) {
         const CallShape& a = calls[i];
         tiles += (int64_t)((a.T + 31) / 32) * a.hkv * a.G * a.n_steps;
+        one_pair = one_pair && a.G * a.n_steps == 1;
         for (int r = 0; r < a.n_docs; ++r) longest = std::max(longest, a.cu_host[r + 1] - a.cu_host[r]);
     }
+    if (one_pair && tiles >= 800 && (head_dim == 128 || longest < 2500)) return false;
     return head_dim == 64 || tiles < 1500 || longest < 512;
 }
 

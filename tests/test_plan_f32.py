@@ -26,3 +26,17 @@ def test_offsets_hold_in_32_bits(d):
 ])
 def test_forward_s_way_that_was_measured_shorter(docs, hq, hkv, d, step, steps, forward):
     assert f32_direct(docs, hq, hkv, d, step, steps)[0] == forward
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,step,steps,backward", [
+    ([476], 8, 1, 64, 2, 1, True),          # tiles 70 us, memory 28
+    ([444], 8, 2, 128, 6, 1, True),         # 129 and 63
+    ([14883], 16, 16, 64, 0, 1, True),      # 15056 and 14700
+    ([16334], 8, 1, 64, 3, 3, True),        # 32152 and 26355
+    ([2000], 32, 8, 128, 0, 2, False),      # 2391 and 2610
+    ([876], 32, 32, 64, 2, 1, False),       # 162 and 182
+    ([153] * 104, 16, 16, 64, 1, 1, False),     # 817 and 879
+    ([1093], 32, 32, 128, 5, 1, False),     # 569 and 613
+])
+def test_backward_s_way_that_was_measured_shorter(docs, hq, hkv, d, step, steps, backward):
+    assert f32_direct(docs, hq, hkv, d, step, steps)[1] == backward
