@@ -22,7 +22,7 @@ CASES = [
     ([20, 30] * 35, 4, 1, 128, 2, 1, (True, True)),       # bounds per token
     ([700], 4, 1, 64, 2, 2, (True, True)),
     ([40] * 40, 64, 4, 64, 2, 2, (False, True)),
-    ([512, 8], 16, 16, 128, 6, 6, (True, False)),
+    ([513, 1, 6], 16, 16, 128, 6, 6, (True, False)),
     ([300, 64, 1, 500], 32, 32, 64, 2, 1, [(True, True), (True, False)]),   # one (step, head) pair: the later step's backward
     ([530], 32, 8, 128, 3, 3, (False, False)),
 ]
