@@ -1900,6 +1900,8 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         constexpr int LDS_DIRECT = BwdF32<D>::kLds;
         constexpr int LDS_KEY_GROUPS = !k16 && D == 64 ? 2 * LDS_Q : LDS;   // fp32 dQ tiles with two key groups
         DkvPlan plans[N];
+        int direct_split[N];
+        if (direct) plan_dkv_f32_direct(shapes, n_slices, D, n_cu, direct_split);
         if constexpr (k16) a.dq_key_groups = plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
         else a.dq_key_groups = !direct && D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
         void (*kern)(BwdArgs<N>);
@@ -1926,10 +1928,7 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
                 sl.n_split = plans[i].n_split;
                 n_units = dkv_units_of(shapes[i].T, n_tiles, sl.chunk_blocks);
             } else if (direct) {
-                double other = 0.;
-                for (int o = 0; o < n_slices; ++o)
-                    if (o != i) other += f32_bwd_dq_work(shapes[o], D, count_keys(shapes[o], 32, 32, 4));
-                sl.n_split = plan_dkv_f32_direct(shapes[i], D, n_cu, other);
+                sl.n_split = direct_split[i];
             } else {
                 const DkvPlanF32 plan = plan_dkv_split_f32(shapes[i], n_cu);
                 sl.n_split = plan.n_split;

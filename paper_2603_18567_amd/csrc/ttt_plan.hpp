@@ -589,7 +589,7 @@ inline bool bwd_slice_alone(const CallShape& a, int head_dim, int n_cu) {
 // The fp32 backward with operands straight from memory (ttt_bwd_f32_kernel): ways to split the (step, head, query block) items of a
 // 32-key unit.  Estimated as the longest chain of a wave, or the work of all over the compute units and 0.15 of that chain (how
 // unevenly they end), by prices (us) fitted to all splits of the 2863 launches of fwd_f32_direct: 1.013 / 1.011 of the best split in the mean
-// (head_dim 64 / 128).  `other`: the work of the other slices of the launch.
+// (head_dim 64 / 128).  Slices that share a launch count each other's dQ tiles and later blocks as work.
 struct F32BwdPrices {
     double unit, step, tile, group, diag;                        // the chains: a unit and four of its items, a dQ tile, four of its key blocks, a diagonal key
     double later, unit_work, step_work, tile_work, group_work, diag_work;
@@ -614,12 +614,11 @@ inline double f32_bwd_dq_work(const CallShape& a, int head_dim, const KeyCount& 
     const double heads = (double)a.hkv * a.G * a.n_steps, later = a.step_begin + a.n_steps > 1 ? (double)a.T * a.hkv * head_dim / 2048. * a.n_steps * a.G : 0.;
     return heads * (n.tiles * (p.tile_work + p.diag_work * (a.step_begin + 0.5 * (a.n_steps - 1))) + n.groups * p.group_work) + later * p.later;
 }
-inline int plan_dkv_f32_direct(const CallShape& a, int head_dim, int n_cu, double other) {
+inline int f32_direct_split(const CallShape& a, int head_dim, int n_cu, const KeyCount& keys, double dq_work) {
     const F32BwdPrices p = f32_bwd_prices(head_dim);
-    const KeyCount keys = count_keys(a, 32, 32, 4);
     const std::vector<int> blocks = f32_query_blocks(a);
     const int64_t n_jh = (int64_t)a.n_steps * a.G;
-    const double dq_chain = p.tile + p.group * keys.longest + p.diag * (a.step_begin + a.n_steps - 1), dq_work = other + f32_bwd_dq_work(a, head_dim, keys);
+    const double dq_chain = p.tile + p.group * keys.longest + p.diag * (a.step_begin + a.n_steps - 1);
     int best = 1;
     double best_us = -1.;
     for (int ns : {1, 2, 3, 4, 6, 8, 12, 16, 24}) {
@@ -638,6 +637,15 @@ inline int plan_dkv_f32_direct(const CallShape& a, int head_dim, int n_cu, doubl
         }
     }
     return best;
+}
+inline void plan_dkv_f32_direct(const CallShape* calls, int n_calls, int head_dim, int n_cu, int* n_split) {
+    std::vector<KeyCount> keys(n_calls);
+    double dq_work = 0.;
+    for (int i = 0; i < n_calls; ++i) {
+        keys[i] = count_keys(calls[i], 32, 32, 4);
+        dq_work += f32_bwd_dq_work(calls[i], head_dim, keys[i]);
+    }
+    for (int i = 0; i < n_calls; ++i) n_split[i] = f32_direct_split(calls[i], head_dim, n_cu, keys[i], dq_work);
 }
 // Over 1100 launches of 150 ... 16384 tokens operands from memory take 0.863 / 0.855 of the time of tiles through LDS
 // (ttt_bwd_main_f32_kernel) in the mean (head_dim 64 / 128; 444 tokens, 8/2 heads of 128, the last of seven steps 129 -> 63 us), but tiles are
