@@ -65,7 +65,6 @@ struct BwdSlice {
     int finish_first, finish_blocks;   // of its block-0 results in the last launch
     int kv_rest, q_rest;    // work items per kv head
     int n_split;            // dK/dV: ways the (step, head) list of one kv tile is split
-    int q_split;            // dK/dV (fp32): ways the query rows of one kv tile are split
     int n_units;            // dK/dV (16-bit): (key tile, query chunk) units per kv head and split
     int chunk_blocks;       // dK/dV (16-bit): 32-row query blocks per chunk (a multiple of 4)
     int diag_units;         // workgroups that make the later blocks' dK, dV,
@@ -79,7 +78,6 @@ struct BwdCommon {
     int pre_blocks;         // workgroups of the preprocess launch that do its main work; after them:
     int bounds_blocks;      // those that write tok_start, tok_end; and the rest clear the block-0 sums
     int64_t clear_n4;       // 16-byte pieces of each block-0 sum to clear
-    int dq_key_groups;      // key groups of a dQ tile, 1 or 2 (fp32: head_dim 64 only)
     int accumulate;         // 0/1
     int carry_reset;        // accumulate mode: this call starts the sweep (carry is overwritten, not read)
     int* tok_start;         // [T] first token of each token's document

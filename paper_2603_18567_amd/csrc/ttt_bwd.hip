@@ -272,26 +272,22 @@ __global__ __launch_bounds__(256) void ttt_bwd_pre_regs_kernel(const BwdArgs<N> 
 // ------------------------------------------------------------------------------------------------
 // dQ: query-stationary
 // ------------------------------------------------------------------------------------------------
-// fp32.  With two key groups (KS = 2) the halves of a workgroup take every second key tile (and diagonal key) of the same
-// rows and add up in LDS: fp32 matrix instructions are slow, and a short launch lasts as long as one wave's tiles
-// (dq_two_key_groups).
-template <typename T, int D, int QB, int NW, int KS>
+// fp32, with tiles in LDS
+template <typename T, int D, int QB, int NW>
 TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const int wg) {
     using E = Elem<T>;
     using frag = typename E::frag;
     constexpr int KT = 64;
     constexpr int KB = KT / 32;
-    constexpr int NWG = NW / KS;   // waves of a key group
-    constexpr int QT = NWG * QB * 32;
+    constexpr int QT = NW * QB * 32;
     constexpr int DC = D / 16;
     constexpr int DB = D / 32;
     constexpr int NT = NW * 64;
     constexpr int TILE_BYTES = KT * D * E::kBytes;
 
-    // LDS of a key group: K stage 0, K stage 1, V stage 0, V stage 1
-    constexpr int GROUP_BYTES = 4 * TILE_BYTES;
-    auto sK = [&](int s, int group) -> char* { return smem + group * GROUP_BYTES + s * TILE_BYTES; };
-    auto sV = [&](int s, int group) -> char* { return smem + group * GROUP_BYTES + (2 + s) * TILE_BYTES; };
+    // LDS: K stage 0, K stage 1, V stage 0, V stage 1
+    auto sK = [&](int s) -> char* { return smem + s * TILE_BYTES; };
+    auto sV = [&](int s) -> char* { return smem + (2 + s) * TILE_BYTES; };
 
     const Geometry& geo = a.geo;
     int g, rest;
@@ -307,8 +303,7 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
     const int q_tile0 = t0 + tile * QT;
-    const int kg = KS == 1 ? 0 : wave / NWG, gwave = wave % NWG;   // key group, wave within it
-    const int wq0 = q_tile0 + gwave * (QB * 32);
+    const int wq0 = q_tile0 + wave * (QB * 32);
     const bool active = wq0 < Tn;
 
     const T* Qj = static_cast<const T*>(a.q[j]) + (int64_t)h * geo.q_sh;
@@ -351,24 +346,20 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
             for (int i = 0; i < 16; ++i) dqacc[qb][db][i] = 0.f;
     const float c = geo.scale_log2;
 
-    auto load = [&](int s, int u0) {   // tiles u0 ... of the key groups
-#pragma unroll
-        for (int x = 0; x < KS; ++x) {
-            if (KS > 1 && u0 + x > u_hi) break;
-            tile_load_async<T, D, KT, NT>(sK(s, x), K0, geo.kv_st, t0 + (u0 + x) * KT, Tn - 1, tid);
-            tile_load_async<T, D, KT, NT>(sV(s, x), V0, geo.kv_st, t0 + (u0 + x) * KT, Tn - 1, tid);
-        }
+    auto load = [&](int s, int u) {
+        tile_load_async<T, D, KT, NT>(sK(s), K0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
+        tile_load_async<T, D, KT, NT>(sV(s), V0, geo.kv_st, t0 + u * KT, Tn - 1, tid);
     };
     load(0, u_lo);
     int stage = 0;
-    for (int u = u_lo; u <= u_hi; u += KS) {
+    for (int u = u_lo; u <= u_hi; ++u) {
         wait_async_copies();
         __syncthreads();
-        if (u + KS <= u_hi) load(stage ^ 1, u + KS);
-        const int kv0 = t0 + (u + kg) * KT;
+        if (u < u_hi) load(stage ^ 1, u + 1);
+        const int kv0 = t0 + u * KT;
         if (active && kv0 <= hi_w && kv0 + KT - 1 >= lo_w) {
-            const char* tk = sK(stage, kg);
-            const char* tv = sV(stage, kg);
+            const char* tk = sK(stage);
+            const char* tv = sV(stage);
             f32x16 sacc[KB][QB], pacc[KB][QB];
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb)
@@ -420,10 +411,10 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
         }
         stage ^= 1;
     }
-    if (KS == 1 && !active) return;
+    if (!active) return;
 
     // diagonal keys of blocks 1..j
-    for (int lb = 1 + kg; lb <= j; lb += KS) {
+    for (int lb = 1; lb <= j; ++lb) {
         const T* Kl = static_cast<const T*>(a.k[lb]) + (int64_t)g * geo.kv_sh;
         const T* Vl = static_cast<const T*>(a.v[lb]) + (int64_t)g * geo.kv_sh;
 #pragma unroll
@@ -455,35 +446,6 @@ TTT_DEV void dq_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const i
                         dqacc[qb][db][i4 * 4 + x] = fmaf(ds, to_f32<T>(kk[x]), dqacc[qb][db][i4 * 4 + x]);
                 }
         }
-    }
-
-    if constexpr (KS == 2) {
-        // the second group's rows join the first one's: 16-byte pieces of the same lane of wave gwave
-        static_assert(NWG * QB * DB * 4 * 1024 <= KS * GROUP_BYTES, "one group's rows fit in the tile stages");
-        f32x4* piece = reinterpret_cast<f32x4*>(smem) + gwave * (QB * DB * 4 * 64) + lane;
-        __syncthreads();   // everybody is done with the tile stages
-        if (kg == 1) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4)
-                        piece[((qb * DB + db) * 4 + i4) * 64] = f32x4{dqacc[qb][db][4 * i4], dqacc[qb][db][4 * i4 + 1],
-                                                                      dqacc[qb][db][4 * i4 + 2], dqacc[qb][db][4 * i4 + 3]};
-        }
-        __syncthreads();
-        if (kg == 1 || !active) return;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int i4 = 0; i4 < 4; ++i4) {
-                    const f32x4 o4 = piece[((qb * DB + db) * 4 + i4) * 64];
-#pragma unroll
-                    for (int x = 0; x < 4; ++x) dqacc[qb][db][4 * i4 + x] += o4[x];
-                }
     }
 
 #pragma unroll
@@ -913,9 +875,7 @@ TTT_DEV void dkv_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const 
     int g, rest;
     if (!decode_block(a.map, sl.kv_rest, wg, g, rest)) return;
     const int sp = rest % sl.n_split;
-    rest /= sl.n_split;
-    const int part = rest % sl.q_split;
-    const int tile = rest / sl.q_split;   // low tiles of a document have the longest query range: first
+    const int tile = rest / sl.n_split;   // low tiles of a document have the longest query range: first
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 31, hh = lane >> 5;
@@ -927,9 +887,7 @@ TTT_DEV void dkv_tile(const BwdCommon& a, const BwdSlice& sl, char* smem, const 
     // query rows that can see this workgroup's / this wave's keys
     const int q_end = __builtin_amdgcn_readfirstlane(a.tok_end[min(kv_tile0 + KVT - 1, Tn - 1)]);
     const int wq_end = active ? __builtin_amdgcn_readfirstlane(a.tok_end[wk_hi]) : 0;
-    const int qt_first = tile * (KVT / QTL), qt_all = (q_end - 1 - t0) / QTL - qt_first + 1;   // query tiles, counted from t0
-    const int qt_lo = qt_first + qt_all * part / sl.q_split;   // this workgroup's part of them
-    const int nqt = qt_first + qt_all * (part + 1) / sl.q_split - qt_lo;
+    const int qt_lo = tile * (KVT / QTL), nqt = (q_end - 1 - t0) / QTL - qt_lo + 1;   // query tiles, counted from t0
     if (nqt <= 0) return;
     const int n_jh = sl.n_steps * geo.G;
     const int n_c = (n_jh - sp + sl.n_split - 1) / sl.n_split;   // (step, head) pairs of this split
@@ -1515,16 +1473,8 @@ __global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs<N> 
         return;
     }
     const BwdSlice& sl = slice_of(a, &BwdSlice::kv_first, wg);
-    if (wg < sl.q_first) {
-        dkv_tile<T, D, 4>(a, sl, smem, wg - sl.kv_first);
-        return;
-    }
-    if constexpr (D == 64)
-        if (a.dq_key_groups == 2) {
-            dq_tile<T, D, 1, 4, 2>(a, sl, smem, wg - sl.q_first);
-            return;
-        }
-    dq_tile<T, D, 1, 4, 1>(a, sl, smem, wg - sl.q_first);
+    if (wg < sl.q_first) dkv_tile<T, D, 4>(a, sl, smem, wg - sl.kv_first);
+    else dq_tile<T, D, 1, 4>(a, sl, smem, wg - sl.q_first);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1898,31 +1848,29 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         constexpr int LDS_KV = k16 ? DkvP8<T, D>::kLds : 2 * (2 * 64 * D * (int)sizeof(T) + 3 * 64 * 4);
         constexpr int LDS = LDS_Q > LDS_KV ? LDS_Q : LDS_KV;
         constexpr int LDS_DIRECT = BwdF32<D>::kLds;
-        constexpr int LDS_KEY_GROUPS = !k16 && D == 64 ? 2 * LDS_Q : LDS;   // fp32 dQ tiles with two key groups
         DkvPlan plans[N];
         int direct_split[N];
         if (direct) plan_dkv_f32_direct(shapes, n_slices, D, n_cu, direct_split);
-        if constexpr (k16) a.dq_key_groups = plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
-        else a.dq_key_groups = !direct && D == 64 && dq_two_key_groups(shapes, n_slices, n_cu) ? 2 : 1;
+        int dq_key_groups = 1;
+        if constexpr (k16) dq_key_groups = plan_dkv_launch(shapes, n_slices, D, n_cu, plans);
         void (*kern)(BwdArgs<N>);
         if constexpr (!k16) kern = direct ? ttt_bwd_f32_kernel<D, N> : ttt_bwd_main_f32_kernel<T, D, N>;
-        else if constexpr (N == 1) kern = a.dq_key_groups == 2 ? ttt_bwd_main_kernel<T, D, N, 2> : ttt_bwd_main_kernel<T, D, N, 1>;
+        else if constexpr (N == 1) kern = dq_key_groups == 2 ? ttt_bwd_main_kernel<T, D, N, 2> : ttt_bwd_main_kernel<T, D, N, 1>;
         else kern = ttt_bwd_main_kernel<T, D, N, 1>;   // (several slices: one key group)
-        const int lds_most = direct ? LDS_DIRECT : LDS_KEY_GROUPS;
+        const int lds_bytes = direct ? LDS_DIRECT : LDS;
         static LdsOptIn lds_opt_in[2];   // one per kernel
-        if ((e = lds_opt_in[k16 ? a.dq_key_groups - 1 : direct ? 1 : 0].ensure((const void*)kern, lds_most)) != hipSuccess) return e;
+        if ((e = lds_opt_in[dq_key_groups == 2 || direct ? 1 : 0].ensure((const void*)kern, lds_bytes)) != hipSuccess) return e;
         // the 16-bit passes address the pieces of up to 64 rows of K or V and 32 rows of Q or dO with
         // 32-bit byte offsets
         if (k16 && geo.kv_st * 64 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         if (k16 && geo.q_st * 32 * (int64_t)sizeof(T) >= (int64_t)1 << 32) return hipErrorInvalidValue;
         // dK/dV: split the (step, head) list of a unit so that the grid fills the device evenly
-        const int q_rows = direct ? 32 : NW * 32 / a.dq_key_groups, kv_rows = direct ? 32 : KVT;
+        const int q_rows = direct ? 32 : NW * 32 / dq_key_groups, kv_rows = direct ? 32 : KVT;
         int64_t grid = 0;
         for (int i = 0; i < n_slices; ++i) {
             BwdSlice& sl = a.slices[i];
             const int n_tiles = (shapes[i].T + kv_rows - 1) / kv_rows;
             int64_t n_units = n_tiles;   // units per kv head and split: key tiles, or (key tile, query chunk) pairs
-            sl.q_split = 1;
             if constexpr (k16) {
                 sl.chunk_blocks = plans[i].chunk_blocks;
                 sl.n_split = plans[i].n_split;
@@ -1930,10 +1878,7 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
             } else if (direct) {
                 sl.n_split = direct_split[i];
             } else {
-                const DkvPlanF32 plan = plan_dkv_split_f32(shapes[i], n_cu);
-                sl.n_split = plan.n_split;
-                sl.q_split = plan.q_split;
-                n_units *= sl.q_split;
+                sl.n_split = plan_dkv_split_f32(shapes[i]);
             }
             if (n_units * sl.n_split > kMaxGrid) return hipErrorInvalidValue;
             sl.n_units = (int)n_units;
@@ -1958,7 +1903,7 @@ static hipError_t launch_bwd_n(const BwdCommon& common, const Slice* slices, int
         }
         {
             ProfileScope prof(k16 ? "ttt_bwd_main_kernel" : direct ? "ttt_bwd_f32_kernel" : "ttt_bwd_main_f32_kernel", stream);
-            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), direct ? LDS_DIRECT : a.dq_key_groups == 2 ? LDS_KEY_GROUPS : LDS, stream, a);
+            hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NW * 64), lds_bytes, stream, a);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }

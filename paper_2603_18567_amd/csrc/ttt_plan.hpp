@@ -671,33 +671,12 @@ inline bool bwd_f32_direct(const CallShape* calls, int n_calls, int head_dim, in
     return head_dim == 64 || tiles < 1500 || longest < 512;
 }
 
-// The fp32 backward with tiles in LDS: ways to split the (step, head) list of a 128-key tile, and its query rows.
-struct DkvPlanF32 {
-    int n_split, q_split;
-};
-
-inline DkvPlanF32 plan_dkv_split_f32(const CallShape& a, int n_cu) {
+// The fp32 backward with tiles in LDS: ways to split the (step, head) list of a 128-key tile.
+inline int plan_dkv_split_f32(const CallShape& a) {
     const int n_jh = a.n_steps * a.G, n_tiles = (a.T + 127) / 128;
-    DkvPlanF32 p{1, 1};
-    while (p.n_split < n_jh && (int64_t)n_tiles * a.hkv * p.n_split < 2048) ++p.n_split;
-    // a short launch lasts as long as one workgroup's query rows: they are split as well while compute units
-    // are idle (whole backward, one step: 300 tokens, 8/2 heads of 64: 64 -> 47 us, 700 tokens, 8/1 of 128: 236 -> 160)
-    while (p.n_split == n_jh && p.q_split < (a.T + 63) / 64 && (int64_t)n_tiles * a.hkv * p.n_split * (p.q_split + 1) <= n_cu)
-        ++p.q_split;
-    return p;
-}
-
-// The fp32 dQ tiles of head_dim 64 (LDS for one workgroup per compute unit): two key groups and 64 rows while all of them
-// together with the dK/dV units have a compute unit each (the streaming launch of three steps on 128 tokens, 4/4 heads 23.2 ->
-// 18.1 us; forward and backward, 128 tokens, 12/2 heads, one step a call of six 328 -> 218 with the later blocks beside).
-inline bool dq_two_key_groups(const CallShape* calls, int n_calls, int n_cu) {
-    int64_t n = 0;
-    for (int i = 0; i < n_calls; ++i) {
-        const CallShape& a = calls[i];
-        const DkvPlanF32 kv = plan_dkv_split_f32(a, n_cu);
-        n += (int64_t)a.hkv * ((a.T + 127) / 128 * kv.n_split * kv.q_split + (a.T + 63) / 64 * a.n_steps * a.G);
-    }
-    return n <= n_cu;
+    int n_split = 1;
+    while (n_split < n_jh && (int64_t)n_tiles * a.hkv * n_split < 2048) ++n_split;
+    return n_split;
 }
 
 // ------------------------------------------------------------------------------------------------

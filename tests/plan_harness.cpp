@@ -51,17 +51,6 @@ int plan_later_blocks(int T, int step_begin, int n_steps, int G, int hkv, int he
     return ttt::diag_blocks_apart(ttt::CallShape{T, step_begin, n_steps, G, hkv, 0, nullptr, 0}, head_dim, n_cu);
 }
 
-void plan_backward_f32(int T, int n_steps, int G, int hkv, int n_cu, int* n_split, int* q_split) {
-    const ttt::DkvPlanF32 p = ttt::plan_dkv_split_f32(ttt::CallShape{T, 0, n_steps, G, hkv, 0, nullptr, 0}, n_cu);
-    *n_split = p.n_split;
-    *q_split = p.q_split;
-}
-
-int plan_dq_key_groups(int T, int n_steps, int G, int hkv, int n_cu) {
-    const ttt::CallShape shape{T, 0, n_steps, G, hkv, 0, nullptr, 0};
-    return ttt::dq_two_key_groups(&shape, 1, n_cu);
-}
-
 // whether the fp32 passes take their operands straight from memory (q_st, kv_st: elements from row to row)
 void plan_f32_direct(int T, int step_begin, int n_steps, int G, int hkv, int n_docs, const int32_t* cu, int head_dim, int n_cu, int64_t q_st,
                      int64_t kv_st, int* fwd, int* bwd) {

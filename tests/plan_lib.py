@@ -65,16 +65,6 @@ def later_blocks_apart(tokens, hq, hkv, d, step_begin, n_steps, n_cu=256):
     return bool(_lib().plan_later_blocks(tokens, step_begin, n_steps, hq // hkv, hkv, d, n_cu))
 
 
-def backward_split_f32(tokens, hq, hkv, n_steps, n_cu=256):
-    """(parts of the (step, head) list, parts of the query rows)"""
-    return _call(_lib().plan_backward_f32, tokens, n_steps, hq // hkv, hkv, n_cu)
-
-
-def dq_key_groups_f32(tokens, hq, hkv, n_steps, n_cu=256):
-    """key groups of the dQ tiles (head_dim 64)"""
-    return 2 if _lib().plan_dq_key_groups(tokens, n_steps, hq // hkv, hkv, n_cu) else 1
-
-
 def f32_direct(docs, hq, hkv, d, step_begin, n_steps, n_cu=256, q_st=None, kv_st=None):
     """whether the fp32 forward and backward take their operands straight from memory; q_st, kv_st: elements from row to row"""
     cu = _cu(docs)

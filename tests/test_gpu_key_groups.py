@@ -8,7 +8,7 @@ import torch
 
 import oracle as O
 from paper_2603_18567_amd.workloads import custom_workload
-from plan_lib import backward_split_f32, forward_split
+from plan_lib import f32_direct, forward_split
 from ttt_testlib import Case, check, compare_full, to_np32
 
 pytestmark = pytest.mark.gpu
@@ -115,16 +115,25 @@ def run_fp32(docs, hq, hkv, d, k, steps):
 @pytest.mark.parametrize("docs,hq,hkv,d,k,steps", [([128], 4, 4, 64, 3, 3), ([300], 8, 2, 64, 1, 1), ([65, 1, 70], 8, 2, 64, 2, 1),
                                                    ([200, 3], 8, 1, 128, 2, 1), ([250], 3, 1, 64, 1, 1)])
 def test_fp32_short_launches_match_oracle(docs, hq, hkv, d, k, steps):
-    """fp32: two key groups in the forward (head_dim 64), query rows of a key tile split over workgroups in the
-    backward, also into more parts than a tile has query tiles."""
-    assert all(s == ("two_key_groups" if d == 64 else "four_waves") for s, _ in splits_of_calls(docs, hq, hkv, d, "f32", k, steps))
-    assert backward_split_f32(sum(docs), hq, hkv, steps, compute_units())[1] > 1
+    """fp32 with work for few compute units: operands straight from memory in both passes."""
+    assert all(f32_direct(docs, hq, hkv, d, j, steps, compute_units()) == (True, True) for j in range(0, k, steps))
     run_fp32(docs, hq, hkv, d, k, steps)
 
 
-@pytest.mark.parametrize("docs,hq,hkv,d,k", [([150, 1, 82], 16, 16, 64, 5), ([200, 60, 70], 64, 16, 64, 3), ([150, 1, 82], 16, 16, 128, 5)])
-def test_fp32_full_launches_match_oracle(docs, hq, hkv, d, k):
-    """fp32 with work for every compute unit: one key group, query rows in one part."""
+@pytest.mark.parametrize("docs,hq,hkv,k,steps,heads", [([98], 64, 4, 6, 2, 2), ([119, 7, 15], 64, 4, 3, 1, 2), ([46, 152, 101, 21], 24, 8, 6, 2, 1),
+                                                       ([83, 175, 164, 13, 85, 30], 12, 12, 6, 2, 1)])
+def test_fp32_two_key_groups_match_oracle(docs, hq, hkv, k, steps, heads):
+    """fp32, head_dim 64: tiles in LDS in the forward, with two key groups."""
+    for j in range(0, k, steps):
+        assert not f32_direct(docs, hq, hkv, 64, j, steps, compute_units())[0]
+    assert all(x == ("two_key_groups", heads) for x in splits_of_calls(docs, hq, hkv, 64, "f32", k, steps))
+    run_fp32(docs, hq, hkv, 64, k, steps)
+
+
+@pytest.mark.parametrize("docs,hq,hkv,d,k,backward", [([150, 1, 82], 32, 32, 64, 8, True), ([200, 60, 70], 64, 16, 64, 3, True), ([150, 1, 82, 290], 32, 8, 128, 5, True),
+                                                      ([530, 1, 82], 32, 8, 128, 3, False)])
+def test_fp32_full_launches_match_oracle(docs, hq, hkv, d, k, backward):
+    """fp32 with work for every compute unit: tiles in LDS in the forward, with one key group; in the backward with long documents alone."""
+    assert f32_direct(docs, hq, hkv, d, 0, k, compute_units()) == (False, backward)
     assert [s for s, _ in splits_of_calls(docs, hq, hkv, d, "f32", k, k)] == ["four_waves"]
-    assert backward_split_f32(sum(docs), hq, hkv, k, compute_units())[1] == 1
     run_fp32(docs, hq, hkv, d, k, k)
