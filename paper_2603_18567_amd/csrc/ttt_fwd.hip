@@ -14,6 +14,8 @@
 // Tiles are cut over the packed token axis, not per document: a row's visible prefix is
 // [tok_start[i], i], so a wave visits the kv tiles that intersect [tok_start[first row], last row]
 // and nothing else; tiles strictly inside that range for every row skip the mask code.
+#include <float.h>
+
 #include <algorithm>
 #include <type_traits>
 
@@ -292,7 +294,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
     // Diagonal keys of blocks 1..j (suffix part of the mask): one key per block and row.  Row-wise dot products on
     // the vector ALU; straight from global memory they are taken first, so that their latency overlaps the first
     // tile copy.
-    auto diag_key = [&](const frag (&dk)[QB][DC], const frag (&dv)[QB][DC]) {
+    // (no_score: the row may have no maximum yet.  A key of score -inf then has weight 0, a NaN stays NaN.)
+    auto diag_key = [&](const frag (&dk)[QB][DC], const frag (&dv)[QB][DC], auto no_score) {
         float s[QB];
         float vv[QB][DB][16];   // the key's value row in accumulator order
 #pragma unroll
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 #pragma unroll
                     for (int i = 0; i < 16; ++i) oacc[qb][db][i] *= alpha;
             }
-            const float p = fast_exp2((sc - (m[qb] == -INFINITY ? 0.f : m[qb])) * c);   // m = -inf: no key of the row yet but of score -inf (p = 0) or NaN
+            const float p = fast_exp2((sc - (decltype(no_score)::value ? fmaxf(m[qb], -FLT_MAX) : m[qb])) * c);
             l[qb] += 0.5f * p;   // the two lane halves are added at the end
 #pragma unroll
             for (int db = 0; db < DB; ++db)
@@ -344,7 +347,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         request(1 + kg, dk, dv);
         for (int lb = 1 + kg; lb <= j; lb += KS) {
             if (lb + KS <= j) request(lb + KS, nk, nv);
-            diag_key(dk, dv);
+            diag_key(dk, dv, IntC<1>{});
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
@@ -372,6 +375,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
         // three blocks at a time, every group's copies were waited for: at 4096 tokens 3.4 us per group of a workgroup's
         // 85.)  j is the same for the whole workgroup: the barriers are uniform.
         const int rb = (wq0 - q_tile0) / 32;   // this wave's first row block inside the workgroup's rows
+        if (diag_first > 0)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) m[qb] = fmaxf(m[qb], -FLT_MAX);   // no key of this group so far, or all of score -inf
         int base = 1, at = KS * GROUP_BYTES;
         for (int nb = diag_first; nb > 0;) {
             const int other = at == 0 ? KS * GROUP_BYTES : 0;
@@ -388,7 +394,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
                             dk[qb][t] = row_frag(drow, rb + qb, t);
                             dv[qb][t] = row_frag(drow + diag_bytes, rb + qb, t);
                         }
-                    diag_key(dk, dv);
+                    diag_key(dk, dv, IntC<0>{});
                 }
             }
             wait_async_copies();
