@@ -1488,6 +1488,8 @@ __global__ __launch_bounds__(256) void ttt_bwd_main_f32_kernel(const BwdArgs<N> 
 // fragments from global memory instead, an item of head_dim 128 took 12.4 us, so 8.5, 7.0 of them matrix instructions).  Whole backward, tiles
 // shared in LDS -> so: 247 tokens, 8/1 heads of 128, one step 67 -> 38 us; 444 tokens, 8/2 of 128, the last of seven 129 -> 63; 128
 // tokens, 4/4 heads of 64, three steps 24.2 -> 18.7.  Errors against 64 bits are smaller too (dQ 4.6e-7, 4.8e-7 before; dK, dV as before or less).
+// With head_dim 128 the rows, sums and operands of a unit are more than 512 registers hold: 32 are spilled (124 bytes of scratch per lane; tiles
+// shared in LDS spill 43), with 64 none.
 template <int D> struct BwdF32 {
     static constexpr int kRows = 32, kWaves = 4;
     static constexpr int kVec = 3 * 32 * 4;                                   // LSE*log2e, D, first token of the document of 32 rows

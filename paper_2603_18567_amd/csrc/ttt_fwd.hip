@@ -485,7 +485,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(WPE))) 
 // operands (32 KB at head_dim 128) need no LDS to keep up with them, and without tiles to share the waves need no
 // barrier before the end: what bounds a short call is one wave's chain of matrix instructions, and this split makes it
 // as short as the keys allow (us, tiles in LDS -> so: 128 tokens, 4/4 heads of 64, three steps 13.7 -> 10.2; 247 tokens, 8/1 heads
-// of 128, one step 56 -> 21; 444 tokens, 8/2 of 128 113 -> 37).  fwd_f32_direct has the rule.
+// of 128, one step 56 -> 21; 444 tokens, 8/2 of 128 113 -> 37).  fwd_f32_direct has the rule.  (Two waves to a SIMD: with head_dim 128 two registers are spilled.)
 template <int D, int N>
 __global__ __launch_bounds__(512) void ttt_fwd_f32_kernel(const FwdArgs<N> a) {
     constexpr int NW = 8;
