@@ -88,7 +88,8 @@ inline bool two_key_groups_end_first(const CallShape* calls, int n_calls, int pa
 
 // The longest and all of what the tiles of `rows` rows of a slice see, in groups of `per` key blocks of `keys` keys.
 struct KeyCount {
-    int64_t tiles = 0, blocks = 0, groups = 0, longest = 0;   // longest: groups of one tile
+    int64_t tiles = 0, blocks = 0, groups = 0;
+    int64_t longest = 0, longest_cut = 0;   // groups of one tile; of one with a document start inside a wave's 32 rows
 };
 inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
     KeyCount n;
@@ -100,6 +101,8 @@ inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
         n.blocks += blocks;
         n.groups += groups;
         n.longest = std::max(n.longest, groups);
+        for (int d = doc + 1; d < a.n_docs && a.cu_host[d] - a.cu_base < row + rows; ++d)
+            if (a.cu_host[d] - a.cu_base < a.T && (a.cu_host[d] - a.cu_base) % 32 != 0) n.longest_cut = std::max(n.longest_cut, groups);
     }
     return n;
 }
@@ -112,21 +115,24 @@ inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
 // of all over the compute units (what each costs of its own counts more where they make no whole rounds) and a part of the longest one (how unevenly they end),
 // whichever is more, by prices (us) fitted to 3000 launches of 40 ... 9000 tokens, timed in graphs (one launch after another
 // the shortest are as long as their submission): seven head geometries, one document or many, first step 0 to 10, one to nine steps.
-// Over 1500 others the choice takes 1.017 of the best of the three in the mean, the lines alone 1.060; 9 launches in 1000 are more than
-// 3 % slower than by the lines, 1.12 at most (40 by the estimates alone, which take 1.009).  566 tokens in two documents, 24/8
+// A document that starts inside a wave's 32 rows masks every key tile of the one before it (4463 tokens and one more, 8/2 heads, one step: 58.7 us
+// with four waves in one document, 96.7 in two), and diagonal keys cost more the fewer of their LDS slots there are.
+// Over 1400 others the choice takes 1.008 of the best of the three in the mean, the lines alone 1.059; 15 launches in 1000 are more than
+// 3 % slower than by the lines, 1.15 at most (28 by the estimates alone, which take 1.007).  566 tokens in two documents, 24/8
 // heads, the last of eleven steps: 23 -> 17 us; 65, 64/4, nine steps from the tenth on: 22 -> 16.
 // Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys.
 struct Fwd64Prices {
     double own, tile, diag;                  // the longest workgroup: of its own, per key tile (or pair of them), per diagonal key
     double wg, wg_tile, wg_diag;             // the work: per workgroup, its tiles, its diagonal keys
     double base, uneven, rounds;             // of the launch; of the longest workgroup; of what the last round leaves idle
-    double from_memory, idle;                // diagonal keys that do not go through LDS: more, by; less for waves without rows, by
+    double masked;                           // per key tile of a workgroup with a document start inside a wave's rows
+    double from_memory, one_slot, idle;      // diagonal keys that do not go through LDS, or through one slot: more, by; less for waves without rows, by
 };
 inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2, int n_cu) {
     constexpr Fwd64Prices kPrices[] = {   // in the order of FwdSplit
-        {0., 1.22, 0.71, 2.54, 0.96, 0.46, 5.33, 0.32, 0.33, 1.58, 0.50},
-        {0., 0.80, 0.52, 1.25, 0.50, 0.28, 5.08, 0.34, 0.39, 0.99, 0.44},
-        {1.79, 1.23, 0.52, 4.08, 1.31, 0.47, 3.53, 0., 0.79, 0., 0.},
+        {0.12, 1.19, 0.69, 2.54, 0.95, 0.46, 4.57, 0.34, 0.35, 0.36, 1.55, 0.34, 0.42},
+        {0.62, 0.80, 0.51, 1.26, 0.50, 0.27, 3.74, 0.36, 0.57, 0.43, 0.95, 0.34, 0.33},
+        {1.66, 1.23, 0.53, 4.14, 1.30, 0.47, 3.24, 0.03, 0.79, 0.39, 0., 0., 0.},
     };
     int64_t n_wgs = 0;
     int longest_doc = 0;
@@ -145,15 +151,16 @@ inline FwdSplit work_split_64(const CallShape* calls, int n_calls, int pack_log2
         const Fwd64Prices& p = kPrices[split];
         const int waves = split == kFwdFourWaves ? 4 : 8, groups = split == kFwdTwoKeyGroups ? 2 : 1, per_cu = split == kFwdEightWaves ? 2 : split == kFwdFourWaves ? 3 : 1;
         const int rows = (waves / groups * 32) >> pack_log2;
-        const double from_memory = fwd_diag_slots(64, waves, groups, per_cu, rows).slots == 0 ? p.from_memory : 0.;
+        const int slots = fwd_diag_slots(64, waves, groups, per_cu, rows).slots;
         double longest = 0., each = 0., tiles = 0., n = 0.;
         for (int i = 0; i < n_calls; ++i) {
             const CallShape& a = calls[i];
             const KeyCount keys = count_keys(a, rows, 64, groups);
-            const double full = std::min(1., (double)a.T / rows), busy = 1. - p.idle * (1. - full), diag = busy * (1. + from_memory * full) * p.diag;
-            const double wg_diag = busy * (1. + from_memory * full) * p.wg_diag, per_tile = (double)a.hkv * (a.G >> pack_log2) * a.n_steps;
-            longest = std::max(longest, p.own + busy * p.tile * keys.longest + diag * (a.step_begin + a.n_steps - 1));
-            each += per_tile * keys.tiles * (p.wg + wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1)));
+            const double full = std::min(1., (double)a.T / rows), busy = 1. - p.idle * (1. - full), per_tile = (double)a.hkv * (a.G >> pack_log2) * a.n_steps;
+            const double diag = busy * (1. + (slots == 0 ? p.from_memory * full : slots == 1 ? p.one_slot : 0.));
+            const double chain = std::max(p.tile * keys.longest, (p.tile + p.masked) * keys.longest_cut);
+            longest = std::max(longest, p.own + busy * chain + diag * p.diag * (a.step_begin + a.n_steps - 1));
+            each += per_tile * keys.tiles * (p.wg + diag * p.wg_diag * (a.step_begin + 0.5 * (a.n_steps - 1)));
             tiles += per_tile * busy * keys.groups * p.wg_tile;
             n += per_tile * keys.tiles;
         }

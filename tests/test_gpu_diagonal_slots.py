@@ -18,7 +18,7 @@ CASES = [
     ([300, 70, 1, 29, 49], 64, 16, 128, 12, 12, "eight_waves", 4),
     ([300, 70, 1, 29, 49], 48, 8, 128, 12, 12, "eight_waves", 2),
     ([33, 64, 2], 8, 2, 64, 10, 1, "four_waves", 4),
-    ([33, 64, 2], 6, 3, 64, 10, 1, "four_waves", 2),
+    ([33, 64, 2], 48, 24, 64, 10, 10, "four_waves", 2),
     ([63, 200, 1, 41], 128, 32, 64, 12, 12, "eight_waves", 4),
     ([63, 200, 1, 41], 192, 96, 64, 15, 15, "eight_waves", 2),
     ([3, 1030, 40], 4, 1, 64, 9, 1, "two_key_groups", 4),

@@ -31,7 +31,7 @@ CASES_64 = [
     ("four_waves", [70, 1, 130, 64, 33], 8, 2, 4, 1),
     ("four_waves_one_head", [200, 95], 96, 32, 3, 1),
     ("eight_waves", [63, 200, 1, 41], 128, 32, 11, 11),
-    ("four_waves_two_heads", [33, 1, 130, 64], 4, 2, 4, 1),       # 64 rows: diagonal rows through LDS
+    ("four_waves_two_heads", [33, 1, 130, 64], 128, 64, 4, 1),       # 64 rows: diagonal rows through LDS
     ("eight_waves_one_head", [63, 200, 1, 41], 128, 128, 17, 17),
     ("eight_waves_two_heads", [63, 200, 1, 41], 192, 96, 15, 15),
     ("eight_waves_70_documents", [9, 1, 0, 17, 5] * 14, 144, 48, 15, 15),

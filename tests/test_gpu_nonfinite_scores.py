@@ -18,7 +18,7 @@ CASES = [
     ("bf16", [300], 8, 2, 128, 4, 1, "two_key_groups"),
     ("bf16", [300, 70, 1, 29, 49], 64, 16, 128, 12, 12, "eight_waves"),
     ("bf16", [500], 32, 8, 64, 4, 1, "two_key_groups"),
-    ("bf16", [33, 1, 130, 64], 4, 2, 64, 4, 1, "four_waves"),
+    ("bf16", [70, 1, 130, 64, 33], 8, 2, 64, 4, 1, "four_waves"),
     ("bf16", [63, 200, 1, 41], 128, 32, 64, 11, 11, "eight_waves"),
 ]
 

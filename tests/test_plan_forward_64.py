@@ -15,6 +15,7 @@ from plan_lib import forward_split
     ([444, 320], 24, 8, 9, 1, "two_key_groups"),      # 33, 23 and 17
     ([2493, 1235, 212], 12, 2, 3, 1, "two_key_groups"),   # 64, 58 and 41
     ([7640], 8, 2, 0, 1, "two_key_groups"),           # 151, 104 and 83
+    ([3613, 2031], 12, 2, 5, 1, "two_key_groups"),    # 90, 83 and 59: a document that starts inside a wave's rows
     ([65536], 16, 4, 0, 7, "eight_waves"),            # more than sixteen of the largest workgroups to a unit
     ([497, 69], 24, 8, 10, 1, "two_key_groups"),      # short packed batches: 34, 23 and 17
     ([183, 183, 66], 16, 16, 10, 4, "two_key_groups"),    # 34, 22 and 16
