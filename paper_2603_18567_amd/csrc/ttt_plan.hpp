@@ -118,7 +118,7 @@ inline KeyCount count_keys(const CallShape& a, int rows, int keys, int per) {
 // A document that starts inside a wave's 32 rows masks every key tile of the one before it (4463 tokens and one more, 8/2 heads, one step: 58.7 us
 // with four waves in one document, 96.7 in two), and diagonal keys cost more the fewer of their LDS slots there are.
 // Over 1400 others the choice takes 1.008 of the best of the three in the mean, the lines alone 1.059; 15 launches in 1000 are more than
-// 3 % slower than by the lines, 1.15 at most (28 by the estimates alone, which take 1.007).  566 tokens in two documents, 24/8
+// 3 % slower than by the lines, 1.12 at most (28 by the estimates alone, which take 1.007).  566 tokens in two documents, 24/8
 // heads, the last of eleven steps: 23 -> 17 us; 65, 64/4, nine steps from the tenth on: 22 -> 16.
 // Beyond sixteen of the largest workgroups per unit (more than were measured) the fewest passes over the keys.
 struct Fwd64Prices {
